@@ -37,18 +37,18 @@ def listed():
         # a server's micro-batch of the unit-norm set, half-precision tables
         _search("64 queries", "unit", 1_000_000, 1024, 48, 8, 64, 20, 10, "fp16"),
         # an odd, middling batch with full-precision tables and short codes
-        _search("777 queries, float table", "grid", 1_000_000, 1024, 32, 8, 777, 33, 50, "fp32"),
+        _search("777 queries float table", "grid", 1_000_000, 1024, 32, 8, 777, 33, 50, "fp32"),
         # offline batch search on 10^6 vectors, the configuration of the repository's smaller benchmark
         _search("batch on 1M", "grid", 1_000_000, 1024, 64, 8, 10_000, 20, 10, "e5m3"),
         # the 10^7 unit-norm set at the paper's k
         _search("batch on 10M", "unit", 10_000_000, 10_000, 48, 8, 10_000, 50, 100, "e5m3"),
         # lists of 2,000 vectors, 32-byte codes, 64 probes, k = 100: the shape of the 10^8-vector benchmark at a
         # size that can be built in seconds
-        _search("batch, long lists", "grid", 10_000_000, 5_000, 32, 8, 10_000, 64, 100, "e5m3"),
+        _search("batch long lists", "grid", 10_000_000, 5_000, 32, 8, 10_000, 64, 100, "e5m3"),
         # the same with 4-bit codes and half tables
-        _search("batch, 4-bit codes", "grid", 4_000_000, 2_000, 64, 4, 10_000, 64, 100, "fp16"),
+        _search("batch 4-bit codes", "grid", 4_000_000, 2_000, 64, 4, 10_000, 64, 100, "fp16"),
         # bit-packed codes
-        _search("batch, 7-bit codes", "grid", 1_000_000, 1024, 64, 7, 10_000, 20, 10, "e5m3"),
+        _search("batch 7-bit codes", "grid", 1_000_000, 1024, 64, 7, 10_000, 20, 10, "e5m3"),
         # high-recall search: 40 candidates re-ranked to 10 with the stored vectors
         {"name": "search and re-rank", "op": "rerank", "data": "grid", "n": 1_000_000, "lists": 1024, "sub": 64, "bits": 8,
          "nq": 4_096, "probes": 20, "wide": 40, "k": 10, "table": "e5m3"},
