@@ -8,6 +8,7 @@ compiled by hipcc for gfx950 only.  No GPU is needed to build.
 import os
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -21,6 +22,7 @@ HIP_FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-function",
 ]
+DEVICE_SOURCES = ("ivfpq_device", "ivfpq_build")       # search kernels; index construction kernels
 HOST_FLAGS = ["-O3", "-std=c++17", "-fPIC", "-fopenmp", "-mavx2", "-mfma", "-Wall"]
 
 
@@ -35,11 +37,13 @@ def build(verbose: bool = False, extra_hip_flags=()) -> str:
     os.makedirs(obj_dir, exist_ok=True)
     host_o = os.path.join(obj_dir, "ivfpq_host.o")
     _run(["g++", *HOST_FLAGS, "-c", os.path.join(CSRC, "ivfpq_host.cpp"), "-o", host_o], verbose)
-    dev_objs = []
-    for name in ("ivfpq_device", "ivfpq_build"):       # search kernels; index construction kernels
-        obj = os.path.join(obj_dir, name + ".o")
-        _run([HIPCC, *HIP_FLAGS, *extra_hip_flags, "-c", os.path.join(CSRC, name + ".hip"), "-o", obj], verbose)
-        dev_objs.append(obj)
+    objs = {name: os.path.join(obj_dir, name + ".o") for name in DEVICE_SOURCES}
+    with ThreadPoolExecutor(max_workers=len(objs)) as pool:
+        jobs = [pool.submit(_run, [HIPCC, *HIP_FLAGS, *extra_hip_flags, "-c", os.path.join(CSRC, name + ".hip"), "-o", obj], verbose)
+                for name, obj in objs.items()]
+        for job in jobs:
+            job.result()
+    dev_objs = list(objs.values())
     _run([HIPCC, "--offload-arch=gfx950", "-shared", "-o", LIB_PATH, host_o, *dev_objs, "-lgomp"], verbose)
     return LIB_PATH
 

@@ -38,6 +38,8 @@
 #include "ivfpq_internal.hpp"
 #include "ivfpq_rank.hpp"
 #include "ivfpq_lds_util.hpp"
+#include "ivfpq_lut.hpp"
+#include "ivfpq_select.hpp"
 
 using namespace ivfpq;
 
@@ -69,413 +71,6 @@ int static_scratch_ptr(void** out) {
     }
     *out = ptr[dev];
     return IVFPQ_OK;
-}
-
-constexpr uint32_t kPadKey = 0xFFFFFFFFu;      // R of a padding lane: sorts after every real distance
-
-// ================================================================================================
-// Exact selection of the k smallest of n keyed elements by one workgroup.
-// Keys are the bit patterns of non-negative floats (order-preserving as unsigned integers); equal
-// keys are ordered by a signed 64-bit tie key, then by position.  MSB-first radix select with 8-bit
-// digits finds the k-th smallest key; everything below it and the needed share of the ties is
-// collected into LDS records and sorted there (bitonic).
-// ================================================================================================
-// (the helpers below are force-inlined: left to the inliner, a few lines more in one of them turned it into a
-// real call with its arguments on the stack, and the probe-selection kernel took twice as long)
-constexpr int SEL_THREADS = 256;
-constexpr int SEL_CAP = 1024;      // record capacity = IVFPQ_MAX_K: the selected elements always fit
-
-// what block_kth_key alone needs
-struct KthShared {
-    uint32_t hist[256];
-    uint32_t digit, need, count;
-    uint32_t n_rec;
-};
-
-// CAP: how many records the selection can return (>= k); kernels whose k is small take a small CAP, so that more of
-// their workgroups share a compute unit (they wait on barriers and memory most of the time: the top-k kernel with
-// k = 100 took 0.25 ms at six workgroups per compute unit and 0.21 ms at eight)
-template <int CAP>
-struct SelectSharedT {
-    static constexpr int kCap = CAP;
-    uint32_t hist[256];
-    uint32_t rec_key[CAP];
-    uint32_t rec_pos[CAP];
-    long long rec_tie[CAP];
-    uint32_t digit, need, count;   // broadcast slots of the digit search
-    uint32_t n_rec, n_eq;
-};
-using SelectShared = SelectSharedT<SEL_CAP>;
-constexpr int SEL_CAP_SMALL = 256;  // >= 2 * kFewMax: block_select_few parks tie keys in the upper half of the records
-
-// The sum of a value over every aligned group of 8 lanes, left in all 8: neighbours, then pairs inside a quad, then
-// the other quad of the group (whose four lanes hold the same value by then, so the mirrored order does not matter).
-// Each step adds the same two numbers in both partners: all 8 lanes end with the same bits.
-__device__ inline float sum_over_8_lanes(float v) {
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, true));     // quad_perm [1,0,3,2]
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, true));     // quad_perm [2,3,0,1]
-    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xF, 0xF, true));    // row_half_mirror
-    return v;
-}
-
-// Sum over this lane and the lanes below it, by data-parallel permutes (no trip through the LDS): a scan inside
-// every row of 16 lanes, then the last lane of a row added to the rows above.  (A lane a permute has no source
-// for, or whose row is masked out, receives 0.)
-template <int CTRL, int ROWS>
-__device__ inline uint32_t dpp_or_zero(uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, true); }
-__device__ inline uint32_t wave_inclusive_scan(uint32_t v) {
-    v += dpp_or_zero<0x111, 0xF>(v);       // row_shr:1
-    v += dpp_or_zero<0x112, 0xF>(v);       // row_shr:2
-    v += dpp_or_zero<0x114, 0xF>(v);       // row_shr:4
-    v += dpp_or_zero<0x118, 0xF>(v);       // row_shr:8
-    v += dpp_or_zero<0x142, 0xA>(v);       // row_bcast:15 into rows 1 and 3
-    v += dpp_or_zero<0x143, 0xC>(v);       // row_bcast:31 into rows 2 and 3
-    return v;
-}
-
-// hist holds digit counts; finds the digit that contains the `need`-th smallest element
-// (1-based).  Result in s.digit (the digit), s.need (rank inside that digit), s.count (its count).
-// Called by all threads; contains barriers.
-template <class Shared>
-__device__ __forceinline__ void find_digit(Shared& s, uint32_t need) {
-    __syncthreads();
-    if (threadIdx.x < kWave) {
-        const int t = threadIdx.x;
-        uint32_t c0 = s.hist[4 * t], c1 = s.hist[4 * t + 1], c2 = s.hist[4 * t + 2], c3 = s.hist[4 * t + 3];
-        uint32_t sum = c0 + c1 + c2 + c3;
-        uint32_t incl = wave_inclusive_scan(sum);
-        uint32_t excl = incl - sum;
-        if (excl < need && need <= incl) {
-            uint32_t r = need - excl, dsel = 0, cnt = c0;
-            if (r > c0) { r -= c0; dsel = 1; cnt = c1;
-                if (r > c1) { r -= c1; dsel = 2; cnt = c2;
-                    if (r > c2) { r -= c2; dsel = 3; cnt = c3; } } }
-            s.digit = 4 * t + dsel;
-            s.need = r;
-            s.count = cnt;
-        }
-    }
-    __syncthreads();
-}
-
-__device__ inline bool rec_less(uint32_t ka, long long ta, uint32_t pa, uint32_t kb, long long tb, uint32_t pb) {
-    if (ka != kb) return ka < kb;
-    if (ta != tb) return ta < tb;
-    return pa < pb;
-}
-
-// sorts records [0, np2) ascending by (key, tie, pos); np2 is a power of two <= the record capacity
-template <class S>
-__device__ __forceinline__ void sort_records(S& s, int np2) {
-    for (int size = 2; size <= np2; size <<= 1) {
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            __syncthreads();
-            for (int t = threadIdx.x; t < (np2 >> 1); t += blockDim.x) {
-                int lo = ((t / stride) * stride * 2) + (t % stride);
-                int hi = lo + stride;
-                bool up = ((lo & size) == 0);
-                uint32_t ka = s.rec_key[lo], kb = s.rec_key[hi];
-                long long ta = s.rec_tie[lo], tb = s.rec_tie[hi];
-                uint32_t pa = s.rec_pos[lo], pb = s.rec_pos[hi];
-                bool b_lt_a = rec_less(kb, tb, pb, ka, ta, pa);
-                if (b_lt_a == up) {
-                    s.rec_key[lo] = kb; s.rec_key[hi] = ka;
-                    s.rec_tie[lo] = tb; s.rec_tie[hi] = ta;
-                    s.rec_pos[lo] = pb; s.rec_pos[hi] = pa;
-                }
-            }
-        }
-    }
-    __syncthreads();
-}
-
-// One histogram increment per active lane, with the increments of a wave folded into a single
-// LDS atomic when all its active lanes hit the same bin (the usual case for the leading digit of
-// distances of similar magnitude, where per-lane atomics on one address would serialise).
-__device__ __forceinline__ void hist_add(uint32_t* hist, uint32_t digit, bool active) {
-    const unsigned long long act = ballot64(active);
-    if (act == 0) return;
-    const int first = __ffsll((long long)act) - 1;
-    const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)digit, first);      // `first` is the same for the whole wave
-    const unsigned long long same = ballot64(active && digit == d0);
-    if (same == act) {
-        if ((int)(threadIdx.x & (kWave - 1)) == first) atomicAdd(&hist[d0], (uint32_t)__popcll(act));
-    } else if (active) {
-        atomicAdd(&hist[digit], 1u);
-    }
-}
-
-// The kk-th smallest (1-based, 1 <= kk <= n) of n keys, by four 8-bit digits from the top.
-// *rank_in_ties = how many elements equal to the result rank at or below kk (1..*n_ties),
-// *n_ties = number of elements equal to the result.  Called by every thread of the workgroup.
-template <class Shared, class KeyFn>
-__device__ __forceinline__ uint32_t block_kth_key(Shared& s, uint32_t n, uint32_t kk, KeyFn key_of,
-                                  uint32_t* rank_in_ties, uint32_t* n_ties) {
-    const int tid = threadIdx.x, nth = blockDim.x;
-    uint32_t prefix = 0, need = kk, n_eq = 0;
-    for (int pass = 3; pass >= 0; --pass) {
-        const int shift = pass * 8;
-        __syncthreads();
-        for (int b = tid; b < 256; b += nth) s.hist[b] = 0;
-        __syncthreads();
-        for (uint32_t base = 0; base < n; base += nth) {
-            const uint32_t i = base + tid;
-            const bool valid = i < n;
-            const uint32_t key = valid ? key_of(i) : 0u;
-            const bool in = valid && ((pass == 3) || ((key >> (shift + 8)) == (prefix >> (shift + 8))));
-            hist_add(s.hist, (key >> shift) & 255u, in);
-        }
-        find_digit(s, need);
-        prefix |= s.digit << shift;
-        need = s.need;
-        n_eq = s.count;
-    }
-    *rank_in_ties = need;
-    *n_ties = n_eq;
-    return prefix;
-}
-
-// KeyFn(i) -> uint32 key of element i; TieFn(i) -> long long tie key of element i.
-// On return records [0, min(k, n)) hold the selected elements in ascending (key, tie, pos) order.
-// Returns min(k, n).  Must be called by every thread of the workgroup.
-template <class S, class KeyFn, class TieFn>
-__device__ __forceinline__ int block_select_smallest(S& s, uint32_t n, uint32_t k, KeyFn key_of, TieFn tie_of) {
-    const uint32_t kk = k < n ? k : n;
-    if (kk == 0) return 0;
-    const int tid = threadIdx.x, nth = blockDim.x;
-
-    uint32_t need = 0, n_eq = 0;
-    const uint32_t T = block_kth_key(s, n, kk, key_of, &need, &n_eq);
-    const uint32_t n_less = kk - need;     // elements strictly below T: all selected
-
-    // ---- collect
-    __syncthreads();
-    if (tid == 0) { s.n_rec = 0; s.n_eq = 0; }
-    __syncthreads();
-    const bool all_fit = (n_less + n_eq) <= (uint32_t)S::kCap;
-    if (all_fit) {
-        // everything <= T goes into the records; the sort decides which ties stay
-        for (uint32_t i = tid; i < n; i += nth) {
-            uint32_t key = key_of(i);
-            if (key <= T) {
-                uint32_t slot = atomicAdd(&s.n_rec, 1u);
-                s.rec_key[slot] = key; s.rec_pos[slot] = i; s.rec_tie[slot] = tie_of(i);
-            }
-        }
-    } else {
-        // too many elements equal to T: pick the `need` smallest tie keys among them with a second,
-        // 64-bit radix select (tie keys mapped to unsigned order by flipping the sign bit)
-        unsigned long long uprefix = 0;
-        uint32_t uneed = need;
-        for (int pass = 7; pass >= 0; --pass) {
-            const int shift = pass * 8;
-            __syncthreads();
-            for (int b = tid; b < 256; b += nth) s.hist[b] = 0;
-            __syncthreads();
-            for (uint32_t base = 0; base < n; base += nth) {
-                const uint32_t i = base + tid;
-                bool in = i < n && key_of(i) == T;
-                unsigned long long u = 0;
-                if (in) {
-                    u = (unsigned long long)tie_of(i) ^ 0x8000000000000000ull;
-                    in = (pass == 7) || ((u >> (shift + 8)) == (uprefix >> (shift + 8)));
-                }
-                hist_add(s.hist, (uint32_t)(u >> shift) & 255u, in);
-            }
-            find_digit(s, uneed);
-            uprefix |= (unsigned long long)s.digit << shift;
-            uneed = s.need;
-        }
-        // uprefix = the need-th smallest tie key; uneed = how many copies of it to take
-        __syncthreads();
-        for (uint32_t i = tid; i < n; i += nth) {
-            uint32_t key = key_of(i);
-            if (key > T) continue;
-            bool take = key < T;
-            long long tie = tie_of(i);
-            if (!take) {
-                unsigned long long u = (unsigned long long)tie ^ 0x8000000000000000ull;
-                if (u < uprefix) take = true;
-                else if (u == uprefix) take = atomicAdd(&s.n_eq, 1u) < uneed;
-            }
-            if (take) {
-                uint32_t slot = atomicAdd(&s.n_rec, 1u);
-                s.rec_key[slot] = key; s.rec_pos[slot] = i; s.rec_tie[slot] = tie;
-            }
-        }
-    }
-    __syncthreads();
-    const uint32_t n_rec = s.n_rec;
-    int np2 = 1;
-    while ((uint32_t)np2 < n_rec) np2 <<= 1;
-    for (int i = n_rec + tid; i < np2; i += nth) {
-        s.rec_key[i] = 0xFFFFFFFFu; s.rec_pos[i] = 0xFFFFFFFFu; s.rec_tie[i] = 0x7FFFFFFFFFFFFFFFll;
-    }
-    sort_records(s, np2);
-    return (int)kk;
-}
-
-// The same selection for few elements (n <= kFewMax <= blockDim.x; key_of must be cheap, every thread
-// calls it n times): thread i ranks element i by counting the elements that precede it in (key, tie,
-// index) order, three barriers in all.  It costs about n instructions per thread where the radix select
-// and the sort cost several hundred whatever n is.  Tie keys are fetched only for elements with fewer than
-// k smaller keys, and wait in the upper half of the record array while the ranks are settled.
-constexpr uint32_t kFewMax = 128;
-template <class S, class KeyFn, class TieFn>
-__device__ __forceinline__ int block_select_few(S& s, uint32_t n, uint32_t k, KeyFn key_of, TieFn tie_of) {
-    static_assert(S::kCap >= 2 * (int)kFewMax, "tie keys wait in the upper half of the records");
-    const uint32_t kk = k < n ? k : n;
-    if (kk == 0) return 0;
-    const uint32_t e = threadIdx.x;
-    constexpr uint32_t SCR = S::kCap / 2;
-    __syncthreads();
-    const uint32_t key = e < n ? key_of(e) : 0xFFFFFFFFu;
-    uint32_t less = 0, same = 0;
-    if (e < n)
-        for (uint32_t j = 0; j < n; ++j) {
-            const uint32_t kj = key_of(j);
-            less += kj < key ? 1u : 0u;
-            same += kj == key ? 1u : 0u;
-        }
-    const bool cand = e < n && less < kk;
-    long long tie = 0;
-    if (cand) { tie = tie_of(e); s.rec_tie[SCR + e] = tie; }
-    __syncthreads();
-    if (cand) {
-        uint32_t r = less;
-        if (same > 1)                        // elements with the same key all have their tie key in place
-            for (uint32_t j = 0; j < n; ++j) {
-                if (j == e || key_of(j) != key) continue;
-                const long long tj = s.rec_tie[SCR + j];
-                r += (tj < tie || (tj == tie && j < e)) ? 1u : 0u;
-            }
-        if (r < kk) { s.rec_key[r] = key; s.rec_tie[r] = tie; s.rec_pos[r] = e; }
-    }
-    __syncthreads();
-    return (int)kk;
-}
-
-// ------------------------------------------------------------------------------------------------
-// The k smallest of a long row of keys in global memory (tens of thousands per query).
-// The k-th smallest key among the first CAND_CAP elements is an upper bound of the k-th smallest
-// of the whole row, so one streaming pass that keeps only keys not above that bound compacts the
-// row into LDS (typically a few times k elements); the exact selection then runs on that small
-// set.  If the compacted set overflows LDS the routine falls back to exact selection over the
-// whole row in global memory.  tie_of_pos(pos, key) gives the tie key of the element at row
-// position pos.  On return records [0, got) hold key, tie and row position in ascending
-// (key, tie) order.
-// ------------------------------------------------------------------------------------------------
-constexpr int CAND_CAP = 1024;   // >= IVFPQ_MAX_K
-
-template <int CAP>
-struct RowSelectSharedT {
-    SelectSharedT<CAP> sel;
-    uint32_t cand_key[CAND_CAP];
-    uint32_t cand_pos[CAND_CAP];
-    uint32_t n_cand;
-};
-using RowSelectShared = RowSelectSharedT<SEL_CAP>;
-
-// pos_of(i): logical position of row element i (what the records report and what tie_of_pos
-// takes); have_bound/bound: an upper bound of the k-th smallest key that the caller already knows
-// (at least k elements of the row are <= it).
-// Hooks for rows whose keys are only approximate (probe selection): widen(bound) is applied to every
-// bound before it filters (it must return a key that no element the exact selection could need
-// exceeds); refine(n_cand) runs once the candidates sit in LDS, may replace their keys by exact ones and
-// drop candidates (it returns how many remain, at the front of the candidate arrays); whole_row() is the
-// fallback when compaction fails and must return the selection itself.
-struct NoWiden { __device__ uint32_t operator()(uint32_t b) const { return b; } };
-struct NoRefine { __device__ uint32_t operator()(uint32_t n) const { return n; } };
-
-template <class T, class PosFn, class TieFn, class WidenFn, class RefineFn, class WholeRowFn>
-__device__ __forceinline__ int block_select_row_ex(T& t, const uint32_t* __restrict__ row, uint32_t n, uint32_t k,
-                                   bool have_bound, uint32_t bound, PosFn pos_of, TieFn tie_of_pos,
-                                   WidenFn widen, RefineFn refine, WholeRowFn whole_row) {
-    auto& s = t.sel;
-    const int tid = threadIdx.x, nth = blockDim.x;
-    const uint32_t kk = k < (uint32_t)CAND_CAP ? k : (uint32_t)CAND_CAP;
-    bool compact = true;
-    uint32_t n_cand = n;
-    __syncthreads();
-    if (n > (uint32_t)CAND_CAP) {
-        uint32_t r0, r1;
-        if (!have_bound) {
-            // the k-th smallest of the first S keys bounds the k-th smallest of the row; about k n / S keys
-            // pass it, so S grows with k n until half the LDS buffer is the expectation (a second pass
-            // over the whole row costs more than a longer sample)
-            const unsigned long long want = (unsigned long long)kk * n / (CAND_CAP / 2);
-            const uint32_t S = want <= (unsigned long long)CAND_CAP ? (uint32_t)CAND_CAP : (want < n ? (uint32_t)want : n);
-            if (S == (uint32_t)CAND_CAP) {
-                for (int i = tid; i < CAND_CAP; i += nth) t.cand_key[i] = row[i];
-                bound = block_kth_key(s, (uint32_t)CAND_CAP, kk, [&](uint32_t i) { return t.cand_key[i]; }, &r0, &r1);
-            } else {
-                bound = block_kth_key(s, S, kk, [&](uint32_t i) { return row[i]; }, &r0, &r1);
-            }
-        }
-        bound = widen(bound);
-        const bool vec = (reinterpret_cast<uintptr_t>(row) & 15u) == 0;      // 16-byte loads, the last n % 4 keys one by one
-        compact = false;
-        // Each pass keeps the elements not above the bound.  If they overflow the LDS buffer, the
-        // k-th smallest of the ones that were kept is a tighter valid bound (they are all members
-        // of the row): the survivor count shrinks by about CAND_CAP / k per pass.
-        for (int pass = 0; pass < 8; ++pass) {
-            __syncthreads();
-            if (tid == 0) t.n_cand = 0;
-            __syncthreads();
-            auto keep = [&](uint32_t key, uint32_t i) {
-                if (key <= bound) {
-                    uint32_t slot = atomicAdd(&t.n_cand, 1u);
-                    if (slot < (uint32_t)CAND_CAP) { t.cand_key[slot] = key; t.cand_pos[slot] = pos_of(i); }
-                }
-            };
-            if (vec) {
-                const uint4* row4 = reinterpret_cast<const uint4*>(row);
-                for (uint32_t i4 = tid; i4 < n / 4; i4 += nth) {
-                    const uint4 v = row4[i4];
-                    keep(v.x, i4 * 4); keep(v.y, i4 * 4 + 1); keep(v.z, i4 * 4 + 2); keep(v.w, i4 * 4 + 3);
-                }
-                for (uint32_t i = (n & ~3u) + tid; i < n; i += nth) keep(row[i], i);
-            } else {
-                for (uint32_t i = tid; i < n; i += nth) keep(row[i], i);
-            }
-            __syncthreads();
-            n_cand = t.n_cand;
-            if (n_cand <= (uint32_t)CAND_CAP) { compact = true; break; }
-            const uint32_t tighter = widen(block_kth_key(s, (uint32_t)CAND_CAP, kk, [&](uint32_t i) { return t.cand_key[i]; }, &r0, &r1));
-            if (tighter >= bound) break;      // a plateau of equal keys: no progress possible this way
-            bound = tighter;
-        }
-    } else {
-        for (uint32_t i = tid; i < n; i += nth) { t.cand_key[i] = row[i]; t.cand_pos[i] = pos_of(i); }
-        __syncthreads();
-    }
-    int got;
-    if (compact) {
-        n_cand = refine(n_cand);
-        auto key_of = [&](uint32_t i) { return t.cand_key[i]; };
-        auto tie_of = [&](uint32_t i) -> long long { return tie_of_pos(t.cand_pos[i], t.cand_key[i]); };
-        got = n_cand <= kFewMax ? block_select_few(s, n_cand, k, key_of, tie_of)
-                                : block_select_smallest(s, n_cand, k, key_of, tie_of);
-        for (int j = tid; j < got; j += nth) s.rec_pos[j] = t.cand_pos[s.rec_pos[j]];   // back to logical positions
-    } else {
-        got = whole_row();
-    }
-    __syncthreads();
-    return got;
-}
-
-template <class T, class PosFn, class TieFn>
-__device__ __forceinline__ int block_select_row(T& t, const uint32_t* __restrict__ row, uint32_t n, uint32_t k,
-                                bool have_bound, uint32_t bound, PosFn pos_of, TieFn tie_of_pos) {
-    auto& s = t.sel;
-    return block_select_row_ex(t, row, n, k, have_bound, bound, pos_of, tie_of_pos, NoWiden{}, NoRefine{},
-        [&]() -> int {
-            const int got = block_select_smallest(s, n, k,
-                [&](uint32_t i) { return row[i]; },
-                [&](uint32_t i) -> long long { return tie_of_pos(pos_of(i), row[i]); });
-            for (int j = threadIdx.x; j < got; j += blockDim.x) s.rec_pos[j] = pos_of(s.rec_pos[j]);
-            return got;
-        });
 }
 
 // ================================================================================================
@@ -747,83 +342,6 @@ layout_probes_kernel(const uint32_t* __restrict__ probes_in, int nq, int n_probe
 // ================================================================================================
 // Steps 2-4: residual, lookup table in LDS, code scan.
 // ================================================================================================
-template <int LUT> struct LutTraits;     // bytes: size of one table entry
-template <> struct LutTraits<IVFPQ_LUT_FP32> { static constexpr int bytes = 4; };
-template <> struct LutTraits<IVFPQ_LUT_FP16> { static constexpr int bytes = 2; };
-template <> struct LutTraits<IVFPQ_LUT_FP8_E5M3> { static constexpr int bytes = 1; };
-template <> struct LutTraits<IVFPQ_LUT_FP8_E4M4> { static constexpr int bytes = 1; };
-// The two 8-bit formats.  shift: how far a code is shifted to line up with the FP32 exponent/mantissa
-// field (23 less the mantissa bits); top_exp: the largest exponent field; bias_min/bias_max: range of
-// the exponent bias for which every code is a finite normal FP32 number.
-template <int LUT> struct Fp8Format {     // e5m3
-    static constexpr int shift = 20, top_exp = 31, bias_min = -96, bias_max = 110;
-};
-template <> struct Fp8Format<IVFPQ_LUT_FP8_E4M4> {
-    static constexpr int shift = 19, top_exp = 15, bias_min = -100, bias_max = 110;
-};
-template <int LUT> constexpr bool kIsFp8 = LUT == IVFPQ_LUT_FP8_E5M3 || LUT == IVFPQ_LUT_FP8_E4M4;
-
-// Constants of a sign-less 8-bit float (Sec. II) with M mantissa bits (shift = 23 - M) and exponent
-// bias B: value(b) = (1 + mant/2^M) * 2^(exp - B).  Both conversions are a shift plus a bias
-// adjustment on the FP32 bit pattern:
-//   code = (clamp_s32(bits, lo, hi) - sub) >> shift        bits = (code << shift) + lo
-// lo = (127 - B) << 23 is the smallest value, hi = lo + (255 << shift) the largest; sub = lo less half
-// an 8-bit ulp, so that the shift rounds to nearest with ties up, or lo itself to truncate.  The clamp
-// acts on the pattern as a signed integer: zero and negatives give code 0, +Inf code 255.
-// e5m3 with B = 15: lo = 0x38000000, hi = 0x47F00000, sub = 0x37F80000.
-struct Fp8Params { int lo, hi, sub; };
-
-__host__ __device__ inline Fp8Params fp8_params(int shift, int bias, int truncate) {
-    Fp8Params p;
-    p.lo = (127 - bias) << 23;
-    p.hi = p.lo + (255 << shift);
-    p.sub = truncate ? p.lo : p.lo - (1 << (shift - 1));
-    return p;
-}
-// The code of x, left in the TOP byte of the result (low bits undefined): the clamp is one
-// three-operand median once the upper limit sits in a vector register (`hi_v`; an instruction takes
-// one scalar operand only), the bias subtraction and the shift are one add-shift.
-template <int SHIFT>
-__device__ inline uint32_t fp8_code_top_byte(float x, const Fp8Params p, int hi_v) {
-    int b;
-    uint32_t t;
-    const int nsub = -p.sub;
-    asm("v_med3_i32 %0, %1, %2, %3" : "=v"(b) : "v"(__float_as_int(x)), "s"(p.lo), "v"(hi_v));     // clamp to [lo, hi]
-    asm("v_add_lshl_u32 %0, %1, %2, %3" : "=v"(t) : "v"(b), "s"(nsub), "n"(24 - SHIFT));            // (b - sub) << (24 - SHIFT)
-    return t;
-}
-// four codes (of f[0..3], lowest byte first) gathered from the top bytes with three byte permutes
-template <int SHIFT>
-__device__ inline uint32_t fp8_pack4(const float f[4], const Fp8Params p, int hi_v) {
-    const uint32_t t0 = fp8_code_top_byte<SHIFT>(f[0], p, hi_v), t1 = fp8_code_top_byte<SHIFT>(f[1], p, hi_v);
-    const uint32_t t2 = fp8_code_top_byte<SHIFT>(f[2], p, hi_v), t3 = fp8_code_top_byte<SHIFT>(f[3], p, hi_v);
-    // selector bytes: 0-3 pick a byte of the second operand, 4-7 of the first, 0x0c gives zero
-    const uint32_t p01 = __builtin_amdgcn_perm(t1, t0, 0x0c0c0703u);
-    const uint32_t p23 = __builtin_amdgcn_perm(t3, t2, 0x07030c0cu);
-    return p01 | p23;
-}
-template <int SHIFT>
-__device__ inline float fp8_to_f32(uint32_t b, const Fp8Params p) { return __uint_as_float((b << SHIFT) + (uint32_t)p.lo); }
-
-// IEEE half, round to nearest even, saturating at the largest finite half.
-__device__ inline uint32_t half_bits_from_f32(float x) {
-    float c = x > 65504.0f ? 65504.0f : x;
-    return (uint32_t)__half_as_ushort(__float2half_rn(c));
-}
-
-// One table entry: sum over the sub-vector, left to right, of (cb - rq)^2 with one rounding per
-// step (subtract, then fused multiply-add into the running sum).
-template <int M>
-__device__ inline float lut_entry(const float* cbv, const float* rq) {
-    float acc = 0.f;
-#pragma unroll
-    for (int t = 0; t < M; ++t) {
-        float diff = cbv[t] - rq[t];
-        acc = __builtin_fmaf(diff, diff, acc);
-    }
-    return acc;
-}
-
 template <int LUT>
 __device__ inline void store4(unsigned char* lut, int e, const float f[4], const Fp8Params fp8, int hi_v) {
     if constexpr (LUT == IVFPQ_LUT_FP32) {
@@ -943,13 +461,6 @@ __device__ __forceinline__ void visit_lut_any_m(const float* __restrict__ codebo
         default: visit_lut<0>(codebooks, rq, e_begin, e_end, BITS, m, sink); break;
     }
 }
-
-// Encoding of an 8-bit table as the caller configured it: fixed constants, or a bias chosen per table.
-struct Fp8Mode {
-    Fp8Params fixed;     // constants for the configured bias and rounding
-    int truncate;        // rounding of the encode: 0 nearest (ties up), 1 truncate
-    int per_table;       // 1: the bias follows the largest entry of each table
-};
 
 // Step 3: builds F[pq_dim][ksub] in LDS in the table's dtype; rq must be complete (barrier passed).
 // Ends with a barrier.  Returns the constants the 8-bit lookups decode with (workgroup-uniform).
