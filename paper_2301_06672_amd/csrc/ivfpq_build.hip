@@ -16,8 +16,9 @@
 //   count/offsets/scatter/sort_groups   rows grouped by label, ascending inside a group
 //   update_centres_kernel  ordered float64 mean of every group
 //   residual_rows_kernel   x - centroid of the own cluster (fp32), for the PQ training rows
-//   pq_codes_kernel        nearest codeword per sub-space by float64 distances: training labels, or
-//                          the packed PQ codes of all rows in list order
+//   pq_codes_mfma_kernel, pq_codes_kernel   nearest codeword per sub-space by float64 distances, of the few codewords
+//                          that MFMA ranking values leave or of all: training labels, or the packed PQ codes of
+//                          all rows in list order
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -34,6 +35,8 @@ namespace {
 
 constexpr size_t kRankTileBytes = (size_t)2 << 30;   // ranking values of one tile of rows
 constexpr int SORT_CAP = 4096;                       // elements one workgroup sorts in LDS
+constexpr int kPqTilesPerWave = 4;                   // pq_codes_mfma_kernel: tiles of 32 positions a wave takes
+constexpr int kPqBlockPositions = 4 * 32 * kPqTilesPerWave;      // ... and the positions of a workgroup of four waves
 
 __global__ void fill_u32_kernel(uint32_t* p, size_t n, uint32_t v) {
     size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -472,6 +475,206 @@ pq_codes_kernel(const float* __restrict__ X, const uint32_t* __restrict__ order,
     }
 }
 
+
+// x of the lane 32 below / above: .x is the value that the lower lane of the pair (L, L + 32) holds, .y the upper one's
+__device__ inline uint2 both_halves(uint32_t x) {
+    const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    return make_uint2(r[0], r[1]);
+}
+__device__ inline float2 both_halves(float x) {
+    const uint2 r = both_halves(__float_as_uint(x));
+    return make_float2(__uint_as_float(r.x), __uint_as_float(r.y));
+}
+
+// The same results for sub-spaces of M = 2, 4 or 8 components and 32 codewords or more: the ranking values
+//     a(r, c) = |c|^2 / 2 - r.c
+// of all codewords come from v_mfma_f32_32x32x2_f32 (codewords along the rows, 32 positions along the columns, |c|^2 / 2
+// as the initial accumulator), so a lane holds 16 codewords of ONE position per instruction; only their minimum is
+// taken (two values per three-operand minimum), and of all tiles' minima a lane keeps the two smallest.  a() decides
+// nothing: every run of 16 codewords whose minimum lies within twice the error bound of the smallest is compared by
+// the float64 distances that define the code (all of a lane's runs where its second minimum does as well).
+// Error of a(): the operands are exact, |c|^2 / 2 is rounded once, and each of the M products and sums rounds at the
+// magnitude |c|^2 / 2 + |r||c| <= |r|^2 + |c|^2 =: s at most twice, so |error| < (M + 2) 2^-23 s; the tile's number in the
+// low bits of a minimum moves it by 2^-20 s at most.  The bound takes (M + 8) 2^-22 s, and 1e-30 for operands that the matrix unit may flush as denormal.  Where s is not below 1e37
+// (overflow, infinities, NaN) all codewords are compared in float64.
+// A wave takes 4 tiles of 32 positions, so that the accumulators' initial values are read from LDS once for all four, and
+// an "octet" of 8 components (8 / M sub-spaces) at a time, whose codebooks the workgroup stages (12 KB at most);
+// the code groups of the same positions run on one XCD (workgroup b runs on XCD b % 8), which then
+// fetches their rows once.
+// Bound by the vector ALU (the float64 comparisons and the minima; the matrix instructions take about 0.4 ms of it).
+// 10^6 rows, 64 sub-spaces of two components, 8 bits: 2.05 ms; every codeword in float64 (pq_codes_kernel): 15.2 ms.
+template <int BITS, int M>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3)))
+pq_codes_mfma_kernel(const float* __restrict__ X, const uint32_t* __restrict__ order, const int32_t* __restrict__ labels,
+                     const float* __restrict__ C, const float* __restrict__ codebooks, size_t n_pos, int d, int pq_dim,
+                     int32_t* __restrict__ train_labels, uint32_t* __restrict__ codes32) {
+    static_assert(BITS >= 5 && BITS <= 8 && (M == 2 || M == 4 || M == 8), "whole tiles of 32 codewords, whole octets");
+    constexpr int G = (BITS % 8 == 0) ? 8 : (BITS % 4 == 0) ? 4 : (BITS % 2 == 0) ? 2 : 1;   // gcd(BITS, 32)
+    constexpr int SPW = 32 / G, WPG = BITS / G, KSUB = 1 << BITS;
+    constexpr int NT = KSUB / 32, T = kPqTilesPerWave;
+    constexpr int SO = 8 / M, OPG = SPW * M / 8;             // sub-spaces per octet, octets per code group
+    __shared__ __attribute__((aligned(16))) float book[SO * KSUB * M];
+    __shared__ __attribute__((aligned(16))) float half_norm[SO * KSUB];
+    __shared__ uint32_t norm_max[2][SO];                     // bit pattern of the largest |c|^2 / 2, per octet parity
+    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
+    const int n_groups = pq_dim / SPW;
+    const uint32_t rank = blockIdx.x >> 3;
+    const int group = (int)(rank % (uint32_t)n_groups);
+    const size_t block = (size_t)(rank / (uint32_t)n_groups) * 8 + (blockIdx.x & 7);
+    const size_t p0 = block * kPqBlockPositions + (size_t)(tid >> 6) * (32 * T) + l32;
+    if (block * kPqBlockPositions >= n_pos) return;          // the grid is padded to 8 position blocks
+    uint32_t row[T];
+    int32_t label[T];
+#pragma unroll
+    for (int i = 0; i < T; ++i) {
+        const size_t p = p0 + 32 * i < n_pos ? p0 + 32 * i : n_pos - 1;
+        row[i] = order ? order[p] : (uint32_t)p;
+        label[i] = C ? labels[row[i]] : 0;
+    }
+    unsigned long long acc_bits[T];                          // codes waiting to fill a word, lowest sub-space in the low bits
+#pragma unroll
+    for (int i = 0; i < T; ++i) acc_bits[i] = 0;
+    int have = 0, word = 0;
+    const size_t words_per_code = (size_t)n_groups * WPG;
+    if (tid < 2 * SO) norm_max[tid / SO][tid % SO] = 0u;
+    for (int oct = 0; oct < OPG; ++oct) {
+        const int j0 = group * SPW + oct * SO, par = oct & 1;
+        // this lane's operands: the negated residual, components 2 u + half of the octet
+        float b[T][4];
+#pragma unroll
+        for (int i = 0; i < T; ++i) {
+            const float4* x = reinterpret_cast<const float4*>(X + (size_t)row[i] * d + (size_t)j0 * M);
+            const float4* c = reinterpret_cast<const float4*>(C + (size_t)label[i] * d + (size_t)j0 * M);
+#pragma unroll
+            for (int v = 0; v < 2; ++v) {
+                const float4 xv = x[v];
+                float4 cv = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (C) cv = c[v];
+                b[i][2 * v] = half ? cv.y - xv.y : cv.x - xv.x;
+                b[i][2 * v + 1] = half ? cv.w - xv.w : cv.z - xv.z;
+            }
+        }
+        __syncthreads();                                     // the previous octet's codebooks are no longer read
+        for (int e = tid; e < SO * KSUB; e += 256) {
+            const float* src = codebooks + (size_t)j0 * KSUB * M + (size_t)e * M;
+            double n2 = 0.0;
+#pragma unroll
+            for (int t = 0; t < M; ++t) {
+                const float v = src[t];
+                book[e * M + t] = v;
+                n2 += (double)v * (double)v;
+            }
+            const float h = (float)(0.5 * n2);
+            half_norm[e] = h;
+            uint32_t bits = __float_as_uint(h) & 0x7FFFFFFFu;
+            constexpr int RUN = KSUB < 64 ? KSUB : 64;       // lanes whose codewords belong to one sub-space
+#pragma unroll
+            for (int off = RUN / 2; off > 0; off >>= 1) {
+                const uint32_t o = (uint32_t)__shfl_xor((int)bits, off, kWave);
+                bits = bits > o ? bits : o;
+            }
+            if ((lane & (RUN - 1)) == 0) atomicMax(&norm_max[par][e / KSUB], bits);
+        }
+        if (tid < SO) norm_max[par ^ 1][tid] = 0u;
+        __syncthreads();
+#pragma unroll
+        for (int s = 0; s < SO; ++s) {
+            // the two smallest tile minima of this lane (over its 16 codewords of every tile), the tile in the low three bits
+            float low1[T], low2[T];
+#pragma unroll
+            for (int i = 0; i < T; ++i) { low1[i] = 3.4e38f; low2[i] = 3.4e38f; }
+#pragma unroll 1
+            for (int t = 0; t < NT; ++t) {
+                floatx16 init;
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const float4 h4 = *reinterpret_cast<const float4*>(&half_norm[s * KSUB + t * 32 + 8 * g + 4 * half]);
+                    init[4 * g] = h4.x; init[4 * g + 1] = h4.y; init[4 * g + 2] = h4.z; init[4 * g + 3] = h4.w;
+                }
+                float a[M / 2];
+#pragma unroll
+                for (int k = 0; k < M / 2; ++k) a[k] = book[(s * KSUB + t * 32 + l32) * M + 2 * k + half];
+#pragma unroll
+                for (int i = 0; i < T; ++i) {
+                    floatx16 acc = init;
+#pragma unroll
+                    for (int k = 0; k < M / 2; ++k)
+                        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[k], b[i][s * (M / 2) + k], acc, 0, 0, 0);
+                    float m = __builtin_fminf(acc[0], acc[1]);
+#pragma unroll
+                    for (int v = 2; v < 16; ++v) m = __builtin_fminf(m, acc[v]);
+                    m = __uint_as_float((__float_as_uint(m) & ~7u) | (uint32_t)t);
+                    low2[i] = __builtin_amdgcn_fmed3f(low1[i], m, low2[i]);
+                    low1[i] = __builtin_fminf(low1[i], m);
+                }
+            }
+            const float c2_max = 2.f * __uint_as_float(norm_max[par][s]);
+#pragma unroll
+            for (int i = 0; i < T; ++i) {
+                float part = 0.f;
+#pragma unroll
+                for (int k = 0; k < M / 2; ++k) part = __builtin_fmaf(b[i][s * (M / 2) + k], b[i][s * (M / 2) + k], part);
+                const float2 g2 = both_halves(low1[i]), part2 = both_halves(part);
+                const float size = part2.x + part2.y + c2_max;
+                float limit = __builtin_fminf(g2.x, g2.y) + (size * ((float)(M + 8) * 4.7683716e-07f) + 2e-30f);
+                limit += __builtin_fabsf(limit) * 2.3841858e-07f;
+                // bit t + 8 h: the 16 codewords of tile t that the lanes of half h ranked have to be compared
+                uint32_t mine = low1[i] <= limit ? 1u << (__float_as_uint(low1[i]) & 7u) : 0u;
+                if (low2[i] <= limit || !(size < 1e37f)) mine = (1u << NT) - 1u;
+                const uint2 mask2 = both_halves(mine);
+                uint32_t mask = mask2.x | (mask2.y << 8);
+                double r[M];
+#pragma unroll
+                for (int k = 0; k < M / 2; ++k) {
+                    const float2 r2 = both_halves(b[i][s * (M / 2) + k]);
+                    r[2 * k] = -(double)r2.x;
+                    r[2 * k + 1] = -(double)r2.y;
+                }
+                double best = __longlong_as_double(0x7FF0000000000000ll);
+                uint32_t arg = 0u;
+                while (mask) {
+                    const uint32_t run = (uint32_t)__builtin_ctz(mask);
+                    mask &= mask - 1u;
+                    // the lower lane of a pair compares the first eight of the 16 codewords, the upper one the others
+                    const uint32_t first = (run & 7u) * 32u + (run >> 3) * 4u + 16u * half;
+                    double run_best = __longlong_as_double(0x7FF0000000000000ll);
+                    uint32_t run_arg = 0u;
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const uint32_t code = first + (u >> 2) * 8u + (u & 3);
+                        const float* c = book + ((size_t)s * KSUB + code) * M;
+                        double dist = 0.0;
+#pragma unroll
+                        for (int t = 0; t < M; ++t) { const double diff = r[t] - (double)c[t]; dist += diff * diff; }
+                        if (dist < run_best) { run_best = dist; run_arg = code; }
+                    }
+                    if (run_best < best || (run_best == best && run_arg < arg)) { best = run_best; arg = run_arg; }
+                }
+                const unsigned long long bb = (unsigned long long)__double_as_longlong(best);
+                const uint2 lo2 = both_halves((uint32_t)bb), hi2 = both_halves((uint32_t)(bb >> 32)), arg2 = both_halves(arg);
+                const double d0 = __longlong_as_double((long long)(((unsigned long long)hi2.x << 32) | lo2.x));
+                const double d1 = __longlong_as_double((long long)(((unsigned long long)hi2.y << 32) | lo2.y));
+                arg = (d1 < d0 || (d1 == d0 && arg2.y < arg2.x)) ? arg2.y : arg2.x;
+                const size_t p = p0 + 32 * i;
+                if (train_labels && half == (i & 1) && p < n_pos) train_labels[p * pq_dim + j0 + s] = (j0 + s) * KSUB + (int32_t)arg;
+                acc_bits[i] |= (unsigned long long)arg << have;
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            have += BITS;
+            if (have >= 32) {
+#pragma unroll
+                for (int i = 0; i < T; ++i) {
+                    const size_t p = p0 + 32 * i;
+                    if (codes32 && half == (i & 1) && p < n_pos) codes32[p * words_per_code + (size_t)group * WPG + word] = (uint32_t)acc_bits[i];
+                    acc_bits[i] >>= 32;
+                }
+                have -= 32;
+                ++word;
+            }
+        }
+    }
+}
+
 // ---- host side ----------------------------------------------------------------------------------
 inline int sub_spaces_per_group(int bits) { return bits % 8 == 0 ? 4 : bits % 4 == 0 ? 8 : bits % 2 == 0 ? 16 : 32; }
 
@@ -643,12 +846,34 @@ int launch_pq_codes(const BuildPlan& P, const float* X, const uint32_t* order, c
         HIP_TRY(hipGetLastError());
         return IVFPQ_OK;
     };
+    // On the matrix cores where a sub-space has 2, 4 or 8 components and 32 codewords or more and rows are read 16 bytes at a
+    // time (8 bits, m = 2, 10^6 x 64: 2.05 ms against 15.2 ms); 16 codewords are as many as a float64 comparison of one run
+    // takes here, so 4-bit codes have nothing to gain.
+    auto mfma = [&](auto kernel) -> int {
+        const size_t blocks = (n_pos + kPqBlockPositions - 1) / kPqBlockPositions;
+        const size_t grid_x = (blocks + 7) / 8 * 8 * (size_t)(P.pq_dim / spw);
+        if (grid_x > 0x7FFFFFFFull) return fail(IVFPQ_EUNSUPPORTED, "encoding the rows would need %zu workgroups", grid_x);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)grid_x), dim3(256), 0, st, X, order, labels, C, codebooks, n_pos, P.d, P.pq_dim,
+                           train_labels, codes32);
+        HIP_TRY(hipGetLastError());
+        return IVFPQ_OK;
+    };
+    const bool aligned = P.d % 4 == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0;
+    auto pick = [&](auto bits) -> int {
+        constexpr int B = decltype(bits)::value;
+        if constexpr (B >= 5) {
+            if (aligned && P.m == 2) return mfma(pq_codes_mfma_kernel<B, 2>);
+            if (aligned && P.m == 4) return mfma(pq_codes_mfma_kernel<B, 4>);
+            if (aligned && P.m == 8) return mfma(pq_codes_mfma_kernel<B, 8>);
+        }
+        return go(pq_codes_kernel<B>);
+    };
     switch (P.pq_bits) {
-        case 8: return go(pq_codes_kernel<8>);
-        case 7: return go(pq_codes_kernel<7>);
-        case 6: return go(pq_codes_kernel<6>);
-        case 5: return go(pq_codes_kernel<5>);
-        default: return go(pq_codes_kernel<4>);
+        case 8: return pick(std::integral_constant<int, 8>{});
+        case 7: return pick(std::integral_constant<int, 7>{});
+        case 6: return pick(std::integral_constant<int, 6>{});
+        case 5: return pick(std::integral_constant<int, 5>{});
+        default: return pick(std::integral_constant<int, 4>{});
     }
 }
 

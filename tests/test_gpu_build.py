@@ -105,6 +105,32 @@ def test_build_device_is_identical_to_oracle_build(P, n, d, n_lists, pq_dim, pq_
     _assert_same_index(gidx, oidx)
 
 
+@pytest.mark.parametrize("m,pq_bits", [(2, 8), (4, 8), (8, 8), (4, 7), (8, 7), (2, 6), (4, 6), (8, 6), (2, 5), (4, 5), (8, 5)])
+@pytest.mark.parametrize("n,kind", [(255, "intgrid"), (513, "gauss"), (4097, "huge"), (1500, "offset")])
+def test_codes_on_the_matrix_cores(P, m, pq_bits, n, kind):
+    # workgroups of 512 positions, ragged at both ends; tied codewords (intgrid, and more codewords than distinct
+    # rows); magnitudes whose squares overflow fp32, so that every codeword is compared in float64 (huge); residuals
+    # that are small beside their codewords' error bound (offset: one list, far from the rows' mean)
+    pq_dim = 32 if pq_bits in (5, 7) else 16
+    d, n_lists = pq_dim * m, 1 if kind == "offset" else 4
+    x = _data(n, d, 7 * n + m, 0.0, "intgrid" if kind == "intgrid" else "gauss")
+    if kind == "huge":
+        x = (x * np.float32(4e18)).astype(np.float32)
+    if kind == "offset":
+        x[::2] += 300.0
+    n_t = min(n, 700)
+    ct, ci, pt, pi = _rows(n, n_lists, pq_dim, pq_bits, n_t, n_t, salt=n + d) if n_t >= (1 << pq_bits) else (None,) * 4
+    if ct is None:
+        ct = pt = np.arange(n)
+        ci = np.arange(n_lists) * (n // n_lists)
+        pi = np.tile(np.arange(1 << pq_bits) % n, (pq_dim, 1))      # the same row twice: equal codewords
+    _step(f"codes n={n} m={m} p={pq_bits} {kind}")
+    gidx = P.Index.ivfpq_build_device(x, n_lists, pq_dim, pq_bits, 2, coarse_train_rows=ct, coarse_init_rows=ci,
+                                      pq_train_rows=pt, pq_init_rows=pi)
+    oidx = oracle.build_index(x, n_lists, pq_dim, pq_bits, 2, ci, pi, coarse_train_rows=ct, pq_train_rows=pt)
+    _assert_same_index(gidx, oidx)
+
+
 def test_build_device_default_draws_and_search(P):
     # rows drawn from the seed inside the library: a valid index that searches as well as the host-built one
     w = si.WORKLOADS["tiny"]
