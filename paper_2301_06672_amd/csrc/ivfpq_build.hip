@@ -13,9 +13,10 @@
 //                          few centres, else the two smallest of every strip of 32 / 64 centres)
 //   nearest_kernel, nearest_strips_kernel   per row the smallest ranking value; a second value within the
 //                          rigorous error bound of the first sends the row to exact float64 distances
-//   count/offsets/scatter/sort_groups   rows grouped by label, ascending inside a group
+//   group_count/prefix/offsets/group_scatter   rows grouped by label, ascending inside a group (count_labels/
+//                          scatter_rows/sort_groups for more labels than LDS counters hold)
 //   update_centres_kernel  ordered float64 mean of every group
-//   residual_rows_kernel   x - centroid of the own cluster (fp32), for the PQ training rows
+//   residual_rows_kernel   x - centroid of the own cluster (fp32), for the PQ training rows, by row and by sub-space
 //   pq_codes_mfma_kernel, pq_codes_kernel   nearest codeword per sub-space by float64 distances, of the few codewords
 //                          that MFMA ranking values leave or of all: training labels, or the packed PQ codes of
 //                          all rows in list order
@@ -280,32 +281,129 @@ nearest_strips_kernel(const StripSummary* __restrict__ S, int strip_w, const flo
     }
 }
 
+// Items grouped by label, ascending inside a group, for n_sets independent sets of n items with labels 0..k-1
+// (labels[set][item]): a counting sort that keeps the order.  The items of a set are cut into chunks:
+//   group_count_kernel    counts[set][chunk][label], in LDS
+//   group_prefix_kernel   counts -> number of items of the label in the earlier chunks; totals[set][label]
+//   offsets_kernel        first item of every group, over all sets
+//   group_scatter_kernel  a wave walks through a chunk, 64 items at a time; lanes with the same label find each other
+//                         by ballots over the label's bits, and the label's cursor in LDS gives the place
+// Nothing is sorted and no counter is shared between workgroups.  10^6 labels of 1024: 80 us (counted and placed
+// by device-wide atomics, then every group sorted: 640 us); 64 x 262,144 of 256, pairs moved along: 260 us (1300 us).
+// The labels' counters have to fit the LDS (k <= kGroupLabelsMax); beyond that the atomics and the sort are used.
+constexpr int kGroupLabelsMax = 32768;
+inline size_t group_chunk(size_t n, int k) {
+    // long enough for the counters of a chunk to be worth their passes, at most 512 chunks
+    const size_t c = std::max<size_t>(std::max<size_t>(4096, (n + 511) / 512), (size_t)k);
+    return (c + 63) / 64 * 64;
+}
+inline size_t group_chunks(size_t n, int k) { return (n + group_chunk(n, k) - 1) / group_chunk(n, k); }
+
+__global__ void __launch_bounds__(256)
+group_count_kernel(const int32_t* __restrict__ labels, size_t n, int k, size_t chunk, uint32_t n_chunks, uint32_t* __restrict__ counts) {
+    extern __shared__ uint32_t hist[];
+    const size_t set = blockIdx.x / n_chunks, lo = (size_t)(blockIdx.x % n_chunks) * chunk, hi = lo + chunk < n ? lo + chunk : n;
+    for (int l = threadIdx.x; l < k; l += 256) hist[l] = 0u;
+    __syncthreads();
+    const int32_t* in = labels + set * n;
+    for (size_t i = lo + threadIdx.x; i < hi; i += 256) atomicAdd(&hist[in[i]], 1u);
+    __syncthreads();
+    for (int l = threadIdx.x; l < k; l += 256) counts[(size_t)blockIdx.x * k + l] = hist[l];
+}
+
+__global__ void __launch_bounds__(64)
+group_prefix_kernel(uint32_t* __restrict__ counts, size_t n_groups, int k, uint32_t n_chunks, uint32_t* __restrict__ totals) {
+    const size_t g = (size_t)blockIdx.x * 64 + threadIdx.x;
+    if (g >= n_groups) return;
+    const size_t set = g / (uint32_t)k;
+    uint32_t* at = counts + set * n_chunks * k + (g - set * (uint32_t)k);
+    uint32_t sum = 0;
+    for (uint32_t c = 0; c < n_chunks; c += 16) {
+        uint32_t v[16];
+#pragma unroll
+        for (uint32_t u = 0; u < 16; ++u) v[u] = c + u < n_chunks ? at[(size_t)(c + u) * k] : 0u;
+#pragma unroll
+        for (uint32_t u = 0; u < 16; ++u) {
+            if (c + u < n_chunks) at[(size_t)(c + u) * k] = sum;
+            sum += v[u];
+        }
+    }
+    totals[g] = sum;
+}
+
+// order: the items' numbers in their set, in group order (when src is null); else the m components src[set][item][:] of
+// every item, in that order, to values[][m].
+__global__ void __launch_bounds__(64)
+group_scatter_kernel(const int32_t* __restrict__ labels, size_t n, int k, int label_bits, size_t chunk, uint32_t n_chunks,
+                     const uint32_t* __restrict__ counts, const int64_t* __restrict__ offsets, uint32_t* __restrict__ order,
+                     const float* __restrict__ src, int m, float* __restrict__ values) {
+    extern __shared__ uint32_t cursor[];
+    const int lane = threadIdx.x;
+    const size_t set = blockIdx.x / n_chunks, lo = (size_t)(blockIdx.x % n_chunks) * chunk, hi = lo + chunk < n ? lo + chunk : n;
+    for (int l = lane; l < k; l += 64) cursor[l] = (uint32_t)offsets[set * (uint32_t)k + l] + counts[(size_t)blockIdx.x * k + l];
+    __syncthreads();
+    const int32_t* in = labels + set * n;
+    const unsigned long long below = (1ull << lane) - 1ull;
+    int32_t next = lo + lane < hi ? in[lo + lane] : 0;
+    for (size_t i0 = lo; i0 < hi; i0 += 64) {
+        const size_t i = i0 + lane;
+        const bool valid = i < hi;
+        const int32_t label = next;
+        if (i + 64 < hi) next = in[i + 64];
+        unsigned long long same = __ballot(valid);
+        for (int b = 0; b < label_bits; ++b) {
+            const bool bit = (label >> b) & 1;
+            const unsigned long long set_lanes = __ballot(bit);
+            same &= bit ? set_lanes : ~set_lanes;
+        }
+        const uint32_t at = cursor[label] + (uint32_t)__popcll(same & below);
+        __syncthreads();                                     // one wave: orders the read above and the write below
+        if (valid && (same >> lane) == 1ull) cursor[label] = at + 1u;
+        __syncthreads();
+        if (valid) {
+            if (src) {
+                const float* from = src + (set * n + i) * (uint32_t)m;
+                float* to = values + (size_t)at * (uint32_t)m;
+                if (m == 2) *reinterpret_cast<float2*>(to) = *reinterpret_cast<const float2*>(from);
+                else if (m == 4) *reinterpret_cast<float4*>(to) = *reinterpret_cast<const float4*>(from);
+                else for (int t = 0; t < m; ++t) to[t] = from[t];
+            } else {
+                order[at] = (uint32_t)i;
+            }
+        }
+    }
+}
+
+// ---- the same with more labels than LDS counters hold: placed by atomics, then sorted -------------------
 __global__ void count_labels_kernel(const int32_t* __restrict__ labels, size_t n, uint32_t* __restrict__ counts) {
     size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) atomicAdd(&counts[labels[i]], 1u);
 }
 
-// offsets[0] = 0, offsets[g+1] = counts[0] + ... + counts[g]; one workgroup
+// offsets[0] = 0, offsets[g+1] = counts[0] + ... + counts[g] (below 2^32 in all); one workgroup
 __global__ void __launch_bounds__(1024)
 offsets_kernel(const uint32_t* __restrict__ counts, int k, int64_t* __restrict__ offsets) {
-    __shared__ unsigned long long part[1024];
-    __shared__ unsigned long long carry;
-    const int tid = threadIdx.x;
-    if (tid == 0) { carry = 0; offsets[0] = 0; }
-    __syncthreads();
+    __shared__ uint32_t wave_sum[16];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    uint32_t carry = 0;
+    if (tid == 0) offsets[0] = 0;
+    uint32_t next = tid < k ? counts[tid] : 0u;
     for (int base = 0; base < k; base += 1024) {
         const int g = base + tid;
-        part[tid] = g < k ? counts[g] : 0u;
-        __syncthreads();
-        for (int off = 1; off < 1024; off <<= 1) {
-            unsigned long long v = tid >= off ? part[tid - off] : 0ull;
-            __syncthreads();
-            part[tid] += v;
-            __syncthreads();
+        uint32_t sum = next;
+        if (g + 1024 < k) next = counts[g + 1024]; else next = 0u;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t o = (uint32_t)__shfl_up((int)sum, off, kWave);
+            if (lane >= off) sum += o;
         }
-        if (g < k) offsets[g + 1] = (int64_t)(carry + part[tid]);
+        if (lane == 63) wave_sum[wave] = sum;
         __syncthreads();
-        if (tid == 1023) carry += part[1023];
+        uint32_t before = 0, all = 0;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) { const uint32_t v = wave_sum[w]; before += w < wave ? v : 0u; all += v; }
+        if (g < k) offsets[g + 1] = (int64_t)(carry + before + sum);
+        carry += all;
         __syncthreads();
     }
 }
@@ -377,38 +475,74 @@ sort_groups_kernel(uint32_t* __restrict__ order, uint32_t* __restrict__ tmp, con
     }
 }
 
-// One wave per group: centre = float64 sum of the members in ascending order / count, rounded to
-// fp32; an empty group keeps its centre.  Item i of `order` is (row, sub) = (i / items_per_row,
-// i % items_per_row); its components are X[row * row_stride + sub * dim + t].
-__global__ void __launch_bounds__(256)
-update_centres_kernel(const float* __restrict__ X, size_t row_stride, int items_per_row, int dim,
-                      const uint32_t* __restrict__ order, const int64_t* __restrict__ offsets, int k,
-                      float* __restrict__ centres) {
-    const int lane = threadIdx.x & 63, g = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (g >= k) return;
+// One lane per (group, component): centre = float64 sum of the members in ascending row order / count, rounded to
+// fp32; an empty group keeps its centre.  GATHER: member i of the order is row order[i] of X, dim components
+// each; otherwise the members' values lie in group order themselves (X[i][dim]).
+// The order of the additions is fixed, so a group is a serial chain: what counts is that the loads of the next
+// kMeanAhead members are in flight at once.  262,144 rows of 128 components in 1024 groups: 80 us; one
+// member at a time, a wave per group: 1500 us.  64 x 262,144 pairs in 64 x 256 groups: 160 us, with the two components on
+// two lanes of a wave per group and the rows gathered 1900 us.
+constexpr int kMeanAhead = 16;
+template <bool GATHER>
+__global__ void __launch_bounds__(64)
+update_centres_kernel(const float* __restrict__ X, const uint32_t* __restrict__ order, const int64_t* __restrict__ offsets,
+                      int k, int dim, float* __restrict__ centres) {
+    const size_t e = (size_t)blockIdx.x * 64 + threadIdx.x;
+    const size_t g = e / (uint32_t)dim;
+    if (g >= (size_t)k) return;
+    const uint32_t t = (uint32_t)(e - g * (uint32_t)dim);
     const size_t lo = (size_t)offsets[g], hi = (size_t)offsets[g + 1];
     if (lo == hi) return;
-    for (int t = lane; t < dim; t += 64) {
-        double acc = 0.0;
-        for (size_t i = lo; i < hi; ++i) {
-            const uint32_t item = order[i];
-            const size_t row = item / (uint32_t)items_per_row, sub = item % (uint32_t)items_per_row;
-            acc += (double)X[row * row_stride + sub * dim + t];
-        }
-        centres[(size_t)g * dim + t] = (float)(acc / (double)(hi - lo));
+    const size_t last = hi - 1;
+    double acc = 0.0;
+    uint32_t row[kMeanAhead];
+    if constexpr (GATHER) {
+#pragma unroll
+        for (int u = 0; u < kMeanAhead; ++u) row[u] = order[lo + u < last ? lo + u : last];
     }
+    for (size_t i = lo; i < hi; i += kMeanAhead) {
+        float v[kMeanAhead];
+#pragma unroll
+        for (int u = 0; u < kMeanAhead; ++u) {
+            const size_t at = GATHER ? (size_t)row[u] : (i + u < last ? i + u : last);
+            v[u] = X[at * (uint32_t)dim + t];
+        }
+        if constexpr (GATHER) {
+            const size_t n = i + kMeanAhead;
+#pragma unroll
+            for (int u = 0; u < kMeanAhead; ++u) row[u] = order[n + u < last ? n + u : last];
+        }
+        // (a sum that began with 0.0 is never -0.0, so the zeros past the end change nothing)
+#pragma unroll
+        for (int u = 0; u < kMeanAhead; ++u) acc += i + u < hi ? (double)v[u] : 0.0;
+    }
+    centres[e] = (float)(acc / (double)(hi - lo));
 }
 
-// Rt[i][:] = data[rows[i]][:] - C[labels[rows[i]]][:]   (fp32)
-__global__ void residual_rows_kernel(const float* __restrict__ data, const int64_t* __restrict__ rows, int64_t n_rows,
-                                     const int32_t* __restrict__ labels, const float* __restrict__ C, int d,
-                                     float* __restrict__ Rt) {
-    size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= (size_t)n_rows * d) return;
-    size_t i = e / d;
-    int t = (int)(e - i * d);
-    const int64_t row = rows[i];
-    Rt[e] = data[(size_t)row * d + t] - C[(size_t)labels[row] * d + t];
+// Rt[i][:] = data[rows[i]][:] - C[labels[rows[i]]][:]   (fp32), and the same by sub-space, Rs[j][i][:] (m components each).
+// A workgroup takes kResidualRows rows x `slab` components (whole sub-spaces) and turns them round in LDS.
+constexpr int kResidualRows = 32;
+__global__ void __launch_bounds__(256)
+residual_rows_kernel(const float* __restrict__ data, const int64_t* __restrict__ rows, int64_t n_rows,
+                     const int32_t* __restrict__ labels, const float* __restrict__ C, int d, int m, int slab,
+                     float* __restrict__ Rt, float* __restrict__ Rs) {
+    extern __shared__ float part[];            // [kResidualRows][slab + 1]
+    const int n_slabs = (d + slab - 1) / slab;
+    const int64_t i0 = (int64_t)(blockIdx.x / (unsigned)n_slabs) * kResidualRows;
+    const int t0 = (int)(blockIdx.x % (unsigned)n_slabs) * slab;
+    const int width = d - t0 < slab ? d - t0 : slab, n = (int)(n_rows - i0 < kResidualRows ? n_rows - i0 : kResidualRows);
+    for (int e = threadIdx.x; e < n * width; e += 256) {
+        const int i = e / width, t = e - i * width;
+        const int64_t row = rows[i0 + i];
+        const float r = data[(size_t)row * d + t0 + t] - C[(size_t)labels[row] * d + t0 + t];
+        Rt[(size_t)(i0 + i) * d + t0 + t] = r;
+        part[i * (slab + 1) + t] = r;
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < n * width; e += 256) {
+        const int j = e / (n * m), rest = e - j * (n * m), i = rest / m, t = rest - i * m;
+        Rs[((size_t)(t0 / m + j) * n_rows + i0 + i) * m + t] = part[i * (slab + 1) + j * m + t];
+    }
 }
 
 // Nearest codeword per sub-space.  The codes of a vector are one bit string, sub-space j in bits
@@ -416,8 +550,7 @@ __global__ void residual_rows_kernel(const float* __restrict__ data, const int64
 // (SPG sub-spaces in WPG words: 8 in 1 for 4-bit codes, 4 in 1 for 8-bit, 32 in 5 / 16 in 3 / 32 in 7
 // for 5 / 6 / 7 bits).  A thread handles position p (blockIdx.x * 256 + threadIdx.x) and the code
 // group blockIdx.y; the group's codebooks sit in LDS.  Row of position p: order[p] (or p); residual = X[row] - C[labels[row]] in
-// fp32 (or X[row] itself when C is null).  Outputs (either may be null): train_labels[p][j] =
-// j * ksub + code; codes32[p][...] = the group's words of the packed code.
+// fp32 (or X[row] itself when C is null).  Outputs (either may be null): train_labels[j][p] = code; codes32[p][...] = the group's words of the packed code.
 template <int BITS>
 __global__ void __launch_bounds__(256)
 pq_codes_kernel(const float* __restrict__ X, const uint32_t* __restrict__ order, const int32_t* __restrict__ labels,
@@ -463,7 +596,7 @@ pq_codes_kernel(const float* __restrict__ X, const uint32_t* __restrict__ order,
                 if (dist < best) { best = dist; arg = code; }
             }
         }
-        if (train_labels) train_labels[p * pq_dim + j] = j * KSUB + arg;
+        if (train_labels) train_labels[(size_t)j * n_pos + p] = arg;
         acc_bits |= (unsigned long long)arg << have;
         have += BITS;
         if (have >= 32) {
@@ -656,7 +789,7 @@ pq_codes_mfma_kernel(const float* __restrict__ X, const uint32_t* __restrict__ o
                 const double d1 = __longlong_as_double((long long)(((unsigned long long)hi2.y << 32) | lo2.y));
                 arg = (d1 < d0 || (d1 == d0 && arg2.y < arg2.x)) ? arg2.y : arg2.x;
                 const size_t p = p0 + 32 * i;
-                if (train_labels && half == (i & 1) && p < n_pos) train_labels[p * pq_dim + j0 + s] = (j0 + s) * KSUB + (int32_t)arg;
+                if (train_labels && half == (i & 1) && p < n_pos) train_labels[(size_t)(j0 + s) * n_pos + p] = (int32_t)arg;
                 acc_bits[i] |= (unsigned long long)arg << have;
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -689,7 +822,7 @@ struct BuildPlan {
     // offsets into the workspace
     bool use_strips;                // nearest centres from strip summaries instead of all ranking values
     size_t Xt, A, S, split, C, cnorm, cmax, labels_t, labels_all, order, tmp, counts, cursor, offsets, ct_rows, pt_rows,
-           init_rows, Rt, pq_labels, codebooks, codes, total;
+           init_rows, Rt, Rs, pq_labels, codebooks, codes, total;
 };
 
 // Scratch of the nearest-centre step for up to n_rows_max rows against k centres: the tile height and
@@ -713,24 +846,26 @@ BuildPlan make_build_plan(int64_t n, int d, int n_lists, int pq_dim, int pq_bits
     BuildPlan P{};
     P.n = n; P.n_ct = n_ct; P.n_pt = n_pt; P.d = d; P.n_lists = n_lists; P.pq_dim = pq_dim; P.pq_bits = pq_bits;
     P.m = d / pq_dim; P.ksub = 1 << pq_bits;
-    P.n_group = std::max<size_t>((size_t)n, (size_t)n_pt * pq_dim);
+    P.n_group = std::max<size_t>((size_t)n, (size_t)n_ct);
     P.k_group = std::max<size_t>((size_t)n_lists, (size_t)pq_dim * P.ksub);
     size_t at = 0;
     auto take = [&](size_t bytes) { size_t o = at; at = align_up(at + bytes); return o; };
-    P.Xt = take((size_t)n_ct * d * 4);
+    P.Xt = take((size_t)std::max(n_ct, n_pt) * d * 4);     // the cluster training rows; later the sub-vectors in group order
     plan_nearest(P, (size_t)std::max<int64_t>(n, n_ct), n_lists, d, take);
     P.C = take((size_t)n_lists * d * 4);
     P.labels_t = take((size_t)n_ct * 4);
     P.labels_all = take((size_t)n * 4);
     P.order = take(P.n_group * 4);
-    P.tmp = take(P.n_group * 4);
-    P.counts = take(P.k_group * 4);
+    P.tmp = take(n_lists > kGroupLabelsMax ? P.n_group * 4 : 0);
+    const size_t coarse_counts = std::max(group_chunks((size_t)n, n_lists), group_chunks((size_t)n_ct, n_lists)) * n_lists;
+    P.counts = take(std::max<size_t>(std::max<size_t>(P.k_group, coarse_counts), group_chunks((size_t)n_pt, P.ksub) * P.ksub * pq_dim) * 4);
     P.cursor = take(P.k_group * 4);
     P.offsets = take((P.k_group + 1) * 8);
     P.ct_rows = take((size_t)n_ct * 8);
     P.pt_rows = take((size_t)n_pt * 8);
     P.init_rows = take(P.k_group * 8);
     P.Rt = take((size_t)n_pt * d * 4);
+    P.Rs = take((size_t)n_pt * d * 4);
     P.pq_labels = take((size_t)n_pt * pq_dim * 4);
     P.codebooks = take((size_t)pq_dim * P.ksub * P.m * 4);
     P.codes = take((size_t)n * (pq_dim * pq_bits / 8));
@@ -767,7 +902,7 @@ int check_build_plan(const BuildPlan& P) {
     if (P.use_strips && P.tile_rows * strips >= ((size_t)1 << 32))
         return fail(IVFPQ_EUNSUPPORTED, "internal: %zu strip summaries per tile (limit 2^32)", P.tile_rows * strips);
     const size_t sections[] = {P.Xt, P.A, P.S, P.split, P.cnorm, P.cmax, P.C, P.labels_t, P.labels_all, P.order, P.tmp, P.counts,
-                               P.cursor, P.offsets, P.ct_rows, P.pt_rows, P.init_rows, P.Rt, P.pq_labels, P.codebooks, P.codes};
+                               P.cursor, P.offsets, P.ct_rows, P.pt_rows, P.init_rows, P.Rt, P.Rs, P.pq_labels, P.codebooks, P.codes};
     size_t prev = 0;
     for (size_t off : sections) {
         if (off % kAlign != 0 || off < prev || off > P.total)
@@ -808,13 +943,34 @@ int assign_rows_device(const BuildPlan& P, unsigned char* ws, const float* X, si
     return IVFPQ_OK;
 }
 
-// order = items grouped by label (ascending inside a group), offsets = group boundaries
-int group_by_label(const BuildPlan& P, unsigned char* ws, const int32_t* labels, size_t n_items, int k, hipStream_t st) {
+// order = items grouped by label (ascending inside a group), offsets = group boundaries; n_sets sets of n_items labels
+// 0..k-1 each, one after the other.  With src (m components per item) the items' values are written in that order
+// instead (n_sets > 1 and src only where k <= kGroupLabelsMax).
+int group_by_label(const BuildPlan& P, unsigned char* ws, const int32_t* labels, size_t n_items, int k, hipStream_t st,
+                   int n_sets = 1, const float* src = nullptr, int m = 0, float* values = nullptr) {
     uint32_t* counts = (uint32_t*)(ws + P.counts);
     uint32_t* cursor = (uint32_t*)(ws + P.cursor);
     int64_t* offsets = (int64_t*)(ws + P.offsets);
     uint32_t* order = (uint32_t*)(ws + P.order);
     uint32_t* tmp = (uint32_t*)(ws + P.tmp);
+    if (n_items > 0 && k <= kGroupLabelsMax) {
+        const size_t chunk = group_chunk(n_items, k), n_chunks = group_chunks(n_items, k), n_groups = (size_t)n_sets * k;
+        int label_bits = 1;
+        while (label_bits < 31 && (1 << label_bits) < k) ++label_bits;
+        const dim3 grid((unsigned)(n_sets * n_chunks));
+        if (int s = allow_full_lds(group_count_kernel)) return s;
+        if (int s = allow_full_lds(group_scatter_kernel)) return s;
+        hipLaunchKernelGGL(group_count_kernel, grid, dim3(256), (size_t)k * 4, st, labels, n_items, k, chunk, (uint32_t)n_chunks, counts);
+        HIP_TRY(hipGetLastError());
+        hipLaunchKernelGGL(group_prefix_kernel, dim3(blocks_for(n_groups, 64)), dim3(64), 0, st, counts, n_groups, k, (uint32_t)n_chunks, cursor);
+        HIP_TRY(hipGetLastError());
+        hipLaunchKernelGGL(offsets_kernel, dim3(1), dim3(1024), 0, st, cursor, (int)n_groups, offsets);
+        HIP_TRY(hipGetLastError());
+        hipLaunchKernelGGL(group_scatter_kernel, grid, dim3(64), (size_t)k * 4, st, labels, n_items, k, label_bits, chunk,
+                           (uint32_t)n_chunks, counts, offsets, order, src, m, values);
+        HIP_TRY(hipGetLastError());
+        return IVFPQ_OK;
+    }
     if (int s = fill_u32(counts, (size_t)k, 0u, st)) return s;
     if (int s = fill_u32(cursor, (size_t)k, 0u, st)) return s;
     if (n_items > 0) {
@@ -1000,6 +1156,7 @@ int build_device_impl(const float* d_data, int64_t n, int32_t d, int32_t n_lists
     int64_t* d_pt_rows = (int64_t*)(ws + P.pt_rows);
     int64_t* d_init = (int64_t*)(ws + P.init_rows);
     float* Rt = (float*)(ws + P.Rt);
+    float* Rs = (float*)(ws + P.Rs);
     int32_t* pq_labels = (int32_t*)(ws + P.pq_labels);
     float* codebooks = (float*)(ws + P.codebooks);
     uint32_t* codes32 = (uint32_t*)(ws + P.codes);
@@ -1015,8 +1172,8 @@ int build_device_impl(const float* d_data, int64_t n, int32_t d, int32_t n_lists
     for (int it = 0; it < kmeans_iters; ++it) {
         if (int s = assign_rows_device(P, ws, Xt, (size_t)n_ct, C, n_lists, labels_t, st)) return s;
         if (int s = group_by_label(P, ws, labels_t, (size_t)n_ct, n_lists, st)) return s;
-        hipLaunchKernelGGL(update_centres_kernel, dim3(blocks_for((size_t)n_lists, 4)), dim3(256), 0, st, Xt, (size_t)d, 1, d,
-                           order, offsets, n_lists, C);
+        hipLaunchKernelGGL(update_centres_kernel<true>, dim3(blocks_for((size_t)n_lists * d, 64)), dim3(64), 0, st, Xt, order, offsets,
+                           n_lists, d, C);
         HIP_TRY(hipGetLastError());
     }
     // membership of every row
@@ -1025,17 +1182,19 @@ int build_device_impl(const float* d_data, int64_t n, int32_t d, int32_t n_lists
     // (2) + (3) residuals of the PQ training rows, one Lloyd k-means per sub-space (all sub-spaces at once)
     HIP_TRY(hipMemcpyAsync(d_pt_rows, pt_rows.data(), (size_t)n_pt * 8, hipMemcpyHostToDevice, st));
     HIP_TRY(hipMemcpyAsync(d_init, pt_init.data(), (size_t)pq_dim * ksub * 8, hipMemcpyHostToDevice, st));
-    hipLaunchKernelGGL(residual_rows_kernel, dim3(blocks_for((size_t)n_pt * d, 256)), dim3(256), 0, st, d_data, d_pt_rows, n_pt,
-                       labels_all, C, d, Rt);
+    const int slab = m <= 64 ? m * (64 / m) : m;
+    if (int s = allow_full_lds(residual_rows_kernel)) return s;
+    hipLaunchKernelGGL(residual_rows_kernel, dim3(blocks_for((size_t)n_pt, kResidualRows) * (unsigned)((d + slab - 1) / slab)), dim3(256),
+                       (size_t)kResidualRows * (slab + 1) * 4, st, d_data, d_pt_rows, n_pt, labels_all, C, d, m, slab, Rt, Rs);
     HIP_TRY(hipGetLastError());
     hipLaunchKernelGGL(init_codebooks_kernel, dim3(blocks_for((size_t)pq_dim * ksub * m, 256)), dim3(256), 0, st, Rt, d_init,
                        pq_dim, ksub, m, d, codebooks);
     HIP_TRY(hipGetLastError());
     for (int it = 0; it < kmeans_iters; ++it) {
         if (int s = launch_pq_codes(P, Rt, nullptr, nullptr, nullptr, codebooks, (size_t)n_pt, pq_labels, nullptr, st)) return s;
-        if (int s = group_by_label(P, ws, pq_labels, (size_t)n_pt * pq_dim, pq_dim * ksub, st)) return s;
-        hipLaunchKernelGGL(update_centres_kernel, dim3(blocks_for((size_t)pq_dim * ksub, 4)), dim3(256), 0, st, Rt, (size_t)d,
-                           pq_dim, m, order, offsets, pq_dim * ksub, codebooks);
+        if (int s = group_by_label(P, ws, pq_labels, (size_t)n_pt, ksub, st, pq_dim, Rs, m, Xt)) return s;
+        hipLaunchKernelGGL(update_centres_kernel<false>, dim3(blocks_for((size_t)pq_dim * ksub * m, 64)), dim3(64), 0, st, Xt,
+                           (const uint32_t*)nullptr, offsets, pq_dim * ksub, m, codebooks);
         HIP_TRY(hipGetLastError());
     }
 

@@ -105,6 +105,21 @@ def test_build_device_is_identical_to_oracle_build(P, n, d, n_lists, pq_dim, pq_
     _assert_same_index(gidx, oidx)
 
 
+def test_more_lists_than_group_counters_fit(P):
+    # above 32,768 lists the rows are grouped by atomics and sorted; one list holds far more than one sort takes in LDS
+    n, d, n_lists = 42_000, 8, 32_800
+    x = _data(n, d, 77)
+    x[3::4] = x[3]
+    ct = np.arange(n_lists)
+    pt = np.arange(1000)
+    pi = np.tile(np.arange(16) * 60, (8, 1))
+    _step(f"build n={n} lists={n_lists}")
+    gidx = P.Index.ivfpq_build_device(x, n_lists, 8, 4, 0, coarse_train_rows=ct, coarse_init_rows=ct, pq_train_rows=pt, pq_init_rows=pi)
+    oidx = oracle.build_index(x, n_lists, 8, 4, 0, ct, pi, coarse_train_rows=ct, pq_train_rows=pt)
+    assert np.diff(oidx.list_offsets).max() > 2 * 4096
+    _assert_same_index(gidx, oidx)
+
+
 @pytest.mark.parametrize("m,pq_bits", [(2, 8), (4, 8), (8, 8), (4, 7), (8, 7), (2, 6), (4, 6), (8, 6), (2, 5), (4, 5), (8, 5)])
 @pytest.mark.parametrize("n,kind", [(255, "intgrid"), (513, "gauss"), (4097, "huge"), (1500, "offset")])
 def test_codes_on_the_matrix_cores(P, m, pq_bits, n, kind):
