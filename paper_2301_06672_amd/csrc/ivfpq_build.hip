@@ -1210,7 +1210,7 @@ int build_device_impl(const float* d_data, int64_t n, int32_t d, int32_t n_lists
     idx->list_offsets.resize((size_t)n_lists + 1);
     idx->codes.resize((size_t)n * cb);
     idx->ids.resize((size_t)n);
-    std::vector<uint32_t> order_h((size_t)n);
+    HostArray<uint32_t> order_h((size_t)n);
     auto copy_out = [&]() -> int {
         HIP_TRY(hipMemcpyAsync(idx->centroids.data(), C, idx->centroids.size() * 4, hipMemcpyDeviceToHost, st));
         HIP_TRY(hipMemcpyAsync(idx->codebooks.data(), codebooks, idx->codebooks.size() * 4, hipMemcpyDeviceToHost, st));

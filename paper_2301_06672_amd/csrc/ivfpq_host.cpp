@@ -7,7 +7,6 @@
 #include <limits>
 #include <memory>
 #include <numeric>
-#include <unordered_set>
 
 #include <omp.h>
 
@@ -65,10 +64,14 @@ std::vector<int64_t> draw_rows(SplitMix64& rng, int64_t n, int k) {
     std::vector<int64_t> rows;
     rows.reserve(k);
     if (n >= k) {
-        std::unordered_set<int64_t> seen;
+        size_t slots = 16;                       // open addressing, at most a quarter full
+        while (slots < (size_t)k * 4) slots <<= 1;
+        std::vector<int64_t> seen(slots, -1);
         while ((int)rows.size() < k) {
-            int64_t r = (int64_t)rng.below((uint64_t)n);
-            if (seen.insert(r).second) rows.push_back(r);
+            const int64_t r = (int64_t)rng.below((uint64_t)n);
+            size_t at = ((uint64_t)r * 0x9E3779B97F4A7C15ull >> 20) & (slots - 1);
+            while (seen[at] >= 0 && seen[at] != r) at = (at + 1) & (slots - 1);
+            if (seen[at] < 0) { seen[at] = r; rows.push_back(r); }
         }
         std::sort(rows.begin(), rows.end());
     } else {
@@ -84,7 +87,15 @@ std::vector<int64_t> stride_rows(int64_t n, int64_t limit) {
         std::iota(rows.begin(), rows.end(), (int64_t)0);
     } else {
         rows.resize(limit);
-        for (int64_t i = 0; i < limit; ++i) rows[i] = (int64_t)(((__int128)i * n) / limit);
+        // floor(i n / limit), one step after the other: the quotient and the remainder of n / limit accumulate
+        const int64_t q = n / limit, r = n % limit;
+        int64_t at = 0, rest = 0;
+        for (int64_t i = 0; i < limit; ++i) {
+            rows[i] = at;
+            at += q;
+            rest += r;
+            if (rest >= limit) { rest -= limit; ++at; }
+        }
     }
     return rows;
 }
@@ -313,8 +324,10 @@ static int from_arrays_impl(int64_t n, int32_t d, int32_t n_lists, int32_t pq_di
     idx->codebooks.assign(codebooks, codebooks + (size_t)pq_dim * ksub * m);
     idx->list_offsets.assign(list_offsets, list_offsets + n_lists + 1);
     if (n > 0) {
-        idx->codes.assign(codes, codes + (size_t)n * cb);
-        idx->ids.assign(ids, ids + n);
+        idx->codes.resize((size_t)n * cb);
+        idx->ids.resize((size_t)n);
+        copy_bytes(idx->codes.data(), codes, (size_t)n * cb);
+        copy_bytes(idx->ids.data(), ids, (size_t)n * sizeof(int64_t));
     }
     finish_import(idx);
     *out = owner.release();
@@ -346,8 +359,8 @@ int ivfpq_index_export(const ivfpq_index_t* index, float* centroids, float* code
     if (centroids) std::memcpy(centroids, index->centroids.data(), index->centroids.size() * sizeof(float));
     if (codebooks) std::memcpy(codebooks, index->codebooks.data(), index->codebooks.size() * sizeof(float));
     if (list_offsets) std::memcpy(list_offsets, index->list_offsets.data(), index->list_offsets.size() * sizeof(int64_t));
-    if (codes && !index->codes.empty()) std::memcpy(codes, index->codes.data(), index->codes.size());
-    if (ids && !index->ids.empty()) std::memcpy(ids, index->ids.data(), index->ids.size() * sizeof(int64_t));
+    if (codes) copy_bytes(codes, index->codes.data(), index->codes.size());
+    if (ids) copy_bytes(ids, index->ids.data(), index->ids.size() * sizeof(int64_t));
     return IVFPQ_OK;
 }
 

@@ -206,6 +206,23 @@ def test_scan_list_R_code_widths(P, d, pq_dim, pq_bits):
             np.testing.assert_allclose(got, want, rtol=RTOL, atol=0)
 
 
+@pytest.mark.parametrize("n,d,pq_dim,pq_bits", [(1, 32, 16, 8), (63, 128, 64, 8), (65, 64, 32, 5), (700, 128, 64, 8),
+                                                (2311, 128, 64, 8), (1500, 24, 24, 8)])
+def test_upload_places_every_code(P, n, d, pq_dim, pq_bits):
+    # the codes travel n * 8 / code_bytes vectors at a time (64 at least): one trip, and several that end inside lists
+    # and between them; empty lists at both ends and in a row in the middle
+    n_lists = 24
+    arrays = si.random_index_arrays(n, d, n_lists, pq_dim, pq_bits, salt=n, empty_lists=(0, 1, 9, 10, 11, 23))
+    oidx = oracle.make_index(d, n_lists, pq_dim, pq_bits, *arrays)
+    gidx = P.Index.ivfpq_index_from_arrays(d, n_lists, pq_dim, pq_bits, *arrays).ivfpq_upload()
+    q = np.random.default_rng(n).standard_normal(d).astype(np.float32)
+    for l in range(n_lists):
+        size = int(oidx.list_offsets[l + 1] - oidx.list_offsets[l])
+        _step(f"uploaded n={n} s={pq_dim} p={pq_bits} list={l} len={size}")
+        want, _ = oracle.scan_list(oidx, oracle.lut_f32(oidx, q, l), l)
+        np.testing.assert_allclose(gidx.ivfpq_scan_list(q, l, P.LUT_FP32, size).cpu().numpy(), want, rtol=RTOL, atol=0)
+
+
 # ---------------------------------------------------------------- probe selection (step 1)
 
 @pytest.mark.parametrize("n_probes", [1, 8, 64])
