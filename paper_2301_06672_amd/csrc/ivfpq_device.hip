@@ -24,6 +24,8 @@
 //                        every query of the group; codebooks and codes are read once for all of them
 //   topk_kernel          step 5: the k smallest R among the survivors of a query, ordered by
 //                        (R, id), and the map from (cluster, position) to the caller's ids
+// Where little is scanned in all (scan_route), launches count more than the work they save: the filtered scan takes its
+// pairs in query order, and below that scan_kernel (mode 3) writes the values of all probes for the top-k step to read.
 // Beside the path: dump_lut_kernel (steps 2-3 of one pair, for inspection) and refine_kernel (exact
 // re-ranking of candidates with the stored vectors).
 #include <hip/hip_runtime.h>
@@ -89,8 +91,8 @@ int static_scratch_ptr(void** out) {
 // ================================================================================================
 // CAP: record capacity, >= n_probes.  The small one serves selections from strip summaries only (S given): the path
 // that streams all keys short-lists up to CAND_CAP indices in the record arrays.
-template <int CAP>
-__global__ void __launch_bounds__(SEL_THREADS)
+template <int CAP, int THREADS>
+__global__ void __launch_bounds__(THREADS)
 select_probes_kernel(uint32_t* __restrict__ A, const StripSummary* __restrict__ S, int strip_w,
                      const float* __restrict__ queries,
                      const float* __restrict__ centroids, float centroid_norm_max, int d,
@@ -99,7 +101,7 @@ select_probes_kernel(uint32_t* __restrict__ A, const StripSummary* __restrict__ 
                      uint32_t* __restrict__ probes, float* __restrict__ probe_dists,
                      uint32_t* __restrict__ roff, uint4* __restrict__ pairs, int k_hint) {
     __shared__ RowSelectSharedT<CAP> t;
-    __shared__ float s_part[SEL_THREADS / kWave];
+    __shared__ float s_part[THREADS / kWave];
     auto& s = t.sel;
     // Workgroup b runs on XCD b % 8.  Inside every block of 64 queries the eight workgroups of one XCD take eight
     // consecutive queries: their strip summaries (16 bytes per query and strip, strip-major) share 128-byte lines,
@@ -306,16 +308,19 @@ select_probes_kernel(uint32_t* __restrict__ A, const StripSummary* __restrict__ 
 }
 
 // One workgroup per query; the small record capacity (more workgroups per compute unit) when the selection works
-// from strip summaries and n_probes allows.
+// from strip summaries and n_probes allows.  Few queries leave most of the chip idle: their workgroups take 1024 threads
+// (search of 1 / 16 / 512 queries, selection and top-k: 40.4 / 68.6 / 173.7 -> 38.0 / 66.5 / 172.4 us; 1024 queries
+// 276 -> 287 us, hence the line at 512).
+constexpr int kFewQueries = 512;
 template <class... Args>
 void launch_select_probes(int nq, hipStream_t st, uint32_t* A, const StripSummary* S, int strip_w, const float* queries,
                           const float* centroids, float centroid_norm_max, int d, int n_lists, int n_probes, Args... rest) {
-    if (S && n_probes <= SEL_CAP_SMALL)
-        hipLaunchKernelGGL(select_probes_kernel<SEL_CAP_SMALL>, dim3(nq), dim3(SEL_THREADS), 0, st, A, S, strip_w, queries, centroids,
-                           centroid_norm_max, d, n_lists, n_probes, rest...);
-    else
-        hipLaunchKernelGGL(select_probes_kernel<SEL_CAP>, dim3(nq), dim3(SEL_THREADS), 0, st, A, S, strip_w, queries, centroids,
-                           centroid_norm_max, d, n_lists, n_probes, rest...);
+    auto go = [&](auto kernel, int threads) {
+        hipLaunchKernelGGL(kernel, dim3(nq), dim3(threads), 0, st, A, S, strip_w, queries, centroids, centroid_norm_max, d, n_lists, n_probes, rest...);
+    };
+    if (nq <= kFewQueries) go(select_probes_kernel<SEL_CAP, 1024>, 1024);
+    else if (S && n_probes <= SEL_CAP_SMALL) go(select_probes_kernel<SEL_CAP_SMALL, SEL_THREADS>, SEL_THREADS);
+    else go(select_probes_kernel<SEL_CAP, SEL_THREADS>, SEL_THREADS);
 }
 
 // Same layout step for caller-given probes.
@@ -560,7 +565,7 @@ struct ScanArgs {
     uint32_t* counts;             // [nq] survivors appended so far (filtered mode)
     uint32_t* Rpos;               // [nq][stride] row position of each appended survivor (filtered mode)
     Fp8Mode fp8;                  // encoding of the 8-bit table dtypes (unused by the other two)
-    int mode;                     // 1: nearest probe of every query, every R written in place;
+    int mode;                     // 1: nearest probe of every query, every R written in place; 3: the same for all probes;
                                   // 2: the other probes, only R <= bound appended behind the nearest probe's segment
     float* R;                     // [nq][stride]
     size_t stride;
@@ -604,6 +609,9 @@ scan_kernel(ScanArgs a) {
         if (a.mode == 1) {
             q = blockIdx.x;
             pair_idx = (size_t)q * a.n_probes;
+        } else if (a.mode == 3) {                              // all probes of a query in a row, unfiltered
+            q = blockIdx.x / a.n_probes;
+            pair_idx = blockIdx.x;
         } else if (a.order == nullptr) {
             q = blockIdx.x / (a.n_probes - 1);
             pair_idx = (size_t)q * a.n_probes + 1 + (blockIdx.x - q * (a.n_probes - 1));
@@ -1029,17 +1037,16 @@ bound_kernel(float* __restrict__ R, uint32_t* __restrict__ Rpos, size_t stride, 
 }
 
 // ================================================================================================
-// Step 5: the k smallest (R, id) of a query.  With several probes the candidates are the survivor list
-// (the nearest cluster's values under the bound, then what the filtered scan kept); with one probe, the
-// cluster's segment itself.
+// Step 5: the k smallest (R, id) of a query.  Candidates: the survivor list of the filtered scan (listed: the nearest
+// cluster's values under the bound, then what the scan kept), or the segments of all probes themselves.
 // ================================================================================================
-template <int CAP>          // record capacity, >= k
-__global__ void __launch_bounds__(SEL_THREADS)
+template <int CAP, int THREADS>          // record capacity, >= k
+__global__ void __launch_bounds__(THREADS)
 topk_kernel(const float* __restrict__ R, const uint32_t* __restrict__ Rpos, size_t stride,
             const uint32_t* __restrict__ roff, const uint32_t* __restrict__ probes,
             const uint32_t* __restrict__ bounds, const uint32_t* __restrict__ counts, int n_probes, int k,
             const int64_t* __restrict__ list_offsets, const int64_t* __restrict__ ids,
-            int64_t* __restrict__ out_ids, float* __restrict__ out_dists) {
+            int64_t* __restrict__ out_ids, float* __restrict__ out_dists, bool listed) {
     __shared__ RowSelectSharedT<CAP> t;
     auto& s = t.sel;
     const int q = blockIdx.x;
@@ -1047,8 +1054,7 @@ topk_kernel(const float* __restrict__ R, const uint32_t* __restrict__ Rpos, size
     const uint32_t* s_roff = roff + (size_t)q * (n_probes + 1);     // read through the vector cache:
     const uint32_t* s_probe = probes + (size_t)q * n_probes;        // only the few survivors look them up
     const uint32_t seg0 = s_roff[1];          // padded length of the nearest probe's segment (a multiple of 64)
-    const bool listed = n_probes > 1;         // candidates = the survivor list behind that segment
-    const uint32_t n = listed ? counts[q] : seg0;
+    const uint32_t n = listed ? counts[q] : s_roff[n_probes];
     const uint32_t* row = reinterpret_cast<const uint32_t*>(R + (size_t)q * stride) + (listed ? seg0 : 0u);
     const uint32_t* row_pos = Rpos + (size_t)q * stride + (listed ? seg0 : 0u);
 
@@ -1252,7 +1258,26 @@ int scan_threads(const ivfpq_index* idx, int lut_dtype) {
 // The filtered scan runs its pairs grouped by cluster unless their number does not fit the 32-bit
 // order array.  Measured on MI355X (10,000 queries): scan stage 10.4 -> 6.8 ms at 10^8 vectors,
 // 1.91 -> 1.51 ms at 10^7, 3.92 -> 3.73 ms at 10^6 (sort kernels included).
+constexpr size_t kWaveSlots = 256 * 32;  // waves the chip holds at once
 constexpr uint32_t kOrderBlock = 64;     // consecutive pairs of the grouped order that stay on one XCD
+
+// How the probes of a tile are scanned, by the number of vectors that are looked up (lists of average length):
+//   kWholeRows  every value of every probe is written and the top-k step reads them all: one scan launch in place of
+//               the nearest probe's, the bound's, the grouping's and the others'.  Up to 16,384 vectors a query and 2.5 M
+//               in all.  (1 / 16 / 128 queries; whole rows, ungrouped: 5 probes of 1,000 vectors 26 / 28 / 39, 31 / 37 / 45 us;
+//               10 of 1,500, 4-bit codes 53 / 57 / 85, 67 / 76 / 95 us; but 20 of 1,000, 64 sub-spaces 43 / 54 / 113, 38 / 67 / 99 us)
+//   kInOrder    the filtered scan takes its pairs query by query: below 5 M vectors the grouping costs more than shared
+//               clusters and tables give back.  (20 probes of 1,000, 1 / 64 / 256 / 1,024 queries: 40 / 82 / 125 / 276 us, grouped
+//               60 / 87 / 134 / 266; 64 probes of 2,000, 1 / 16 / 64 queries 73 / 162 / 235, grouped 156 / 188 / 230)
+//   kGrouped    pairs grouped by cluster (and always beyond 2^20 pairs, of lists that are nearly empty).  A caller that sets one of the knobs of the grouped scan gets it.
+enum class ScanRoute { kWholeRows, kInOrder, kGrouped };
+ScanRoute scan_route(const ivfpq_index* idx, int nq, int n_probes) {
+    const ivfpq::Tuning& t = idx->tuning;
+    if (t.order_block != 0 || t.scan_share != 0 || t.early_exit != 0 || (size_t)nq * n_probes > ((size_t)1 << 20)) return ScanRoute::kGrouped;
+    const double per_query = (double)n_probes * (double)idx->n / (double)idx->n_lists, all = per_query * nq;
+    if (per_query <= 16384.0 && all <= 2.5e6) return ScanRoute::kWholeRows;
+    return all <= 5e6 ? ScanRoute::kInOrder : ScanRoute::kGrouped;
+}
 
 bool group_pairs_by_cluster(size_t n_pairs) { return n_pairs < ((size_t)1 << 32) - 8 * (size_t)kOrderBlock; }
 
@@ -1402,7 +1427,12 @@ int launch_scan_group(const ivfpq_index* idx, const ScanArgs& a, int lut_dtype, 
 }
 
 int launch_scan(const ivfpq_index* idx, ScanArgs a, int lut_dtype, dim3 grid, hipStream_t st) {
-    const int threads = scan_threads(idx, lut_dtype);
+    int threads = scan_threads(idx, lut_dtype);
+    // A grid that leaves wave slots of the chip empty takes larger workgroups: tables are built and lists walked by more
+    // waves at once (filtered scan of one query, 19 pairs: 21.6 -> 9 us with 1024 threads instead of 256).
+    if (!idx->tuning.scan_threads)
+        while (threads < 1024 && (size_t)grid.x * (threads / 64) < kWaveSlots &&
+               scan_lds_bytes_staged(idx, lut_dtype, threads * 2) <= kLdsBytes) threads *= 2;
     const size_t lds = scan_lds_bytes_staged(idx, lut_dtype, threads);
     if (lds > kLdsBytes)
         return fail(IVFPQ_EUNSUPPORTED, "lookup table + residual + staging need %zu bytes of LDS (limit %zu)", lds, kLdsBytes);
@@ -1541,23 +1571,29 @@ int search_impl(const ivfpq_index* idx, const float* d_queries, int64_t nq, cons
         // steps 2-4
         StageTimer t1(idx, st, 1);
         if (int s = t1.begin()) return s;
-        // nearest probe of every query first: its R values give the bound that filters the rest
+        // nearest probe of every query first: its R values give the bound that filters the rest (little work: all probes at once)
         ScanArgs a = base_scan_args(idx, lut_dtype);
         a.queries = qt; a.pairs = w_pairs; a.R = w_R; a.stride = plan.stride;
         a.n_probes = n_probes; a.bounds = w_bounds; a.counts = w_counts; a.Rpos = w_Rpos;
-        a.mode = 1;
+        const ScanRoute route = scan_route(idx, tq, n_probes);
+        const bool whole_rows = route == ScanRoute::kWholeRows;
+        a.mode = whole_rows ? 3 : 1;
         StageTimer t5(idx, st, 5);
-        if (int s = t5.begin()) return s;
-        if (int s = launch_scan(idx, a, lut_dtype, dim3((unsigned)tq), st)) return s;
-        if (int s = t5.end()) return s;
         StageTimer t6(idx, st, 6);
-        if (n_probes > 1) {
+        if (int s = t5.begin()) return s;
+        if (whole_rows)                          // one launch does the work of both: it is reported as both
+            if (int s = t6.begin()) return s;
+        if (int s = launch_scan(idx, a, lut_dtype, dim3((unsigned)((size_t)tq * (whole_rows ? n_probes : 1))), st)) return s;
+        if (int s = t5.end()) return s;
+        if (whole_rows)
+            if (int s = t6.end()) return s;
+        if (n_probes > 1 && !whole_rows) {
             hipLaunchKernelGGL(bound_kernel, dim3(tq), dim3(SEL_THREADS), 0, st, w_R, w_Rpos, plan.stride, w_pairs, n_probes, k,
                                w_bounds, w_counts);
             HIP_TRY(hipGetLastError());
             a.mode = 2;
             const size_t n_pairs = (size_t)tq * (n_probes - 1);
-            if (group_pairs_by_cluster(n_pairs)) {
+            if (route == ScanRoute::kGrouped && group_pairs_by_cluster(n_pairs)) {
                 uint32_t* w_order = (uint32_t*)(ws + plan.order);
                 uint32_t* w_lc = (uint32_t*)(ws + plan.list_counts);
                 uint32_t* w_cur = (uint32_t*)(ws + plan.list_cursor);
@@ -1603,14 +1639,14 @@ int search_impl(const ivfpq_index* idx, const float* d_queries, int64_t nq, cons
         // step 5
         StageTimer t2(idx, st, 2);
         if (int s = t2.begin()) return s;
-        if (k <= SEL_CAP_SMALL)
-            hipLaunchKernelGGL(topk_kernel<SEL_CAP_SMALL>, dim3(tq), dim3(SEL_THREADS), 0, st, w_R, w_Rpos, plan.stride, w_roff, w_probes,
-                               w_bounds, w_counts, n_probes, k, idx->dev.list_offsets, idx->dev.ids, d_ids + (size_t)q0 * k,
-                               d_dists + (size_t)q0 * k);
-        else
-            hipLaunchKernelGGL(topk_kernel<SEL_CAP>, dim3(tq), dim3(SEL_THREADS), 0, st, w_R, w_Rpos, plan.stride, w_roff, w_probes,
-                               w_bounds, w_counts, n_probes, k, idx->dev.list_offsets, idx->dev.ids, d_ids + (size_t)q0 * k,
-                               d_dists + (size_t)q0 * k);
+        auto topk = [&](auto kernel, int threads) {
+            hipLaunchKernelGGL(kernel, dim3(tq), dim3(threads), 0, st, w_R, w_Rpos, plan.stride, w_roff, w_probes, w_bounds, w_counts,
+                               n_probes, k, idx->dev.list_offsets, idx->dev.ids, d_ids + (size_t)q0 * k, d_dists + (size_t)q0 * k,
+                               n_probes > 1 && !whole_rows);
+        };
+        if (tq <= kFewQueries) topk(topk_kernel<SEL_CAP, 1024>, 1024);
+        else if (k <= SEL_CAP_SMALL) topk(topk_kernel<SEL_CAP_SMALL, SEL_THREADS>, SEL_THREADS);
+        else topk(topk_kernel<SEL_CAP, SEL_THREADS>, SEL_THREADS);
         HIP_TRY(hipGetLastError());
         if (int s = t2.end()) return s;
     }

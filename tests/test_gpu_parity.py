@@ -657,6 +657,40 @@ def test_search_group_of_pairs_per_workgroup(P, d, pq_dim, pq_bits, n_lists, n_p
     gidx.ivfpq_set_tuning(P.TUNE_SCAN_SHARE, 0)
 
 
+@pytest.mark.parametrize("n,d,pq_dim,pq_bits,n_lists,n_probes,nq,k", [
+    (9000, 128, 64, 8, 20, 12, 1, 10),       # one query, every value of every probe
+    (9000, 96, 48, 8, 20, 12, 257, 100),     # the same for many queries
+    (9000, 64, 32, 7, 10, 8, 512, 10),       # 3.7 M vectors looked up: filtered, pairs in query order
+    (9000, 64, 32, 5, 10, 8, 513, 1000),     # one query more than the large selection workgroups take
+    (9000, 32, 16, 8, 10, 8, 800, 10),       # 5.8 M: pairs grouped by cluster
+    (40000, 64, 64, 4, 8, 5, 40, 100),       # 25,000 vectors a query: filtered, in query order
+    (300, 24, 24, 8, 6, 5, 33, 400),         # k above the candidates
+    (5000, 32, 16, 8, 9, 1, 50, 10),         # a single probe
+])
+@pytest.mark.parametrize("dtype", [oracle.LUT_E5M3, oracle.LUT_FP16, oracle.LUT_FP32])
+def test_scan_routes_agree(P, n, d, pq_dim, pq_bits, n_lists, n_probes, nq, k, dtype):
+    # whichever way the probes are scanned (all values of all probes; filtered in query order; filtered and grouped, one or
+    # several pairs per workgroup) every distance is the same sum in the same order: equal results, bit for bit
+    oidx, gidx = random_pair(P, n, d, n_lists, pq_dim, pq_bits, salt=640 + nq, empty_lists=(2,))
+    q = np.random.default_rng(nq).standard_normal((nq, d)).astype(np.float32)
+    probes = np.stack([np.random.default_rng(i).permutation(n_lists)[:n_probes] for i in range(nq)]).astype(np.uint32)
+    probes[0, -1] = 0xFFFFFFFF               # out of range: skipped
+    probes[-1, -1] = probes[-1, 0]           # the same cluster twice
+    out = {}
+    for name, knob, value in (("own", P.TUNE_SCAN_SHARE, 0), ("one pair", P.TUNE_SCAN_SHARE, 1), ("grouped", P.TUNE_EARLY_EXIT, 1)):
+        gidx.ivfpq_set_tuning(knob, value)
+        _step(f"routes n={n} s={pq_dim} p={pq_bits} P={n_probes} nq={nq} k={k} dtype={dtype}: {name}")
+        out[name] = [t.cpu().numpy() for t in (*gidx.ivfpq_search(q, n_probes, k, dtype),
+                                               *gidx.ivfpq_search_with_probes(q, probes, k, dtype),
+                                               *gidx.ivfpq_search_static(q, n_probes, k, dtype))]
+        gidx.ivfpq_set_tuning(knob, 0)
+    for name in ("one pair", "grouped"):
+        for a, b in zip(out["own"], out[name]):
+            np.testing.assert_array_equal(a, b, err_msg=name)
+    ids_o, d_o = oracle.search(oidx, q[:40], n_probes, k, dtype)
+    assert_topk_matches(out["own"][0][:40], out["own"][1][:40], ids_o, d_o, context="own route")
+
+
 def test_group_kernel_survivor_overflow_and_small_batches(P):
     # a bound that admits everything (nearest cluster smaller than k) makes every vector of the big cluster a
     # survivor: groups with more survivors than a wave stages are appended directly; also 1, 2 and 3 queries
