@@ -19,7 +19,8 @@
 //   scan_kernel (mode 2) steps 2-4 for the other probes, in cluster-grouped, XCD-aware order (a
 //                        cluster's codes then come from one XCD's L2); only R values under the bound
 //                        are kept
-//   scan_group_kernel    the same for up to four neighbouring pairs of one cluster per workgroup (8- and 4-bit codes):
+//   scan_group_kernel    the same for up to four neighbouring pairs of one cluster per workgroup (8- and 4-bit codes, 64
+//                        sub-spaces of the others):
 //                        their tables are interleaved entry by entry, so one LDS read serves one lookup of
 //                        every query of the group; codebooks and codes are read once for all of them
 //   topk_kernel          step 5: the k smallest R among the survivors of a query, ordered by
@@ -1352,15 +1353,19 @@ int scan_group_threads(const ivfpq_index* idx, int lut_dtype, int G) {
     return long_lists && scan_group_lds_bytes(idx, lut_dtype, G, 128) <= 24 * 1024 ? 128 : 256;
 }
 // How many pairs of a cluster share a workgroup (0: the group kernel does not apply).  It serves 8-bit and 4-bit
-// codes in 16-byte chunks, sub-vectors of 1, 2 or 4 components and fixed encoding constants.  The widest layout
+// codes in 16-byte chunks, 64 sub-spaces of 5- to 7-bit codes, sub-vectors of 1, 2 or 4 components and fixed encoding constants.  The widest layout
 // whose workgroup leaves room for four workgroups per compute unit (40 KB of LDS) is taken.  With 8-bit codes,
 // four pairs only for the one-byte table dtypes: with wider entries the LDS read of four entries costs what it
 // saves.  Measured (filtered scan, 10,000 queries; one / two / four pairs): e5m3 at 10^8 vectors, 32 sub-spaces:
 // 6.02 / 4.81 / 4.58 ms; at 10^7, 48 sub-spaces: 1.08 / 0.96 / 1.05; half at 10^8: 6.58 / 5.63 / 7.19; float:
 // 8.30 / 8.75 / -.  With 4-bit codes (16-entry rows, a few KB of tables) four pairs for every dtype: 10^8 vectors,
-// 64 sub-spaces, e5m3 6.67 / 5.95 / 5.21 ms, half 7.56 / 6.48 / 4.62, float 6.31 / 4.71 / 4.02.
+// 64 sub-spaces, e5m3 6.67 / 5.95 / 5.21 ms, half 7.56 / 6.48 / 4.62, float 6.31 / 4.71 / 4.02.  Bit-packed codes, whole
+// search of 10^6 vectors, 20 probes: 7 bits e5m3 2.35 / 1.67 / 1.46 ms, half 2.45 / 1.90 / -; 6 bits 1.91 / 1.59 / 1.37, half
+// 1.98 / 1.76, float 1.97 / 1.37; 5 bits 2.03 / 1.58 / 1.37, half 2.09 / 1.72, float 1.74 / 1.23.  (Other numbers of sub-spaces
+// of these widths, 4 pairs of their wider tables and the split scan of one pair are not built: each is more kernels to compile.)
 int scan_group_width(const ivfpq_index* idx, int lut_dtype, const Fp8Mode& fp8, uint32_t order_block) {
-    if ((idx->pq_bits != 8 && idx->pq_bits != 4) || chunk_width(idx) != 16 || fp8.per_table) return 0;
+    const bool packed = idx->pq_bits != 8 && idx->pq_bits != 4;
+    if (fp8.per_table || (packed ? idx->pq_dim != 64 : chunk_width(idx) != 16)) return 0;
     if (idx->pq_bits == 4 && idx->pq_dim % 16 != 0) return 0;      // the table is built in blocks of 256 entries
     const int m = idx->d / idx->pq_dim;
     if (m != 1 && m != 2 && m != 4) return 0;
@@ -1370,6 +1375,7 @@ int scan_group_width(const ivfpq_index* idx, int lut_dtype, const Fp8Mode& fp8, 
     for (int G : {4, 2}) {
         if (want != 0 && want != G) continue;
         if (order_block < (uint32_t)G || order_block % (uint32_t)G) continue;
+        if (packed && G == 4 && !one_byte) continue;
         const size_t lds = scan_group_lds_bytes(idx, lut_dtype, G, scan_group_threads(idx, lut_dtype, G));
         if (want == G) { if (lds <= kLdsBytes) return G; continue; }
         if (idx->pq_bits == 8) {
@@ -1396,9 +1402,18 @@ int launch_scan_group(const ivfpq_index* idx, const ScanArgs& a, int lut_dtype, 
         HIP_TRY(hipGetLastError());
         return IVFPQ_OK;
     };
-    const int nch = idx->code_bytes() / 16;
+    const int nch = a.n_chunks;
+    auto by_bits = [&](auto lut_tag, auto g_tag, auto bits_tag) -> int {
+        constexpr int LUT = decltype(lut_tag)::value, GG = decltype(g_tag)::value, BITS = decltype(bits_tag)::value;
+        constexpr int NCH = BITS == 6 ? 3 : 2 * BITS;            // 64 sub-spaces: 40 or 56 bytes in words, 48 in 16-byte chunks
+        if constexpr (GG == 4 && !kIsFp8<LUT>) return fail(IVFPQ_EUNSUPPORTED, "internal: no group kernel for four pairs of %d-bit codes", BITS);
+        else return a.early_exit ? go(scan_group_kernel<LUT, NCH, GG, BITS, true>) : go(scan_group_kernel<LUT, NCH, GG, BITS, false>);
+    };
     auto by_nch = [&](auto lut_tag, auto g_tag) -> int {
         constexpr int LUT = decltype(lut_tag)::value, GG = decltype(g_tag)::value;
+        if (idx->pq_bits == 7) return by_bits(lut_tag, g_tag, std::integral_constant<int, 7>{});
+        if (idx->pq_bits == 6) return by_bits(lut_tag, g_tag, std::integral_constant<int, 6>{});
+        if (idx->pq_bits == 5) return by_bits(lut_tag, g_tag, std::integral_constant<int, 5>{});
         if (idx->pq_bits == 4)
             switch (nch) {
                 case 1: return go(scan_group_kernel<LUT, 1, GG, 4, false>);
@@ -1623,7 +1638,7 @@ int search_impl(const ivfpq_index* idx, const float* d_queries, int64_t nq, cons
                 a.order_block = blk;
                 if (int s = t6.begin()) return s;
                 if (const int G = scan_group_width(idx, lut_dtype, a.fp8, blk)) {
-                    a.n_chunks = idx->code_bytes() / 16;
+                    a.n_chunks = idx->code_bytes() / chunk_width(idx);
                     if (int s = launch_scan_group(idx, a, lut_dtype, G, st)) return s;
                 } else {
                     const size_t grid = (n_pairs + 8 * (size_t)blk - 1) / (8 * (size_t)blk) * (8 * (size_t)blk);

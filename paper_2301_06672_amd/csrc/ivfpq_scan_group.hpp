@@ -1,5 +1,5 @@
 // The filtered scan for up to G (query, probe) pairs of ONE cluster per workgroup (8-bit or 4-bit codes in
-// 16-byte chunks, every table dtype).  Included by ivfpq_device.hip after the table helpers it uses.
+// 16-byte chunks, 64 sub-spaces of bit-packed 5- to 7-bit codes; every table dtype).  Included by ivfpq_device.hip after the table helpers it uses.
 //
 // In the cluster-grouped order neighbouring pairs share their cluster, and everything that depends on the
 // cluster alone is then done once for all of them: a codebook entry is loaded once and becomes R table
@@ -25,6 +25,8 @@
 // 4-bit codes: a byte holds the codes of sub-spaces 2b (low nibble) and 2b + 1; the low and the high nibbles of a
 // code word are masked and shifted to entry offsets four at a time (two instructions per four offsets), so that
 // byte b of the one result is the LDS offset for sub-space 2b and byte b of the other that for 2b + 1.
+// 5- to 7-bit codes: a field and its scaling to an entry offset are one (funnel) shift and one mask, shared by the R
+// queries; every field position is a constant, since 32 sub-spaces fill whole words.
 //
 // A run of 1, 2, 3 or 4 pairs of one cluster is processed at once (3 in the 4-wide layout with one byte of
 // every entry unused).  A workgroup takes G consecutive pairs of the grouped order and cuts them into
@@ -72,9 +74,15 @@ __device__ __forceinline__ void store_packed(unsigned char* dst, const float (&f
 template <int LUT, int NCH, int R, int Q, int BITS, bool SPLIT>
 __device__ __forceinline__ void group_run(const ScanArgs& a, unsigned char* smem, const int (&q)[Q], const uint4 (&pair)[Q]) {
     static_assert(Q >= 1 && Q <= R, "queries of a run fit its interleave width");
-    static_assert(BITS == 8 || BITS == 4, "codes of 8 or 4 bits");
+    static_assert(BITS >= 4 && BITS <= 8, "codes of 4 to 8 bits");
+    constexpr bool PACKED = BITS != 8 && BITS != 4;     // fields that straddle bytes and words
+    constexpr int CW = PACKED && BITS != 6 ? 4 : 16;    // bytes of a chunk (chunk_width)
+    static_assert(!PACKED || NCH * CW == 8 * BITS, "bit-packed codes come in 64 sub-spaces");
+    using chunk_t = typename std::conditional<CW == 16, uint4, uint32_t>::type;
+    constexpr int STEPS = PACKED ? 4 : NCH;             // steps of an accumulation, with the early exit's test between them: a chunk,
+                                                        // or 16 bit-packed sub-spaces
     constexpr int E = LutTraits<LUT>::bytes, W = E * R, LOGW = ilog2(W), KSUB = 1 << BITS;
-    static_assert(BITS == 8 || 15 * W < 256, "a 4-bit code's entry offset fits a byte");
+    static_assert(BITS != 4 || 15 * W < 256, "a 4-bit code's entry offset fits a byte");
     constexpr int kGroupStage = kGroupStageAll / R;
     const uint32_t len = pair[0].y;
     if (len == 0) return;
@@ -97,12 +105,12 @@ __device__ __forceinline__ void group_run(const ScanArgs& a, unsigned char* smem
         stage[g] = reinterpret_cast<uint2*>(after_rq) + ((size_t)wave * Q + g) * kGroupStage;
     }
     const int n_groups = (int)((len + 63u) >> 6);
-    const uint4* cbase = reinterpret_cast<const uint4*>(a.codes + (size_t)pair[0].z * 64 * ((size_t)NCH * 16));
-    auto load_group = [&](uint4 (&buf)[NCH], int grp) {
+    const chunk_t* cbase = reinterpret_cast<const chunk_t*>(a.codes + (size_t)pair[0].z * 64 * ((size_t)NCH * CW));
+    auto load_group = [&](chunk_t (&buf)[NCH], int grp) {
 #pragma unroll
         for (int c = 0; c < NCH; ++c) buf[c] = cbase[((size_t)grp * NCH + c) * 64 + lane];
     };
-    uint4 buf_a[NCH], buf_b[NCH];
+    chunk_t buf_a[NCH], buf_b[NCH];
     int grp = wave;
     if (grp < n_groups) load_group(buf_a, grp);       // HBM latency overlaps the table build
 
@@ -116,10 +124,10 @@ __device__ __forceinline__ void group_run(const ScanArgs& a, unsigned char* smem
     // step 3: all R tables from one pass over the codebooks.  A wave takes blocks of 256 consecutive entries of the
     // table, 4 codes per lane: one row of an 8-bit sub-space, 16 rows of 4-bit sub-spaces (a lane's four codes
     // then belong to sub-space 16 block + lane / 4; the host admits only tables that are whole blocks)
-    // 64 sub-spaces of 8-bit codes with the early exit on: most groups are over every bound after half of the
+    // 64 sub-spaces of 5- to 8-bit codes with the early exit on: most groups are over every bound after half of the
     // sub-spaces, so only the first 32 rows are built now; the rest follows if some group is still in the race
     // (scan_kernel's split scan, for a run of queries)
-    static_assert(!SPLIT || (BITS == 8 && NCH == 4), "the split scan is for 64 sub-spaces of 8-bit codes");
+    static_assert(!SPLIT || PACKED || (BITS == 8 && NCH == 4), "the split scan is for 64 sub-spaces of 5- to 8-bit codes");
     constexpr bool lazy = SPLIT;
     uint32_t* any_alive = reinterpret_cast<uint32_t*>(after_rq + (size_t)n_waves * kGroupStageAll * 8);
     uint16_t* alive = reinterpret_cast<uint16_t*>(any_alive + 4) + (size_t)wave * kAliveCap;
@@ -144,7 +152,7 @@ __device__ __forceinline__ void group_run(const ScanArgs& a, unsigned char* smem
 #pragma unroll
                 for (int g = 0; g < Q; ++g) {
                     float r[M];
-                    const int sub = BITS == 8 ? j : j * 16 + (lane >> 2);
+                    const int sub = BITS == 8 ? j : j * (256 / KSUB) + ((lane * 4) >> BITS);
 #pragma unroll
                     for (int t = 0; t < M; ++t) r[t] = rq[g * a.d + sub * M + t];
 #pragma unroll
@@ -174,7 +182,7 @@ __device__ __forceinline__ void group_run(const ScanArgs& a, unsigned char* smem
             default: rows(std::integral_constant<int, 4>{}); break;      // the host admits m = 1, 2, 4 only
         }
     };
-    build(0, lazy ? 32 : a.pq_dim * KSUB / 256);
+    build(0, a.pq_dim * KSUB / (lazy ? 512 : 256));
     __syncthreads();
 
     // step 4: Eq. (1) for all R queries
@@ -233,7 +241,7 @@ __device__ __forceinline__ void group_run(const ScanArgs& a, unsigned char* smem
             }
         }
     };
-    auto chunk = [&](const uint4& v, int c, float (&acc)[Q]) __attribute__((always_inline)) {
+    [[maybe_unused]] auto chunk = [&](const uint4& v, int c, float (&acc)[Q]) __attribute__((always_inline)) {
         const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -266,19 +274,42 @@ __device__ __forceinline__ void group_run(const ScanArgs& a, unsigned char* smem
             }
         }
     };
+    // sub-spaces 16 step .. 16 step + 15 of bit-packed codes: field s is bits [s BITS, (s + 1) BITS) of the vector's words
+    auto fields = [&](const chunk_t (&buf)[NCH], int step, float (&acc)[Q]) __attribute__((always_inline)) {
+        auto word = [&](int i) __attribute__((always_inline)) -> uint32_t {
+            if constexpr (CW == 16) return (i & 3) == 0 ? buf[i >> 2].x : (i & 3) == 1 ? buf[i >> 2].y : (i & 3) == 2 ? buf[i >> 2].z : buf[i >> 2].w;
+            else return buf[i];
+        };
+        constexpr uint32_t kMask = (uint32_t)(KSUB - 1) << LOGW;
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            word_t x[8];                 // read before the first is used
+#pragma unroll
+            for (int b = 0; b < 8; ++b) {
+                const int sub = step * 16 + half * 8 + b, wi = (sub * BITS) >> 5, sh = (sub * BITS) & 31;
+                uint32_t v = word(wi);
+                if (sh + BITS > 32) v = __builtin_amdgcn_alignbit(word(wi + 1), v, sh - LOGW);       // the field straddles two words
+                else v = sh >= LOGW ? v >> (sh - LOGW) : v << (LOGW - sh);
+                x[b] = lds_word(sub, v & kMask);
+            }
+#pragma unroll
+            for (int pr = 0; pr < 4; ++pr) add_two(x[2 * pr], x[2 * pr + 1], acc);
+        }
+    };
     // Table entries are never negative, so the partial sums only grow: once all 64 x R of them are over their
     // queries' bounds no vector of the group can survive for any of the queries, and the remaining chunks are
     // skipped (the partial sums then fail the filter as the full sums would).
-    auto accumulate = [&](const uint4 (&buf)[NCH], float (&acc)[Q], auto chunks_tag) __attribute__((always_inline)) {
-        constexpr int CHUNKS = decltype(chunks_tag)::value;      // the leading chunks to add; NCH = all
+    auto accumulate = [&](const chunk_t (&buf)[NCH], float (&acc)[Q], auto steps_tag) __attribute__((always_inline)) {
+        constexpr int N = decltype(steps_tag)::value;            // the leading steps to add; STEPS = all
 #pragma unroll
         for (int g = 0; g < Q; ++g) acc[g] = 0.f;
         bool over = false;                  // wave-uniform
 #pragma unroll
-        for (int c = 0; c < CHUNKS; ++c) {
+        for (int c = 0; c < N; ++c) {
             if (over) continue;
-            chunk(buf[c], c, acc);
-            if (c + 1 < CHUNKS && a.early_exit) {
+            if constexpr (PACKED) fields(buf, c, acc);
+            else chunk(buf[c], c, acc);
+            if (c + 1 < N && a.early_exit) {
                 unsigned long long in_race = 0;
 #pragma unroll
                 for (int g = 0; g < Q; ++g) in_race |= ballot64(__float_as_uint(acc[g]) <= bound[g]);
@@ -355,18 +386,18 @@ __device__ __forceinline__ void group_run(const ScanArgs& a, unsigned char* smem
         });
     };
     float acc[Q];
-    constexpr std::integral_constant<int, NCH> kAllChunks{};
+    constexpr std::integral_constant<int, STEPS> kAllSteps{};
     if constexpr (SPLIT) {
         {
-            constexpr int HCH = NCH / 2;            // chunks of the first pass: the codes of the 32 leading sub-spaces
+            constexpr int HCH = (4 * BITS + CW - 1) / CW;       // chunks of the first pass: the codes of the 32 leading sub-spaces
             uint32_t n_alive = 0;                   // wave-uniform
             bool redo_all = false;                  // more groups in the race than the list holds: take them all again
-            auto load_head = [&](uint4 (&buf)[NCH], int g) __attribute__((always_inline)) {
+            auto load_head = [&](chunk_t (&buf)[NCH], int g) __attribute__((always_inline)) {
 #pragma unroll
                 for (int c = 0; c < HCH; ++c) buf[c] = cbase[((size_t)g * NCH + c) * 64 + lane];
             };
-            auto first_pass = [&](int g, const uint4 (&buf)[NCH]) __attribute__((always_inline)) {
-                accumulate(buf, acc, std::integral_constant<int, HCH>{});
+            auto first_pass = [&](int g, const chunk_t (&buf)[NCH]) __attribute__((always_inline)) {
+                accumulate(buf, acc, std::integral_constant<int, STEPS / 2>{});
                 unsigned long long in_race = 0;
 #pragma unroll
                 for (int gq = 0; gq < Q; ++gq) in_race |= ballot64(__float_as_uint(acc[gq]) <= bound[gq]);
@@ -389,19 +420,19 @@ __device__ __forceinline__ void group_run(const ScanArgs& a, unsigned char* smem
             if (lane == 0 && (n_alive != 0 || redo_all)) atomicOr(any_alive, 1u);
             __syncthreads();
             if (*any_alive == 0u) return;           // the same for every wave
-            build(32, a.pq_dim * KSUB / 256);
+            build(a.pq_dim * KSUB / 512, a.pq_dim * KSUB / 256);
             __syncthreads();
             if (redo_all) {
                 for (grp = wave; grp < n_groups; grp += n_waves) {
                     load_group(buf_a, grp);
-                    accumulate(buf_a, acc, kAllChunks);
+                    accumulate(buf_a, acc, kAllSteps);
                     keep(grp, acc);
                 }
             } else {
                 for (uint32_t t = 0; t < n_alive; ++t) {
                     grp = (int)alive[t] * n_waves + wave;
                     load_group(buf_a, grp);
-                    accumulate(buf_a, acc, kAllChunks);
+                    accumulate(buf_a, acc, kAllSteps);
                     keep(grp, acc);
                 }
             }
@@ -412,12 +443,12 @@ __device__ __forceinline__ void group_run(const ScanArgs& a, unsigned char* smem
     while (grp < n_groups) {
         const int gn = grp + n_waves;
         if (gn < n_groups) load_group(buf_b, gn);
-        accumulate(buf_a, acc, kAllChunks);
+        accumulate(buf_a, acc, kAllSteps);
         keep(grp, acc);
         if (gn >= n_groups) break;
         grp = gn + n_waves;
         if (grp < n_groups) load_group(buf_a, grp);
-        accumulate(buf_b, acc, kAllChunks);
+        accumulate(buf_b, acc, kAllSteps);
         keep(gn, acc);
     }
     flush_all();

@@ -691,6 +691,37 @@ def test_scan_routes_agree(P, n, d, pq_dim, pq_bits, n_lists, n_probes, nq, k, d
     assert_topk_matches(out["own"][0][:40], out["own"][1][:40], ids_o, d_o, context="own route")
 
 
+@pytest.mark.parametrize("d,pq_bits,n_lists,n_probes,k", [
+    (64, 5, 7, 5, 10),            # m = 1, 40-byte codes, few clusters: most neighbouring pairs share theirs
+    (128, 6, 20, 12, 100),        # m = 2, 48-byte codes in 16-byte chunks
+    (128, 7, 33, 8, 10),          # m = 2, 56-byte codes
+    (256, 7, 3, 3, 1000),         # m = 4; two pairs per query: odd and even runs
+    (128, 7, 200, 40, 10),        # many seams between clusters
+])
+@pytest.mark.parametrize("dtype", [oracle.LUT_E5M3, oracle.LUT_E4M4, oracle.LUT_FP16, oracle.LUT_FP32])
+def test_group_kernel_bit_packed_codes(P, d, pq_bits, n_lists, n_probes, k, dtype):
+    # 64 sub-spaces of 5- to 7-bit codes: one pair per workgroup, two and four, and the library's choice, with the early
+    # exit (tables built by halves) and without it, add the same entries in the same order: equal bits
+    oidx, gidx = random_pair(P, 9000, d, n_lists, 64, pq_bits, salt=960 + d + pq_bits, empty_lists=(1,) if n_lists > 3 else ())
+    q = np.random.default_rng(960 + d).standard_normal((257, d)).astype(np.float32)
+    gidx.ivfpq_set_tuning(P.TUNE_SCAN_SHARE, 1)
+    ids_one, d_one = [t.cpu().numpy() for t in gidx.ivfpq_search(q, n_probes, k, dtype)]
+    ids_o, d_o = oracle.search(oidx, q[:40], n_probes, k, dtype)
+    assert_topk_matches(ids_one[:40], d_one[:40], ids_o, d_o, context="one pair per workgroup")
+    grouped = 0
+    for share in (0, 2, 4):
+        gidx.ivfpq_set_tuning(P.TUNE_SCAN_SHARE, share)
+        info = gidx.ivfpq_scan_kernel_info(dtype)
+        grouped += info.startswith("scan_group_kernel")
+        for early in (1, -1):
+            gidx.ivfpq_set_tuning(P.TUNE_EARLY_EXIT, early)
+            _step(f"bit-packed d={d} p={pq_bits} L={n_lists} P={n_probes} k={k} dtype={dtype} share={share} early={early}: {info}")
+            ids_g, d_g = [t.cpu().numpy() for t in gidx.ivfpq_search(q, n_probes, k, dtype)]
+            np.testing.assert_array_equal(d_g, d_one)
+            np.testing.assert_array_equal(ids_g, ids_one)
+    assert grouped > 0
+
+
 def test_group_kernel_survivor_overflow_and_small_batches(P):
     # a bound that admits everything (nearest cluster smaller than k) makes every vector of the big cluster a
     # survivor: groups with more survivors than a wave stages are appended directly; also 1, 2 and 3 queries
