@@ -35,7 +35,7 @@ PROFILED_TRAFFIC = {
     # (workload, table dtype): (bytes per launch of the dominant kernel, early exit off; summary file)
     ("intgrid_100m_p8", "e5m3"): (4658953375, "profiles/scan_kernel_intgrid_100m_p8_e5m3_hbm_traffic.txt"),
     ("unitnorm_10m", "e5m3"): (745721453, "profiles/scan_kernel_unitnorm_10m_e5m3_hbm_traffic.txt"),
-    ("intgrid_1m", "e5m3"): (300197912, "profiles/scan_kernel_intgrid_1m_e5m3_hbm_traffic.txt"),
+    ("intgrid_1m", "e5m3"): (302465152, "profiles/scan_kernel_intgrid_1m_e5m3_hbm_traffic.txt"),
     ("intgrid_100m_p4", "e5m3"): (5692997573, "profiles/scan_kernel_intgrid_100m_p4_e5m3_hbm_traffic.txt"),
 }
 
@@ -45,7 +45,7 @@ PROFILED_TRAFFIC = {
 PROFILED_UNITS = {
     ("intgrid_100m_p8", "e5m3"): ({"valu_busy": 0.94, "lds_busy": 0.56}, "profiles/scan_kernel_intgrid_100m_p8_lds_counters.txt"),
     ("unitnorm_10m", "e5m3"): ({"valu_busy": 0.90, "lds_busy": 0.68}, "profiles/scan_kernel_unitnorm_10m_lds_counters.txt"),
-    ("intgrid_1m", "e5m3"): ({"valu_busy": 0.95, "lds_busy": 0.92}, "profiles/scan_kernel_intgrid_1m_lds_counters.txt"),
+    ("intgrid_1m", "e5m3"): ({"valu_busy": 0.97, "lds_busy": 0.60}, "profiles/scan_kernel_intgrid_1m_lds_counters.txt"),
     ("intgrid_100m_p4", "e5m3"): ({"valu_busy": 0.97, "lds_busy": 0.28}, "profiles/scan_kernel_intgrid_100m_p4_lds_counters.txt"),
 }
 

@@ -1346,19 +1346,30 @@ size_t scan_group_lds_bytes(const ivfpq_index* idx, int lut_dtype, int G, int th
 // Workgroup size of the group kernel.  Measured on MI355X (filtered scan, 10,000 queries): with long lists (24 or
 // more 64-vector groups on average) two-wave workgroups win when six or more of them share a compute unit's LDS
 // (e5m3, two pairs, 10^8 vectors: 4.81 ms against 5.30 with four waves) and lose badly otherwise (half table, two
-// pairs, 35 KB: 8.04 ms against 5.63).
+// pairs, 35 KB: 8.04 ms against 5.63).  Tables too large for four workgroups of four waves per compute unit take eight
+// waves, two workgroups: the same 16 waves with half as many tables (whole search, 10,000 queries on 10^6 vectors, 256 / 512
+// threads: half, 64 sub-spaces, two pairs 2.26 / 1.92 ms; float, 32 sub-spaces, two pairs 1.96 / 1.68; half, 32, four pairs
+// 1.57 / 1.32; e5m3, 64, four pairs 1.89 / 1.64).
+constexpr size_t kGroupLds4 = 40 * 1024, kGroupLds2 = 80 * 1024;      // LDS of a workgroup of which four / two share a compute unit
 int scan_group_threads(const ivfpq_index* idx, int lut_dtype, int G) {
     if (idx->tuning.scan_threads) return std::min(idx->tuning.scan_threads, 512);       // the kernel's launch bound
     const bool long_lists = idx->n_lists > 0 && idx->n / idx->n_lists >= 24 * 64;
-    return long_lists && scan_group_lds_bytes(idx, lut_dtype, G, 128) <= 24 * 1024 ? 128 : 256;
+    if (long_lists && scan_group_lds_bytes(idx, lut_dtype, G, 128) <= 24 * 1024) return 128;
+    return scan_group_lds_bytes(idx, lut_dtype, G, 256) <= kGroupLds4 ? 256 : 512;
 }
 // How many pairs of a cluster share a workgroup (0: the group kernel does not apply).  It serves 8-bit and 4-bit
 // codes in 16-byte chunks, 64 sub-spaces of 5- to 7-bit codes, sub-vectors of 1, 2 or 4 components and fixed encoding constants.  The widest layout
-// whose workgroup leaves room for four workgroups per compute unit (40 KB of LDS) is taken.  With 8-bit codes,
-// four pairs only for the one-byte table dtypes: with wider entries the LDS read of four entries costs what it
-// saves.  Measured (filtered scan, 10,000 queries; one / two / four pairs): e5m3 at 10^8 vectors, 32 sub-spaces:
-// 6.02 / 4.81 / 4.58 ms; at 10^7, 48 sub-spaces: 1.08 / 0.96 / 1.05; half at 10^8: 6.58 / 5.63 / 7.19; float:
-// 8.30 / 8.75 / -.  With 4-bit codes (16-entry rows, a few KB of tables) four pairs for every dtype: 10^8 vectors,
+// is taken that leaves room for 16 waves per compute unit (scan_group_threads: 40 KB of LDS with four waves, 80 KB with eight),
+// but not four pairs on eight waves where two pairs leave room for more than 16 waves (five workgroups of 32 KB).  Eight
+// waves pay where the shared table build is heavy: half tables at four pairs with sub-vectors of four components (two components, 32
+// sub-spaces: two pairs 1.00 ms, four 1.04*), the others from two components on (one was not measured).
+// Measured, whole search of 10^6 vectors, 10,000 queries and 20 probes, 8-bit codes (one pair / two / four, the figure of eight waves marked *):
+//   e5m3  32 sub-spaces 1.35 (two) / 1.22 (four); 48: 1.23 (two) / 1.33* (four); 64: 1.69 (two) / 1.64* (four)
+//   half  32 sub-spaces 1.39 (two) / 1.32* (four); 48: 1.58 / 1.47* / 1.97; 64: 2.48 / 1.92* / 2.17
+//   float 32 sub-spaces 2.27 / 1.68* / 2.14; 48: 2.11 / 2.24 / -; 64: 3.00 / 2.88 / - (one workgroup per compute unit: left with one pair);
+//         16: 0.91 / 0.79 / 0.99* (hence no four pairs of float tables with 8-bit codes)
+// and 64 probes of 2,000 vectors, 32 sub-spaces: e5m3 3.03 / 2.62, half 3.20 / 3.02* (two / four), float 5.36 / 4.01* (one / two).
+// With 4-bit codes (16-entry rows, a few KB of tables) four pairs for every dtype: filtered scan, 10^8 vectors,
 // 64 sub-spaces, e5m3 6.67 / 5.95 / 5.21 ms, half 7.56 / 6.48 / 4.62, float 6.31 / 4.71 / 4.02.  Bit-packed codes, whole
 // search of 10^6 vectors, 20 probes: 7 bits e5m3 2.35 / 1.67 / 1.46 ms, half 2.45 / 1.90 / -; 6 bits 1.91 / 1.59 / 1.37, half
 // 1.98 / 1.76, float 1.97 / 1.37; 5 bits 2.03 / 1.58 / 1.37, half 2.09 / 1.72, float 1.74 / 1.23.  (Other numbers of sub-spaces
@@ -1376,16 +1387,14 @@ int scan_group_width(const ivfpq_index* idx, int lut_dtype, const Fp8Mode& fp8, 
         if (want != 0 && want != G) continue;
         if (order_block < (uint32_t)G || order_block % (uint32_t)G) continue;
         if (packed && G == 4 && !one_byte) continue;
-        const size_t lds = scan_group_lds_bytes(idx, lut_dtype, G, scan_group_threads(idx, lut_dtype, G));
+        const int threads = scan_group_threads(idx, lut_dtype, G);
+        const size_t lds = scan_group_lds_bytes(idx, lut_dtype, G, threads);
         if (want == G) { if (lds <= kLdsBytes) return G; continue; }
-        if (idx->pq_bits == 8) {
-            if (G == 4 && !one_byte) continue;
-            if (lut_dtype == IVFPQ_LUT_FP32) continue;
-        }
-        // (64 sub-spaces with the early exit on: both kernels build the second half of the tables only if some group
-        // still needs it; 10^6 vectors, e5m3, one / two pairs: 1.43-1.51 / 1.32 ms; half and float tables of two queries
-        // exceed the 40 KB and stay with one pair: 1.95 / 2.44 and 2.46 / 3.81 ms)
-        if (lds <= 40 * 1024) return G;
+        if (lds > (threads >= 512 ? kGroupLds2 : kGroupLds4)) continue;
+        if (idx->pq_bits == 8 && G == 4 && lut_dtype == IVFPQ_LUT_FP32) continue;
+        if (threads == 512 && m < (G == 4 && !one_byte ? 4 : 2)) continue;
+        if (G == 4 && lds > kGroupLds4 && scan_group_lds_bytes(idx, lut_dtype, 2, 256) <= kLdsBytes / 5) continue;
+        return G;
     }
     return 0;
 }
