@@ -264,7 +264,8 @@ int ivfpq_refine(const float* d_data, int64_t n_data, int32_t d, const float* d_
  * the grouping of the other pairs by cluster, the scan kernel over the remaining probes), ms[2] = top-k
  * (step 5), ms[3] = whole call; and single launches inside those stages: ms[4] = the ranking GEMM of
  * step 1, ms[5] = the scan kernel over the nearest probes, ms[6] = the scan kernel over the remaining
- * probes (the dominant kernel), ms[7] = 0 (reserved). */
+ * probes (the dominant kernel), ms[7] = 0 (reserved).  Small searches scan all probes in one launch: its
+ * time is divided between ms[5] and ms[6] by the number of pairs, 1 : n_probes - 1. */
 int ivfpq_set_stage_timing(ivfpq_index_t* index, int32_t enabled);
 int ivfpq_stage_times_ms(ivfpq_index_t* index, float ms[8]);
 

@@ -1520,8 +1520,16 @@ struct StageTimer {
         if (!on) return IVFPQ_OK;
         void* b = nullptr;
         if (int s = timing_mark(idx, st, &b)) return s;
-        idx->spans.push_back({a, b, stage});
+        idx->spans.push_back({a, b, stage, 1.f});
         return IVFPQ_OK;
+    }
+    // the span just ended covers the work of `other` as well: that stage gets all of it but `share`
+    void divide(int other, float share) {
+        if (!on) return;
+        auto& own = idx->spans.back();
+        own.share = share;
+        const auto rest = ivfpq_index::Span{own.a, own.b, other, 1.f - share};
+        idx->spans.push_back(rest);
     }
 };
 
@@ -1605,12 +1613,9 @@ int search_impl(const ivfpq_index* idx, const float* d_queries, int64_t nq, cons
         StageTimer t5(idx, st, 5);
         StageTimer t6(idx, st, 6);
         if (int s = t5.begin()) return s;
-        if (whole_rows)                          // one launch does the work of both: it is reported as both
-            if (int s = t6.begin()) return s;
         if (int s = launch_scan(idx, a, lut_dtype, dim3((unsigned)((size_t)tq * (whole_rows ? n_probes : 1))), st)) return s;
         if (int s = t5.end()) return s;
-        if (whole_rows)
-            if (int s = t6.end()) return s;
+        if (whole_rows) t5.divide(6, 1.f / (float)n_probes);      // one launch does the work of both: divided by their pairs
         if (n_probes > 1 && !whole_rows) {
             hipLaunchKernelGGL(bound_kernel, dim3(tq), dim3(SEL_THREADS), 0, st, w_R, w_Rpos, plan.stride, w_pairs, n_probes, k,
                                w_bounds, w_counts);
@@ -1972,7 +1977,7 @@ int ivfpq_stage_times_ms(ivfpq_index_t* index, float ms[8]) {
     for (const auto& sp : index->spans) {
         float t = 0.f;
         HIP_TRY(hipEventElapsedTime(&t, (hipEvent_t)sp.a, (hipEvent_t)sp.b));
-        ms[sp.stage] += t;
+        ms[sp.stage] += t * sp.share;
     }
     return IVFPQ_OK;
 }

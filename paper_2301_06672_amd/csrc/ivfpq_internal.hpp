@@ -134,7 +134,7 @@ struct ivfpq_index {
     // handle as const and record into these: with timing enabled, calls on one index must not overlap.
     bool timing = false;
     mutable bool stage_valid = false;
-    struct Span { void* a; void* b; int stage; };
+    struct Span { void* a; void* b; int stage; float share; };    // share: the part of the time between the events that is the stage's
     mutable std::vector<void*> event_pool;
     mutable std::vector<Span> spans;
     mutable size_t events_used = 0;

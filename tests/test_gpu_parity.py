@@ -546,6 +546,31 @@ def test_stage_timing_reports(P, tiny):
     assert ms["scan_nearest_kernel"] + ms["scan_filtered_kernel"] <= ms["scan"] * 1.05 + 0.05
 
 
+@pytest.mark.parametrize("share,one_launch", [(0, True), (1, False)])
+def test_stage_times_of_single_launches_are_parts_of_their_stage(P, tiny, share, one_launch):
+    # all probes in one launch (this little work, no knob set) and the grouped scan: the two entries never count the
+    # same time twice.  The spans are nested in the scan stage's, so their sum cannot exceed it but for the rounding
+    # of an event's time (the events tick every 10 ns at the finest; 1 us is allowed)
+    w, data, oidx, gidx = tiny
+    q = torch.from_numpy(si.queries(w, 256)).cuda()
+    gidx.ivfpq_set_tuning(P.TUNE_SCAN_SHARE, share)
+    gidx.ivfpq_set_stage_timing(True)
+    try:
+        for n_probes in (1, 8):
+            _step(f"stage times share={share} P={n_probes}")
+            gidx.ivfpq_search(q, n_probes, 10, oracle.LUT_E5M3)
+            torch.cuda.synchronize()
+            ms = gidx.ivfpq_stage_times_ms()
+            near, rest = ms["scan_nearest_kernel"], ms["scan_filtered_kernel"]
+            assert near > 0 and (rest > 0) == (n_probes > 1)
+            assert near + rest <= ms["scan"] + 1e-3
+            if one_launch:
+                np.testing.assert_allclose(rest, near * (n_probes - 1), rtol=1e-5)
+    finally:
+        gidx.ivfpq_set_stage_timing(False)
+        gidx.ivfpq_set_tuning(P.TUNE_SCAN_SHARE, 0)
+
+
 def test_library_builder_index_searches_like_oracle_builder(P, tiny):
     # the two builders run different k-means code: compare them by recall only
     w, data, oidx, _ = tiny
