@@ -172,11 +172,16 @@ typedef enum {
     IVFPQ_TUNE_ORDER_BLOCK = 1,  /* consecutive (query, probe) pairs of the cluster-grouped order that stay on one
                                     XCD (>= 1; the scan that shares a workgroup between pairs needs an even value) */
     IVFPQ_TUNE_SCAN_SHARE = 2,   /* 1: one (query, probe) pair per scan workgroup; 2 or 4: up to that many pairs of
-                                    one cluster per workgroup wherever the kernel for it applies (8- and 4-bit codes) */
+                                    one cluster per workgroup wherever the kernel for it applies */
     IVFPQ_TUNE_EARLY_EXIT = 3,   /* 1: on (the default: a 64-vector group stops adding once all its partial sums are
-                                    over the query's bound); -1: off, every lookup of Eq. (1) is made */
-    IVFPQ_TUNE_LDS_PAD = 4       /* extra bytes of LDS requested per scan workgroup (lowers occupancy without
+                                    over the query's bound); -1: off, every lookup of Eq. (1) is made.  Leaves the
+                                    route (SCAN_ROUTE) as it is */
+    IVFPQ_TUNE_LDS_PAD = 4,      /* extra bytes of LDS requested per scan workgroup (lowers occupancy without
                                     changing the table: separates the two effects of a smaller table dtype) */
+    IVFPQ_TUNE_SCAN_ROUTE = 5    /* how the probes of a query are scanned; the library chooses by the amount of work.
+                                    1: all of them in one launch, no filter (small searches); 2: the nearest one
+                                    first, the others filtered, query by query; 3: the same with the pairs grouped
+                                    by cluster (large batches; implied by a non-zero SCAN_SHARE or ORDER_BLOCK) */
 } ivfpq_tuning_t;
 int ivfpq_set_tuning(ivfpq_index_t* index, int32_t knob, int32_t value);
 

@@ -23,7 +23,7 @@ ROUND_NEAREST, ROUND_TRUNCATE = 0, 1
 MAX_K = 1024
 MAX_PROBES = 1024
 STATIC_SCRATCH_BYTES = 64 << 20
-TUNE_SCAN_THREADS, TUNE_ORDER_BLOCK, TUNE_SCAN_SHARE, TUNE_EARLY_EXIT, TUNE_LDS_PAD = 0, 1, 2, 3, 4
+TUNE_SCAN_THREADS, TUNE_ORDER_BLOCK, TUNE_SCAN_SHARE, TUNE_EARLY_EXIT, TUNE_LDS_PAD, TUNE_SCAN_ROUTE = 0, 1, 2, 3, 4, 5
 
 OK, EINVAL, ENOSPACE, EHIP, EUNSUPPORTED, ESTATE = 0, -1, -2, -3, -4, -5
 

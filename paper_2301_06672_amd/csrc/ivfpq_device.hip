@@ -1270,11 +1270,14 @@ constexpr uint32_t kOrderBlock = 64;     // consecutive pairs of the grouped ord
 //   kInOrder    the filtered scan takes its pairs query by query: below 5 M vectors the grouping costs more than shared
 //               clusters and tables give back.  (20 probes of 1,000, 1 / 64 / 256 / 1,024 queries: 40 / 82 / 125 / 276 us, grouped
 //               60 / 87 / 134 / 266; 64 probes of 2,000, 1 / 16 / 64 queries 73 / 162 / 235, grouped 156 / 188 / 230)
-//   kGrouped    pairs grouped by cluster (and always beyond 2^20 pairs, of lists that are nearly empty).  A caller that sets one of the knobs of the grouped scan gets it.
-enum class ScanRoute { kWholeRows, kInOrder, kGrouped };
+//   kGrouped    pairs grouped by cluster (and always beyond 2^20 pairs, of lists that are nearly empty).
+// A caller may name the route (IVFPQ_TUNE_SCAN_ROUTE); one that sets a knob of the grouped scan alone gets that.
+enum class ScanRoute { kWholeRows = 1, kInOrder = 2, kGrouped = 3 };
 ScanRoute scan_route(const ivfpq_index* idx, int nq, int n_probes) {
     const ivfpq::Tuning& t = idx->tuning;
-    if (t.order_block != 0 || t.scan_share != 0 || t.early_exit != 0 || (size_t)nq * n_probes > ((size_t)1 << 20)) return ScanRoute::kGrouped;
+    const size_t pairs = (size_t)nq * n_probes;
+    if (t.scan_route != 0 && pairs <= 0x7FFFFFFFull) return (ScanRoute)t.scan_route;      // a workgroup per pair: one dimension of a grid
+    if (t.order_block != 0 || t.scan_share != 0 || pairs > ((size_t)1 << 20)) return ScanRoute::kGrouped;
     const double per_query = (double)n_probes * (double)idx->n / (double)idx->n_lists, all = per_query * nq;
     if (per_query <= 16384.0 && all <= 2.5e6) return ScanRoute::kWholeRows;
     return all <= 5e6 ? ScanRoute::kInOrder : ScanRoute::kGrouped;

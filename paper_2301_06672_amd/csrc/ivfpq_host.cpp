@@ -412,6 +412,10 @@ int ivfpq_set_tuning(ivfpq_index_t* index, int32_t knob, int32_t value) {
             if (value < 0 || value > 160 * 1024 || (value & 15)) return fail(IVFPQ_EINVAL, "LDS pad %d (a multiple of 16 in [0, 163840])", value);
             index->tuning.lds_pad = value;
             return IVFPQ_OK;
+        case IVFPQ_TUNE_SCAN_ROUTE:
+            if (value < 0 || value > 3) return fail(IVFPQ_EINVAL, "scan route %d (0, 1, 2 or 3)", value);
+            index->tuning.scan_route = value;
+            return IVFPQ_OK;
         default:
             return fail(IVFPQ_EINVAL, "unknown tuning knob %d", knob);
     }

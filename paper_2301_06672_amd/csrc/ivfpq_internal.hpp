@@ -33,6 +33,7 @@ struct Tuning {
     int32_t scan_share = 0;     // 0: heuristic; 1: one (query, probe) pair per workgroup; 2 or 4: up to that many pairs of a cluster
     int32_t early_exit = 0;     // 0: on (default); 1: on; -1: off (every lookup of Eq. (1) is made)
     int32_t lds_pad = 0;        // extra bytes of LDS requested per scan workgroup (occupancy experiments)
+    int32_t scan_route = 0;     // 0: by the amount of work; 1: whole rows; 2: filtered, query by query; 3: filtered, grouped by cluster
 };
 
 // Storage of the large host arrays (codes, ids): elements are not cleared when the array is made, since every one of

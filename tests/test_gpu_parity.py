@@ -571,6 +571,33 @@ def test_stage_times_of_single_launches_are_parts_of_their_stage(P, tiny, share,
         gidx.ivfpq_set_tuning(P.TUNE_SCAN_SHARE, 0)
 
 
+def test_early_exit_knob_leaves_the_route_alone(P, tiny):
+    # 128 queries x 8 probes of 156 vectors: all probes in one launch (the scan entries divide its time by the pairs),
+    # whatever the early exit is set to; and the three routes can be asked for by name
+    w, data, oidx, gidx = tiny
+    q = torch.from_numpy(si.queries(w, 128)).cuda()
+    gidx.ivfpq_set_stage_timing(True)
+
+    def one_launch():
+        gidx.ivfpq_search(q, 8, 10, oracle.LUT_E5M3)
+        torch.cuda.synchronize()
+        ms = gidx.ivfpq_stage_times_ms()
+        return abs(ms["scan_filtered_kernel"] / ms["scan_nearest_kernel"] - 7.0) < 1e-4
+    try:
+        for early in (0, 1, -1):
+            _step(f"route with early exit {early}")
+            gidx.ivfpq_set_tuning(P.TUNE_EARLY_EXIT, early)
+            assert one_launch()
+        for route in (1, 2, 3):
+            _step(f"route {route}")
+            gidx.ivfpq_set_tuning(P.TUNE_SCAN_ROUTE, route)
+            assert one_launch() == (route == 1)
+    finally:
+        gidx.ivfpq_set_stage_timing(False)
+        gidx.ivfpq_set_tuning(P.TUNE_EARLY_EXIT, 0)
+        gidx.ivfpq_set_tuning(P.TUNE_SCAN_ROUTE, 0)
+
+
 def test_library_builder_index_searches_like_oracle_builder(P, tiny):
     # the two builders run different k-means code: compare them by recall only
     w, data, oidx, _ = tiny
@@ -702,14 +729,16 @@ def test_scan_routes_agree(P, n, d, pq_dim, pq_bits, n_lists, n_probes, nq, k, d
     probes[0, -1] = 0xFFFFFFFF               # out of range: skipped
     probes[-1, -1] = probes[-1, 0]           # the same cluster twice
     out = {}
-    for name, knob, value in (("own", P.TUNE_SCAN_SHARE, 0), ("one pair", P.TUNE_SCAN_SHARE, 1), ("grouped", P.TUNE_EARLY_EXIT, 1)):
+    ways = (("own", P.TUNE_SCAN_ROUTE, 0), ("whole rows", P.TUNE_SCAN_ROUTE, 1), ("in order", P.TUNE_SCAN_ROUTE, 2),
+            ("grouped", P.TUNE_SCAN_ROUTE, 3), ("one pair", P.TUNE_SCAN_SHARE, 1))
+    for name, knob, value in ways:
         gidx.ivfpq_set_tuning(knob, value)
         _step(f"routes n={n} s={pq_dim} p={pq_bits} P={n_probes} nq={nq} k={k} dtype={dtype}: {name}")
         out[name] = [t.cpu().numpy() for t in (*gidx.ivfpq_search(q, n_probes, k, dtype),
                                                *gidx.ivfpq_search_with_probes(q, probes, k, dtype),
                                                *gidx.ivfpq_search_static(q, n_probes, k, dtype))]
         gidx.ivfpq_set_tuning(knob, 0)
-    for name in ("one pair", "grouped"):
+    for name, _, _ in ways[1:]:
         for a, b in zip(out["own"], out[name]):
             np.testing.assert_array_equal(a, b, err_msg=name)
     ids_o, d_o = oracle.search(oidx, q[:40], n_probes, k, dtype)
@@ -780,17 +809,19 @@ def test_early_exit_changes_nothing(P, d, pq_dim, pq_bits, dtype):
     # a group whose partial sums are all over the bound stops early: the survivors, hence the results, are the same
     oidx, gidx = random_pair(P, 12000, d, 9, pq_dim, pq_bits, salt=950 + d + pq_bits)
     q = np.random.default_rng(950 + d).standard_normal((130, d)).astype(np.float32)
-    out = {}
-    for mode in ("0", "1"):
-        gidx.ivfpq_set_tuning(P.TUNE_EARLY_EXIT, 1 if mode == "1" else -1)
-        _step(f"early exit {mode}: d={d} s={pq_dim} p={pq_bits} dtype={dtype}")
-        ids, dist = gidx.ivfpq_search(q, 6, 10, dtype)
-        out[mode] = (ids.cpu().numpy(), dist.cpu().numpy())
-    np.testing.assert_array_equal(out["0"][0], out["1"][0])
-    np.testing.assert_array_equal(out["0"][1], out["1"][1])
-    gidx.ivfpq_set_tuning(P.TUNE_EARLY_EXIT, 0)
-    ids_g, d_g, ids_o, d_o = _search_both(gidx, oidx, q, 6, 10, dtype)
-    assert_topk_matches(ids_g, d_g, ids_o, d_o, context="early exit")
+    for route in (2, 3):                 # the filtered routes: only they can stop early
+        out = {}
+        gidx.ivfpq_set_tuning(P.TUNE_SCAN_ROUTE, route)
+        for mode in ("0", "1"):
+            gidx.ivfpq_set_tuning(P.TUNE_EARLY_EXIT, 1 if mode == "1" else -1)
+            _step(f"early exit {mode}: route={route} d={d} s={pq_dim} p={pq_bits} dtype={dtype}")
+            ids, dist = gidx.ivfpq_search(q, 6, 10, dtype)
+            out[mode] = (ids.cpu().numpy(), dist.cpu().numpy())
+        np.testing.assert_array_equal(out["0"][0], out["1"][0])
+        np.testing.assert_array_equal(out["0"][1], out["1"][1])
+        gidx.ivfpq_set_tuning(P.TUNE_EARLY_EXIT, 0)
+        ids_g, d_g, ids_o, d_o = _search_both(gidx, oidx, q, 6, 10, dtype)
+        assert_topk_matches(ids_g, d_g, ids_o, d_o, context="early exit")
 
 
 def test_split_scan_when_every_group_stays_in_the_race(P):

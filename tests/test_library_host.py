@@ -113,12 +113,12 @@ def test_fp8_encoding_setter_validates(P):
 def test_tuning_setter_validates(P):
     idx = P.Index.ivfpq_index_from_arrays(32, 9, 16, 4, *si.random_index_arrays(100, 32, 9, 16, 4, salt=2))
     for knob, good in ((P.TUNE_SCAN_THREADS, (0, 64, 1024)), (P.TUNE_ORDER_BLOCK, (0, 1, 64)), (P.TUNE_SCAN_SHARE, (0, 1, 2)),
-                       (P.TUNE_EARLY_EXIT, (-1, 0, 1)), (P.TUNE_LDS_PAD, (0, 16, 65536))):
+                       (P.TUNE_EARLY_EXIT, (-1, 0, 1)), (P.TUNE_LDS_PAD, (0, 16, 65536)), (P.TUNE_SCAN_ROUTE, (0, 1, 3))):
         for v in good:
             idx.ivfpq_set_tuning(knob, v)
         idx.ivfpq_set_tuning(knob, 0)
     for knob, bad in ((P.TUNE_SCAN_THREADS, 100), (P.TUNE_ORDER_BLOCK, -1), (P.TUNE_SCAN_SHARE, 3), (P.TUNE_EARLY_EXIT, 2),
-                      (P.TUNE_LDS_PAD, 8), (P.TUNE_LDS_PAD, 1 << 20), (99, 0)):
+                      (P.TUNE_LDS_PAD, 8), (P.TUNE_LDS_PAD, 1 << 20), (P.TUNE_SCAN_ROUTE, 4), (P.TUNE_SCAN_ROUTE, -1), (99, 0)):
         with pytest.raises(P.IvfpqError) as e:
             idx.ivfpq_set_tuning(knob, bad)
         assert e.value.status == P.EINVAL
