@@ -1256,21 +1256,30 @@ int scan_threads(const ivfpq_index* idx, int lut_dtype) {
     return 512;
 }
 
-// The filtered scan runs its pairs grouped by cluster unless their number does not fit the 32-bit
-// order array.  Measured on MI355X (10,000 queries): scan stage 10.4 -> 6.8 ms at 10^8 vectors,
-// 1.91 -> 1.51 ms at 10^7, 3.92 -> 3.73 ms at 10^6 (sort kernels included).
 constexpr size_t kWaveSlots = 256 * 32;  // waves the chip holds at once
 constexpr uint32_t kOrderBlock = 64;     // consecutive pairs of the grouped order that stay on one XCD
 
 // How the probes of a tile are scanned, by the number of vectors that are looked up (lists of average length):
 //   kWholeRows  every value of every probe is written and the top-k step reads them all: one scan launch in place of
-//               the nearest probe's, the bound's, the grouping's and the others'.  Up to 16,384 vectors a query and 2.5 M
-//               in all.  (1 / 16 / 128 queries; whole rows, ungrouped: 5 probes of 1,000 vectors 26 / 28 / 39, 31 / 37 / 45 us;
-//               10 of 1,500, 4-bit codes 53 / 57 / 85, 67 / 76 / 95 us; but 20 of 1,000, 64 sub-spaces 43 / 54 / 113, 38 / 67 / 99 us)
-//   kInOrder    the filtered scan takes its pairs query by query: below 5 M vectors the grouping costs more than shared
-//               clusters and tables give back.  (20 probes of 1,000, 1 / 64 / 256 / 1,024 queries: 40 / 82 / 125 / 276 us, grouped
-//               60 / 87 / 134 / 266; 64 probes of 2,000, 1 / 16 / 64 queries 73 / 162 / 235, grouped 156 / 188 / 230)
-//   kGrouped    pairs grouped by cluster (and always beyond 2^20 pairs, of lists that are nearly empty).
+//               the nearest probe's, the bound's, the grouping's and the others'.  Up to 16,384 vectors a query and
+//               3.2 M in all.
+//   kInOrder    the filtered scan takes its pairs query by query: up to 7.2 M vectors the grouping costs more than
+//               shared clusters and tables give back.
+//   kGrouped    pairs grouped by cluster, which pays in batches (scan stage of 10,000 queries at 10^8 vectors 10.4 ->
+//               6.8 ms, at 10^7 1.91 -> 1.51; and always beyond 2^20 pairs, of lists that are nearly empty).
+// Measured, us a search (M: vectors looked up by this reckoning; whole rows / in order / grouped):
+//   64 sub-spaces of 8 bits, e5m3, lists of 1,000    5 probes: 2.5 M 106 / 108 / 113, 5 M 163 / 138 / 144
+//                                                    20 probes: 5 M 156 / 115 / 126, 10 M 265 / 164 / 170, 20 M - / 264 / 251
+//   48 of 8 bits, half                               5 probes: 2.5 M 71 / 80 / 87, 5 M 113 / 111 / 117; 20: 10 M 171 / 142 / 140
+//   64 of 4 bits, half, lists of 2,000               5 probes: 2.6 M 127 / 153 / 218, 5.1 M 195 / 198 / 239, 10 M 408 / 306 / 296
+//   64 of 7 bits, e5m3                               5 probes: 2.5 M 101 / 104 / 126, 5 M 156 / 140 / 146; 20: 10 M 251 / 181 / 167
+//   32 of 8 bits, float                              5 probes: 5 M 144 / 143 / 145, 10 M 243 / 219 / 214; 33: 8 M 182 / 168 / 161
+//   more than 16,384 a query, one query              33 probes, float 46 / 38 / 52; 20 of 2,000, 4 bits 82 / 45 / 176
+// Lists of average length on purpose, also where they are uneven: the filtered routes wait there for one workgroup per
+// query that walks the longest list and then for its bound, which costs more than the values the filter saves
+// (10^6 vectors, the longest list 134,000: 5 probes, 64 / 256 queries 311 / 446 us whole, 856 / 1067 in order; 5 probes of
+// which one has 290,000: 472 / 876 and 2156 / 2646).  Reckoned by the length of the list that a vector lies in (sum of
+// len^2 / n) these searches would leave the whole rows, and lose.
 // A caller may name the route (IVFPQ_TUNE_SCAN_ROUTE); one that sets a knob of the grouped scan alone gets that.
 enum class ScanRoute { kWholeRows = 1, kInOrder = 2, kGrouped = 3 };
 ScanRoute scan_route(const ivfpq_index* idx, int nq, int n_probes) {
@@ -1279,8 +1288,8 @@ ScanRoute scan_route(const ivfpq_index* idx, int nq, int n_probes) {
     if (t.scan_route != 0 && pairs <= 0x7FFFFFFFull) return (ScanRoute)t.scan_route;      // a workgroup per pair: one dimension of a grid
     if (t.order_block != 0 || t.scan_share != 0 || pairs > ((size_t)1 << 20)) return ScanRoute::kGrouped;
     const double per_query = (double)n_probes * (double)idx->n / (double)idx->n_lists, all = per_query * nq;
-    if (per_query <= 16384.0 && all <= 2.5e6) return ScanRoute::kWholeRows;
-    return all <= 5e6 ? ScanRoute::kInOrder : ScanRoute::kGrouped;
+    if (per_query <= 16384.0 && all <= 3.2e6) return ScanRoute::kWholeRows;
+    return all <= 7.2e6 ? ScanRoute::kInOrder : ScanRoute::kGrouped;
 }
 
 bool group_pairs_by_cluster(size_t n_pairs) { return n_pairs < ((size_t)1 << 32) - 8 * (size_t)kOrderBlock; }

@@ -713,8 +713,10 @@ def test_search_group_of_pairs_per_workgroup(P, d, pq_dim, pq_bits, n_lists, n_p
     (9000, 128, 64, 8, 20, 12, 1, 10),       # one query, every value of every probe
     (9000, 96, 48, 8, 20, 12, 257, 100),     # the same for many queries
     (9000, 64, 32, 7, 10, 8, 512, 10),       # 3.7 M vectors looked up: filtered, pairs in query order
+    (9000, 64, 32, 5, 10, 8, 444, 10),       # 3.2 M less a little: whole rows still
     (9000, 64, 32, 5, 10, 8, 513, 1000),     # one query more than the large selection workgroups take
-    (9000, 32, 16, 8, 10, 8, 800, 10),       # 5.8 M: pairs grouped by cluster
+    (9000, 32, 16, 8, 10, 8, 800, 10),       # 5.8 M: in query order
+    (9000, 32, 16, 8, 10, 8, 1010, 10),      # 7.3 M: pairs grouped by cluster
     (40000, 64, 64, 4, 8, 5, 40, 100),       # 25,000 vectors a query: filtered, in query order
     (300, 24, 24, 8, 6, 5, 33, 400),         # k above the candidates
     (5000, 32, 16, 8, 9, 1, 50, 10),         # a single probe
