@@ -38,6 +38,25 @@ def tiny(P):
     return w, data, oidx, to_library(P, oidx)
 
 
+@pytest.fixture(params=[0, 2, 3], ids=["own-route", "in-order", "grouped"])
+def route(P, request, monkeypatch):
+    """Runs a test on the library's own route (at these sizes: all probes in one unfiltered launch), and with every
+    index it uploads sent through the filtered scan in query order and grouped by cluster, which batches take."""
+    upload = P.Index.ivfpq_upload
+
+    def routed(self, *args, **kw):
+        upload(self, *args, **kw)
+        self.ivfpq_set_tuning(P.TUNE_SCAN_ROUTE, request.param)
+        return self
+    monkeypatch.setattr(P.Index, "ivfpq_upload", routed)
+    shared = [request.getfixturevalue("tiny")[3]] if "tiny" in request.fixturenames else []
+    for gidx in shared:
+        gidx.ivfpq_set_tuning(P.TUNE_SCAN_ROUTE, request.param)
+    yield request.param
+    for gidx in shared:
+        gidx.ivfpq_set_tuning(P.TUNE_SCAN_ROUTE, 0)
+
+
 def _step(msg):
     print(f"[parity] {msg}", flush=True)
 
@@ -77,6 +96,7 @@ def test_lut_bytes_identical_shapes_and_ranges(P, d, pq_dim, pq_bits):
             assert F.min() < 2.0 ** -15     # and the flooring end
 
 
+@pytest.mark.usefixtures("route")
 @pytest.mark.parametrize("bias", [-2, 1, 7, 14])
 def test_e4m4_lut_bytes_and_search(P, tiny, bias):
     # the 4+4 split with a caller-chosen exponent bias: table bytes identical, search results as the oracle's
@@ -96,6 +116,7 @@ def test_e4m4_lut_bytes_and_search(P, tiny, bias):
     gidx.ivfpq_set_e4m4_bias(7)
 
 
+@pytest.mark.usefixtures("route")
 def test_e4m4_other_shapes(P):
     for d, pq_dim, pq_bits in ((128, 64, 4), (128, 32, 8), (24, 8, 4)):
         oidx, gidx = random_pair(P, 2000, d, 5, pq_dim, pq_bits, salt=900 + d + pq_bits)
@@ -116,6 +137,7 @@ def _reset_fp8(P, gidx):
     gidx.ivfpq_set_fp8_encoding(P.LUT_FP8_E4M4, 7)
 
 
+@pytest.mark.usefixtures("route")
 @pytest.mark.parametrize("dtype", list(FP8))
 @pytest.mark.parametrize("bias,trunc,per_table", [(15, True, False), (22, False, False), (3, True, False),
                                                   (0, False, True), (0, True, True)])
@@ -207,7 +229,7 @@ def test_scan_list_R_code_widths(P, d, pq_dim, pq_bits):
 
 
 @pytest.mark.parametrize("n,d,pq_dim,pq_bits", [(1, 32, 16, 8), (63, 128, 64, 8), (65, 64, 32, 5), (700, 128, 64, 8),
-                                                (2311, 128, 64, 8), (1500, 24, 24, 8)])
+                                                (2311, 128, 64, 8), (2311, 128, 64, 6), (1500, 24, 24, 8)])
 def test_upload_places_every_code(P, n, d, pq_dim, pq_bits):
     # the codes travel n * 8 / code_bytes vectors at a time (64 at least): one trip, and several that end inside lists
     # and between them; empty lists at both ends and in a row in the middle
@@ -324,6 +346,7 @@ def test_select_probes_bf16_tiles_with_padded_dimension(P):
         assert (probes.cpu().numpy().view(np.uint32) == want).mean() > 0.999
 
 
+@pytest.mark.usefixtures("route")
 @pytest.mark.parametrize("nq", [40, 3000])
 def test_non_finite_queries_stay_in_range(P, nq):
     # NaN, infinite and huge queries: the call returns, every index it returns is valid, and the finite
@@ -385,6 +408,7 @@ def _search_both(gidx, oidx, q, n_probes, k, dtype):
     return ids_g.cpu().numpy(), d_g.cpu().numpy(), ids_o, d_o
 
 
+@pytest.mark.usefixtures("route")
 @pytest.mark.parametrize("dtype", DTYPES)
 def test_search_tiny_config(P, tiny, dtype):
     w, data, oidx, gidx = tiny
@@ -400,6 +424,7 @@ def test_search_tiny_config(P, tiny, dtype):
     assert abs(oracle.recall(ids_g[:200], gt) - oracle.recall(ids_oo[:200], gt)) < 1e-3
 
 
+@pytest.mark.usefixtures("route")
 @pytest.mark.parametrize("n_probes,k", [(1, 1), (3, 100), (64, 10), (8, 1024)])
 def test_search_tiny_probe_and_k_range(P, tiny, n_probes, k):
     w, data, oidx, gidx = tiny
@@ -410,6 +435,7 @@ def test_search_tiny_probe_and_k_range(P, tiny, n_probes, k):
         assert_topk_matches(ids_g, d_g, ids_o, d_o, context=f"P={n_probes} k={k} dtype={dtype}")
 
 
+@pytest.mark.usefixtures("route")
 @pytest.mark.parametrize("d,pq_dim,pq_bits", [(128, 64, 8), (96, 48, 8), (128, 64, 4), (128, 32, 8), (24, 8, 4),
                                               (64, 32, 5), (128, 64, 6), (32, 16, 6), (128, 64, 7)])
 def test_search_random_index_ragged_and_empty_lists(P, d, pq_dim, pq_bits):
@@ -422,6 +448,7 @@ def test_search_random_index_ragged_and_empty_lists(P, d, pq_dim, pq_bits):
             assert_topk_matches(ids_g, d_g, ids_o, d_o, context=f"d={d} p={pq_bits} dtype={dtype}")
 
 
+@pytest.mark.usefixtures("route")
 def test_search_fewer_candidates_than_k_pads(P):
     oidx, gidx = random_pair(P, 70, 32, 9, 16, 8, salt=500, empty_lists=(1, 2))
     q = np.random.default_rng(500).standard_normal((8, 32)).astype(np.float32)
@@ -435,6 +462,7 @@ def test_search_fewer_candidates_than_k_pads(P):
     assert (ids_g.cpu().numpy() == -1).all() and np.isinf(d_g.cpu().numpy()).all()
 
 
+@pytest.mark.usefixtures("route")
 def test_search_massive_ties_order_by_id(P):
     # 6000 identical codes in one cluster: every R is equal, the answer is the k smallest ids
     # (more ties than the selection's LDS record capacity -> the 64-bit tie-key path)
@@ -451,9 +479,10 @@ def test_search_massive_ties_order_by_id(P):
             np.testing.assert_array_equal(d_g, d_o)
 
 
+@pytest.mark.usefixtures("route")
 def test_search_small_nearest_cluster_admits_everything(P):
     # the nearest probe holds fewer than k vectors, so its R values give no bound: every vector of
-    # the large second cluster survives the filter (each wave appends several staged batches)
+    # the large second cluster survives the filter of the filtered routes (each wave appends several staged batches)
     n, d = 3300, 32
     cent, cb, _, codes, ids = si.random_index_arrays(n, d, 3, 16, 8, salt=800)
     offs = np.array([0, 40, 3240, 3300], dtype=np.int64)
@@ -469,6 +498,7 @@ def test_search_small_nearest_cluster_admits_everything(P):
             assert_topk_matches(ids_g.cpu().numpy(), d_g.cpu().numpy(), ids_o, d_o, context=f"probes={probes_row} k={k}")
 
 
+@pytest.mark.usefixtures("route")
 def test_search_cluster_listed_twice_is_scanned_twice(P, tiny):
     w, data, oidx, gidx = tiny
     q = si.queries(w, 10)
@@ -478,6 +508,7 @@ def test_search_cluster_listed_twice_is_scanned_twice(P, tiny):
     assert_topk_matches(ids_g.cpu().numpy(), d_g.cpu().numpy(), ids_o, d_o, context="dup cluster")
 
 
+@pytest.mark.usefixtures("route")
 def test_empty_inputs(P, tiny):
     w, data, oidx, gidx = tiny
     ids, d = gidx.ivfpq_search(np.zeros((0, w.d), np.float32), 4, 10, oracle.LUT_E5M3)
@@ -850,6 +881,7 @@ def test_split_scan_when_every_group_stays_in_the_race(P):
     gidx.ivfpq_set_tuning(P.TUNE_SCAN_SHARE, 0)
 
 
+@pytest.mark.usefixtures("route")
 def test_search_nearest_cluster_smaller_than_k(P):
     # the cluster nearest to these queries holds 5 vectors, fewer than k: the search takes its bound from the
     # next probe that holds at least k (and scans that one unfiltered); the answer is the oracle's all the same
@@ -870,6 +902,7 @@ def test_search_nearest_cluster_smaller_than_k(P):
 
 # ---------------------------------------------------------------- the search inside a HIP graph
 
+@pytest.mark.usefixtures("route")
 def test_search_replays_correctly_from_a_hip_graph(P, tiny):
     # a serving loop may capture the search call once and replay it: the call only enqueues kernels
     # (no allocation, no synchronisation, no memset), so every replay must give the eager result
@@ -897,6 +930,7 @@ def test_search_replays_correctly_from_a_hip_graph(P, tiny):
         del g
 
 
+@pytest.mark.usefixtures("route")
 def test_workspace_limit_changes_tiling_not_results(P, tiny):
     w, data, oidx, gidx = tiny
     q = torch.from_numpy(si.queries(w, 300)).cuda()
@@ -919,6 +953,7 @@ def test_workspace_limit_changes_tiling_not_results(P, tiny):
 
 # ---------------------------------------------------------------- seeded random configurations
 
+@pytest.mark.usefixtures("route")
 def test_search_seeded_random_configurations(P):
     # thirty configurations drawn from a seeded generator: code widths 4-8 bits, sub-vector lengths 1-6,
     # few or many clusters (some empty), any table dtype and encoding option, k and n_probes up to the
@@ -955,6 +990,7 @@ def test_search_seeded_random_configurations(P):
         gidx.ivfpq_free()
 
 
+@pytest.mark.usefixtures("route")
 def test_search_index_without_vectors(P):
     # every cluster empty: nothing faults, every result slot is padding
     d, n_lists, pq_dim = 32, 12, 16

@@ -60,6 +60,23 @@ def test_import_export_round_trip(P):
     idx.ivfpq_free()   # idempotent
 
 
+@pytest.mark.parametrize("n", [1 << 19, (1 << 20) - 1, 1 << 20, 1_200_007])
+def test_import_export_of_large_arrays(P, n):
+    # 16-byte codes and 8-byte ids: arrays of 8 MiB and more are copied by several threads into memory that nothing
+    # cleared (4 MiB and more: aligned to huge pages); below, at and above the sizes where that begins, with a last part
+    # that is no whole page
+    rng = np.random.default_rng(n)
+    cent = rng.standard_normal((3, 16)).astype(np.float32)
+    cb = rng.standard_normal((16, 256, 1)).astype(np.float32)
+    offs = np.array([0, n // 3, n // 3, n], np.int64)
+    codes = rng.integers(0, 256, size=(n, 16), dtype=np.uint8)
+    ids = rng.permutation(n).astype(np.int64)
+    idx = P.Index.ivfpq_index_from_arrays(16, 3, 16, 8, cent, cb, offs, codes, ids)
+    for a, b in zip((cent, cb, offs, codes, ids), idx.ivfpq_index_export()):
+        np.testing.assert_array_equal(a, b)
+    idx.ivfpq_free()
+
+
 @pytest.mark.parametrize("kw,needle", [
     (dict(d=30, pq_dim=16), "multiple of pq_dim"),
     (dict(pq_bits=3), "pq_bits"),
