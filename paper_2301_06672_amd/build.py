@@ -22,7 +22,9 @@ HIP_FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-function",
 ]
-DEVICE_SOURCES = ("ivfpq_device", "ivfpq_build")       # search kernels; index construction kernels
+# (object, source, flags): search, its scan of groups of pairs (one object per table dtype), index construction
+DEVICE_OBJECTS = [("ivfpq_device", "ivfpq_device", []), ("ivfpq_build", "ivfpq_build", []),
+                  *((f"ivfpq_scan_group_{lut}", "ivfpq_scan_group", [f"-DIVFPQ_GROUP_LUT={lut}"]) for lut in range(4))]
 HOST_FLAGS = ["-O3", "-std=c++17", "-fPIC", "-fopenmp", "-mavx2", "-mfma", "-Wall"]
 
 
@@ -37,13 +39,12 @@ def build(verbose: bool = False, extra_hip_flags=()) -> str:
     os.makedirs(obj_dir, exist_ok=True)
     host_o = os.path.join(obj_dir, "ivfpq_host.o")
     _run(["g++", *HOST_FLAGS, "-c", os.path.join(CSRC, "ivfpq_host.cpp"), "-o", host_o], verbose)
-    objs = {name: os.path.join(obj_dir, name + ".o") for name in DEVICE_SOURCES}
-    with ThreadPoolExecutor(max_workers=len(objs)) as pool:
-        jobs = [pool.submit(_run, [HIPCC, *HIP_FLAGS, *extra_hip_flags, "-c", os.path.join(CSRC, name + ".hip"), "-o", obj], verbose)
-                for name, obj in objs.items()]
+    dev_objs = [os.path.join(obj_dir, name + ".o") for name, _, _ in DEVICE_OBJECTS]
+    with ThreadPoolExecutor(max_workers=len(dev_objs)) as pool:
+        jobs = [pool.submit(_run, [HIPCC, *HIP_FLAGS, *extra_hip_flags, *flags, "-c", os.path.join(CSRC, source + ".hip"), "-o", obj], verbose)
+                for (_, source, flags), obj in zip(DEVICE_OBJECTS, dev_objs)]
         for job in jobs:
             job.result()
-    dev_objs = list(objs.values())
     _run([HIPCC, "--offload-arch=gfx950", "-shared", "-o", LIB_PATH, host_o, *dev_objs, "-lgomp"], verbose)
     return LIB_PATH
 

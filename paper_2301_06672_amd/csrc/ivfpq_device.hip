@@ -41,6 +41,7 @@
 #include "ivfpq_rank.hpp"
 #include "ivfpq_lds_util.hpp"
 #include "ivfpq_lut.hpp"
+#include "ivfpq_scan_args.hpp"
 #include "ivfpq_select.hpp"
 
 using namespace ivfpq;
@@ -551,35 +552,7 @@ __device__ inline float add_group(float acc, const unsigned char* lut, const uin
     return acc;
 }
 
-constexpr int kAliveCap = 64;    // groups of a wave that the first pass of the split scan can note for the second
 constexpr int kStageCap = 128;   // survivors a wave stages in LDS before it appends them (8 bytes each)
-
-struct ScanArgs {
-    const float* queries;         // [nq][d] (tile base)
-    const float* centroids;
-    const float* codebooks;
-    const uint32_t* list_sizes;
-    const int64_t* group_offsets;
-    const uint8_t* codes;
-    const uint4* pairs;           // [nq][n_probes] {cluster, length, first group, R offset}; unused in single-list mode
-    const uint32_t* bounds;       // [nq] per-query upper bound of the k-th smallest R (filtered mode)
-    uint32_t* counts;             // [nq] survivors appended so far (filtered mode)
-    uint32_t* Rpos;               // [nq][stride] row position of each appended survivor (filtered mode)
-    Fp8Mode fp8;                  // encoding of the 8-bit table dtypes (unused by the other two)
-    int mode;                     // 1: nearest probe of every query, every R written in place; 3: the same for all probes;
-                                  // 2: the other probes, only R <= bound appended behind the nearest probe's segment
-    float* R;                     // [nq][stride]
-    size_t stride;
-    int n_probes;
-    int n_lists;
-    int d, pq_dim, m, bits;
-    int n_chunks;                 // chunks per vector (code_bytes / CW)
-    int single_list;              // >= 0: scan this cluster for query 0, R written from offset 0
-    const uint32_t* order;        // mode 2: pairs (as q * (n_probes - 1) + probe - 1) grouped by cluster, or null
-    uint32_t n_pairs;             // mode 2: number of such pairs
-    uint32_t order_block;         // mode 2: consecutive pairs of the grouped order that stay on one XCD
-    int early_exit;               // mode 2: stop adding for a 64-vector group once every partial sum is over the bound
-};
 
 // Code layout of one cluster (written by ivfpq_upload): vectors in groups of 64 (the last one
 // zero-padded); inside a group, chunk c of all 64 vectors is contiguous:
@@ -834,8 +807,6 @@ scan_kernel(ScanArgs a) {
     }
     if (filtered) flush_stage();
 }
-
-#include "ivfpq_scan_group.hpp"
 
 // Steps 2-3 only: the table of one pair, copied out of LDS byte for byte.
 template <int LUT>
@@ -1294,23 +1265,6 @@ ScanRoute scan_route(const ivfpq_index* idx, int nq, int n_probes) {
 
 bool group_pairs_by_cluster(size_t n_pairs) { return n_pairs < ((size_t)1 << 32) - 8 * (size_t)kOrderBlock; }
 
-// The scan kernels address their tables by LDS offsets counted from 0: their dynamic LDS must be the first
-// thing in the workgroup's LDS, which holds when the compiled kernel has no static LDS.  Checked once per
-// kernel (hipFuncGetAttributes is not a stream operation; later launches make no call besides the launch).
-int require_no_static_lds(const void* kernel) {
-    static std::mutex mu;
-    static std::vector<const void*> ok;
-    std::lock_guard<std::mutex> lock(mu);
-    for (const void* k : ok)
-        if (k == kernel) return IVFPQ_OK;
-    hipFuncAttributes attr;
-    HIP_TRY(hipFuncGetAttributes(&attr, kernel));
-    if (attr.sharedSizeBytes != 0)
-        return fail(IVFPQ_EUNSUPPORTED, "internal: a scan kernel was built with %zu bytes of static LDS", (size_t)attr.sharedSizeBytes);
-    ok.push_back(kernel);
-    return IVFPQ_OK;
-}
-
 template <int LUT, int BITS>
 int launch_scan_bits(const ScanArgs& a, int cw, int nch, dim3 grid, int threads, size_t lds, hipStream_t st) {
     auto go = [&](auto kernel) -> int {
@@ -1414,51 +1368,11 @@ int launch_scan_group(const ivfpq_index* idx, const ScanArgs& a, int lut_dtype, 
     const int threads = scan_group_threads(idx, lut_dtype, G);
     const size_t lds = scan_group_lds_bytes(idx, lut_dtype, G, threads);
     if (lds > kLdsBytes) return fail(IVFPQ_EUNSUPPORTED, "tables + staging + pad need %zu bytes of LDS (limit %zu)", lds, kLdsBytes);
-    const uint32_t n_slots = (a.n_pairs + (uint32_t)G - 1u) / (uint32_t)G, per = 8u * (a.order_block / (uint32_t)G);
-    const dim3 grid((n_slots + per - 1) / per * per);
-    auto go = [&](auto kernel) -> int {
-        if (int s = allow_full_lds(kernel)) return s;
-        if (int s = require_no_static_lds(reinterpret_cast<const void*>(kernel))) return s;
-        hipLaunchKernelGGL(kernel, grid, dim3(threads), lds, st, a);
-        HIP_TRY(hipGetLastError());
-        return IVFPQ_OK;
-    };
-    const int nch = a.n_chunks;
-    auto by_bits = [&](auto lut_tag, auto g_tag, auto bits_tag) -> int {
-        constexpr int LUT = decltype(lut_tag)::value, GG = decltype(g_tag)::value, BITS = decltype(bits_tag)::value;
-        constexpr int NCH = BITS == 6 ? 3 : 2 * BITS;            // 64 sub-spaces: 40 or 56 bytes in words, 48 in 16-byte chunks
-        if constexpr (GG == 4 && !kIsFp8<LUT>) return fail(IVFPQ_EUNSUPPORTED, "internal: no group kernel for four pairs of %d-bit codes", BITS);
-        else return a.early_exit ? go(scan_group_kernel<LUT, NCH, GG, BITS, true>) : go(scan_group_kernel<LUT, NCH, GG, BITS, false>);
-    };
-    auto by_nch = [&](auto lut_tag, auto g_tag) -> int {
-        constexpr int LUT = decltype(lut_tag)::value, GG = decltype(g_tag)::value;
-        if (idx->pq_bits == 7) return by_bits(lut_tag, g_tag, std::integral_constant<int, 7>{});
-        if (idx->pq_bits == 6) return by_bits(lut_tag, g_tag, std::integral_constant<int, 6>{});
-        if (idx->pq_bits == 5) return by_bits(lut_tag, g_tag, std::integral_constant<int, 5>{});
-        if (idx->pq_bits == 4)
-            switch (nch) {
-                case 1: return go(scan_group_kernel<LUT, 1, GG, 4, false>);
-                case 2: return go(scan_group_kernel<LUT, 2, GG, 4, false>);
-                case 3: return go(scan_group_kernel<LUT, 3, GG, 4, false>);
-                default: return go(scan_group_kernel<LUT, 4, GG, 4, false>);
-            }
-        switch (nch) {
-            case 1: return go(scan_group_kernel<LUT, 1, GG, 8, false>);
-            case 2: return go(scan_group_kernel<LUT, 2, GG, 8, false>);
-            case 3: return go(scan_group_kernel<LUT, 3, GG, 8, false>);
-            default:
-                // 64 sub-spaces with the early exit on: the second half of the tables is built only if needed
-                return a.early_exit ? go(scan_group_kernel<LUT, 4, GG, 8, true>) : go(scan_group_kernel<LUT, 4, GG, 8, false>);
-        }
-    };
-    auto by_g = [&](auto lut_tag) -> int {
-        return G == 4 ? by_nch(lut_tag, std::integral_constant<int, 4>{}) : by_nch(lut_tag, std::integral_constant<int, 2>{});
-    };
     switch (lut_dtype) {
-        case IVFPQ_LUT_FP32: return by_g(std::integral_constant<int, IVFPQ_LUT_FP32>{});
-        case IVFPQ_LUT_FP16: return by_g(std::integral_constant<int, IVFPQ_LUT_FP16>{});
-        case IVFPQ_LUT_FP8_E5M3: return by_g(std::integral_constant<int, IVFPQ_LUT_FP8_E5M3>{});
-        default: return by_g(std::integral_constant<int, IVFPQ_LUT_FP8_E4M4>{});
+        case IVFPQ_LUT_FP32: return launch_scan_group_kernel<IVFPQ_LUT_FP32>(a, G, threads, lds, st);
+        case IVFPQ_LUT_FP16: return launch_scan_group_kernel<IVFPQ_LUT_FP16>(a, G, threads, lds, st);
+        case IVFPQ_LUT_FP8_E5M3: return launch_scan_group_kernel<IVFPQ_LUT_FP8_E5M3>(a, G, threads, lds, st);
+        default: return launch_scan_group_kernel<IVFPQ_LUT_FP8_E4M4>(a, G, threads, lds, st);
     }
 }
 

@@ -1,5 +1,5 @@
 // Small device helpers of the scan kernels: LDS reads from integer addresses, sub-dword shifts, half-precision
-// accumulation in one instruction, compile-time loops.  Included by ivfpq_device.hip only.
+// accumulation in one instruction, compile-time loops.  Included by .hip translation units only.
 #pragma once
 
 #include <cstdint>

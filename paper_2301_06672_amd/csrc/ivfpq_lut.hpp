@@ -1,5 +1,5 @@
 // Table entries: the conversions between FP32 and the storage types of a lookup table (fp32, half, e5m3, e4m4), and
-// the direct-form distance of one entry.  Included by .hip translation units only; everything has internal linkage.
+// the direct-form distance of one entry.  Included by .hip translation units only; the code has internal linkage.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -7,7 +7,23 @@
 
 #include "ivfpq_internal.hpp"
 
+namespace ivfpq {
+
+struct Fp8Params { int lo, hi, sub; };   // of fp8_params below
+
+// Encoding of an 8-bit table as the caller configured it: fixed constants, or a bias chosen per table.
+struct Fp8Mode {
+    Fp8Params fixed;     // constants for the configured bias and rounding
+    int truncate;        // rounding of the encode: 0 nearest (ties up), 1 truncate
+    int per_table;       // 1: the bias follows the largest entry of each table
+};
+
+}  // namespace ivfpq
+
 namespace {
+
+using ivfpq::Fp8Mode;
+using ivfpq::Fp8Params;
 
 template <int LUT> struct LutTraits;     // bytes: size of one table entry
 template <> struct LutTraits<IVFPQ_LUT_FP32> { static constexpr int bytes = 4; };
@@ -33,8 +49,6 @@ template <int LUT> constexpr bool kIsFp8 = LUT == IVFPQ_LUT_FP8_E5M3 || LUT == I
 // an 8-bit ulp, so that the shift rounds to nearest with ties up, or lo itself to truncate.  The clamp
 // acts on the pattern as a signed integer: zero and negatives give code 0, +Inf code 255.
 // e5m3 with B = 15: lo = 0x38000000, hi = 0x47F00000, sub = 0x37F80000.
-struct Fp8Params { int lo, hi, sub; };
-
 __host__ __device__ inline Fp8Params fp8_params(int shift, int bias, int truncate) {
     Fp8Params p;
     p.lo = (127 - bias) << 23;
@@ -85,12 +99,4 @@ __device__ inline float lut_entry(const float* cbv, const float* rq) {
     }
     return acc;
 }
-
-// Encoding of an 8-bit table as the caller configured it: fixed constants, or a bias chosen per table.
-struct Fp8Mode {
-    Fp8Params fixed;     // constants for the configured bias and rounding
-    int truncate;        // rounding of the encode: 0 nearest (ties up), 1 truncate
-    int per_table;       // 1: the bias follows the largest entry of each table
-};
-
 }  // namespace

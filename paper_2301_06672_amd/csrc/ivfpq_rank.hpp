@@ -1,51 +1,15 @@
-// Device code shared by the search kernels and the index builder: HIP error macro, small constants,
-// order-preserving float keys and the MFMA ranking GEMMs |c|^2 - 2 x.c (fp32, and bf16 on split operands)
-// with their epilogue (all keys, or per-strip summaries) and the bound of their error.
+// Device code shared by the search kernels and the index builder: order-preserving float keys and the MFMA ranking
+// GEMMs |c|^2 - 2 x.c (fp32, and bf16 on split operands) with their epilogue (all keys, or per-strip summaries) and the bound of their error.
 // Included by .hip translation units only; everything has internal linkage.
 #pragma once
 
 #include <hip/hip_runtime.h>
 
-#include <mutex>
 #include <type_traits>
-#include <utility>
-#include <vector>
 
-#include "ivfpq_internal.hpp"
-
-#define HIP_TRY(expr)                                                                               \
-    do {                                                                                            \
-        hipError_t e_ = (expr);                                                                     \
-        if (e_ != hipSuccess)                                                                       \
-            return ivfpq::fail(IVFPQ_EHIP, "%s failed: %s (%s:%d)", #expr, hipGetErrorString(e_), __FILE__, __LINE__); \
-    } while (0)
+#include "ivfpq_hip_util.hpp"
 
 namespace {
-
-using ivfpq::fail;
-
-constexpr int kWave = 64;
-constexpr size_t kLdsBytes = 160 * 1024;       // LDS of one gfx950 compute unit
-constexpr size_t kAlign = 256;
-
-inline size_t align_up(size_t x, size_t a = kAlign) { return (x + a - 1) / a * a; }
-
-// Lets `kernel` use dynamic LDS up to the whole compute unit's; done once per kernel and device, so
-// that later launches make no call besides the launch itself (a caller may be capturing a HIP graph).
-inline int allow_full_lds_ptr(const void* kernel) {
-    static std::mutex mu;
-    static std::vector<std::pair<const void*, int>> done;
-    int dev = 0;
-    HIP_TRY(hipGetDevice(&dev));
-    std::lock_guard<std::mutex> lock(mu);
-    for (const auto& e : done)
-        if (e.first == kernel && e.second == dev) return IVFPQ_OK;
-    HIP_TRY(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes));
-    done.emplace_back(kernel, dev);
-    return IVFPQ_OK;
-}
-template <class Kernel>
-int allow_full_lds(Kernel kernel) { return allow_full_lds_ptr(reinterpret_cast<const void*>(kernel)); }
 
 // ================================================================================================
 // Ranking values on the matrix cores (search step 1a; the assignment step of the index build).

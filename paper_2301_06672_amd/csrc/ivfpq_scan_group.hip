@@ -1,5 +1,6 @@
 // The filtered scan for up to G (query, probe) pairs of ONE cluster per workgroup (8-bit or 4-bit codes in
-// 16-byte chunks, 64 sub-spaces of bit-packed 5- to 7-bit codes; every table dtype).  Included by ivfpq_device.hip after the table helpers it uses.
+// 16-byte chunks, 64 sub-spaces of bit-packed 5- to 7-bit codes; every table dtype).  Compiled once per table dtype,
+// IVFPQ_GROUP_LUT, so that its many kernels compile side by side.
 //
 // In the cluster-grouped order neighbouring pairs share their cluster, and everything that depends on the
 // cluster alone is then done once for all of them: a codebook entry is loaded once and becomes R table
@@ -33,11 +34,18 @@
 // such runs at the seams between clusters.
 // LDS: the slot's pair descriptors | tables | R residuals of d floats | per wave kGroupStageAll staged survivors |
 // a flag and, per wave, kAliveCap group numbers of the split scan.
-#pragma once
+#include <hip/hip_runtime.h>
 
-constexpr int kGroupStageAll = 128;  // survivors a wave stages before it appends them, over all queries of a run: 128 / R per query
-                                     // (a 64-vector group with more survivors than that goes straight to the list)
-constexpr int kGroupHead = 128;      // bytes at the start of the kernel's LDS that hold the slot's pair descriptors
+#include <type_traits>
+
+#include "ivfpq_hip_util.hpp"
+#include "ivfpq_lds_util.hpp"
+#include "ivfpq_lut.hpp"
+#include "ivfpq_scan_args.hpp"
+
+using namespace ivfpq;
+
+namespace {
 
 // 4 * R table entries -- codes u = 0..3 of one lane, queries g = 0..R-1, f[u * R + g] -- converted to the
 // table dtype and stored at `dst` (their place in the interleaved table: 4 * R * entry_bytes contiguous bytes)
@@ -517,3 +525,49 @@ scan_group_kernel(ScanArgs a) {
         i += r;
     }
 }
+
+}  // namespace
+
+template <int LUT>
+int ivfpq::launch_scan_group_kernel(const ScanArgs& a, int G, int threads, size_t lds, hipStream_t st) {
+    const uint32_t n_slots = (a.n_pairs + (uint32_t)G - 1u) / (uint32_t)G, per = 8u * (a.order_block / (uint32_t)G);
+    const dim3 grid((n_slots + per - 1) / per * per);
+    auto go = [&](auto kernel) -> int {
+        if (int s = allow_full_lds(kernel)) return s;
+        if (int s = require_no_static_lds(reinterpret_cast<const void*>(kernel))) return s;
+        hipLaunchKernelGGL(kernel, grid, dim3(threads), lds, st, a);
+        HIP_TRY(hipGetLastError());
+        return IVFPQ_OK;
+    };
+    const int nch = a.n_chunks;
+    auto by_bits = [&](auto g_tag, auto bits_tag) -> int {
+        constexpr int GG = decltype(g_tag)::value, BITS = decltype(bits_tag)::value;
+        constexpr int NCH = BITS == 6 ? 3 : 2 * BITS;            // 64 sub-spaces: 40 or 56 bytes in words, 48 in 16-byte chunks
+        if constexpr (GG == 4 && !kIsFp8<LUT>) return fail(IVFPQ_EUNSUPPORTED, "internal: no group kernel for four pairs of %d-bit codes", BITS);
+        else return a.early_exit ? go(scan_group_kernel<LUT, NCH, GG, BITS, true>) : go(scan_group_kernel<LUT, NCH, GG, BITS, false>);
+    };
+    auto by_nch = [&](auto g_tag) -> int {
+        constexpr int GG = decltype(g_tag)::value;
+        if (a.bits == 7) return by_bits(g_tag, std::integral_constant<int, 7>{});
+        if (a.bits == 6) return by_bits(g_tag, std::integral_constant<int, 6>{});
+        if (a.bits == 5) return by_bits(g_tag, std::integral_constant<int, 5>{});
+        if (a.bits == 4)
+            switch (nch) {
+                case 1: return go(scan_group_kernel<LUT, 1, GG, 4, false>);
+                case 2: return go(scan_group_kernel<LUT, 2, GG, 4, false>);
+                case 3: return go(scan_group_kernel<LUT, 3, GG, 4, false>);
+                default: return go(scan_group_kernel<LUT, 4, GG, 4, false>);
+            }
+        switch (nch) {
+            case 1: return go(scan_group_kernel<LUT, 1, GG, 8, false>);
+            case 2: return go(scan_group_kernel<LUT, 2, GG, 8, false>);
+            case 3: return go(scan_group_kernel<LUT, 3, GG, 8, false>);
+            default:
+                // 64 sub-spaces with the early exit on: the second half of the tables is built only if needed
+                return a.early_exit ? go(scan_group_kernel<LUT, 4, GG, 8, true>) : go(scan_group_kernel<LUT, 4, GG, 8, false>);
+        }
+    };
+    return G == 4 ? by_nch(std::integral_constant<int, 4>{}) : by_nch(std::integral_constant<int, 2>{});
+}
+
+template int ivfpq::launch_scan_group_kernel<IVFPQ_GROUP_LUT>(const ScanArgs&, int, int, size_t, hipStream_t);

@@ -143,7 +143,7 @@ def test_tuning_setter_validates(P):
 
 def test_library_reads_no_environment_variable():
     # tuning is per index (ivfpq_set_tuning): no hidden process-global state
-    for name in ("ivfpq_device.hip", "ivfpq_build.hip", "ivfpq_host.cpp", "ivfpq_rank.hpp", "ivfpq_internal.hpp"):
+    for name in ("ivfpq_device.hip", "ivfpq_scan_group.hip", "ivfpq_build.hip", "ivfpq_host.cpp", "ivfpq_rank.hpp", "ivfpq_internal.hpp", "ivfpq_hip_util.hpp"):
         text = open(os.path.join(ROOT, "paper_2301_06672_amd", "csrc", name)).read()
         assert "getenv" not in text, name
 
