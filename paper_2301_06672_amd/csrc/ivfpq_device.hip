@@ -1323,8 +1323,16 @@ int scan_group_threads(const ivfpq_index* idx, int lut_dtype, int G) {
     if (long_lists && scan_group_lds_bytes(idx, lut_dtype, G, 128) <= 24 * 1024) return 128;
     return scan_group_lds_bytes(idx, lut_dtype, G, 256) <= kGroupLds4 ? 256 : 512;
 }
+// Bit-packed codes of how many sub-spaces the group kernel is built for: whole words with no more than 21 of them (two
+// buffers of a vector's words beside the sums of four queries fill the registers), 16 sub-spaces aside (fewer than two
+// steps).
+bool scan_group_packed(int pq_bits, int pq_dim) {
+    return pq_dim == 32 || pq_dim == 64 || pq_dim == 96 || (pq_bits == 6 && pq_dim == 48);
+}
+
 // How many pairs of a cluster share a workgroup (0: the group kernel does not apply).  It serves 8-bit and 4-bit
-// codes in 16-byte chunks, 64 sub-spaces of 5- to 7-bit codes, sub-vectors of 1, 2 or 4 components and fixed encoding constants.  The widest layout
+// codes in 16-byte chunks, 5- to 7-bit codes of 32 to 96 sub-spaces, sub-vectors of 1, 2 or 4 components and fixed
+// encoding constants.  The widest layout
 // is taken that leaves room for 16 waves per compute unit (scan_group_threads: 40 KB of LDS with four waves, 80 KB with eight),
 // but not four pairs on eight waves where two pairs leave room for more than 16 waves (five workgroups of 32 KB).  Eight
 // waves pay where the shared table build is heavy: half tables at four pairs with sub-vectors of four components (two components, 32
@@ -1338,11 +1346,19 @@ int scan_group_threads(const ivfpq_index* idx, int lut_dtype, int G) {
 // With 4-bit codes (16-entry rows, a few KB of tables) four pairs for every dtype: filtered scan, 10^8 vectors,
 // 64 sub-spaces, e5m3 6.67 / 5.95 / 5.21 ms, half 7.56 / 6.48 / 4.62, float 6.31 / 4.71 / 4.02.  Bit-packed codes, whole
 // search of 10^6 vectors, 20 probes: 7 bits e5m3 2.35 / 1.67 / 1.46 ms, half 2.45 / 1.90 / -; 6 bits 1.91 / 1.59 / 1.37, half
-// 1.98 / 1.76, float 1.97 / 1.37; 5 bits 2.03 / 1.58 / 1.37, half 2.09 / 1.72, float 1.74 / 1.23.  (Other numbers of sub-spaces
-// of these widths, 4 pairs of their wider tables and the split scan of one pair are not built: each is more kernels to compile.)
+// 1.98 / 1.76, float 1.97 / 1.37; 5 bits 2.03 / 1.58 / 1.37, half 2.09 / 1.72, float 1.74 / 1.23 (64 sub-spaces).
+// Other numbers of them, e5m3 one / two / four pairs, half and float one / two:
+//   32  7 bits 2.03 / 1.28 / 1.09, 2.21 / 1.40, 2.48 / 1.20; 6 bits 1.33 / 1.18 / 1.01, 1.40 / 1.28, 1.30 / 1.07;
+//       5 bits 1.87 / 1.11 / 0.95, 1.94 / 1.20, 1.61 / 0.97
+//   48  6 bits 1.08 / 1.03 / 0.93, 1.14 / 1.12, 1.06 / 0.93
+//   96  (one component) 7 bits 1.78 / 1.42 / 1.47, 2.21 / 1.94*, 2.69 / 2.50*; 6 bits 1.62 / 1.35 / 1.23, 1.72 / 1.51,
+//       1.93 / 1.46*; 5 bits 1.52 / 1.29 / 1.16, 1.58 / 1.42, 1.32 / 1.08
+// (Four pairs of their wider tables and the split scan of one pair are not built.  One kernel per width that walks any
+// number of sub-spaces in units of 32 costs 64 of them 8 to 12 %: the unit's place joins every address and the walk's
+// state spills.)
 int scan_group_width(const ivfpq_index* idx, int lut_dtype, const Fp8Mode& fp8, uint32_t order_block) {
     const bool packed = idx->pq_bits != 8 && idx->pq_bits != 4;
-    if (fp8.per_table || (packed ? idx->pq_dim != 64 : chunk_width(idx) != 16)) return 0;
+    if (fp8.per_table || (packed ? !scan_group_packed(idx->pq_bits, idx->pq_dim) : chunk_width(idx) != 16)) return 0;
     if (idx->pq_bits == 4 && idx->pq_dim % 16 != 0) return 0;      // the table is built in blocks of 256 entries
     const int m = idx->d / idx->pq_dim;
     if (m != 1 && m != 2 && m != 4) return 0;

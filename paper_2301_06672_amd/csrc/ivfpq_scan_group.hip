@@ -1,5 +1,5 @@
-// The filtered scan for up to G (query, probe) pairs of ONE cluster per workgroup (8-bit or 4-bit codes in
-// 16-byte chunks, 64 sub-spaces of bit-packed 5- to 7-bit codes; every table dtype).  Compiled once per table dtype,
+// The filtered scan for up to G (query, probe) pairs of ONE cluster per workgroup (8-bit or 4-bit codes in 16-byte
+// chunks, bit-packed 5- to 7-bit codes of up to 96 sub-spaces; every table dtype).  Compiled once per table dtype,
 // IVFPQ_GROUP_LUT, so that its many kernels compile side by side.
 //
 // In the cluster-grouped order neighbouring pairs share their cluster, and everything that depends on the
@@ -27,7 +27,7 @@
 // code word are masked and shifted to entry offsets four at a time (two instructions per four offsets), so that
 // byte b of the one result is the LDS offset for sub-space 2b and byte b of the other that for 2b + 1.
 // 5- to 7-bit codes: a field and its scaling to an entry offset are one (funnel) shift and one mask, shared by the R
-// queries; every field position is a constant, since 32 sub-spaces fill whole words.
+// queries; every field position is a constant of the kernel, which is built for a number of code words.
 //
 // A run of 1, 2, 3 or 4 pairs of one cluster is processed at once (3 in the 4-wide layout with one byte of
 // every entry unused).  A workgroup takes G consecutive pairs of the grouped order and cuts them into
@@ -78,17 +78,20 @@ __device__ __forceinline__ void store_packed(unsigned char* dst, const float (&f
 }
 
 // Q pairs of one cluster, q[g], pair[g], with tables interleaved R >= Q wide (Q < R: the entries of the missing
-// queries are zero bytes that nobody decodes; three pairs run as Q = 3 in the R = 4 layout)
-template <int LUT, int NCH, int R, int Q, int BITS, bool SPLIT>
+// queries are zero bytes that nobody decodes; three pairs run as Q = 3 in the R = 4 layout).
+// LEN: length of a vector's code, in 16-byte chunks; of bit-packed codes, in 4-byte words.
+template <int LUT, int LEN, int R, int Q, int BITS, bool SPLIT>
 __device__ __forceinline__ void group_run(const ScanArgs& a, unsigned char* smem, const int (&q)[Q], const uint4 (&pair)[Q]) {
     static_assert(Q >= 1 && Q <= R, "queries of a run fit its interleave width");
     static_assert(BITS >= 4 && BITS <= 8, "codes of 4 to 8 bits");
     constexpr bool PACKED = BITS != 8 && BITS != 4;     // fields that straddle bytes and words
-    constexpr int CW = PACKED && BITS != 6 ? 4 : 16;    // bytes of a chunk (chunk_width)
-    static_assert(!PACKED || NCH * CW == 8 * BITS, "bit-packed codes come in 64 sub-spaces");
+    constexpr int WORDS = PACKED ? LEN : 4 * LEN;
+    constexpr int CW = PACKED && !(BITS == 6 && WORDS == 12) ? 4 : 16;      // bytes of a chunk (chunk_width)
+    constexpr int NCH = WORDS * 4 / CW, SUBS = WORDS * 32 / BITS;           // chunks and sub-spaces of a vector
+    static_assert(NCH * CW == WORDS * 4 && SUBS * BITS == WORDS * 32 && SUBS % 16 == 0, "whole chunks, whole steps");
     using chunk_t = typename std::conditional<CW == 16, uint4, uint32_t>::type;
-    constexpr int STEPS = PACKED ? 4 : NCH;             // steps of an accumulation, with the early exit's test between them: a chunk,
-                                                        // or 16 bit-packed sub-spaces
+    constexpr int STEPS = PACKED ? SUBS / 16 : NCH;     // steps of an accumulation, with the early exit's test between
+                                                        // them: a chunk, or 16 bit-packed sub-spaces
     constexpr int E = LutTraits<LUT>::bytes, W = E * R, LOGW = ilog2(W), KSUB = 1 << BITS;
     static_assert(BITS != 4 || 15 * W < 256, "a 4-bit code's entry offset fits a byte");
     constexpr int kGroupStage = kGroupStageAll / R;
@@ -135,7 +138,7 @@ __device__ __forceinline__ void group_run(const ScanArgs& a, unsigned char* smem
     // 64 sub-spaces of 5- to 8-bit codes with the early exit on: most groups are over every bound after half of the
     // sub-spaces, so only the first 32 rows are built now; the rest follows if some group is still in the race
     // (scan_kernel's split scan, for a run of queries)
-    static_assert(!SPLIT || PACKED || (BITS == 8 && NCH == 4), "the split scan is for 64 sub-spaces of 5- to 8-bit codes");
+    static_assert(!SPLIT || (BITS != 4 && SUBS >= 64), "the split scan is for 64 sub-spaces of 5- to 8-bit codes");
     constexpr bool lazy = SPLIT;
     uint32_t* any_alive = reinterpret_cast<uint32_t*>(after_rq + (size_t)n_waves * kGroupStageAll * 8);
     uint16_t* alive = reinterpret_cast<uint16_t*>(any_alive + 4) + (size_t)wave * kAliveCap;
@@ -397,7 +400,7 @@ __device__ __forceinline__ void group_run(const ScanArgs& a, unsigned char* smem
     constexpr std::integral_constant<int, STEPS> kAllSteps{};
     if constexpr (SPLIT) {
         {
-            constexpr int HCH = (4 * BITS + CW - 1) / CW;       // chunks of the first pass: the codes of the 32 leading sub-spaces
+            constexpr int HCH = (SUBS / 2 * BITS / 8 + CW - 1) / CW;     // chunks of the first pass: half of the sub-spaces
             uint32_t n_alive = 0;                   // wave-uniform
             bool redo_all = false;                  // more groups in the race than the list holds: take them all again
             auto load_head = [&](chunk_t (&buf)[NCH], int g) __attribute__((always_inline)) {
@@ -466,7 +469,7 @@ __device__ __forceinline__ void group_run(const ScanArgs& a, unsigned char* smem
 // XCDs in blocks of order_block / G, which is the dealing of scan_kernel's pairs in blocks of order_block.
 // The first kGroupHead bytes of the LDS hold the slot's pair descriptors (the runs read them by position);
 // group_run's `smem` starts behind them.
-template <int LUT, int NCH, int G, int BITS, bool SPLIT>
+template <int LUT, int LEN, int G, int BITS, bool SPLIT>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 8)))
 scan_group_kernel(ScanArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -502,12 +505,12 @@ scan_group_kernel(ScanArgs a) {
             if (r == 4) {
                 const int qq[4] = {q_at(i), q_at(i + 1), q_at(i + 2), q_at(i + 3)};
                 const uint4 pp[4] = {pair_at(i), pair_at(i + 1), pair_at(i + 2), pair_at(i + 3)};
-                group_run<LUT, NCH, 4, 4, BITS, SPLIT>(a, body, qq, pp);
+                group_run<LUT, LEN, 4, 4, BITS, SPLIT>(a, body, qq, pp);
                 done = true;
             } else if (r == 3) {
                 const int qq[3] = {q_at(i), q_at(i + 1), q_at(i + 2)};
                 const uint4 pp[3] = {pair_at(i), pair_at(i + 1), pair_at(i + 2)};
-                group_run<LUT, NCH, 4, 3, BITS, SPLIT>(a, body, qq, pp);
+                group_run<LUT, LEN, 4, 3, BITS, SPLIT>(a, body, qq, pp);
                 done = true;
             }
         }
@@ -515,11 +518,11 @@ scan_group_kernel(ScanArgs a) {
             if (r == 2) {
                 const int qq[2] = {q_at(i), q_at(i + 1)};
                 const uint4 pp[2] = {pair_at(i), pair_at(i + 1)};
-                group_run<LUT, NCH, 2, 2, BITS, SPLIT>(a, body, qq, pp);
+                group_run<LUT, LEN, 2, 2, BITS, SPLIT>(a, body, qq, pp);
             } else {
                 const int qq[1] = {q_at(i)};
                 const uint4 pp[1] = {pair_at(i)};
-                group_run<LUT, NCH, 1, 1, BITS, SPLIT>(a, body, qq, pp);
+                group_run<LUT, LEN, 1, 1, BITS, SPLIT>(a, body, qq, pp);
             }
         }
         i += r;
@@ -542,9 +545,19 @@ int ivfpq::launch_scan_group_kernel(const ScanArgs& a, int G, int threads, size_
     const int nch = a.n_chunks;
     auto by_bits = [&](auto g_tag, auto bits_tag) -> int {
         constexpr int GG = decltype(g_tag)::value, BITS = decltype(bits_tag)::value;
-        constexpr int NCH = BITS == 6 ? 3 : 2 * BITS;            // 64 sub-spaces: 40 or 56 bytes in words, 48 in 16-byte chunks
-        if constexpr (GG == 4 && !kIsFp8<LUT>) return fail(IVFPQ_EUNSUPPORTED, "internal: no group kernel for four pairs of %d-bit codes", BITS);
-        else return a.early_exit ? go(scan_group_kernel<LUT, NCH, GG, BITS, true>) : go(scan_group_kernel<LUT, NCH, GG, BITS, false>);
+        if constexpr (GG == 2 || kIsFp8<LUT>) {
+            // 64 sub-spaces or more with the early exit on: the second half of the tables is built only if needed
+            switch (a.pq_dim) {
+                case 32: return go(scan_group_kernel<LUT, BITS, GG, BITS, false>);
+                case 48:
+                    if constexpr (BITS == 6) return go(scan_group_kernel<LUT, 9, GG, BITS, false>);
+                    break;
+                case 64: return a.early_exit ? go(scan_group_kernel<LUT, 2 * BITS, GG, BITS, true>) : go(scan_group_kernel<LUT, 2 * BITS, GG, BITS, false>);
+                case 96: return a.early_exit ? go(scan_group_kernel<LUT, 3 * BITS, GG, BITS, true>) : go(scan_group_kernel<LUT, 3 * BITS, GG, BITS, false>);
+                default: break;
+            }
+        }
+        return fail(IVFPQ_EUNSUPPORTED, "internal: no group kernel for %d pairs of %d sub-spaces of %d bits", GG, a.pq_dim, BITS);
     };
     auto by_nch = [&](auto g_tag) -> int {
         constexpr int GG = decltype(g_tag)::value;
