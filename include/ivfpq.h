@@ -276,7 +276,9 @@ int ivfpq_stage_times_ms(ivfpq_index_t* index, float ms[8]);
 
 /* Writes into buf (host, buf_bytes > 0, always terminated) the name, workgroup size and LDS request of the
  * kernel that scans the probes other than the nearest one (the dominant kernel of a search) for this index,
- * table dtype and current tuning: what to look for in a profiler's kernel list. */
+ * table dtype and current tuning: what to look for in a profiler's kernel list.  It describes large batches, whose
+ * pairs run grouped by cluster, unless IVFPQ_TUNE_SCAN_ROUTE names another route: the searches of little work that the
+ * library sends there run scan_kernel, and with more threads than the index asks for where its workgroups are few. */
 int ivfpq_scan_kernel_info(const ivfpq_index_t* index, int32_t lut_dtype, char* buf, size_t buf_bytes);
 
 /* Measurement aid, not a step of the method: a plain streaming read of `bytes` bytes of device memory

@@ -1896,7 +1896,8 @@ int ivfpq_scan_kernel_info(const ivfpq_index_t* idx, int32_t lut_dtype, char* bu
     static const char* const names[4] = {"fp32", "fp16", "e5m3", "e4m4"};
     const int threads = scan_threads(idx, lut_dtype), cw = chunk_width(idx), nch = idx->code_bytes() / cw;
     const uint32_t blk = idx->tuning.order_block > 0 ? (uint32_t)idx->tuning.order_block : kOrderBlock;
-    if (const int G = scan_group_width(idx, lut_dtype, fp8_mode(idx, lut_dtype), blk))
+    const bool grouped = idx->tuning.scan_route == 0 || idx->tuning.scan_route == (int)ScanRoute::kGrouped;      // 0: what large batches take
+    if (const int G = grouped ? scan_group_width(idx, lut_dtype, fp8_mode(idx, lut_dtype), blk) : 0)
         snprintf(buf, buf_bytes, "scan_group_kernel<%s, %d-bit codes, %d chunks, %d pairs> %d threads, %zu bytes of LDS", names[lut_dtype], idx->pq_bits, nch, G,
                  scan_group_threads(idx, lut_dtype, G), scan_group_lds_bytes(idx, lut_dtype, G, scan_group_threads(idx, lut_dtype, G)));
     else

@@ -141,6 +141,14 @@ def test_tuning_setter_validates(P):
         assert e.value.status == P.EINVAL
 
 
+def test_scan_kernel_info_follows_the_route(P):
+    # only the route that groups pairs by cluster (large batches, the default of the description) shares a workgroup
+    idx = P.Index.ivfpq_index_from_arrays(32, 9, 16, 8, *si.random_index_arrays(100, 32, 9, 16, 8, salt=3))
+    for route, kernel in ((0, "scan_group_kernel<"), (1, "scan_kernel<"), (2, "scan_kernel<"), (3, "scan_group_kernel<")):
+        idx.ivfpq_set_tuning(P.TUNE_SCAN_ROUTE, route)
+        assert idx.ivfpq_scan_kernel_info(P.LUT_FP8_E5M3).startswith(kernel)
+
+
 def test_library_reads_no_environment_variable():
     # tuning is per index (ivfpq_set_tuning): no hidden process-global state
     for name in ("ivfpq_device.hip", "ivfpq_scan_group.hip", "ivfpq_build.hip", "ivfpq_host.cpp", "ivfpq_rank.hpp", "ivfpq_internal.hpp", "ivfpq_hip_util.hpp"):
