@@ -549,8 +549,9 @@ residual_rows_kernel(const float* __restrict__ data, const int64_t* __restrict__
 // [j*BITS, (j+1)*BITS); a code group is the shortest run of sub-spaces that ends on a 32-bit boundary
 // (SPG sub-spaces in WPG words: 8 in 1 for 4-bit codes, 4 in 1 for 8-bit, 32 in 5 / 16 in 3 / 32 in 7
 // for 5 / 6 / 7 bits).  A thread handles position p (blockIdx.x * 256 + threadIdx.x) and the code
-// group blockIdx.y; the group's codebooks sit in LDS.  Row of position p: order[p] (or p); residual = X[row] - C[labels[row]] in
-// fp32 (or X[row] itself when C is null).  Outputs (either may be null): train_labels[j][p] = code; codes32[p][...] = the group's words of the packed code.
+// group blockIdx.y; the group's codebooks sit in LDS.  Row of position p: order[p] (or p); residual = X[row] -
+// C[labels[row]] in fp32 (or X[row] itself when C is null).  Outputs (either may be null): train_labels[j][p] = code;
+// codes32[p][...] = the group's words of the packed code.
 template <int BITS>
 __global__ void __launch_bounds__(256)
 pq_codes_kernel(const float* __restrict__ X, const uint32_t* __restrict__ order, const int32_t* __restrict__ labels,
@@ -628,8 +629,9 @@ __device__ inline float2 both_halves(float x) {
 // the float64 distances that define the code (all of a lane's runs where its second minimum does as well).
 // Error of a(): the operands are exact, |c|^2 / 2 is rounded once, and each of the M products and sums rounds at the
 // magnitude |c|^2 / 2 + |r||c| <= |r|^2 + |c|^2 =: s at most twice, so |error| < (M + 2) 2^-23 s; the tile's number in the
-// low bits of a minimum moves it by 2^-20 s at most.  The bound takes (M + 8) 2^-22 s, and 1e-30 for operands that the matrix unit may flush as denormal.  Where s is not below 1e37
-// (overflow, infinities, NaN) all codewords are compared in float64.
+// low bits of a minimum moves it by 2^-20 s at most.  The bound takes (M + 8) 2^-22 s, and 1e-30 for operands that the
+// matrix unit may flush as denormal.  Where s is not below 1e37 (overflow, infinities, NaN) all codewords are compared
+// in float64.
 // A wave takes 4 tiles of 32 positions, so that the accumulators' initial values are read from LDS once for all four, and
 // an "octet" of 8 components (8 / M sub-spaces) at a time, whose codebooks the workgroup stages (12 KB at most);
 // the code groups of the same positions run on one XCD (workgroup b runs on XCD b % 8), which then
@@ -817,7 +819,7 @@ struct BuildPlan {
     int64_t n, n_ct, n_pt;          // rows, coarse training rows, PQ training rows
     int d, n_lists, pq_dim, pq_bits, m, ksub;
     size_t tile_rows;               // rows per ranking tile
-    size_t n_group;                 // largest number of items grouped at once
+    size_t n_group;                 // items of the order array: rows grouped by cluster (PQ training moves the values instead)
     size_t k_group;                 // largest number of groups
     // offsets into the workspace
     bool use_strips;                // nearest centres from strip summaries instead of all ranking values

@@ -135,10 +135,10 @@ __device__ __forceinline__ void group_run(const ScanArgs& a, unsigned char* smem
     // step 3: all R tables from one pass over the codebooks.  A wave takes blocks of 256 consecutive entries of the
     // table, 4 codes per lane: one row of an 8-bit sub-space, 16 rows of 4-bit sub-spaces (a lane's four codes
     // then belong to sub-space 16 block + lane / 4; the host admits only tables that are whole blocks)
-    // 64 sub-spaces of 5- to 8-bit codes with the early exit on: most groups are over every bound after half of the
-    // sub-spaces, so only the first 32 rows are built now; the rest follows if some group is still in the race
+    // 64 sub-spaces or more of 5- to 8-bit codes with the early exit on: most groups are over every bound after half
+    // of the sub-spaces, so only that half of the rows is built now; the rest follows if some group is still in the race
     // (scan_kernel's split scan, for a run of queries)
-    static_assert(!SPLIT || (BITS != 4 && SUBS >= 64), "the split scan is for 64 sub-spaces of 5- to 8-bit codes");
+    static_assert(!SPLIT || (BITS != 4 && SUBS >= 64), "the split scan is for 64 sub-spaces or more of 5- to 8-bit codes");
     constexpr bool lazy = SPLIT;
     uint32_t* any_alive = reinterpret_cast<uint32_t*>(after_rq + (size_t)n_waves * kGroupStageAll * 8);
     uint16_t* alive = reinterpret_cast<uint16_t*>(any_alive + 4) + (size_t)wave * kAliveCap;
