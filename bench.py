@@ -325,15 +325,17 @@ def main():
     for name in order:
         results[name] = run(name, args.steps if name == args.lut else other_steps, args.warmup)
         log(f"lut={name}: {fmt(results[name])}")
-    # the same headline run with the filtered scan adding up every sub-space of every vector (no exit once a
-    # group's partial sums are all over the bound): same results, the rate a kernel without that test has, and
+    # the same headline run with the filtered scan adding up every sub-space of every vector from lookup tables (no matrix-core
+    # filter, no exit once a group's partial sums are all over the bound): same results, the rate of the table kernel, and
     # the run whose lookup count is known exactly (what the roofline fraction is taken from)
     if args.no_full_run or args.early_exit == 0:
         full = results[args.lut]
         full_is_exact = args.early_exit == 0
+        full_kernel = idx.ivfpq_scan_kernel_info(lut_ids[args.lut])
     else:
         idx.ivfpq_set_tuning(pkg.TUNE_EARLY_EXIT, -1)
         full = run(args.lut, other_steps, 1)
+        full_kernel = idx.ivfpq_scan_kernel_info(lut_ids[args.lut])
         idx.ivfpq_set_tuning(pkg.TUNE_EARLY_EXIT, 0 if args.early_exit is None else 1)
         full_is_exact = True
         log(f"lut={args.lut} without early exit: {fmt(full)}")
@@ -423,8 +425,7 @@ def main():
         one_launch = nearest_ms > 0 and abs(kern_ms_full / (nearest_ms * (n_probes - 1)) - 1.0) < 1e-4
         roofline = {
             "bound": "lds",
-            "kernel": "scan_kernel, one launch for all probes (kernel_ms_per_step: the share of the pairs counted)" if one_launch else
-                      idx.ivfpq_scan_kernel_info(lut_ids[args.lut]),
+            "kernel": "scan_kernel, one launch for all probes (kernel_ms_per_step: the share of the pairs counted)" if one_launch else full_kernel,
             "achieved": round(rate, 1), "peak": LDS_PEAK_LOOKUPS, "unit": "table lookups/s",
             "frac": round(rate / LDS_PEAK_LOOKUPS, 4),
             "lookups_per_step": lookups, "kernel_ms_per_step": round(kern_ms_full, 4),
@@ -443,9 +444,10 @@ def main():
             "hbm_algorithmic": {"bytes_per_step": kern_bytes, "achieved": round(kern_bytes / (kern_ms_full * 1e-3) / 1e9, 1),
                                 "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(kern_bytes / (kern_ms_full * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
                                 "streaming_read_ceiling": round(ceiling, 1)},
-            "default_run": {"kernel_ms_per_step": round(kern_ms, 4),
-                            "note": "with the early exit (library default) a 64-vector group stops adding once all its partial sums "
-                                    "are over the query's bound: same results, fewer lookups made"},
+            "default_run": {"kernel": idx.ivfpq_scan_kernel_info(lut_ids[args.lut]), "kernel_ms_per_step": round(kern_ms, 4),
+                            "note": "library default: large batches list the vectors that can have R <= bound with a matrix product and add up "
+                                    "those alone (or, where that does not apply, a 64-vector group stops adding once all its partial sums are "
+                                    "over the query's bound): same results, fewer lookups made"},
             "whole_scan_stage": {"scanned_vectors_per_step": scanned_vectors, "code_bytes_per_step": code_bytes,
                                  "stage_ms": round(head["stage_ms"]["scan"], 4), "stage_ms_without_early_exit": round(full["stage_ms"]["scan"], 4)},
             "note": "achieved = table lookups the kernel makes per step (vectors of every probed cluster but the one scanned "

@@ -173,9 +173,10 @@ typedef enum {
                                     XCD (>= 1; the scan that shares a workgroup between pairs needs an even value) */
     IVFPQ_TUNE_SCAN_SHARE = 2,   /* 1: one (query, probe) pair per scan workgroup; 2 or 4: up to that many pairs of
                                     one cluster per workgroup wherever the kernel for it applies */
-    IVFPQ_TUNE_EARLY_EXIT = 3,   /* 1: on (the default: a 64-vector group stops adding once all its partial sums are
-                                    over the query's bound); -1: off, every lookup of Eq. (1) is made.  Leaves the
-                                    route (SCAN_ROUTE) as it is */
+    IVFPQ_TUNE_EARLY_EXIT = 3,   /* 1: on (the default: large batches add up only the vectors that a matrix product
+                                    finds able to be among the results; in the table kernels a 64-vector group stops
+                                    adding once all its partial sums are over the query's bound); -1: off, every lookup
+                                    of Eq. (1) is made.  Leaves the route (SCAN_ROUTE) as it is */
     IVFPQ_TUNE_LDS_PAD = 4,      /* extra bytes of LDS requested per scan workgroup (lowers occupancy without
                                     changing the table: separates the two effects of a smaller table dtype) */
     IVFPQ_TUNE_SCAN_ROUTE = 5    /* how the probes of a query are scanned; the library chooses by the amount of work.
@@ -278,7 +279,9 @@ int ivfpq_stage_times_ms(ivfpq_index_t* index, float ms[8]);
  * kernel that scans the probes other than the nearest one (the dominant kernel of a search) for this index,
  * table dtype and current tuning: what to look for in a profiler's kernel list.  It describes large batches, whose
  * pairs run grouped by cluster, unless IVFPQ_TUNE_SCAN_ROUTE names another route: the searches of little work that the
- * library sends there run scan_kernel, and with more threads than the index asks for where its workgroups are few. */
+ * library sends there run scan_kernel, and with more threads than the index asks for where its workgroups are few.
+ * Where a matrix product lists the vectors to add up (an uploaded index, its usual shapes, no knob that asks for the
+ * table kernels) it names that kernel and the one that adds them up. */
 int ivfpq_scan_kernel_info(const ivfpq_index_t* index, int32_t lut_dtype, char* buf, size_t buf_bytes);
 
 /* Measurement aid, not a step of the method: a plain streaming read of `bytes` bytes of device memory

@@ -22,8 +22,10 @@ HIP_FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-function",
 ]
-# (object, source, flags): search, its scan of groups of pairs (one object per table dtype), index construction
-DEVICE_OBJECTS = [("ivfpq_device", "ivfpq_device", []), ("ivfpq_build", "ivfpq_build", []),
+# (object, source, flags): search, the matrix-core filter of its scan and the sums of what that lists, the scan of groups of
+# pairs (one object per table dtype each), index construction
+DEVICE_OBJECTS = [("ivfpq_device", "ivfpq_device", []), ("ivfpq_build", "ivfpq_build", []), ("ivfpq_scan_filter", "ivfpq_scan_filter", []),
+                  *((f"ivfpq_candidates_{lut}", "ivfpq_candidates", [f"-DIVFPQ_CANDIDATE_LUT={lut}"]) for lut in range(4)),
                   *((f"ivfpq_scan_group_{lut}", "ivfpq_scan_group", [f"-DIVFPQ_GROUP_LUT={lut}"]) for lut in range(4))]
 HOST_FLAGS = ["-O3", "-std=c++17", "-fPIC", "-fopenmp", "-mavx2", "-mfma", "-Wall"]
 

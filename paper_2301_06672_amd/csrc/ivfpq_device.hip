@@ -23,6 +23,8 @@
 //                        to 96 sub-spaces of the others):
 //                        their tables are interleaved entry by entry, so one LDS read serves one lookup of
 //                        every query of the group; codebooks and codes are read once for all of them
+//   scan_filter_kernel / candidate_kernel   large batches instead: a matrix product lists the vectors that can have R <= bound, and
+//                        only those are added up (ivfpq_scan_filter.hip, ivfpq_candidates.hip); filter_items_kernel lays out its work
 //   topk_kernel          step 5: the k smallest R among the survivors of a query, ordered by
 //                        (R, id), and the map from (cluster, position) to the caller's ids
 // Where little is scanned in all (scan_route), launches count more than the work they save: the filtered scan takes its
@@ -33,6 +35,7 @@
 #include <hip/hip_fp16.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstring>
 #include <type_traits>
 #include <utility>
@@ -42,6 +45,7 @@
 #include "ivfpq_lds_util.hpp"
 #include "ivfpq_lut.hpp"
 #include "ivfpq_scan_args.hpp"
+#include "ivfpq_scan_filter.hpp"
 #include "ivfpq_select.hpp"
 
 using namespace ivfpq;
@@ -860,13 +864,42 @@ __global__ void fill_u32_kernel(uint32_t* p, size_t n, uint32_t v) {
     if (i < n) p[i] = v;
 }
 
+// Pairs whose cluster cannot hold a vector with R <= bound.  Every decoded residual y of the cluster has |y| <= its radius,
+// so |r - y| >= |r| - radius, and a vector with R <= bound has |r - y|^2 <= bound * scale + add (filter_constants) unless an
+// entry of its sum saturated, which alone makes R >= top.  The counting pass marks such a pair (its distance turned negative); the
+// scatter leaves it out.  (10^7 vectors, 50 probes, k = 100, 2,000 Gaussian components: 74 % of the pairs.)
+struct PairCull {
+    float* probe_dists;             // null: no pair is left out
+    const uint32_t* bounds;
+    const float* radii2;            // [n_lists] largest |y|^2
+    float scale, add, top;
+    __device__ bool keep(uint32_t i, int n_probes, uint32_t l) const {
+        if (!probe_dists) return true;
+        const uint32_t q = i / (uint32_t)(n_probes - 1), p = 1 + i - q * (uint32_t)(n_probes - 1);
+        float* const at = probe_dists + (size_t)q * n_probes + p;
+        const uint32_t bnd = bounds[q];
+        const float rr = *at, bound = __uint_as_float(bnd);
+        // (a relative 2^-13 for the rounding of either norm: sums of at most 128 squares)
+        const float gap = __builtin_sqrtf(rr) * 0.99987f - __builtin_sqrtf(radii2[l]) * 1.00013f;
+        const bool out = bnd < 0x7F800000u && bound < top * 0.9999f && gap > 0.f && gap * gap > __builtin_fmaf(bound, scale, add) * 1.0001f && rr < 1.0e30f;
+        if (out) *at = -1.f;
+        return !out;
+    }
+    __device__ bool kept(uint32_t i, int n_probes) const {
+        if (!probe_dists) return true;
+        const uint32_t q = i / (uint32_t)(n_probes - 1), p = 1 + i - q * (uint32_t)(n_probes - 1);
+        return !(probe_dists[(size_t)q * n_probes + p] < 0.f);
+    }
+};
+
 __global__ void pair_count_kernel(const uint4* __restrict__ pairs, uint32_t n_pairs, int n_probes, int n_lists,
-                                  uint32_t* __restrict__ counts) {
+                                  uint32_t* __restrict__ counts, PairCull cull) {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n_pairs) return;
     const uint32_t q = i / (uint32_t)(n_probes - 1), p = 1 + i - q * (uint32_t)(n_probes - 1);
     const uint32_t l = pairs[(size_t)q * n_probes + p].x;
-    atomicAdd(&counts[l < (uint32_t)n_lists ? l : 0u], 1u);       // a caller-given probe may be out of range
+    const uint32_t at = l < (uint32_t)n_lists ? l : 0u;           // a caller-given probe may be out of range
+    if (cull.keep(i, n_probes, at)) atomicAdd(&counts[at], 1u);
 }
 
 // The same two steps for few clusters, where many pairs name the same cluster and one global atomic per
@@ -881,14 +914,30 @@ __device__ inline uint32_t pair_cluster(const uint4* __restrict__ pairs, uint32_
     return l < (uint32_t)n_lists ? l : 0u;                        // a caller-given probe may be out of range
 }
 
+// What the grouped order holds of pair i: its number, or (records given) what the matrix-core filter works from, {query, slot
+// of the probe, squared distance to the centroid, bound}, so that a work item's pairs are one read.
+struct PairRecords {
+    uint4* records;
+    const float* probe_dists;
+    const uint32_t* bounds;
+};
+__device__ inline void store_pair(uint32_t at, uint32_t i, int n_probes, uint32_t* __restrict__ order, const PairRecords& r) {
+    if (!r.records) { order[at] = i; return; }
+    const uint32_t q = i / (uint32_t)(n_probes - 1), p = 1 + i - q * (uint32_t)(n_probes - 1);
+    r.records[at] = make_uint4(q, p, __float_as_uint(r.probe_dists[(size_t)q * n_probes + p]), r.bounds[q]);
+}
+
 __global__ void __launch_bounds__(1024)
 pair_count_lds_kernel(const uint4* __restrict__ pairs, uint32_t n_pairs, int n_probes, int n_lists,
-                      uint32_t* __restrict__ counts) {
+                      uint32_t* __restrict__ counts, PairCull cull) {
     extern __shared__ uint32_t s_cnt[];
     for (int l = threadIdx.x; l < n_lists; l += blockDim.x) s_cnt[l] = 0;
     __syncthreads();
     const uint32_t i0 = blockIdx.x * kPairChunk, i1 = i0 + kPairChunk < n_pairs ? i0 + kPairChunk : n_pairs;
-    for (uint32_t i = i0 + threadIdx.x; i < i1; i += blockDim.x) atomicAdd(&s_cnt[pair_cluster(pairs, i, n_probes, n_lists)], 1u);
+    for (uint32_t i = i0 + threadIdx.x; i < i1; i += blockDim.x) {
+        const uint32_t l = pair_cluster(pairs, i, n_probes, n_lists);
+        if (cull.keep(i, n_probes, l)) atomicAdd(&s_cnt[l], 1u);
+    }
     __syncthreads();
     for (int l = threadIdx.x; l < n_lists; l += blockDim.x)
         if (s_cnt[l]) atomicAdd(&counts[l], s_cnt[l]);
@@ -896,14 +945,15 @@ pair_count_lds_kernel(const uint4* __restrict__ pairs, uint32_t n_pairs, int n_p
 
 __global__ void __launch_bounds__(1024)
 pair_scatter_lds_kernel(const uint4* __restrict__ pairs, uint32_t n_pairs, int n_probes, int n_lists,
-                        const uint32_t* __restrict__ offsets, uint32_t* __restrict__ cursor, uint32_t* __restrict__ order) {
+                        const uint32_t* __restrict__ offsets, uint32_t* __restrict__ cursor, uint32_t* __restrict__ order, PairRecords rec, PairCull cull) {
     extern __shared__ uint32_t s_mem[];
     uint32_t* s_cnt = s_mem;                  // pairs of this chunk per cluster, then the running rank
     uint32_t* s_base = s_mem + n_lists;       // first slot of this chunk's pairs inside the cluster's range
     for (int l = threadIdx.x; l < n_lists; l += blockDim.x) s_cnt[l] = 0;
     __syncthreads();
     const uint32_t i0 = blockIdx.x * kPairChunk, i1 = i0 + kPairChunk < n_pairs ? i0 + kPairChunk : n_pairs;
-    for (uint32_t i = i0 + threadIdx.x; i < i1; i += blockDim.x) atomicAdd(&s_cnt[pair_cluster(pairs, i, n_probes, n_lists)], 1u);
+    for (uint32_t i = i0 + threadIdx.x; i < i1; i += blockDim.x)
+        if (cull.kept(i, n_probes)) atomicAdd(&s_cnt[pair_cluster(pairs, i, n_probes, n_lists)], 1u);
     __syncthreads();
     for (int l = threadIdx.x; l < n_lists; l += blockDim.x) {
         const uint32_t c = s_cnt[l];
@@ -912,8 +962,9 @@ pair_scatter_lds_kernel(const uint4* __restrict__ pairs, uint32_t n_pairs, int n
     }
     __syncthreads();
     for (uint32_t i = i0 + threadIdx.x; i < i1; i += blockDim.x) {
+        if (!cull.kept(i, n_probes)) continue;
         const uint32_t l = pair_cluster(pairs, i, n_probes, n_lists);
-        order[s_base[l] + atomicAdd(&s_cnt[l], 1u)] = i;
+        store_pair(s_base[l] + atomicAdd(&s_cnt[l], 1u), i, n_probes, order, rec);
     }
 }
 
@@ -953,13 +1004,48 @@ pair_offsets_kernel(const uint32_t* __restrict__ counts, int n_lists, uint32_t* 
 
 __global__ void pair_scatter_kernel(const uint4* __restrict__ pairs, uint32_t n_pairs, int n_probes, int n_lists,
                                     const uint32_t* __restrict__ offsets, uint32_t* __restrict__ cursor,
-                                    uint32_t* __restrict__ order) {
+                                    uint32_t* __restrict__ order, PairRecords rec, PairCull cull) {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_pairs) return;
+    if (i >= n_pairs || !cull.kept(i, n_probes)) return;
     const uint32_t q = i / (uint32_t)(n_probes - 1), p = 1 + i - q * (uint32_t)(n_probes - 1);
     uint32_t l = pairs[(size_t)q * n_probes + p].x;
     if (l >= (uint32_t)n_lists) l = 0u;
-    order[offsets[l] + atomicAdd(&cursor[l], 1u)] = i;
+    store_pair(offsets[l] + atomicAdd(&cursor[l], 1u), i, n_probes, order, rec);
+}
+
+// Work items of the matrix-core filter, and the place of every cluster's pairs in the grouped order (any disjoint ranges
+// will do): 64 clusters per workgroup, their ranges taken with one addition each; its 16 waves write the items, one cluster after the
+// other.  per_item: vectors of an item.  totals: pairs, items.
+__global__ void __launch_bounds__(1024)
+filter_items_kernel(const uint32_t* __restrict__ counts, const uint32_t* __restrict__ list_sizes, const int64_t* __restrict__ group_offsets,
+                    int n_lists, uint32_t per_item, uint32_t* __restrict__ offsets, uint32_t* __restrict__ totals, uint4* __restrict__ items, uint32_t cap) {
+    __shared__ uint32_t s_base[2];
+    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), l = blockIdx.x * kWave + lane;
+    const uint32_t n = l < n_lists ? counts[l] : 0u, len = l < n_lists ? list_sizes[l] : 0u, group = l < n_lists ? (uint32_t)group_offsets[l] : 0u;
+    const uint32_t tiles = (n + (uint32_t)kFilterPairs - 1u) / (uint32_t)kFilterPairs, chunks = (len + per_item - 1u) / per_item;
+    const uint32_t mine = tiles * chunks, upto_n = wave_inclusive_scan(n), upto_items = wave_inclusive_scan(mine);
+    if (threadIdx.x == kWave - 1) {
+        s_base[0] = upto_n ? atomicAdd(&totals[0], upto_n) : 0u;
+        s_base[1] = upto_items ? atomicAdd(&totals[1], upto_items) : 0u;
+    }
+    __syncthreads();
+    const uint32_t first = s_base[0] + upto_n - n, at = s_base[1] + upto_items - mine;
+    if (wave == 0 && n != 0) offsets[l] = first;
+    for (int s = wave; s < kWave; s += 16) {
+        auto of = [&](uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)v, s); };
+        const uint32_t mine_s = of(mine);
+        if (mine_s == 0) continue;
+        const uint32_t n_s = of(n), first_s = of(first), tiles_s = of(tiles), at_s = of(at), l_s = of((uint32_t)l), len_s = of(len), group_s = of(group);
+        for (uint32_t i = (uint32_t)lane; i < mine_s; i += kWave) {
+            const uint32_t c = i / tiles_s, t = i - c * tiles_s;       // the items that read the same codes are neighbours
+            const uint32_t done = t * (uint32_t)kFilterPairs, n_here = n_s - done < (uint32_t)kFilterPairs ? n_s - done : (uint32_t)kFilterPairs;
+            const uint32_t v0 = c * per_item, v_here = len_s - v0 < per_item ? len_s - v0 : per_item;
+            if (at_s + i < cap) {
+                items[2 * (size_t)(at_s + i)] = make_uint4(l_s, first_s + done, n_here, v_here);
+                items[2 * (size_t)(at_s + i) + 1] = make_uint4(v0, group_s + v0 / 64u, 0u, 0u);
+            }
+        }
+    }
 }
 
 // ================================================================================================
@@ -973,12 +1059,16 @@ constexpr uint32_t kAdmitAll = 0xFFFFFFFEu;   // every real R is below this, the
 
 __global__ void __launch_bounds__(SEL_THREADS)
 bound_kernel(float* __restrict__ R, uint32_t* __restrict__ Rpos, size_t stride, const uint4* __restrict__ pairs,
-             int n_probes, int k, uint32_t* __restrict__ bounds, uint32_t* __restrict__ counts) {
+             int n_probes, int k, uint32_t* __restrict__ bounds, uint32_t* __restrict__ counts, uint32_t* __restrict__ starts,
+             uint32_t* __restrict__ clear_a, uint32_t n_clear_a, uint32_t* __restrict__ clear_b, uint32_t n_clear_b) {
     constexpr uint32_t KEYS = 4096;         // segments up to this length are selected from LDS
     __shared__ KthShared s;
     __shared__ uint32_t keys[KEYS];
     const int q = blockIdx.x;
     const int tid = threadIdx.x, nth = blockDim.x;
+    // the counters of the grouping that follows
+    for (uint32_t i = (uint32_t)q * nth + tid; i < n_clear_a; i += gridDim.x * nth) clear_a[i] = 0u;
+    if (q == 0 && (uint32_t)tid < n_clear_b) clear_b[tid] = 0u;
     const uint32_t seg0 = n_probes > 1 ? pairs[(size_t)q * n_probes + 1].w : 0u;
     const uint32_t len0 = pairs[(size_t)q * n_probes].y;       // real values in the segment (the rest is padding)
     uint32_t* row = reinterpret_cast<uint32_t*>(R + (size_t)q * stride);
@@ -1005,7 +1095,11 @@ bound_kernel(float* __restrict__ R, uint32_t* __restrict__ Rpos, size_t stride, 
         }
     }
     __syncthreads();
-    if (tid == 0) { bounds[q] = bound; counts[q] = s.n_rec; }
+    if (tid == 0) {
+        bounds[q] = bound;
+        counts[q] = s.n_rec;
+        if (starts) starts[q] = s.n_rec;
+    }
 }
 
 // ================================================================================================
@@ -1101,7 +1195,7 @@ refine_kernel(const float* __restrict__ data, long long n_data, int d, const flo
 // Host side
 // ================================================================================================
 struct ImageLayout {
-    size_t centroids, centroid_norms, codebooks, list_offsets, list_sizes, group_offsets, codes, ids, total;
+    size_t centroids, centroid_norms, codebooks, word_norms, list_offsets, list_sizes, list_radii, group_offsets, codes, ids, total;
 };
 
 int chunk_width(const ivfpq_index* idx) {
@@ -1117,8 +1211,10 @@ ImageLayout image_layout(const ivfpq_index* idx) {
     L.centroids = take(idx->centroids.size() * sizeof(float));
     L.centroid_norms = take((size_t)idx->n_lists * sizeof(float));
     L.codebooks = take(idx->codebooks.size() * sizeof(float));
+    L.word_norms = take(((size_t)idx->pq_dim << idx->pq_bits) * sizeof(float));
     L.list_offsets = take(((size_t)idx->n_lists + 1) * sizeof(int64_t));
     L.list_sizes = take((size_t)idx->n_lists * sizeof(uint32_t));
+    L.list_radii = take((size_t)idx->n_lists * sizeof(float));
     L.group_offsets = take(((size_t)idx->n_lists + 1) * sizeof(int64_t));
     L.codes = take((size_t)idx->total_groups * 64 * idx->code_bytes());
     // (the ids' place holds the codes in transit during the upload: one group at least)
@@ -1134,13 +1230,45 @@ struct Plan {
 };
 
 
+// Vectors of a work item: as many as leave every wave of the chip (eight per compute unit) two items to take, lists of average length
+// reckoned (32 lists of 1,900 vectors, 3,500 pairs: 256 items of 512 vectors took 93 us).
+uint32_t filter_item_vectors(const ivfpq_index* idx, size_t n_pairs) {
+    const double tiles = (double)n_pairs / kFilterPairs + 0.5 * (double)std::min<size_t>(n_pairs, (size_t)idx->n_lists);
+    uint32_t v = kFilterVectors;
+    while (v > 64 && tiles * ((double)idx->n / (double)idx->n_lists / v + 0.5) < 4096.0) v /= 2;
+    return v;
+}
+// How many can be needed: a cluster of c pairs and v vectors has ceil(c / 64) ceil(v / per_item).
+size_t filter_items_max(const ivfpq_index* idx, size_t n_pairs, uint32_t per_item) {
+    const size_t longest = idx->sorted_padded_sizes.empty() ? 0 : idx->sorted_padded_sizes[0];
+    const size_t chunks = (longest + per_item - 1) / per_item;
+    return n_pairs / kFilterPairs * chunks + chunks + (size_t)idx->total_groups * 64 / per_item + (size_t)idx->n_lists;
+}
+// The filter's lists in the workspace: a query's starting length, totals, pairs, work items (offsets from the place of the ranking values).
+struct FilterLists {
+    uint32_t per_item;
+    size_t max_items, totals, records, items, bytes;
+};
+FilterLists filter_lists(const ivfpq_index* idx, size_t nq, int n_probes, uint32_t per_item) {
+    FilterLists f;
+    const size_t n_pairs = nq * (size_t)(n_probes - 1);
+    f.per_item = per_item;
+    f.max_items = filter_items_max(idx, n_pairs, f.per_item);
+    f.totals = align_up(nq * 4);
+    f.records = f.totals + kAlign;
+    f.items = f.records + align_up(n_pairs * sizeof(uint4));
+    f.bytes = f.items + align_up(f.max_items * 2 * sizeof(uint4));
+    return f;
+}
+
 // given_probes: the caller chooses the clusters and may name one several times, so the bound on a
 // query's candidates is n_probes times the largest cluster rather than the n_probes largest ones
 // limit: the bytes the plan should stay within (0: the index's workspace limit); a tile holds at least one
 // query, so the caller compares plan->total with what it has.
-int make_plan(const ivfpq_index* idx, int64_t nq, int32_t n_probes, bool given_probes, Plan* plan, size_t limit = 0) {
+int make_plan(const ivfpq_index* idx, int64_t nq, int32_t n_probes, bool given_probes, Plan* plan, size_t limit = 0, bool with_filter = true) {
     if (limit == 0) limit = idx->workspace_limit;
     const bool need_D = !given_probes;
+    with_filter = with_filter && need_D && n_probes > 1;
     int64_t stride = given_probes
         ? (int64_t)n_probes * (idx->sorted_padded_sizes.empty() ? 0 : idx->sorted_padded_sizes[0])
         : idx->max_padded_candidates(n_probes);
@@ -1154,6 +1282,7 @@ int make_plan(const ivfpq_index* idx, int64_t nq, int32_t n_probes, bool given_p
     // what does not grow with the tile: three per-cluster counter arrays, the centroids' bf16 halves, alignment slack
     const size_t fixed = 3 * align_up((size_t)idx->n_lists * 4)
                          + (need_D ? coarse_split_bytes(128, (size_t)idx->n_lists, idx->d) : 0) + 24 * kAlign;      // 128: the query rows' padding
+    if (with_filter) per_query += (size_t)n_probes * 16;
     per_query += (size_t)n_probes * 28 + 16;      // probe lists, distances, offsets, descriptors, order, bound, counter
     int64_t tile = limit > fixed ? (int64_t)((limit - fixed) / per_query) : 1;
     tile = std::max<int64_t>(1, std::min<int64_t>(tile, std::max<int64_t>(nq, 1)));
@@ -1170,6 +1299,11 @@ int make_plan(const ivfpq_index* idx, int64_t nq, int32_t n_probes, bool given_p
     plan->D = take(need_D ? (size_t)tile * idx->n_lists * 4 : 0);
     plan->S = take(need_D ? (size_t)tile * strips * sizeof(StripSummary) : 0);
     plan->split = take(need_D ? coarse_split_bytes((size_t)tile, (size_t)idx->n_lists, idx->d) : 0);
+    if (with_filter) {                // the filter's lists, where the ranking values leave too little room for them
+        // (for items of the most vectors, so that a smaller batch never needs more than a larger one)
+        const size_t want = filter_lists(idx, (size_t)tile, n_probes, kFilterVectors).bytes;
+        if (want > at - plan->D) take(want - (at - plan->D));
+    }
     plan->R = take((size_t)tile * stride * 4);
     plan->Rpos = take((size_t)tile * stride * 4);
     plan->order = take((size_t)tile * (n_probes > 1 ? n_probes - 1 : 0) * 4);
@@ -1177,6 +1311,8 @@ int make_plan(const ivfpq_index* idx, int64_t nq, int32_t n_probes, bool given_p
     plan->list_cursor = take((size_t)idx->n_lists * 4);
     plan->list_offsets = take((size_t)idx->n_lists * 4);
     plan->total = at;
+    // one query that fits the limit only without them does without
+    if (with_filter && tile == 1 && plan->total > limit) return make_plan(idx, nq, n_probes, given_probes, plan, limit, false);
     return IVFPQ_OK;
 }
 
@@ -1441,6 +1577,60 @@ ScanArgs base_scan_args(const ivfpq_index* idx, int lut_dtype) {
     return a;
 }
 
+// ---- the matrix-core filter: for the grouped route, unless a knob asks for the table kernels ----
+// Tables that saturate below (2 x the largest codeword)^2 hide so much of far vectors' distances that most pass, and a listed
+// vector costs several table lookups' worth (e4m4 of 31,744 against codewords of 100 and more, 17 M vectors looked up: 351 us, table kernels
+// 164).
+float table_top(int lut_dtype, const Fp8Mode& fp8) {
+    float top = __builtin_inff();
+    if (lut_dtype == IVFPQ_LUT_FP16) top = 65504.f;
+    else if (lut_dtype != IVFPQ_LUT_FP32) std::memcpy(&top, &fp8.fixed.hi, 4);
+    return top;
+}
+bool filter_applies(const ivfpq_index* idx, int lut_dtype, const Fp8Mode& fp8) {
+    const ivfpq::Tuning& t = idx->tuning;
+    if (!(4.f * idx->word_norm_max * idx->word_norm_max <= table_top(lut_dtype, fp8))) return false;
+    return t.early_exit >= 0 && t.scan_share == 0 && t.order_block == 0 && t.scan_threads == 0 && t.lds_pad == 0 && !fp8.per_table &&
+           idx->word_norm_max >= 0.f && filter_supported(idx->pq_bits, idx->pq_dim, idx->d, chunk_width(idx));
+}
+// By the number of vectors that are looked up, as scan_route: its four more launches and the codebooks that two kernels load cost what the
+// tables do up to 10 M (us, table kernels / filter, unit-norm rows in 555 lists, 56 queries, 62 probes: 8.6 M 120 / 122; 440 lists, 4
+// probes: 7.3 M 129 / 143; 832 lists, 12 probes: 10.6 M 152 / 140; 32 lists, 20 probes: 11.7 M 121 / 94).
+bool filter_pays(const ivfpq_index* idx, int nq, int n_probes) {
+    return idx->tuning.scan_route != 0 || (double)nq * n_probes * ((double)idx->n / (double)idx->n_lists) >= 1e7;
+}
+// What |r - y|^2 of a vector with R <= bound is limited by: bound * scale + add, where no entry saturates (the kernel sees to
+// those that may).  A stored entry is below its distance by at most the share `loss` (half: 2^-11, and 2^-25 where the half is
+// subnormal; 8-bit formats of M mantissa bits: 1 / (2^(M+1) + 1) rounded to nearest, 1 / (2^M + 1) truncated); the 2^-16 cover the
+// sum of up to 128 entries and the rounding of an entry's own distance.  eta: r.y is formed from bf16 operands (2^-8 + 2^-18 of the sum
+// of magnitudes, which is at most (|r|^2 + |y|^2) / 2), summed with the threshold in any order (4 (d + 2) 2^-24 of either, with
+// a factor 4 of slack as for the ranking values), |r|^2 is a sum of d squares.
+void filter_constants(const ivfpq_index* idx, int lut_dtype, const Fp8Mode& fp8, FilterArgs* a) {
+    double loss = 0.0, below = 0.0;
+    if (lut_dtype == IVFPQ_LUT_FP16) {
+        loss = 1.0 / 2048;
+        below = idx->pq_dim * std::ldexp(1.0, -25);
+    } else if (lut_dtype != IVFPQ_LUT_FP32) {
+        const int mantissa = lut_dtype == IVFPQ_LUT_FP8_E5M3 ? 3 : 4;
+        loss = 1.0 / ((1 << (fp8.truncate ? mantissa : mantissa + 1)) + 1);
+    }
+    a->scale = (float)((1.0 + std::ldexp(1.0, -15)) / (1.0 - loss));
+    a->add = (float)(below / (1.0 - loss) * 1.001 + 1e-30);
+    a->top = table_top(lut_dtype, fp8);
+    a->word_norm_max = idx->word_norm_max;
+    a->eta = (float)(0.00392 + (12.0 * idx->d + 64.0) * std::ldexp(1.0, -24));
+    a->fp8 = fp8.fixed;
+    a->truncate = fp8.truncate;
+}
+int launch_candidates(const FilterArgs& a, int lut_dtype, hipStream_t st) {
+    switch (lut_dtype) {
+        case IVFPQ_LUT_FP32: return launch_candidates_lut<IVFPQ_LUT_FP32>(a, st);
+        case IVFPQ_LUT_FP16: return launch_candidates_lut<IVFPQ_LUT_FP16>(a, st);
+        case IVFPQ_LUT_FP8_E5M3: return launch_candidates_lut<IVFPQ_LUT_FP8_E5M3>(a, st);
+        default: return launch_candidates_lut<IVFPQ_LUT_FP8_E4M4>(a, st);
+    }
+}
+
 // ---- stage timing ----
 int timing_mark(const ivfpq_index* idx, hipStream_t st, void** out) {
     if (idx->events_used == idx->event_pool.size()) {
@@ -1559,33 +1749,52 @@ int search_impl(const ivfpq_index* idx, const float* d_queries, int64_t nq, cons
         if (int s = t5.end()) return s;
         if (whole_rows) t5.divide(6, 1.f / (float)n_probes);      // one launch does the work of both: divided by their pairs
         if (n_probes > 1 && !whole_rows) {
+            const size_t n_pairs = (size_t)tq * (n_probes - 1);
+            const bool grouped = route == ScanRoute::kGrouped && group_pairs_by_cluster(n_pairs);
+            // The filter's lists take the place of the ranking values, which nothing reads any more (a search with given probes has none).
+            FilterLists lists = filter_lists(idx, (size_t)tq, n_probes, filter_item_vectors(idx, n_pairs));
+            while (lists.bytes > plan.R - plan.D && lists.per_item < (uint32_t)kFilterVectors) lists = filter_lists(idx, (size_t)tq, n_probes, lists.per_item * 2);
+            const bool filter = grouped && filter_applies(idx, lut_dtype, a.fp8) && filter_pays(idx, tq, n_probes) && ((uintptr_t)qt & 7) == 0 &&
+                                lists.max_items < ((size_t)1 << 31) && lists.bytes <= plan.R - plan.D;
+            uint32_t* w_starts = filter ? (uint32_t*)(ws + plan.D) : nullptr;
+            uint32_t* w_lc = (uint32_t*)(ws + plan.list_counts);         // counts and cursors are neighbours in the plan
             hipLaunchKernelGGL(bound_kernel, dim3(tq), dim3(SEL_THREADS), 0, st, w_R, w_Rpos, plan.stride, w_pairs, n_probes, k,
-                               w_bounds, w_counts);
+                               w_bounds, w_counts, w_starts, w_lc, grouped ? (uint32_t)((plan.list_offsets - plan.list_counts) / 4) : 0u,
+                               filter ? (uint32_t*)(ws + plan.D + lists.totals) : nullptr, filter ? 2u : 0u);
             HIP_TRY(hipGetLastError());
             a.mode = 2;
-            const size_t n_pairs = (size_t)tq * (n_probes - 1);
-            if (route == ScanRoute::kGrouped && group_pairs_by_cluster(n_pairs)) {
+            if (grouped) {
                 uint32_t* w_order = (uint32_t*)(ws + plan.order);
-                uint32_t* w_lc = (uint32_t*)(ws + plan.list_counts);
                 uint32_t* w_cur = (uint32_t*)(ws + plan.list_cursor);
                 uint32_t* w_lo = (uint32_t*)(ws + plan.list_offsets);
                 const unsigned pb = (unsigned)((n_pairs + 255) / 256);
-                // counts and cursors are adjacent in the plan only up to alignment: two fills
-                hipLaunchKernelGGL(fill_u32_kernel, dim3((idx->n_lists + 255) / 256), dim3(256), 0, st, w_lc, (size_t)idx->n_lists, 0u);
-                hipLaunchKernelGGL(fill_u32_kernel, dim3((idx->n_lists + 255) / 256), dim3(256), 0, st, w_cur, (size_t)idx->n_lists, 0u);
+                uint32_t* w_totals = (uint32_t*)(ws + plan.D + lists.totals);
+                uint4* w_items = (uint4*)(ws + plan.D + lists.items);
+                FilterArgs f{};
+                if (filter) filter_constants(idx, lut_dtype, a.fp8, &f);
+                const PairCull cull{filter ? w_probe_d : nullptr, w_bounds, idx->dev.list_radii, f.scale, f.add, f.top};
+                const PairRecords records{filter ? (uint4*)(ws + plan.D + lists.records) : nullptr, w_probe_d, w_bounds};
+                // the place of every cluster's pairs; with the filter also its work items
+                auto offsets = [&] {
+                    if (filter)
+                        hipLaunchKernelGGL(filter_items_kernel, dim3((idx->n_lists + kWave - 1) / kWave), dim3(1024), 0, st, w_lc, idx->dev.list_sizes,
+                                           idx->dev.group_offsets, idx->n_lists, lists.per_item, w_lo, w_totals, w_items, (uint32_t)lists.max_items);
+                    else
+                        hipLaunchKernelGGL(pair_offsets_kernel, dim3(1), dim3(1024), 0, st, w_lc, idx->n_lists, w_lo);
+                };
                 if (idx->n_lists <= kPairLdsLists) {
                     const unsigned cb = (unsigned)((n_pairs + kPairChunk - 1) / kPairChunk);
                     const size_t lds = (size_t)idx->n_lists * 4;
                     if (int s = allow_full_lds(pair_scatter_lds_kernel)) return s;
-                    hipLaunchKernelGGL(pair_count_lds_kernel, dim3(cb), dim3(1024), lds, st, w_pairs, (uint32_t)n_pairs, n_probes, idx->n_lists, w_lc);
-                    hipLaunchKernelGGL(pair_offsets_kernel, dim3(1), dim3(1024), 0, st, w_lc, idx->n_lists, w_lo);
+                    hipLaunchKernelGGL(pair_count_lds_kernel, dim3(cb), dim3(1024), lds, st, w_pairs, (uint32_t)n_pairs, n_probes, idx->n_lists, w_lc, cull);
+                    offsets();
                     hipLaunchKernelGGL(pair_scatter_lds_kernel, dim3(cb), dim3(1024), 2 * lds, st, w_pairs, (uint32_t)n_pairs, n_probes,
-                                       idx->n_lists, w_lo, w_cur, w_order);
+                                       idx->n_lists, w_lo, w_cur, w_order, records, cull);
                 } else {
-                    hipLaunchKernelGGL(pair_count_kernel, dim3(pb), dim3(256), 0, st, w_pairs, (uint32_t)n_pairs, n_probes, idx->n_lists, w_lc);
-                    hipLaunchKernelGGL(pair_offsets_kernel, dim3(1), dim3(1024), 0, st, w_lc, idx->n_lists, w_lo);
+                    hipLaunchKernelGGL(pair_count_kernel, dim3(pb), dim3(256), 0, st, w_pairs, (uint32_t)n_pairs, n_probes, idx->n_lists, w_lc, cull);
+                    offsets();
                     hipLaunchKernelGGL(pair_scatter_kernel, dim3(pb), dim3(256), 0, st, w_pairs, (uint32_t)n_pairs, n_probes, idx->n_lists,
-                                       w_lo, w_cur, w_order);
+                                       w_lo, w_cur, w_order, records, cull);
                 }
                 HIP_TRY(hipGetLastError());
                 a.order = w_order;
@@ -1593,7 +1802,17 @@ int search_impl(const ivfpq_index* idx, const float* d_queries, int64_t nq, cons
                 const uint32_t blk = idx->tuning.order_block > 0 ? (uint32_t)idx->tuning.order_block : kOrderBlock;
                 a.order_block = blk;
                 if (int s = t6.begin()) return s;
-                if (const int G = scan_group_width(idx, lut_dtype, a.fp8, blk)) {
+                if (filter) {
+                    f.queries = qt; f.centroids = a.centroids; f.codebooks = a.codebooks; f.codes = a.codes;
+                    f.pairs = w_pairs; f.bounds = w_bounds; f.starts = w_starts; f.counts = w_counts;
+                    f.row_key = (uint32_t*)w_R; f.row_pos = w_Rpos; f.stride = plan.stride;
+                    f.records = records.records; f.items = w_items; f.n_items = w_totals + 1;
+                    f.nq = tq; f.n_probes = n_probes;
+                    f.d = idx->d; f.pq_dim = idx->pq_dim; f.m = idx->m(); f.bits = idx->pq_bits;
+                    f.code_bytes = idx->code_bytes(); f.chunk_width = chunk_width(idx);
+                    if (int s = launch_filter(f, st)) return s;
+                    if (int s = launch_candidates(f, lut_dtype, st)) return s;
+                } else if (const int G = scan_group_width(idx, lut_dtype, a.fp8, blk)) {
                     a.n_chunks = idx->code_bytes() / chunk_width(idx);
                     if (int s = launch_scan_group(idx, a, lut_dtype, G, st)) return s;
                 } else {
@@ -1669,6 +1888,55 @@ interleave_codes_kernel(const W* __restrict__ raw, int64_t v0, const int64_t* __
     }
 }
 
+// The largest squared norm of a decoded residual of every cluster, as the bits of a float, from the squared norms of the codewords
+// (in the LDS where they fit).  One wave per run of 64-vector groups; bound by the LDS reads, one per code (10^6 vectors of 48
+// codes: 15 us).
+__global__ void __launch_bounds__(1024)
+list_radii_kernel(const unsigned char* __restrict__ codes, const float* __restrict__ word_norms, const int64_t* __restrict__ list_offsets,
+                  const int64_t* __restrict__ group_offsets, int n_lists, int64_t n_groups, int code_bytes, int chunk_width, int pq_dim, int bits,
+                  int in_lds, uint32_t* __restrict__ radii2) {
+    extern __shared__ float s_norms[];
+    const int n_words = pq_dim << bits;
+    if (in_lds)
+        for (int i = threadIdx.x; i < n_words; i += blockDim.x) s_norms[i] = word_norms[i];
+    __syncthreads();
+    const int lane = threadIdx.x & (kWave - 1), per_word = chunk_width / 4;
+    const int64_t n_waves = (int64_t)gridDim.x * (blockDim.x >> 6), wave = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+    const int64_t g0 = n_groups * wave / n_waves, g1 = n_groups * (wave + 1) / n_waves;
+    int lo = 0, hi = n_lists;                          // the last list that starts at or before group g0
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (group_offsets[mid] <= g0) lo = mid; else hi = mid;
+    }
+    const uint32_t mask = (1u << bits) - 1u;
+    float mx = 0.f;
+    auto give = [&]() {
+        for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, kWave));
+        if (lane == 0 && mx > 0.f) atomicMax(&radii2[lo], __float_as_uint(mx));
+        mx = 0.f;
+    };
+    for (int64_t g = g0; g < g1; ++g) {
+        if (group_offsets[lo + 1] <= g) {
+            give();
+            while (group_offsets[lo + 1] <= g) ++lo;
+        }
+        const uint32_t* w = reinterpret_cast<const uint32_t*>(codes + g * 64 * code_bytes);
+        auto word = [&](int i) { return w[((i / per_word) * 64 + lane) * per_word + i % per_word]; };
+        float sum = 0.f;
+        uint64_t held = 0;
+        int have = 0, next = 0;
+        for (int j = 0; j < pq_dim; ++j) {
+            if (have < bits) { held |= (uint64_t)word(next++) << have; have += 32; }
+            const uint32_t at = ((uint32_t)j << bits) + ((uint32_t)held & mask);
+            sum += in_lds ? s_norms[at] : word_norms[at];
+            held >>= bits;
+            have -= bits;
+        }
+        if (list_offsets[lo] + (g - group_offsets[lo]) * 64 + lane < list_offsets[lo + 1]) mx = fmaxf(mx, sum);
+    }
+    if (g0 < g1) give();
+}
+
 int upload_impl(ivfpq_index_t* idx, void* d_buf, size_t bytes, void* hip_stream) {
     if (!idx || !d_buf) return fail(IVFPQ_EINVAL, "ivfpq_upload: null pointer");
     const ImageLayout L = image_layout(idx);
@@ -1696,9 +1964,21 @@ int upload_impl(ivfpq_index_t* idx, void* d_buf, size_t bytes, void* hip_stream)
         if (cnorm[l] > cn_max) cn_max = cnorm[l];
     }
     idx->centroid_norm_max = cn_max;
+    std::vector<float> wnorm((size_t)idx->pq_dim << idx->pq_bits);
+    float wn_max = 0.f;
+    bool moderate = true;
+    for (size_t i = 0; i < wnorm.size(); ++i) {
+        float acc = 0.f;
+        for (int t = 0, m = idx->m(); t < m; ++t) { const float v = idx->codebooks[i * m + t]; acc += v * v; }
+        wnorm[i] = acc;
+        moderate = moderate && acc <= 1e28f;
+        wn_max = std::max(wn_max, acc);
+    }
+    idx->word_norm_max = moderate ? std::sqrt(wn_max) * 1.0001f : -1.f;
     HIP_TRY(hipMemcpyAsync(base + L.centroid_norms, cnorm.data(), cnorm.size() * 4, hipMemcpyHostToDevice, st));
     HIP_TRY(hipMemcpyAsync(base + L.centroids, idx->centroids.data(), idx->centroids.size() * 4, hipMemcpyHostToDevice, st));
     HIP_TRY(hipMemcpyAsync(base + L.codebooks, idx->codebooks.data(), idx->codebooks.size() * 4, hipMemcpyHostToDevice, st));
+    HIP_TRY(hipMemcpyAsync(base + L.word_norms, wnorm.data(), wnorm.size() * 4, hipMemcpyHostToDevice, st));
     HIP_TRY(hipMemcpyAsync(base + L.list_offsets, idx->list_offsets.data(), idx->list_offsets.size() * 8, hipMemcpyHostToDevice, st));
     HIP_TRY(hipMemcpyAsync(base + L.list_sizes, sizes.data(), sizes.size() * 4, hipMemcpyHostToDevice, st));
     HIP_TRY(hipMemcpyAsync(base + L.group_offsets, goff.data(), goff.size() * 8, hipMemcpyHostToDevice, st));
@@ -1729,6 +2009,16 @@ int upload_impl(ivfpq_index_t* idx, void* d_buf, size_t bytes, void* hip_stream)
         g = g_end;
         v = v_end;
     }
+    hipLaunchKernelGGL(fill_u32_kernel, dim3((idx->n_lists + 255) / 256), dim3(256), 0, st, (uint32_t*)(base + L.list_radii), (size_t)idx->n_lists, 0u);
+    if (idx->total_groups > 0) {
+        const bool in_lds = wnorm.size() * 4 <= kLdsBytes;
+        if (int s = allow_full_lds(list_radii_kernel)) return s;
+        const unsigned blocks = (unsigned)std::min<int64_t>(512, (idx->total_groups + 15) / 16);
+        hipLaunchKernelGGL(list_radii_kernel, dim3(blocks), dim3(1024), in_lds ? wnorm.size() * 4 : 0, st, (const unsigned char*)(base + L.codes),
+                           (const float*)(base + L.word_norms), (const int64_t*)(base + L.list_offsets), (const int64_t*)(base + L.group_offsets),
+                           idx->n_lists, idx->total_groups, cb, cw, idx->pq_dim, idx->pq_bits, in_lds, (uint32_t*)(base + L.list_radii));
+        HIP_TRY(hipGetLastError());
+    }
     if (idx->n > 0)
         HIP_TRY(hipMemcpyAsync(base + L.ids, idx->ids.data(), idx->ids.size() * 8, hipMemcpyHostToDevice, st));
     HIP_TRY(hipStreamSynchronize(st));
@@ -1745,6 +2035,7 @@ int upload_impl(ivfpq_index_t* idx, void* d_buf, size_t bytes, void* hip_stream)
     idx->dev.codebooks = (const float*)(base + L.codebooks);
     idx->dev.list_offsets = (const int64_t*)(base + L.list_offsets);
     idx->dev.list_sizes = (const uint32_t*)(base + L.list_sizes);
+    idx->dev.list_radii = (const float*)(base + L.list_radii);
     idx->dev.group_offsets = (const int64_t*)(base + L.group_offsets);
     idx->dev.codes = (const uint8_t*)(base + L.codes);
     idx->dev.ids = (const int64_t*)(base + L.ids);
@@ -1897,7 +2188,10 @@ int ivfpq_scan_kernel_info(const ivfpq_index_t* idx, int32_t lut_dtype, char* bu
     const int threads = scan_threads(idx, lut_dtype), cw = chunk_width(idx), nch = idx->code_bytes() / cw;
     const uint32_t blk = idx->tuning.order_block > 0 ? (uint32_t)idx->tuning.order_block : kOrderBlock;
     const bool grouped = idx->tuning.scan_route == 0 || idx->tuning.scan_route == (int)ScanRoute::kGrouped;      // 0: what large batches take
-    if (const int G = grouped ? scan_group_width(idx, lut_dtype, fp8_mode(idx, lut_dtype), blk) : 0)
+    if (grouped && filter_applies(idx, lut_dtype, fp8_mode(idx, lut_dtype)))
+        snprintf(buf, buf_bytes, "scan_filter_kernel<%d-bit codes, %d components a sub-space, d = %d> and candidate_kernel<%s>, %zu and %zu bytes of LDS",
+                 idx->pq_bits, idx->m(), idx->d, names[lut_dtype], filter_lds_bytes(idx->pq_bits, idx->d), candidate_lds_bytes(idx->pq_bits, idx->d));
+    else if (const int G = grouped ? scan_group_width(idx, lut_dtype, fp8_mode(idx, lut_dtype), blk) : 0)
         snprintf(buf, buf_bytes, "scan_group_kernel<%s, %d-bit codes, %d chunks, %d pairs> %d threads, %zu bytes of LDS", names[lut_dtype], idx->pq_bits, nch, G,
                  scan_group_threads(idx, lut_dtype, G), scan_group_lds_bytes(idx, lut_dtype, G, scan_group_threads(idx, lut_dtype, G)));
     else

@@ -104,6 +104,7 @@ struct DeviceImage {
     const float* codebooks = nullptr;      // [pq_dim][ksub][m]
     const int64_t* list_offsets = nullptr; // [n_lists+1], unpadded vector offsets (into ids)
     const uint32_t* list_sizes = nullptr;  // [n_lists]
+    const float* list_radii = nullptr;     // [n_lists] largest squared norm of a cluster's decoded residuals
     const int64_t* group_offsets = nullptr;// [n_lists+1], offsets in 64-vector groups (into codes)
     const uint8_t* codes = nullptr;        // interleaved, see ivfpq_upload
     const int64_t* ids = nullptr;          // [n] list order
@@ -127,6 +128,7 @@ struct ivfpq_index {
     ivfpq::DeviceImage dev;
     ivfpq::Fp8Options fp8_opt[2] = {{15, 0, 0}, {7, 0, 0}};   // e5m3, e4m4 (ivfpq_set_fp8_encoding)
     float centroid_norm_max = 0.f;      // largest squared centroid norm (set by ivfpq_upload)
+    float word_norm_max = -1.f;         // largest codeword norm (set by ivfpq_upload); negative: some codeword is not a moderate number
     size_t workspace_limit = (size_t)32 << 30;   // search scratch (R, positions, ranking values) per query tile
 
     ivfpq::Tuning tuning;               // ivfpq_set_tuning

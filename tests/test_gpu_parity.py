@@ -778,6 +778,78 @@ def test_scan_routes_agree(P, n, d, pq_dim, pq_bits, n_lists, n_probes, nq, k, d
     assert_topk_matches(out["own"][0][:40], out["own"][1][:40], ids_o, d_o, context="own route")
 
 
+@pytest.mark.parametrize("d,pq_dim,pq_bits", [
+    (128, 64, 8), (128, 32, 8), (96, 48, 8), (64, 32, 8), (64, 16, 8),     # two and four components a sub-space
+    (96, 24, 8),                                                           # 24-byte codes: 4-byte chunks
+    (128, 64, 4), (96, 48, 4), (128, 32, 4),                               # nibbles, in chunks of 16 and of 4 bytes
+    (128, 64, 7), (128, 64, 6), (64, 32, 6), (128, 64, 5),                 # fields that straddle words
+])
+@pytest.mark.parametrize("scale", [1.0, 40.0])
+def test_matrix_core_filter(P, d, pq_dim, pq_bits, scale):
+    # Grouped batches list the vectors that can have R <= bound from products in bf16 and add up only those.  Survivors, order of
+    # the sums and so every bit are those of the table kernels in query order.  Clusters of 0 to 1,025 vectors (work items of
+    # 512, rounds of 32), pairs per cluster from 1 to beyond 64 (blocks of 32 rows); queries near a cluster, between clusters,
+    # far outside, one not a number and one without a finite distance; k beyond the nearest cluster (no bound).  scale 40: half
+    # tables and e4m4 saturate.
+    sizes = [700, 0, 1, 31, 32, 33, 63, 64, 65, 511, 512, 513, 1025, 400, 900, 2, 640]
+    rng = np.random.default_rng(1000 + d + pq_dim + pq_bits)
+    n, L, m = sum(sizes), len(sizes), d // pq_dim
+    cent = (rng.standard_normal((L, d)) * 2 * scale).astype(np.float32)
+    book = (rng.standard_normal((pq_dim, 1 << pq_bits, m)) * 0.6 * scale).astype(np.float32)
+    offs = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    codes = rng.integers(0, 256, (n, pq_dim * pq_bits // 8), dtype=np.uint8)
+    ids = rng.permutation(n).astype(np.int64)
+    oidx = oracle.make_index(d, L, pq_dim, pq_bits, cent, book, offs, codes, ids)
+    gidx = to_library(P, oidx)
+    q = (cent[rng.integers(0, L, 230)] + rng.standard_normal((230, d)) * scale).astype(np.float32)
+    q[40:80] = ((cent[rng.integers(0, L, 40)] + cent[rng.integers(0, L, 40)]) / 2).astype(np.float32)
+    q[80:90] *= 30
+    q[90, 3], q[91, 5] = np.nan, 3e38
+    for dtype in (oracle.LUT_FP32, oracle.LUT_FP16, oracle.LUT_E5M3, oracle.LUT_E4M4):
+        for nq, n_probes, k in ((230, 9, 10), (230, L, 100), (5, 4, 10), (33, 5, 700)):
+            gidx.ivfpq_set_tuning(P.TUNE_SCAN_ROUTE, 3)
+            info = gidx.ivfpq_scan_kernel_info(dtype)
+            top = {oracle.LUT_FP32: np.inf, oracle.LUT_FP16: 65504.0, oracle.LUT_E5M3: 122880.0, oracle.LUT_E4M4: 496.0}[dtype]
+            assert info.startswith("scan_filter_kernel") == (4 * (book.astype(np.float64) ** 2).sum(2).max() <= top)
+            _step(f"filter d={d} s={pq_dim} p={pq_bits} scale={scale} dtype={dtype} nq={nq} P={n_probes} k={k}")
+            ids_f, d_f = [t.cpu().numpy() for t in gidx.ivfpq_search(q[:nq], n_probes, k, dtype)]
+            gidx.ivfpq_set_tuning(P.TUNE_SCAN_ROUTE, 2)
+            ids_t, d_t = [t.cpu().numpy() for t in gidx.ivfpq_search(q[:nq], n_probes, k, dtype)]
+            np.testing.assert_array_equal(d_f.view(np.uint32), d_t.view(np.uint32))
+            np.testing.assert_array_equal(ids_f, ids_t)
+            if nq == 230:
+                ids_o, d_o = oracle.search(oidx, q[:40], n_probes, k, dtype)
+                assert_topk_matches(ids_f[:40], d_f[:40], ids_o, d_o, context=info)
+
+
+def test_matrix_core_filter_leaves_other_calls_to_the_tables(P):
+    # encoding by a bias per table, knobs of the table kernels, queries that are not 8-byte aligned and codebooks that are no
+    # moderate numbers: the table kernels, with the same results
+    oidx, gidx = random_pair(P, 4000, 64, 9, 32, 8, salt=77)
+    gidx.ivfpq_set_tuning(P.TUNE_SCAN_ROUTE, 3)
+    name = lambda: gidx.ivfpq_scan_kernel_info(oracle.LUT_E5M3).split("<")[0]
+    assert name() == "scan_filter_kernel"
+    for knob, value, back in ((P.TUNE_SCAN_SHARE, 2, 0), (P.TUNE_EARLY_EXIT, -1, 0), (P.TUNE_ORDER_BLOCK, 32, 0), (P.TUNE_SCAN_THREADS, 256, 0)):
+        gidx.ivfpq_set_tuning(knob, value)
+        assert name() == "scan_group_kernel"
+        gidx.ivfpq_set_tuning(knob, back)
+    q = np.random.default_rng(77).standard_normal((301, 64)).astype(np.float32)
+    want = [t.cpu().numpy() for t in gidx.ivfpq_search(q, 6, 10, oracle.LUT_E5M3)]
+    flat = torch.empty(q.size + 1, dtype=torch.float32, device="cuda")
+    flat[1:] = torch.from_numpy(q).cuda().reshape(-1)
+    got = [t.cpu().numpy() for t in gidx.ivfpq_search(flat[1:].view(301, 64), 6, 10, oracle.LUT_E5M3)]
+    for a, b in zip(want, got):
+        np.testing.assert_array_equal(a, b)
+    gidx.ivfpq_set_fp8_encoding(oracle.LUT_E5M3, 15, P.ROUND_NEAREST, True)
+    assert name() != "scan_filter_kernel"
+    arrays = list(si.random_index_arrays(4000, 64, 9, 32, 8, salt=77))
+    arrays[1] = arrays[1].copy()
+    arrays[1][3, 7, 0] = np.inf
+    odd = P.Index.ivfpq_index_from_arrays(64, 9, 32, 8, *arrays).ivfpq_upload()
+    odd.ivfpq_set_tuning(P.TUNE_SCAN_ROUTE, 3)
+    assert not odd.ivfpq_scan_kernel_info(oracle.LUT_FP32).startswith("scan_filter_kernel")
+
+
 @pytest.mark.parametrize("d,pq_dim,pq_bits,n_lists,n_probes,k", [
     (64, 64, 5, 7, 5, 10),            # m = 1, 40-byte codes, few clusters: most neighbouring pairs share theirs
     (128, 64, 6, 20, 12, 100),        # m = 2, 48-byte codes in 16-byte chunks

@@ -89,3 +89,66 @@ def test_tagged_key_brackets_the_key():
         g = back.view(np.float32)
         ok = np.isfinite(g)
         assert np.all(g[ok] <= f[ok]) and np.all((f[ok].astype(np.float64) - g[ok]) <= 2.0 ** -17 * np.abs(f[ok]) + 64 * 2.0 ** -149)
+
+
+# ---- the matrix-core filter of the grouped scan: a vector with R <= bound always passes its two tests
+
+def stored_entry(f, dtype, truncate=False):
+    """A table entry as a lookup returns it: oracle dtypes 0 fp32, 1 half, 2 e5m3 (bias 15), 3 e4m4 (bias 1)."""
+    if dtype == 0:
+        return f
+    if dtype == 1:
+        return np.minimum(f, np.float32(65504.0)).astype(np.float16).astype(np.float32)
+    shift, bias = (20, 15) if dtype == 2 else (19, 1)
+    lo = (127 - bias) << 23
+    b = np.clip(f.view(np.int32).astype(np.int64), lo, lo + (255 << shift))
+    b = (b + (0 if truncate else 1 << (shift - 1))) & ~((1 << shift) - 1)
+    return np.minimum(b, lo + (255 << shift)).astype(np.int32).view(np.float32)
+
+
+@pytest.mark.parametrize("dtype,truncate", [(0, False), (1, False), (2, False), (2, True), (3, False), (3, True)])
+@pytest.mark.parametrize("d,m,scale", [(128, 2, 20.0), (96, 2, 0.05), (128, 4, 60.0), (64, 4, 1e-3)])
+def test_filter_admits_every_survivor(dtype, truncate, d, m, scale):
+    # The host's constants and the kernel's arithmetic, emulated: residuals and codewords in bf16, the product and its start
+    # summed in fp32 in a scrambled order.  The bound is taken at every vector's own R in turn: the tightest case there is.
+    # Queries a little and far (6 sigma a component: half and e4m4 entries saturate at scale 60) off the cluster.
+    rng = np.random.default_rng(d * 10 + m + dtype)
+    f8 = np.float64
+    for far in (1.0, 6.0):
+        r = (rng.standard_normal((12, d)) * scale * far).astype(np.float32)
+        y = (rng.standard_normal((300, d)) * scale).astype(np.float32)
+        y[:150] = (r[rng.integers(0, 12, 150)] + rng.standard_normal((150, d)) * scale * 0.3).astype(np.float32)
+        loss = {0: 0.0, 1: 1 / 2048, 2: 1 / (9 if truncate else 17), 3: 1 / (17 if truncate else 33)}[dtype]
+        top = {0: np.inf, 1: 65504.0, 2: 122880.0, 3: 1.9375 * 2.0 ** 14}[dtype]
+        subs = d // m
+        grow = (1 + 2.0 ** -15) / (1 - loss)
+        add = (subs * 2.0 ** -25 if dtype == 1 else 0.0) / (1 - loss) * 1.001 + 1e-30
+        eta = 0.00392 + (12 * d + 64) * 2.0 ** -24
+        word_max = np.sqrt((y.reshape(300, subs, m).astype(f8) ** 2).sum(2).max()) * 1.0001
+        part = np.concatenate([np.arange(0, d // 4), np.arange(d // 2, 3 * d // 4)])      # what the first half of the steps covers
+        for q in range(12):
+            diff = (y - r[q]).reshape(300, subs, m)
+            ent = np.zeros((300, subs), np.float32)
+            for t in range(m):
+                ent = (diff[:, :, t].astype(f8) ** 2 + ent).astype(np.float32)
+            R = np.zeros(300, np.float32)
+            for j in range(subs):
+                R = R + stored_entry(ent[:, j], dtype, truncate)
+            rb, yb = bf16_round(r[q]), bf16_round(y)
+            n2 = (rb.reshape(subs, m).astype(f8) ** 2).sum(1)
+            hidden = np.maximum((np.sqrt(n2 * 1.008) + word_max) ** 2 * 1.00001 - top, 0).sum() * 1.0001 if np.isfinite(top) else 0.0
+            wide = ((R * grow + add + hidden) * (1 + eta / 16)).astype(np.float32)
+            rr = (r[q].astype(f8) ** 2).sum()
+            for cols, norm, less in ((np.arange(d), rr, 0.0), (part, (rb[part].astype(f8) ** 2).sum(), 0.00394)):
+                start = (0.5 * (wide - (1 - eta - less) * norm)).astype(np.float32)
+                need = (0.5 * (1 - eta - 0.00394) * (yb[:, cols].astype(f8) ** 2).sum(1)).astype(np.float32)
+                acc = start.copy()
+                for t in rng.permutation(cols):
+                    acc = (acc + rb[t] * yb[:, t]).astype(np.float32)
+                assert np.all(acc >= need)
+            # the ball: no pair is left out whose cluster holds a vector with R <= bound
+            radius = np.sqrt((y.astype(f8) ** 2).sum(1).max())
+            gap = np.sqrt(rr) * 0.99987 - radius * 1.00013
+            least = R.min()
+            if least < top * 0.9999 and gap > 0:
+                assert gap * gap <= (least * grow + add) * 1.0001
