@@ -15,8 +15,9 @@ struct ScanArgs {
     const int64_t* group_offsets;
     const uint8_t* codes;
     const uint4* pairs;           // [nq][n_probes] {cluster, length, first group, R offset}; unused in single-list mode
-    const uint32_t* bounds;       // [nq] per-query upper bound of the k-th smallest R (filtered mode)
-    uint32_t* counts;             // [nq] survivors appended so far (filtered mode)
+    uint32_t* bounds;             // [nq] per-query upper bound of the k-th smallest R: written by mode 1, read in filtered mode
+    uint32_t* counts;             // [nq] survivors appended so far (begun by mode 1, extended in filtered mode)
+    uint32_t* starts;             // [nq] mode 1: their number when it ends, or null
     uint32_t* Rpos;               // [nq][stride] row position of each appended survivor (filtered mode)
     Fp8Mode fp8;                  // encoding of the 8-bit table dtypes (unused by the other two)
     int mode;                     // 1: nearest probe of every query, every R written in place; 3: the same for all probes;
@@ -31,6 +32,9 @@ struct ScanArgs {
     const uint32_t* order;        // mode 2: pairs (as q * (n_probes - 1) + probe - 1) grouped by cluster, or null
     uint32_t n_pairs;             // mode 2: number of such pairs
     uint32_t order_block;         // mode 2: consecutive pairs of the grouped order that stay on one XCD
+    int k_bound;                  // mode 1: the k of the bound to take from the nearest probe's values; 0: none is wanted
+    uint32_t* clear[2];           // mode 1: counters of the grouping that follows, n_clear[] words each, to be set to zero
+    uint32_t n_clear[2];
     int early_exit;               // mode 2: stop adding for a 64-vector group once every partial sum is over the bound
 };
 
