@@ -158,8 +158,7 @@ select_probes_kernel(uint32_t* __restrict__ A, const StripSummary* __restrict__ 
     auto refine = [&](uint32_t n_cand) -> uint32_t {
         const uint32_t kk = (uint32_t)n_probes < n_cand ? (uint32_t)n_probes : n_cand;
         if (kk == 0) return n_cand;
-        uint32_t r0, r1;
-        const uint32_t limit = widen(block_kth_key(s, n_cand, kk, [&](uint32_t i) { return t.cand_key[i]; }, &r0, &r1));
+        const uint32_t limit = widen(block_kth_bound<OrderedKey>(s, n_cand, kk, [&](uint32_t i) { return t.cand_key[i]; }));
         __syncthreads();
         if (tid == 0) s.n_rec = 0;
         __syncthreads();
@@ -215,10 +214,9 @@ select_probes_kernel(uint32_t* __restrict__ A, const StripSummary* __restrict__ 
         auto low1 = [&](uint32_t i) { return in_lds ? t.cand_key[i] : mine[i * stride].x; };
         auto low2 = [&](uint32_t i) { return mine[i * stride].y; };
         auto low3 = [&](uint32_t i) { return mine[i * stride].z; };
-        uint32_t r0, r1;
         const uint32_t kk = (uint32_t)n_probes < n_strips ? (uint32_t)n_probes : n_strips;
         // kk strips hold a key not above this, so it bounds the kk-th smallest key of the row
-        const uint32_t bound = widen(block_kth_key(s, n_strips, kk, [&](uint32_t i) { return low1(i) | 63u; }, &r0, &r1));
+        const uint32_t bound = widen(block_kth_bound<OrderedKey>(s, n_strips, kk, [&](uint32_t i) { return low1(i) | 63u; }));
         __syncthreads();
         if (tid == 0) t.n_cand = 0;
         __syncthreads();
@@ -263,7 +261,7 @@ select_probes_kernel(uint32_t* __restrict__ A, const StripSummary* __restrict__ 
         }
         __syncthreads();
     } else if constexpr (CAP == SEL_CAP) {
-        got = block_select_row_ex(t, row, (uint32_t)n_lists, (uint32_t)n_probes, false, 0u,
+        got = block_select_row_ex<OrderedKey>(t, row, (uint32_t)n_lists, (uint32_t)n_probes, false, 0u,
                                   [](uint32_t i) { return i; },
                                   [](uint32_t pos, uint32_t) { return (long long)pos; },
                                   widen, refine, whole_row);

@@ -173,6 +173,150 @@ __device__ __forceinline__ uint32_t block_kth_key(Shared& s, uint32_t n, uint32_
     return prefix;
 }
 
+// How keys stand for floats: the bit pattern itself (distances, never negative) or the monotone map of ordered_key.  Keys from
+// kNotFinite on are infinities, not-a-numbers and padding; below zero, the ordered map's negative ones.
+struct PlainKey {
+    static constexpr uint32_t kNotFinite = 0x7F800000u;
+    static __device__ float value(uint32_t key) { return __uint_as_float(key); }
+    static __device__ uint32_t key(float v) { return __float_as_uint(v); }
+    static __device__ bool finite(uint32_t key) { return key < kNotFinite; }
+};
+struct OrderedKey {
+    static __device__ float value(uint32_t key) { return ordered_key_value(key); }
+    static __device__ uint32_t key(float v) { return ordered_key(v); }
+    static __device__ bool finite(uint32_t key) { return key < 0xFF800000u && key > 0x007FFFFFu; }
+};
+
+// Equal bins over the values of a set of keys.
+constexpr int kBins = 256;
+struct Bins {
+    float from, inv, width, to;
+    bool usable;                 // some keys are finite and their range has a width
+    template <class K>
+    __device__ int of(uint32_t key) const {
+        if (!K::finite(key)) return kBins - 1;
+        const int b = (int)((K::value(key) - from) * inv);
+        return b < kBins - 1 ? b : kBins - 1;
+    }
+};
+
+// Histogram of n keys (s.hist) over equal bins between the least and the largest finite one; not-finite keys fall into the last bin.
+// The numbering is monotone in the key.  Called by every thread; ends with a barrier.
+template <class K, class Shared, class KeyFn>
+__device__ __forceinline__ Bins bin_histogram(Shared& s, uint32_t n, KeyFn key_of) {
+    const int tid = threadIdx.x, nth = blockDim.x;
+    uint32_t lo = 0xFFFFFFFFu, hi = 0;
+    for (uint32_t i = tid; i < n; i += nth) {
+        const uint32_t key = key_of(i);
+        if (K::finite(key)) { lo = lo < key ? lo : key; hi = hi > key ? hi : key; }
+    }
+    __syncthreads();
+    if (tid == 0) { s.digit = 0xFFFFFFFFu; s.need = 0u; }
+    for (int b = tid; b < kBins; b += nth) s.hist[b] = 0;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        const uint32_t l2 = (uint32_t)__shfl_xor((int)lo, off, kWave), h2 = (uint32_t)__shfl_xor((int)hi, off, kWave);
+        lo = lo < l2 ? lo : l2;
+        hi = hi > h2 ? hi : h2;
+    }
+    __syncthreads();
+    if ((tid & (kWave - 1)) == 0) { atomicMin(&s.digit, lo); atomicMax(&s.need, hi); }
+    __syncthreads();
+    Bins bins;
+    bins.from = K::value(s.digit);
+    bins.to = K::value(s.need);
+    bins.usable = s.digit < s.need;
+    bins.width = (bins.to - bins.from) * (1.f / (kBins - 1));
+    bins.usable = bins.usable && bins.width > 0.f && bins.width < 3.0e38f;
+    bins.inv = bins.usable ? 1.f / bins.width : 0.f;
+    if (bins.usable)
+        for (uint32_t i = tid; i < n; i += nth) atomicAdd(&s.hist[bins.of<K>(key_of(i))], 1u);
+    __syncthreads();
+    return bins;
+}
+
+// A key not below the kk-th smallest (1 <= kk <= n), close to it: the upper edge of the bin that holds it, or the exact key where the bin
+// holds many others.  Three barriers for a histogram instead of the four rounds of block_kth_key; for callers that need a bound only.
+template <class K, class Shared, class KeyFn>
+__device__ __forceinline__ uint32_t block_kth_bound(Shared& s, uint32_t n, uint32_t kk, KeyFn key_of) {
+    const Bins bins = bin_histogram<K>(s, n, key_of);
+    uint32_t r0, r1;
+    if (bins.usable) {
+        find_digit(s, kk);
+        const uint32_t bin = s.digit, in_bin = s.count;
+        if (bin < kBins - 1 && in_bin <= 32u + kk / 4u) {
+            // the roundings of a bin's number and of its edge stay within a few 2^-22 of the range or of the value
+            const float edge = bins.from + (float)(bin + 1) * bins.width * 1.000002f;
+            const float up = edge + __builtin_fabsf(edge) * 5.0e-7f;
+            __syncthreads();
+            return K::key(up < bins.to ? up : bins.to);
+        }
+        __syncthreads();
+    }
+    return block_kth_key(s, n, kk, key_of, &r0, &r1);
+}
+
+// The selection of block_select_smallest by bins: elements of the bins up to the one that holds the kk-th are collected bin by bin,
+// each then counts the elements of its own bin that precede it.  Seven barriers instead of some forty (four rounds of digits, a bitonic
+// sort).  Returns 0, with nothing selected, where bins do not spread the keys: ties, values that cluster, a few far outliers.
+template <class S, class KeyFn, class TieFn>
+__device__ __forceinline__ int block_select_bins(S& s, uint32_t n, uint32_t kk, KeyFn key_of, TieFn tie_of) {
+    const int tid = threadIdx.x, nth = blockDim.x;
+    constexpr uint32_t kMost = 64;                       // elements of a bin: the count inside it is quadratic
+    const Bins bins = bin_histogram<PlainKey>(s, n, key_of);
+    if (!bins.usable) return 0;
+    if (tid < kWave) {
+        uint32_t c[kBins / kWave], sum = 0, most = 0;
+#pragma unroll
+        for (int u = 0; u < kBins / kWave; ++u) { c[u] = s.hist[tid * (kBins / kWave) + u]; sum += c[u]; }
+        uint32_t at = wave_inclusive_scan(sum) - sum;
+        if (tid == 0) s.count = 0;
+#pragma unroll
+        for (int u = 0; u < kBins / kWave; ++u) {
+            s.hist[tid * (kBins / kWave) + u] = at;      // the bin's first record
+            if (at < kk) {
+                most = most > c[u] ? most : c[u];
+                if (kk <= at + c[u]) { s.digit = (uint32_t)(tid * (kBins / kWave) + u); s.need = at + c[u]; }
+            }
+            at += c[u];
+        }
+        if (ballot64(most > kMost) != 0 && tid == 0) s.count = 1;
+    }
+    __syncthreads();
+    const uint32_t last = s.digit, total = s.need;
+    if (s.count != 0 || total > (uint32_t)S::kCap || last == (uint32_t)kBins - 1u) { __syncthreads(); return 0; }
+    for (uint32_t i = tid; i < n; i += nth) {
+        const uint32_t key = key_of(i);
+        const uint32_t b = (uint32_t)bins.of<PlainKey>(key);
+        if (b <= last) {
+            const uint32_t slot = atomicAdd(&s.hist[b], 1u);       // in the end the next bin's first record
+            s.rec_key[slot] = key; s.rec_pos[slot] = i; s.rec_tie[slot] = tie_of(i);
+        }
+    }
+    __syncthreads();
+    constexpr int kEach = (S::kCap + SEL_THREADS - 1) / SEL_THREADS;      // records a thread ranks (workgroups of SEL_THREADS or more)
+    uint32_t key[kEach], pos[kEach], rank[kEach];
+    long long tie[kEach];
+#pragma unroll
+    for (int e = 0; e < kEach; ++e) {
+        const uint32_t r = (uint32_t)tid + (uint32_t)(e * nth);
+        rank[e] = 0xFFFFFFFFu;
+        if (r >= total) continue;
+        key[e] = s.rec_key[r]; pos[e] = s.rec_pos[r]; tie[e] = s.rec_tie[r];
+        const int b = bins.of<PlainKey>(key[e]);
+        const uint32_t first = b ? s.hist[b - 1] : 0u, end = s.hist[b];
+        uint32_t before = first;
+        for (uint32_t j = first; j < end; ++j) before += rec_less(s.rec_key[j], s.rec_tie[j], s.rec_pos[j], key[e], tie[e], pos[e]) ? 1u : 0u;
+        rank[e] = before;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < kEach; ++e)
+        if (rank[e] < kk) { s.rec_key[rank[e]] = key[e]; s.rec_pos[rank[e]] = pos[e]; s.rec_tie[rank[e]] = tie[e]; }
+    __syncthreads();
+    return (int)kk;
+}
+
 // KeyFn(i) -> uint32 key of element i; TieFn(i) -> long long tie key of element i.
 // On return records [0, min(k, n)) hold the selected elements in ascending (key, tie, pos) order.
 // Returns min(k, n).  Must be called by every thread of the workgroup.
@@ -181,6 +325,7 @@ __device__ __forceinline__ int block_select_smallest(S& s, uint32_t n, uint32_t 
     const uint32_t kk = k < n ? k : n;
     if (kk == 0) return 0;
     const int tid = threadIdx.x, nth = blockDim.x;
+    if (const int got = block_select_bins(s, n, kk, key_of, tie_of)) return got;
 
     uint32_t need = 0, n_eq = 0;
     const uint32_t T = block_kth_key(s, n, kk, key_of, &need, &n_eq);
@@ -314,6 +459,7 @@ struct RowSelectSharedT {
 };
 using RowSelectShared = RowSelectSharedT<SEL_CAP>;
 
+// K: what the keys stand for (PlainKey, OrderedKey).
 // pos_of(i): logical position of row element i (what the records report and what tie_of_pos
 // takes); have_bound/bound: an upper bound of the k-th smallest key that the caller already knows
 // (at least k elements of the row are <= it).
@@ -325,7 +471,7 @@ using RowSelectShared = RowSelectSharedT<SEL_CAP>;
 struct NoWiden { __device__ uint32_t operator()(uint32_t b) const { return b; } };
 struct NoRefine { __device__ uint32_t operator()(uint32_t n) const { return n; } };
 
-template <class T, class PosFn, class TieFn, class WidenFn, class RefineFn, class WholeRowFn>
+template <class K, class T, class PosFn, class TieFn, class WidenFn, class RefineFn, class WholeRowFn>
 __device__ __forceinline__ int block_select_row_ex(T& t, const uint32_t* __restrict__ row, uint32_t n, uint32_t k,
                                    bool have_bound, uint32_t bound, PosFn pos_of, TieFn tie_of_pos,
                                    WidenFn widen, RefineFn refine, WholeRowFn whole_row) {
@@ -345,9 +491,9 @@ __device__ __forceinline__ int block_select_row_ex(T& t, const uint32_t* __restr
             const uint32_t S = want <= (unsigned long long)CAND_CAP ? (uint32_t)CAND_CAP : (want < n ? (uint32_t)want : n);
             if (S == (uint32_t)CAND_CAP) {
                 for (int i = tid; i < CAND_CAP; i += nth) t.cand_key[i] = row[i];
-                bound = block_kth_key(s, (uint32_t)CAND_CAP, kk, [&](uint32_t i) { return t.cand_key[i]; }, &r0, &r1);
+                bound = block_kth_bound<K>(s, (uint32_t)CAND_CAP, kk, [&](uint32_t i) { return t.cand_key[i]; });
             } else {
-                bound = block_kth_key(s, S, kk, [&](uint32_t i) { return row[i]; }, &r0, &r1);
+                bound = block_kth_bound<K>(s, S, kk, [&](uint32_t i) { return row[i]; });
             }
         }
         bound = widen(bound);
@@ -406,7 +552,7 @@ template <class T, class PosFn, class TieFn>
 __device__ __forceinline__ int block_select_row(T& t, const uint32_t* __restrict__ row, uint32_t n, uint32_t k,
                                 bool have_bound, uint32_t bound, PosFn pos_of, TieFn tie_of_pos) {
     auto& s = t.sel;
-    return block_select_row_ex(t, row, n, k, have_bound, bound, pos_of, tie_of_pos, NoWiden{}, NoRefine{},
+    return block_select_row_ex<PlainKey>(t, row, n, k, have_bound, bound, pos_of, tie_of_pos, NoWiden{}, NoRefine{},
         [&]() -> int {
             const int got = block_select_smallest(s, n, k,
                 [&](uint32_t i) { return row[i]; },
