@@ -126,6 +126,11 @@ select_probes_kernel(uint32_t* __restrict__ A, const StripSummary* __restrict__ 
     };
     // |q|^2, for the error bound of a()
     float part = 0.f;
+    if (S) {             // (the strip minima go the same way, see below: their loads travel with the query's)
+        const uint32_t n_strips = ((uint32_t)n_lists + strip_w - 1) / strip_w;
+        if (n_strips <= (uint32_t)CAND_CAP)
+            for (uint32_t i = tid; i < n_strips; i += nth) t.cand_key[i] = S[q + i * (size_t)gridDim.x].x;
+    }
     for (int c = tid; c < d; c += nth) part = __builtin_fmaf(qv[c], qv[c], part);
     part = wave_sum(part);
     if (lane == 0) s_part[wave] = part;
@@ -153,6 +158,31 @@ select_probes_kernel(uint32_t* __restrict__ A, const StripSummary* __restrict__ 
         acc = sum_over_8_lanes(acc);
         return acc;
     };
+    // n of them, cluster_of(j), each to sink(j, distance) in the first lane of its group; two per group at a time, so that the loads of
+    // both are under way together
+    auto exact_all = [&](uint32_t n, auto cluster_of, auto sink) {
+        const uint32_t per = nth / 8;
+        for (uint32_t base = 0; base < n; base += 2 * per) {
+            const uint32_t j0 = base + (tid >> 3), j1 = j0 + per;
+            const bool v0 = j0 < n, v1 = j1 < n;
+            const float *c0 = centroids + (size_t)(v0 ? cluster_of(j0) : 0u) * d, *c1 = centroids + (size_t)(v1 ? cluster_of(j1) : 0u) * d;
+            float a0 = 0.f, a1 = 0.f;
+            if (v0) {
+#pragma unroll 4
+                for (int u = tid & 7; u < d; u += 8) {
+                    const float x = qv[u], d0 = x - c0[u], d1 = x - c1[u];
+                    a0 = __builtin_fmaf(d0, d0, a0);
+                    a1 = __builtin_fmaf(d1, d1, a1);
+                }
+            }
+            a0 = sum_over_8_lanes(a0);
+            a1 = sum_over_8_lanes(a1);
+            if ((tid & 7) == 0) {
+                if (v0) sink(j0, a0);
+                if (v1) sink(j1, a1);
+            }
+        }
+    };
     // candidates in LDS: keep those whose a() is within 2 delta of the n_probes-th smallest a() among
     // them (every cluster of the exact answer is among these), give them their exact distance
     auto refine = [&](uint32_t n_cand) -> uint32_t {
@@ -169,13 +199,8 @@ select_probes_kernel(uint32_t* __restrict__ A, const StripSummary* __restrict__ 
         }
         __syncthreads();
         const uint32_t n_short = s.n_rec;
-        for (uint32_t base = 0; base < n_short; base += nth / 8) {
-            const uint32_t j = base + (tid >> 3);
-            const bool valid = j < n_short;
-            const uint32_t i = valid ? s.rec_pos[j] : 0u;
-            const float dist = exact8(valid ? t.cand_pos[i] : 0u, valid);
-            if (valid && (tid & 7) == 0) t.cand_key[i] = __float_as_uint(dist);
-        }
+        exact_all(n_short, [&](uint32_t j) { return t.cand_pos[s.rec_pos[j]]; },
+                  [&](uint32_t j, float dist) { t.cand_key[s.rec_pos[j]] = __float_as_uint(dist); });
         __syncthreads();
         if (n_short > kFewMax) return n_cand;        // the others keep the all-ones key and are never selected
         // few enough for the counting selection: move the short list to the front
@@ -207,10 +232,7 @@ select_probes_kernel(uint32_t* __restrict__ A, const StripSummary* __restrict__ 
         const StripSummary* mine = S + q;
         // the strip minima are read several times: from the (still unused) candidate-key array if they fit; the
         // second and third keys are needed only for the few strips whose minimum passes the bound
-        const bool in_lds = n_strips <= (uint32_t)CAND_CAP;
-        if (in_lds)
-            for (uint32_t i = tid; i < n_strips; i += nth) t.cand_key[i] = mine[i * stride].x;
-        __syncthreads();
+        const bool in_lds = n_strips <= (uint32_t)CAND_CAP;         // (put there at the start; a barrier has passed)
         auto low1 = [&](uint32_t i) { return in_lds ? t.cand_key[i] : mine[i * stride].x; };
         auto low2 = [&](uint32_t i) { return mine[i * stride].y; };
         auto low3 = [&](uint32_t i) { return mine[i * stride].z; };
@@ -244,12 +266,7 @@ select_probes_kernel(uint32_t* __restrict__ A, const StripSummary* __restrict__ 
         __syncthreads();
         const uint32_t n_cand = t.n_cand;
         if (n_cand >= (uint32_t)n_probes && n_cand <= (uint32_t)CAND_CAP) {
-            for (uint32_t base = 0; base < n_cand; base += nth / 8) {
-                const uint32_t j = base + (tid >> 3);
-                const bool valid = j < n_cand;
-                const float dist = exact8(valid ? t.cand_pos[j] : 0u, valid);
-                if (valid && (tid & 7) == 0) t.cand_key[j] = __float_as_uint(dist);
-            }
+            exact_all(n_cand, [&](uint32_t j) { return t.cand_pos[j]; }, [&](uint32_t j, float dist) { t.cand_key[j] = __float_as_uint(dist); });
             __syncthreads();
             auto key_of = [&](uint32_t i) { return t.cand_key[i]; };
             auto tie_of = [&](uint32_t i) { return (long long)t.cand_pos[i]; };
@@ -287,19 +304,22 @@ select_probes_kernel(uint32_t* __restrict__ A, const StripSummary* __restrict__ 
     uint32_t* slot_of = reinterpret_cast<uint32_t*>(s.rec_tie);          // 2 CAP words: slot of probe p, then offsets
     uint32_t* offs = slot_of + CAP;
     __syncthreads();
-    if (tid == 0) {
-        int pivot = 0;
+    if (tid < kWave) {                     // the first wave: the pivot, then a running sum of the padded lengths in slot order
+        int pivot = got;
         if (k_hint > 0)
-            for (int p = 0; p < got; ++p)
-                if (t.cand_key[p] >= (uint32_t)k_hint) { pivot = p; break; }
+            for (int p0 = 0; p0 < got && pivot == got; p0 += kWave) {
+                const unsigned long long m = ballot64(p0 + tid < got && t.cand_key[p0 + tid < got ? p0 + tid : 0] >= (uint32_t)k_hint);
+                if (m != 0) pivot = p0 + __ffsll((long long)m) - 1;
+            }
+        if (pivot == got) pivot = 0;
         uint32_t at = 0;
-        for (int i = 0; i < got; ++i) {
-            const int p = i == 0 ? pivot : (i <= pivot ? i - 1 : i);
-            slot_of[p] = (uint32_t)i;
-            offs[p] = at;
-            at += (t.cand_key[p] + 63u) & ~63u;
+        for (int i0 = 0; i0 < got; i0 += kWave) {
+            const int i = i0 + tid, p = i == 0 ? pivot : (i <= pivot ? i - 1 : i);
+            const uint32_t len = i < got ? (t.cand_key[p] + 63u) & ~63u : 0u, upto = wave_inclusive_scan(len);
+            if (i < got) { slot_of[p] = (uint32_t)i; offs[p] = at + upto - len; }
+            at += (uint32_t)__builtin_amdgcn_readlane((int)upto, kWave - 1);
         }
-        roff[(size_t)q * (n_probes + 1) + got] = at;
+        if (tid == 0) roff[(size_t)q * (n_probes + 1) + got] = at;
     }
     __syncthreads();
     for (int p = tid; p < got; p += nth) {
@@ -1166,15 +1186,27 @@ template <int CAP, int THREADS>          // record capacity, >= k
 __global__ void __launch_bounds__(THREADS)
 topk_kernel(const float* __restrict__ R, const uint32_t* __restrict__ Rpos, size_t stride,
             const uint32_t* __restrict__ roff, const uint32_t* __restrict__ probes,
-            const uint32_t* __restrict__ bounds, const uint32_t* __restrict__ counts, int n_probes, int k,
+            const uint32_t* __restrict__ bounds, const uint32_t* __restrict__ counts, int n_probes, int n_lists, int k,
             const int64_t* __restrict__ list_offsets, const int64_t* __restrict__ ids,
             int64_t* __restrict__ out_ids, float* __restrict__ out_dists, bool listed) {
     __shared__ RowSelectSharedT<CAP> t;
+    // where the segments of up to kInLds probes start and their clusters' first ids: a survivor's search and id are then one read from
+    // global memory instead of a chain of nine
+    constexpr int kInLds = 128;
+    __shared__ uint32_t l_roff[kInLds];
+    __shared__ long long l_first[kInLds];
     auto& s = t.sel;
     const int q = blockIdx.x;
     const int tid = threadIdx.x, nth = blockDim.x;
-    const uint32_t* s_roff = roff + (size_t)q * (n_probes + 1);     // read through the vector cache:
-    const uint32_t* s_probe = probes + (size_t)q * n_probes;        // only the few survivors look them up
+    const uint32_t* s_roff = roff + (size_t)q * (n_probes + 1);
+    const uint32_t* s_probe = probes + (size_t)q * n_probes;
+    const bool in_lds = n_probes <= kInLds;
+    if (in_lds)
+        for (int p = tid; p < n_probes; p += nth) {
+            const uint32_t l = s_probe[p];
+            l_roff[p] = s_roff[p];
+            l_first[p] = l < (uint32_t)n_lists ? (long long)list_offsets[l] : 0ll;         // (a caller-given probe out of range has no vectors)
+        }
     const uint32_t seg0 = s_roff[1];          // padded length of the nearest probe's segment (a multiple of 64)
     const uint32_t n = listed ? counts[q] : s_roff[n_probes];
     const uint32_t* row = reinterpret_cast<const uint32_t*>(R + (size_t)q * stride) + (listed ? seg0 : 0u);
@@ -1186,6 +1218,13 @@ topk_kernel(const float* __restrict__ R, const uint32_t* __restrict__ Rpos, size
     auto id_of = [&](uint32_t pos, uint32_t key) -> long long {
         if (key == kPadKey) return 0x7FFFFFFFFFFFFFFFll;
         int lo = 0, hi = n_probes;            // largest probe slot with roff[slot] <= pos
+        if (in_lds) {
+            while (hi - lo > 1) {
+                const int mid = (lo + hi) >> 1;
+                if (l_roff[mid] <= pos) lo = mid; else hi = mid;
+            }
+            return (long long)ids[l_first[lo] + (long long)(pos - l_roff[lo])];
+        }
         while (hi - lo > 1) {
             int mid = (lo + hi) >> 1;
             if (s_roff[mid] <= pos) lo = mid; else hi = mid;
@@ -1890,7 +1929,7 @@ int search_impl(const ivfpq_index* idx, const float* d_queries, int64_t nq, cons
         if (int s = t2.begin()) return s;
         auto topk = [&](auto kernel, int threads) {
             hipLaunchKernelGGL(kernel, dim3(tq), dim3(threads), 0, st, w_R, w_Rpos, plan.stride, w_roff, w_probes, w_bounds, w_counts,
-                               n_probes, k, idx->dev.list_offsets, idx->dev.ids, d_ids + (size_t)q0 * k, d_dists + (size_t)q0 * k,
+                               n_probes, idx->n_lists, k, idx->dev.list_offsets, idx->dev.ids, d_ids + (size_t)q0 * k, d_dists + (size_t)q0 * k,
                                n_probes > 1 && !whole_rows);
         };
         if (tq <= kFewQueries) topk(topk_kernel<SEL_CAP, 1024>, 1024);
