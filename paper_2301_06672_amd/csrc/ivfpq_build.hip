@@ -13,6 +13,7 @@
 //                          few centres, else the two smallest of every strip of 32 / 64 centres)
 //   nearest_kernel, nearest_strips_kernel   per row the smallest ranking value; a second value within the
 //                          rigorous error bound of the first sends the row to exact float64 distances
+//   near_*_kernel          the same decision from one product in half precision, for many rows and centres (ivfpq_nearest.hpp)
 //   group_count/prefix/offsets/group_scatter   rows grouped by label, ascending inside a group (count_labels/
 //                          scatter_rows/sort_groups for more labels than LDS counters hold)
 //   update_centres_kernel  ordered float64 mean of every group
@@ -43,6 +44,12 @@ __global__ void fill_u32_kernel(uint32_t* p, size_t n, uint32_t v) {
     size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = v;
 }
+
+}  // namespace
+
+#include "ivfpq_nearest.hpp"
+
+namespace {
 
 // dst[i][:] = src[rows[i]][:]
 __global__ void gather_rows_kernel(const float* __restrict__ src, const int64_t* __restrict__ rows, int64_t n_rows,
@@ -921,6 +928,11 @@ int fill_u32(uint32_t* p, size_t n, uint32_t v, hipStream_t st) {
     return IVFPQ_OK;
 }
 
+// One product in half precision (nearest_by_halves), from 12 M values on: its ten launches cost more than the three products below that
+// (us, strip summaries / one product: 2.4 M 115 / 118, 5.1 M 83 / 122, 15 M 172 / 127, 20 M 150 / 104, 27 M 183 / 97, 150 M 231 / 139,
+// 500 M 899 / 326, 5,000 M 4,290 / 1,500).
+bool near_pays(size_t n_rows, int k) { return n_rows * (size_t)k >= 12000000; }
+
 // labels[i] = nearest centre of X[i], for n_rows rows
 int assign_rows_device(const BuildPlan& P, unsigned char* ws, const float* X, size_t n_rows, const float* C, int k,
                        int32_t* labels, hipStream_t st) {
@@ -928,6 +940,16 @@ int assign_rows_device(const BuildPlan& P, unsigned char* ws, const float* X, si
     uint32_t* cmax = (uint32_t*)(ws + P.cmax);
     uint32_t* A = (uint32_t*)(ws + P.A);
     StripSummary* S = (StripSummary*)(ws + P.S);
+    // One product in half precision, in the place of the strip summaries and the split operands (P.cnorm follows them).
+    if (P.use_strips && near_dims(P.d) && near_pays(n_rows, k)) {
+        size_t tile = n_rows;
+        while (tile > 4096 && near_layout(tile, k, P.d).bytes > P.cnorm - P.S) tile = (tile + 1) / 2;
+        if (near_layout(tile, k, P.d).bytes <= P.cnorm - P.S) {
+            for (size_t r0 = 0; r0 < n_rows; r0 += tile)
+                if (int s = nearest_by_halves(ws + P.S, X + r0 * P.d, std::min(tile, n_rows - r0), C, k, P.d, labels + r0, st)) return s;
+            return IVFPQ_OK;
+        }
+    }
     if (int s = fill_u32(cmax, 1, 0u, st)) return s;
     hipLaunchKernelGGL(centre_norms_kernel, dim3(blocks_for((size_t)k, 4)), dim3(256), 0, st, C, k, P.d, cnorm, cmax);
     HIP_TRY(hipGetLastError());

@@ -64,6 +64,48 @@ def test_assign_device_equals_oracle(P, n, d, k, offset, kind):
         assert not np.any(got == 5)
 
 
+@pytest.mark.parametrize("n,d,k,kind", [
+    (12001, 128, 1000, "gauss"),      # three blocks of rows per wave, a last tile of one row, a last stage of 40 centres
+    (9000, 96, 1345, "gauss"),        # splits of the centres among workgroups; one centre past a stage
+    (50000, 33, 257, "gauss"),        # two slices padded from 33 components
+    (8000, 64, 1600, "offset"),       # a common offset of 1000 sigma: the mean comes off before the rounding to half
+    (7000, 24, 2000, "same"),         # 60 copies of one centre: more centres within the bound than a row's list holds
+    (6500, 16, 2048, "scales"),       # rows 10^6 times the centres' size and 10^-6 of it; components past the range of a half
+    (9000, 100, 1400, "tiny"),        # values about 1e-30
+])
+def test_assign_device_half_precision_product(P, n, d, k, kind):
+    # one product in half precision decides where the margin is larger than twice its error; the others are listed and compared in
+    # float64: the oracle's labels, always
+    rng = np.random.default_rng(n + d)
+    x = _data(n, d, 31 + n, 1000.0 if kind == "offset" else 0.0, "gauss")
+    if kind == "tiny":
+        x *= np.float32(1e-30)
+    c = x[np.sort(rng.choice(n, size=k, replace=False))].copy()
+    c += (rng.standard_normal(c.shape) * 0.05 * x.std()).astype(np.float32)
+    if kind == "same":
+        c[700:760] = c[3]
+        x[100:400] = c[3] + (rng.standard_normal((300, d)) * 0.01).astype(np.float32)
+    if kind == "scales":
+        x[::7] *= np.float32(1e6)
+        x[1::7] *= np.float32(1e-6)
+    c[11] = c[4]
+    assert n * k >= 12_000_000                # what this way of deciding is taken from
+    _step(f"assign, half-precision product: n={n} d={d} k={k} {kind}")
+    got = P.ivfpq_assign_device(x, c).cpu().numpy()
+    want, _ = oracle.assign(x, c)
+    np.testing.assert_array_equal(got, want)
+    if kind == "gauss":
+        x[5, 2], x[n - 1, 0] = np.nan, np.inf                      # no nearest centre: a label in range, the other rows as before
+        c2 = c.copy()
+        c2[20, 3] = np.nan                                         # never the nearest
+        got = P.ivfpq_assign_device(x, c2).cpu().numpy()
+        want, _ = oracle.assign(x, c2)
+        ok = np.ones(n, bool)
+        ok[[5, n - 1]] = False
+        np.testing.assert_array_equal(got[ok], want[ok])
+        assert 0 <= got[5] < k and 0 <= got[n - 1] < k and not np.any(got == 20)
+
+
 # ---------------------------------------------------------------- the whole build
 
 def _rows(n, n_lists, pq_dim, pq_bits, n_ct, n_pt, salt):
