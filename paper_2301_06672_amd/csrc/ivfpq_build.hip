@@ -48,6 +48,7 @@ __global__ void fill_u32_kernel(uint32_t* p, size_t n, uint32_t v) {
 }  // namespace
 
 #include "ivfpq_nearest.hpp"
+#include "ivfpq_transfer.hpp"
 
 namespace {
 
@@ -1234,18 +1235,13 @@ int build_device_impl(const float* d_data, int64_t n, int32_t d, int32_t n_lists
     idx->list_offsets.resize((size_t)n_lists + 1);
     idx->codes.resize((size_t)n * cb);
     idx->ids.resize((size_t)n);
-    HostArray<uint32_t> order_h((size_t)n);
-    auto copy_out = [&]() -> int {
-        HIP_TRY(hipMemcpyAsync(idx->centroids.data(), C, idx->centroids.size() * 4, hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipMemcpyAsync(idx->codebooks.data(), codebooks, idx->codebooks.size() * 4, hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipMemcpyAsync(idx->list_offsets.data(), offsets, idx->list_offsets.size() * 8, hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipMemcpyAsync(idx->codes.data(), codes32, idx->codes.size(), hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipMemcpyAsync(order_h.data(), order, order_h.size() * 4, hipMemcpyDeviceToHost, st));
-        HIP_TRY(hipStreamSynchronize(st));
-        return IVFPQ_OK;
-    };
-    if (int s = copy_out()) return s;
-    for (int64_t i = 0; i < n; ++i) idx->ids[(size_t)i] = (int64_t)order_h[(size_t)i];
+    HostTransfer transfer(st);
+    transfer.add(idx->codes.data(), codes32, idx->codes.size());
+    transfer.add(idx->ids.data(), order, (size_t)n * 4, true);
+    transfer.add(idx->centroids.data(), C, idx->centroids.size() * 4);
+    transfer.add(idx->codebooks.data(), codebooks, idx->codebooks.size() * 4);
+    transfer.add(idx->list_offsets.data(), offsets, idx->list_offsets.size() * 8);
+    if (int s = transfer.run()) return s;
     finish_import(idx);
     *out = owner.release();
     return IVFPQ_OK;

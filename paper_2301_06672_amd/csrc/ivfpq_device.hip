@@ -989,11 +989,6 @@ __global__ void __launch_bounds__(256) stream_read_kernel(const uint4* __restric
     if (threadIdx.x == 0) out[blockIdx.x] = part[0] ^ part[1] ^ part[2] ^ part[3];
 }
 
-__global__ void fill_u32_kernel(uint32_t* p, size_t n, uint32_t v) {
-    size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
-}
-
 // Pairs whose cluster cannot hold a vector with R <= bound.  Every decoded residual y of the cluster has |y| <= its radius,
 // so |r - y| >= |r| - radius, and a vector with R <= bound has |r - y|^2 <= bound * scale + add (filter_constants) unless an
 // entry of its sum saturated, which alone makes R >= top.  The counting pass marks such a pair (its distance turned negative); the
@@ -2046,26 +2041,38 @@ int upload_impl(ivfpq_index_t* idx, void* d_buf, size_t bytes, void* hip_stream)
     unsigned char* base = (unsigned char*)d_buf;
     const int cb = idx->code_bytes(), cw = chunk_width(idx), nch = cb / cw;
 
-    std::vector<uint32_t> sizes((size_t)idx->n_lists);
-    std::vector<int64_t> goff((size_t)idx->n_lists + 1, 0);
+    // Everything before the codes is put together on the host and travels as one (a copy of a few kB costs what 1 MB costs).
+    ivfpq::HostArray<unsigned char> head(L.codes);
+    std::memset(head.data(), 0, head.size());
+    std::memcpy(head.data() + L.centroids, idx->centroids.data(), idx->centroids.size() * 4);
+    std::memcpy(head.data() + L.codebooks, idx->codebooks.data(), idx->codebooks.size() * 4);
+    std::memcpy(head.data() + L.list_offsets, idx->list_offsets.data(), idx->list_offsets.size() * 8);
+    uint32_t* sizes = (uint32_t*)(head.data() + L.list_sizes);
+    int64_t* goff = (int64_t*)(head.data() + L.group_offsets);
     for (int l = 0; l < idx->n_lists; ++l) {
         int64_t len = idx->list_offsets[l + 1] - idx->list_offsets[l];
         sizes[l] = (uint32_t)len;
         goff[l + 1] = goff[l] + (len + 63) / 64;
     }
-    std::vector<float> cnorm((size_t)idx->n_lists);
+    float* cnorm = (float*)(head.data() + L.centroid_norms);
     float cn_max = 0.f;
-    for (int l = 0; l < idx->n_lists; ++l) {
-        double acc = 0.0;
-        for (int t = 0; t < idx->d; ++t) { double v = idx->centroids[(size_t)l * idx->d + t]; acc += v * v; }
-        cnorm[l] = (float)acc;
-        if (cnorm[l] > cn_max) cn_max = cnorm[l];
+    for (int l = 0; l < idx->n_lists; l += 8) {                                           // eight sums at a time: each is one chain of additions
+        double acc[8] = {};
+        const float* c[8];
+        for (int u = 0; u < 8; ++u) c[u] = idx->centroids.data() + (size_t)std::min(l + u, idx->n_lists - 1) * idx->d;
+        for (int t = 0; t < idx->d; ++t)
+            for (int u = 0; u < 8; ++u) { double v = c[u][t]; acc[u] += v * v; }
+        for (int u = 0; u < 8 && l + u < idx->n_lists; ++u) {
+            cnorm[l + u] = (float)acc[u];
+            if (cnorm[l + u] > cn_max) cn_max = cnorm[l + u];
+        }
     }
     idx->centroid_norm_max = cn_max;
-    std::vector<float> wnorm((size_t)idx->pq_dim << idx->pq_bits);
+    const size_t n_words = (size_t)idx->pq_dim << idx->pq_bits;
+    float* wnorm = (float*)(head.data() + L.word_norms);
     float wn_max = 0.f;
     bool moderate = true;
-    for (size_t i = 0; i < wnorm.size(); ++i) {
+    for (size_t i = 0; i < n_words; ++i) {
         float acc = 0.f;
         for (int t = 0, m = idx->m(); t < m; ++t) { const float v = idx->codebooks[i * m + t]; acc += v * v; }
         wnorm[i] = acc;
@@ -2073,13 +2080,8 @@ int upload_impl(ivfpq_index_t* idx, void* d_buf, size_t bytes, void* hip_stream)
         wn_max = std::max(wn_max, acc);
     }
     idx->word_norm_max = moderate ? std::sqrt(wn_max) * 1.0001f : -1.f;
-    HIP_TRY(hipMemcpyAsync(base + L.centroid_norms, cnorm.data(), cnorm.size() * 4, hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemcpyAsync(base + L.centroids, idx->centroids.data(), idx->centroids.size() * 4, hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemcpyAsync(base + L.codebooks, idx->codebooks.data(), idx->codebooks.size() * 4, hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemcpyAsync(base + L.word_norms, wnorm.data(), wnorm.size() * 4, hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemcpyAsync(base + L.list_offsets, idx->list_offsets.data(), idx->list_offsets.size() * 8, hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemcpyAsync(base + L.list_sizes, sizes.data(), sizes.size() * 4, hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemcpyAsync(base + L.group_offsets, goff.data(), goff.size() * 8, hipMemcpyHostToDevice, st));
+
+    HIP_TRY(hipMemcpyAsync(base, head.data(), head.size(), hipMemcpyHostToDevice, st));
     // The codes travel in list order, as many whole groups at a time as fit the place of the ids, and are interleaved
     // from there on the device; the ids follow.
     const int64_t cap = idx->n == 0 ? 0 : (int64_t)((L.total - L.ids) / (size_t)cb);      // vectors in transit, 64 or more
@@ -2107,12 +2109,11 @@ int upload_impl(ivfpq_index_t* idx, void* d_buf, size_t bytes, void* hip_stream)
         g = g_end;
         v = v_end;
     }
-    hipLaunchKernelGGL(fill_u32_kernel, dim3((idx->n_lists + 255) / 256), dim3(256), 0, st, (uint32_t*)(base + L.list_radii), (size_t)idx->n_lists, 0u);
     if (idx->total_groups > 0) {
-        const bool in_lds = wnorm.size() * 4 <= kLdsBytes;
+        const bool in_lds = n_words * 4 <= kLdsBytes;
         if (int s = allow_full_lds(list_radii_kernel)) return s;
-        const unsigned blocks = (unsigned)std::min<int64_t>(512, (idx->total_groups + 15) / 16);
-        hipLaunchKernelGGL(list_radii_kernel, dim3(blocks), dim3(1024), in_lds ? wnorm.size() * 4 : 0, st, (const unsigned char*)(base + L.codes),
+        const unsigned radii_blocks = (unsigned)std::min<int64_t>(512, (idx->total_groups + 15) / 16);
+        hipLaunchKernelGGL(list_radii_kernel, dim3(radii_blocks), dim3(1024), in_lds ? n_words * 4 : 0, st, (const unsigned char*)(base + L.codes),
                            (const float*)(base + L.word_norms), (const int64_t*)(base + L.list_offsets), (const int64_t*)(base + L.group_offsets),
                            idx->n_lists, idx->total_groups, cb, cw, idx->pq_dim, idx->pq_bits, in_lds, (uint32_t*)(base + L.list_radii));
         HIP_TRY(hipGetLastError());

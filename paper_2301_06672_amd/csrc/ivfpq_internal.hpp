@@ -68,7 +68,7 @@ template <class T> using HostArray = std::vector<T, HostAllocator<T>>;
 // memcpy by a few threads: one thread is bound by the page faults of a destination that is touched for the first time
 // (48 MB into new memory: 3.6 ms by one thread)
 inline void copy_bytes(void* dst, const void* src, size_t bytes) {
-    constexpr size_t kPerThread = (size_t)4 << 20;
+    constexpr size_t kPerThread = (size_t)2 << 20;
     const size_t hw = std::thread::hardware_concurrency();
     size_t parts = bytes / kPerThread;
     parts = parts > 8 ? 8 : parts;
@@ -77,7 +77,7 @@ inline void copy_bytes(void* dst, const void* src, size_t bytes) {
         if (bytes) std::memcpy(dst, src, bytes);
         return;
     }
-    const size_t step = (bytes / parts + 4095) / 4096 * 4096;
+    const size_t step = (bytes / parts + kPerThread - 1) / kPerThread * kPerThread;   // no huge page is touched by two
     std::thread pool[8];
     size_t at = step;                                        // the first part is this thread's own
     try {

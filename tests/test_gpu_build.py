@@ -215,6 +215,22 @@ def test_build_device_default_draws_and_search(P):
     assert abs(rec["device"] - rec["host"]) < 0.05 and rec["device"] > 0.5
 
 
+@pytest.mark.parametrize("n", [5001, 800001])    # copied out by the runtime; by pieces through the pinned ring, the last one ragged
+def test_build_device_arrays_arrive_whole(P, n):
+    d, n_lists, pq_dim, bits = 16, 40, 16, 4
+    x = _data(n, d, 5)
+    _step(f"build_device n={n}, every id and code checked")
+    cent, books, offs, codes, ids = P.Index.ivfpq_build_device(x, n_lists, pq_dim, bits, 1, seed=2).ivfpq_index_export()
+    assert np.array_equal(np.sort(ids), np.arange(n))
+    lists = np.repeat(np.arange(n_lists), np.diff(offs))
+    assert np.all((np.diff(ids) > 0) | (np.diff(lists) > 0))
+    word = np.stack([codes & 15, codes >> 4], axis=2).reshape(n, pq_dim)
+    for j in range(pq_dim):                      # one component each: |residual - word| is the least there is, ties and rounding aside
+        r = (x[ids, j] - cent[lists, j]).astype(np.float64)
+        gap = np.abs(r[:, None] - books[j, :, 0].astype(np.float64))
+        assert np.all(gap[np.arange(n), word[:, j]] <= gap.min(axis=1) + 1e-12)
+
+
 def test_build_device_rejects_bad_arguments(P):
     x = torch.zeros((100, 16), device="cuda")
     for kw, status in ((dict(coarse_init_rows=np.full(4, 100)), P.EINVAL),
