@@ -6,6 +6,7 @@
 //                        matrix cores: bf16 instructions on operands split in two for large problems,
 //                        fp32 otherwise; stored as all keys (few clusters) or as the three smallest
 //                        tagged keys of every strip of 32 / 64 clusters
+//   cluster_distance_kernel  few queries instead: the exact distances, which step 1b then selects from as they are
 //   select_probes_kernel step 1b: candidates by ranking value with a rigorous error bound, exact
 //                        direct-form distances for them, exact selection of the n_probes nearest
 //                        clusters; per-pair descriptors and R offsets
@@ -97,7 +98,7 @@ int static_scratch_ptr(void** out) {
 // ================================================================================================
 // CAP: record capacity, >= n_probes.  The small one serves selections from strip summaries only (S given): the path
 // that streams all keys short-lists up to CAND_CAP indices in the record arrays.
-template <int CAP, int THREADS>
+template <int CAP, int THREADS, bool EXACT = false>
 __global__ void __launch_bounds__(THREADS)
 select_probes_kernel(uint32_t* __restrict__ A, const StripSummary* __restrict__ S, int strip_w,
                      const float* __restrict__ queries,
@@ -125,18 +126,19 @@ select_probes_kernel(uint32_t* __restrict__ A, const StripSummary* __restrict__ 
         return v;
     };
     // |q|^2, for the error bound of a()
-    float part = 0.f;
+    float part = 0.f, qn = 0.f;
     if (S) {             // (the strip minima go the same way, see below: their loads travel with the query's)
         const uint32_t n_strips = ((uint32_t)n_lists + strip_w - 1) / strip_w;
         if (n_strips <= (uint32_t)CAND_CAP)
             for (uint32_t i = tid; i < n_strips; i += nth) t.cand_key[i] = S[q + i * (size_t)gridDim.x].x;
     }
-    for (int c = tid; c < d; c += nth) part = __builtin_fmaf(qv[c], qv[c], part);
-    part = wave_sum(part);
-    if (lane == 0) s_part[wave] = part;
-    __syncthreads();
-    float qn = 0.f;
-    for (int w = 0; w < n_waves; ++w) qn += s_part[w];
+    if constexpr (!EXACT) {
+        for (int c = tid; c < d; c += nth) part = __builtin_fmaf(qv[c], qv[c], part);
+        part = wave_sum(part);
+        if (lane == 0) s_part[wave] = part;
+        __syncthreads();
+        for (int w = 0; w < n_waves; ++w) qn += s_part[w];
+    }
     // |a_computed - a_exact| <= delta
     const float delta = rank_error_bound(d, qn, centroid_norm_max);
     // keys up to this one can belong to a cluster whose exact rank is within the bound's rank
@@ -226,7 +228,10 @@ select_probes_kernel(uint32_t* __restrict__ A, const StripSummary* __restrict__ 
             [&](uint32_t i) { return row[i]; }, [&](uint32_t i) { return (long long)i; });
     };
     int got;
-    if (S) {
+    if constexpr (EXACT) {
+        got = block_select_row(t, row, (uint32_t)n_lists, (uint32_t)n_probes, false, 0u, [](uint32_t i) { return i; },
+                               [](uint32_t pos, uint32_t) { return (long long)pos; });
+    } else if (S) {
         const uint32_t n_strips = ((uint32_t)n_lists + strip_w - 1) / strip_w, sw = (uint32_t)strip_w;
         const size_t stride = gridDim.x;
         const StripSummary* mine = S + q;
@@ -336,13 +341,85 @@ select_probes_kernel(uint32_t* __restrict__ A, const StripSummary* __restrict__ 
 // (search of 1 / 16 / 512 queries, selection and top-k: 40.4 / 68.6 / 173.7 -> 38.0 / 66.5 / 172.4 us; 1024 queries
 // 276 -> 287 us, hence the line at 512).
 constexpr int kFewQueries = 512;
+
+// Few queries: step 1a as the exact distances, for which the selection needs neither an error bound nor a short list.  The
+// same sum as exact8 above: a group of 8 adjacent lanes per cluster, each lane every 8th component, three exchange steps; a
+// group keeps the sums of QT queries, whose components wait in the LDS.
+constexpr int kDirectClusters = 32;                     // per workgroup of 256 threads
+template <int QT>
+__global__ void __launch_bounds__(8 * kDirectClusters)
+cluster_distance_kernel(const float* __restrict__ queries, const float* __restrict__ centroids, int nq, int n_lists, int d,
+                        uint32_t* __restrict__ A) {
+    constexpr int CH = 128;                             // components of the queries in the LDS at a time
+    __shared__ float qs[CH][QT];
+    const int tid = threadIdx.x, l = blockIdx.x * kDirectClusters + (tid >> 3), q0 = blockIdx.y * QT;
+    const float* c = centroids + (size_t)(l < n_lists ? l : n_lists - 1) * d;
+    float acc[QT];
+#pragma unroll
+    for (int j = 0; j < QT; ++j) acc[j] = 0.f;
+    for (int k0 = 0; k0 < d; k0 += CH) {
+        const int n = d - k0 < CH ? d - k0 : CH;
+        float x[CH / 8];
+#pragma unroll
+        for (int i = 0; i < CH / 8; ++i) {
+            const int u = (tid & 7) + 8 * i;
+            x[i] = u < n ? c[k0 + u] : 0.f;
+        }
+        if (k0 > 0) __syncthreads();
+        for (int i = tid; i < CH * QT; i += 8 * kDirectClusters) {
+            const int j = i / CH, u = i % CH, q = q0 + j < nq ? q0 + j : nq - 1;
+            qs[u][j] = u < n ? queries[(size_t)q * d + k0 + u] : 0.f;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < CH / 8; ++i) {
+            const int u = (tid & 7) + 8 * i;           // past the last component both sides are 0, which adds nothing
+            if (8 * i < n)
+#pragma unroll
+                for (int j = 0; j < QT; ++j) { const float diff = qs[u][j] - x[i]; acc[j] = __builtin_fmaf(diff, diff, acc[j]); }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < QT; ++j) {
+        const float dist = sum_over_8_lanes(acc[j]);
+        if ((tid & 7) == 0 && l < n_lists && q0 + j < nq) A[(size_t)(q0 + j) * n_lists + l] = __float_as_uint(dist);
+    }
+}
+// Where the distances take less than the ranking values and the short list they need.  Both kernels of the probe stage, 20 probes, us,
+// ranked / two queries a group / eight:
+//   128 components   1,024 clusters: 1 query 12.4 / 8.3 / 8.2, 64 14.7 / 10.2 / 11.2, 130 14.8 / 12.1 / 11.2, 512 22.3 / 19.9 / 16.1
+//                    3,000: 16 queries 14.6 / 10.1 / 11.3, 64 15.6 / 13.0 / 11.5, 130 14.8 / 16.7 / 14.2, 256 15.5 / - / 17.6
+//                    8,000: 1 query 12.5 / 10.7 / 10.9, 16 13.3 / 13.1 / 12.9, 64 13.3 / 20.7 / 16.9
+//   512 components   1,024: 1 query 25.7 / 11.9, 64 28.1 / 15.8 / 19.0, 512 39.1 / 45.2 / 30.4; 8,000: 16 queries 31.1 / 24.7 / 22.3
+// (Of many clusters the selection reads strip summaries, a thirtieth of the distances.)
+bool direct_distances(int nq, int n_lists) {
+    return nq <= kFewQueries && (n_lists <= 1024 || (n_lists <= 8192 && (size_t)nq * n_lists <= (size_t)3 << 16));
+}
+// Step 1a for nq queries: exact distances or ranking keys in A, or strip summaries in S (null on return: not made).
+int launch_step_1a(const ivfpq_index* idx, const float* q, int nq, int n_probes, uint32_t* A, StripSummary** S, bool* exact, void* split_ws, hipStream_t st) {
+    const int n_lists = idx->n_lists, d = idx->d;
+    *exact = direct_distances(nq, n_lists);
+    if (*exact || !coarse_use_strips(nq, n_lists, n_probes)) *S = nullptr;
+    if (!*exact) return launch_coarse(q, idx->dev.centroids, idx->dev.centroid_norms, nq, n_lists, d, A, *S, split_ws, st);
+    const float* centroids = idx->dev.centroids;
+    const unsigned blocks = (unsigned)((n_lists + kDirectClusters - 1) / kDirectClusters);
+    auto go = [&](auto kernel, int qt) {
+        hipLaunchKernelGGL(kernel, dim3(blocks, (unsigned)((nq + qt - 1) / qt)), dim3(8 * kDirectClusters), 0, st, q, centroids, nq, n_lists, d, A);
+    };
+    if ((size_t)nq * n_lists <= (size_t)1 << 16) go(cluster_distance_kernel<2>, 2);       // (the figures above)
+    else go(cluster_distance_kernel<8>, 8);
+    HIP_TRY(hipGetLastError());
+    return IVFPQ_OK;
+}
+
 template <class... Args>
-void launch_select_probes(int nq, hipStream_t st, uint32_t* A, const StripSummary* S, int strip_w, const float* queries,
+void launch_select_probes(int nq, bool exact, hipStream_t st, uint32_t* A, const StripSummary* S, int strip_w, const float* queries,
                           const float* centroids, float centroid_norm_max, int d, int n_lists, int n_probes, Args... rest) {
     auto go = [&](auto kernel, int threads) {
         hipLaunchKernelGGL(kernel, dim3(nq), dim3(threads), 0, st, A, S, strip_w, queries, centroids, centroid_norm_max, d, n_lists, n_probes, rest...);
     };
-    if (nq <= kFewQueries) go(select_probes_kernel<SEL_CAP, 1024>, 1024);
+    if (exact) go(select_probes_kernel<SEL_CAP, 1024, true>, 1024);
+    else if (nq <= kFewQueries) go(select_probes_kernel<SEL_CAP, 1024>, 1024);
     else if (S && n_probes <= SEL_CAP_SMALL) go(select_probes_kernel<SEL_CAP_SMALL, SEL_THREADS>, SEL_THREADS);
     else go(select_probes_kernel<SEL_CAP, SEL_THREADS>, SEL_THREADS);
 }
@@ -1805,12 +1882,13 @@ int search_impl(const ivfpq_index* idx, const float* d_queries, int64_t nq, cons
         StageTimer t0(idx, st, 0);
         if (int s = t0.begin()) return s;
         if (!d_probes_in) {
-            StripSummary* strips = coarse_use_strips(tq, idx->n_lists, n_probes) ? w_S : nullptr;
+            StripSummary* strips = w_S;
+            bool exact = false;
             StageTimer t4(idx, st, 4);
             if (int s = t4.begin()) return s;
-            if (int s = launch_coarse(qt, idx->dev.centroids, idx->dev.centroid_norms, tq, idx->n_lists, idx->d, (uint32_t*)w_D, strips, ws + plan.split, st)) return s;
+            if (int s = launch_step_1a(idx, qt, tq, n_probes, (uint32_t*)w_D, &strips, &exact, ws + plan.split, st)) return s;
             if (int s = t4.end()) return s;
-            launch_select_probes((int)tq, st, (uint32_t*)w_D, (const StripSummary*)strips,
+            launch_select_probes((int)tq, exact, st, (uint32_t*)w_D, (const StripSummary*)strips,
                                  coarse_strip_width(tq, idx->n_lists), qt,
                                  idx->dev.centroids, idx->centroid_norm_max, idx->d, idx->n_lists,
                                  n_probes, idx->dev.list_sizes, idx->dev.group_offsets, w_probes, w_probe_d, w_roff, w_pairs, k);
@@ -2202,11 +2280,12 @@ int ivfpq_select_probes(const ivfpq_index_t* idx, const float* d_queries, int64_
     StripSummary* w_S = (StripSummary*)((unsigned char*)d_workspace + plan.S);
     for (int64_t q0 = 0; q0 < nq; q0 += plan.tile) {
         const int tq = (int)std::min<int64_t>(plan.tile, nq - q0);
-        StripSummary* strips = coarse_use_strips(tq, idx->n_lists, n_probes) ? w_S : nullptr;
-        if (int s = launch_coarse(d_queries + (size_t)q0 * idx->d, idx->dev.centroids, idx->dev.centroid_norms, tq,
-                                  idx->n_lists, idx->d, (uint32_t*)w_D, strips, (unsigned char*)d_workspace + plan.split, st))
+        StripSummary* strips = w_S;
+        bool exact = false;
+        if (int s = launch_step_1a(idx, d_queries + (size_t)q0 * idx->d, tq, n_probes, (uint32_t*)w_D, &strips, &exact,
+                                   (unsigned char*)d_workspace + plan.split, st))
             return s;
-        launch_select_probes((int)tq, st, (uint32_t*)w_D, (const StripSummary*)strips,
+        launch_select_probes((int)tq, exact, st, (uint32_t*)w_D, (const StripSummary*)strips,
                              coarse_strip_width(tq, idx->n_lists), d_queries + (size_t)q0 * idx->d, idx->dev.centroids, idx->centroid_norm_max, idx->d,
                              idx->n_lists, n_probes, idx->dev.list_sizes, idx->dev.group_offsets, d_probes + (size_t)q0 * n_probes,
                              d_probe_dists ? d_probe_dists + (size_t)q0 * n_probes : nullptr, (uint32_t*)nullptr,

@@ -309,6 +309,30 @@ def test_select_probes_6000_lists_ties_and_outliers(P):
         assert_topk_matches(ids_g, d_g, ids_o, d_o, context=f"6000 lists dtype={dtype}")
 
 
+@pytest.mark.parametrize("n_lists,d,pq_dim", [(1, 20, 4), (33, 20, 4), (1024, 128, 64), (1025, 300, 4), (8192, 96, 48)])
+def test_select_probes_direct_and_ranked_agree(P, n_lists, d, pq_dim):
+    # few queries get every cluster's distance, more of them ranking values and a short list: the same lists and the same
+    # bits, at odd numbers of components (one and several pieces of the queries) and on both sides of the rule's lines
+    arrays = list(si.random_index_arrays(64, d, n_lists, pq_dim, 8, salt=330 + n_lists))
+    if n_lists > 40:
+        arrays[0][31:33] = arrays[0][5]
+    gidx = to_library(P, oracle.make_index(d, n_lists, pq_dim, 8, *arrays))
+    rng = np.random.default_rng(330)
+    q = rng.standard_normal((513, d)).astype(np.float32)
+    q[:3] = arrays[0][min(5, n_lists - 1)] + 0.01 * rng.standard_normal((3, d)).astype(np.float32)
+    q[3, 1] = np.inf
+    q[4, d - 1] = np.nan
+    for n_probes in sorted({1, min(n_lists, 20), min(n_lists, 1000)}):
+        _step(f"select_probes L={n_lists} d={d} P={n_probes}")
+        probes, pd = (x.cpu().numpy() for x in gidx.ivfpq_select_probes(q, n_probes))
+        exact = ((q[:64, None].astype(np.float64) - arrays[0][probes[:64]]) ** 2).sum(-1)
+        np.testing.assert_allclose(pd[:64], exact, rtol=RTOL)
+        for nq in (1, 2, 9, 24, 512):
+            few, few_d = (x.cpu().numpy() for x in gidx.ivfpq_select_probes(q[:nq], n_probes))
+            np.testing.assert_array_equal(few, probes[:nq])
+            np.testing.assert_array_equal(few_d.view(np.uint32), pd[:nq].view(np.uint32))
+
+
 def test_select_probes_strip_minima_large_batch(P):
     # enough queries x clusters that the ranking GEMM runs its 128 x 128 tiles and hands the selection
     # the minima of 64-cluster strips; n_probes on both sides of the rule that decides whether they are used
