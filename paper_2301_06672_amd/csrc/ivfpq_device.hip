@@ -1134,9 +1134,16 @@ __global__ void pair_count_kernel(const uint4* __restrict__ pairs, uint32_t n_pa
 }
 
 // The same two steps for few clusters, where many pairs name the same cluster and one global atomic per
-// pair would serialise: a workgroup of 1024 threads takes kPairChunk pairs, counts them per cluster in LDS
+// pair would serialise: a workgroup of 1024 threads takes `chunk` pairs, counts them per cluster in LDS
 // and issues one global atomic per cluster it met.  Dynamic LDS: n_lists words (count) or 2 n_lists (scatter).
-constexpr uint32_t kPairChunk = 8192;
+// Pairs a workgroup takes: a workgroup walks through its share 1,024 at a time, each step waiting for the one before, so the share is what
+// leaves one for every compute unit.  Both kernels, us, at 24 / 64 / 128 / 256 workgroups aimed at: 190,000 pairs of 1,024 clusters
+// 26 / 15 / 14 / 15, 237,000 of 5,000 29 / 24 / 20 / 18, 630,000 of 2,000 37 / 36 / 29 / 28, 261,000 of 8,000 31 / 21 / 17 / 14; 25,000 of 1,024
+// 24 at four workgroups, 10 at 25.
+inline uint32_t pair_chunk(size_t n_pairs) {
+    const size_t share = (n_pairs / 256 + 1023) / 1024 * 1024;
+    return (uint32_t)std::min<size_t>(std::max<size_t>(share, 1024), 8192);
+}
 constexpr int kPairLdsLists = 8192;       // up to this many clusters
 
 __device__ inline uint32_t pair_cluster(const uint4* __restrict__ pairs, uint32_t i, int n_probes, int n_lists) {
@@ -1159,12 +1166,12 @@ __device__ inline void store_pair(uint32_t at, uint32_t i, int n_probes, uint32_
 }
 
 __global__ void __launch_bounds__(1024)
-pair_count_lds_kernel(const uint4* __restrict__ pairs, uint32_t n_pairs, int n_probes, int n_lists,
+pair_count_lds_kernel(const uint4* __restrict__ pairs, uint32_t n_pairs, uint32_t chunk, int n_probes, int n_lists,
                       uint32_t* __restrict__ counts, PairCull cull) {
     extern __shared__ uint32_t s_cnt[];
     for (int l = threadIdx.x; l < n_lists; l += blockDim.x) s_cnt[l] = 0;
     __syncthreads();
-    const uint32_t i0 = blockIdx.x * kPairChunk, i1 = i0 + kPairChunk < n_pairs ? i0 + kPairChunk : n_pairs;
+    const uint32_t i0 = blockIdx.x * chunk, i1 = i0 + chunk < n_pairs ? i0 + chunk : n_pairs;
     for (uint32_t i = i0 + threadIdx.x; i < i1; i += blockDim.x) {
         const uint32_t l = pair_cluster(pairs, i, n_probes, n_lists);
         if (cull.keep(i, n_probes, l)) atomicAdd(&s_cnt[l], 1u);
@@ -1175,14 +1182,14 @@ pair_count_lds_kernel(const uint4* __restrict__ pairs, uint32_t n_pairs, int n_p
 }
 
 __global__ void __launch_bounds__(1024)
-pair_scatter_lds_kernel(const uint4* __restrict__ pairs, uint32_t n_pairs, int n_probes, int n_lists,
+pair_scatter_lds_kernel(const uint4* __restrict__ pairs, uint32_t n_pairs, uint32_t chunk, int n_probes, int n_lists,
                         const uint32_t* __restrict__ offsets, uint32_t* __restrict__ cursor, uint32_t* __restrict__ order, PairRecords rec, PairCull cull) {
     extern __shared__ uint32_t s_mem[];
     uint32_t* s_cnt = s_mem;                  // pairs of this chunk per cluster, then the running rank
     uint32_t* s_base = s_mem + n_lists;       // first slot of this chunk's pairs inside the cluster's range
     for (int l = threadIdx.x; l < n_lists; l += blockDim.x) s_cnt[l] = 0;
     __syncthreads();
-    const uint32_t i0 = blockIdx.x * kPairChunk, i1 = i0 + kPairChunk < n_pairs ? i0 + kPairChunk : n_pairs;
+    const uint32_t i0 = blockIdx.x * chunk, i1 = i0 + chunk < n_pairs ? i0 + chunk : n_pairs;
     for (uint32_t i = i0 + threadIdx.x; i < i1; i += blockDim.x)
         if (cull.kept(i, n_probes)) atomicAdd(&s_cnt[pair_cluster(pairs, i, n_probes, n_lists)], 1u);
     __syncthreads();
@@ -1983,12 +1990,13 @@ int search_impl(const ivfpq_index* idx, const float* d_queries, int64_t nq, cons
                         hipLaunchKernelGGL(pair_offsets_kernel, dim3(1), dim3(1024), 0, st, w_lc, idx->n_lists, w_lo);
                 };
                 if (idx->n_lists <= kPairLdsLists) {
-                    const unsigned cb = (unsigned)((n_pairs + kPairChunk - 1) / kPairChunk);
+                    const uint32_t chunk = pair_chunk(n_pairs);
+                    const unsigned cb = (unsigned)((n_pairs + chunk - 1) / chunk);
                     const size_t lds = (size_t)idx->n_lists * 4;
                     if (int s = allow_full_lds(pair_scatter_lds_kernel)) return s;
-                    hipLaunchKernelGGL(pair_count_lds_kernel, dim3(cb), dim3(1024), lds, st, w_pairs, (uint32_t)n_pairs, n_probes, idx->n_lists, w_lc, cull);
+                    hipLaunchKernelGGL(pair_count_lds_kernel, dim3(cb), dim3(1024), lds, st, w_pairs, (uint32_t)n_pairs, chunk, n_probes, idx->n_lists, w_lc, cull);
                     offsets();
-                    hipLaunchKernelGGL(pair_scatter_lds_kernel, dim3(cb), dim3(1024), 2 * lds, st, w_pairs, (uint32_t)n_pairs, n_probes,
+                    hipLaunchKernelGGL(pair_scatter_lds_kernel, dim3(cb), dim3(1024), 2 * lds, st, w_pairs, (uint32_t)n_pairs, chunk, n_probes,
                                        idx->n_lists, w_lo, w_cur, w_order, records, cull);
                 } else {
                     hipLaunchKernelGGL(pair_count_kernel, dim3(pb), dim3(256), 0, st, w_pairs, (uint32_t)n_pairs, n_probes, idx->n_lists, w_lc, cull);
