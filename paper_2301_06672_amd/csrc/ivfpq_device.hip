@@ -1573,11 +1573,12 @@ constexpr uint32_t kOrderBlock = 64;     // consecutive pairs of the grouped ord
 //   kWholeRows  every value of every probe is written and the top-k step reads them all: one scan launch in place of
 //               the nearest probe's, the bound's, the grouping's and the others'.  Up to 16,384 vectors a query and
 //               3.2 M in all.
-//   kInOrder    the filtered scan takes its pairs query by query: up to 7.2 M vectors the grouping costs more than
+//   kInOrder    the filtered scan takes its pairs query by query: up to 6 M vectors the grouping costs more than
 //               shared clusters and tables give back.
 //   kGrouped    pairs grouped by cluster, which pays in batches (scan stage of 10,000 queries at 10^8 vectors 10.4 ->
 //               6.8 ms, at 10^7 1.91 -> 1.51; and always beyond 2^20 pairs, of lists that are nearly empty).
-// Measured, us a search (M: vectors looked up by this reckoning; whole rows / in order / grouped):
+// Measured, us a search (M: vectors looked up by this reckoning; whole rows / in order / grouped with the table kernels, when the
+// grouping took 14 us more than it does; now the two are even at 6 M: 75 / 76, 75 / 75, 94 / 84, 72 / 68, 95 / 82, in order / grouped):
 //   64 sub-spaces of 8 bits, e5m3, lists of 1,000    5 probes: 2.5 M 106 / 108 / 113, 5 M 163 / 138 / 144
 //                                                    20 probes: 5 M 156 / 115 / 126, 10 M 265 / 164 / 170, 20 M - / 264 / 251
 //   48 of 8 bits, half                               5 probes: 2.5 M 71 / 80 / 87, 5 M 113 / 111 / 117; 20: 10 M 171 / 142 / 140
@@ -1599,7 +1600,7 @@ ScanRoute scan_route(const ivfpq_index* idx, int nq, int n_probes) {
     if (t.order_block != 0 || t.scan_share != 0 || pairs > ((size_t)1 << 20)) return ScanRoute::kGrouped;
     const double per_query = (double)n_probes * (double)idx->n / (double)idx->n_lists, all = per_query * nq;
     if (per_query <= 16384.0 && all <= 3.2e6) return ScanRoute::kWholeRows;
-    return all <= 7.2e6 ? ScanRoute::kInOrder : ScanRoute::kGrouped;
+    return all <= 6e6 ? ScanRoute::kInOrder : ScanRoute::kGrouped;
 }
 
 bool group_pairs_by_cluster(size_t n_pairs) { return n_pairs < ((size_t)1 << 32) - 8 * (size_t)kOrderBlock; }
@@ -1796,11 +1797,17 @@ bool filter_applies(const ivfpq_index* idx, int lut_dtype, const Fp8Mode& fp8) {
     return t.early_exit >= 0 && t.scan_share == 0 && t.order_block == 0 && t.scan_threads == 0 && t.lds_pad == 0 && !fp8.per_table &&
            idx->word_norm_max >= 0.f && filter_supported(idx->pq_bits, idx->pq_dim, idx->d, chunk_width(idx));
 }
-// By the number of vectors that are looked up, as scan_route: its four more launches and the codebooks that two kernels load cost what the
-// tables do up to 10 M (us, table kernels / filter, unit-norm rows in 555 lists, 56 queries, 62 probes: 8.6 M 120 / 122; 440 lists, 4
-// probes: 7.3 M 129 / 143; 832 lists, 12 probes: 10.6 M 152 / 140; 32 lists, 20 probes: 11.7 M 121 / 94).
-bool filter_pays(const ivfpq_index* idx, int nq, int n_probes) {
-    return idx->tuning.scan_route != 0 || (double)nq * n_probes * ((double)idx->n / (double)idx->n_lists) >= 1e7;
+// By the number of vectors that are looked up, as scan_route, and by k against the length of a list: the bound is the k-th of one list,
+// so k / length is the share of a similar list that passes and is added up.  The filter has a cost of its own (codebooks that two
+// kernels load, every listed vector); us a search, the better table route / filter:
+//   k / length 0.01  6 M 75 / 64, 75 / 77, 84 / 81, 68 / 71, 93 / 72, 82 / 78; 9 M 91 / 64, 91 / 81, 102 / 92, 82 / 83, 121 / 91, 125 / 85
+//              0.05  6 M 80 / 76, 90 / 88, 83 / 92; 9 M 97 / 75, 108 / 96, 97 / 107; 12 M 118 / 89, 132 / 107, 108 / 110
+//              0.1   6 M 92 / 97, 96 / 125, 97 / 95, 145 / 122; 12 M 134 / 116, 142 / 160, 140 / 113, 237 / 164; 30 M 270 / 144, 244 / 206
+// (200,000 unit-norm rows in 200 lists, 60 and 20 probes; 10^6 in 1,024, 20; 200,000 of 128 components in 100, 30, where 0.05; 100,000 in
+// 100, 30, where 0.01 and 0.1; 10^6 in 555, 4-bit codes, 30).
+bool filter_pays(const ivfpq_index* idx, int nq, int n_probes, int k) {
+    const double length = (double)idx->n / (double)idx->n_lists;
+    return idx->tuning.scan_route != 0 || (double)nq * n_probes * length >= 5e6 + 1e8 * (double)k / length;
 }
 // What |r - y|^2 of a vector with R <= bound is limited by: bound * scale + add, where no entry saturates (the kernel sees to
 // those that may).  A stored entry is below its distance by at most the share `loss` (half: 2^-11, and 2^-25 where the half is
@@ -1951,7 +1958,7 @@ int search_impl(const ivfpq_index* idx, const float* d_queries, int64_t nq, cons
         // The filter's lists take the place of the ranking values, which nothing reads any more (a search with given probes has none).
         FilterLists lists = filter_lists(idx, (size_t)tq, n_probes, filter_item_vectors(idx, n_pairs));
         while (lists.bytes > plan.R - plan.D && lists.per_item < (uint32_t)kFilterVectors) lists = filter_lists(idx, (size_t)tq, n_probes, lists.per_item * 2);
-        const bool filter = grouped && filter_applies(idx, lut_dtype, a.fp8) && filter_pays(idx, tq, n_probes) && ((uintptr_t)qt & 7) == 0 &&
+        const bool filter = grouped && filter_applies(idx, lut_dtype, a.fp8) && filter_pays(idx, tq, n_probes, k) && ((uintptr_t)qt & 7) == 0 &&
                             lists.max_items < ((size_t)1 << 31) && lists.bytes <= plan.R - plan.D;
         uint32_t* w_starts = filter ? (uint32_t*)(ws + plan.D) : nullptr;
         uint32_t* w_lc = (uint32_t*)(ws + plan.list_counts);         // counts and cursors are neighbours in the plan

@@ -874,6 +874,21 @@ def test_matrix_core_filter_leaves_other_calls_to_the_tables(P):
     assert not odd.ivfpq_scan_kernel_info(oracle.LUT_FP32).startswith("scan_filter_kernel")
 
 
+@pytest.mark.parametrize("nq", [1, 31, 33, 500, 2047, 2049])
+def test_candidates_of_few_queries_are_shared_by_workgroups(P, nq):
+    # long candidate lists (k a third of a list) of few queries are summed by several workgroups each, of many by one: every
+    # listed vector is summed once, the same bits as a scan of every vector in query order
+    oidx, gidx = random_pair(P, 20000, 64, 20, 32, 8, salt=870, empty_lists=(1,))
+    q = np.random.default_rng(870).standard_normal((nq, 64)).astype(np.float32)
+    got = []
+    for route in (2, 3):
+        gidx.ivfpq_set_tuning(P.TUNE_SCAN_ROUTE, route)
+        _step(f"candidates nq={nq} route={route}")
+        got.append([t.cpu().numpy() for t in gidx.ivfpq_search(q, 15, 300, oracle.LUT_E5M3)])
+    np.testing.assert_array_equal(got[0][0], got[1][0])
+    np.testing.assert_array_equal(got[0][1].view(np.uint32), got[1][1].view(np.uint32))
+
+
 @pytest.mark.parametrize("d,pq_dim,pq_bits,n_lists,n_probes,k", [
     (64, 64, 5, 7, 5, 10),            # m = 1, 40-byte codes, few clusters: most neighbouring pairs share theirs
     (128, 64, 6, 20, 12, 100),        # m = 2, 48-byte codes in 16-byte chunks
