@@ -1805,9 +1805,17 @@ bool filter_applies(const ivfpq_index* idx, int lut_dtype, const Fp8Mode& fp8) {
 //              0.1   6 M 92 / 97, 96 / 125, 97 / 95, 145 / 122; 12 M 134 / 116, 142 / 160, 140 / 113, 237 / 164; 30 M 270 / 144, 244 / 206
 // (200,000 unit-norm rows in 200 lists, 60 and 20 probes; 10^6 in 1,024, 20; 200,000 of 128 components in 100, 30, where 0.05; 100,000 in
 // 100, 30, where 0.01 and 0.1; 10^6 in 555, 4-bit codes, 30).
-bool filter_pays(const ivfpq_index* idx, int nq, int n_probes, int k) {
-    const double length = (double)idx->n / (double)idx->n_lists;
-    return idx->tuning.scan_route != 0 || (double)nq * n_probes * length >= 5e6 + 1e8 * (double)k / length;
+// Probes that are a small share of the lists lie all about the query, and their vectors compete with those of the nearest list: with one-byte
+// tables, whose rounding (a seventeenth) widens the filter's limit, or 4-bit codes, whose tables are cheap, the tables are faster then
+// where k / length is not small.  10,000 queries, 10^8 vectors in 50,000 lists, 64 probes, 0.05, ms, tables / filter: e5m3 5.2 / 6.6, half 6.2 / 4.8,
+// float 7.9 / 4.7; 4-bit codes e5m3 5.9 / 7.0, half 4.8 / 5.0; 10^7 in 10,000, 20 probes, 0.01: e5m3 1.5 / 0.65; 50 probes, 0.1: 2.8 / 1.0; us,
+// 5,000 queries, 2 10^6 in 2,800 lists, 0.14, e5m3, 8 probes 276 / 322 and 262 / 244 (either family), 16 probes 317 / 346 and 358 / 261.
+bool filter_pays(const ivfpq_index* idx, int lut_dtype, int nq, int n_probes, int k) {
+    if (idx->tuning.scan_route != 0) return true;
+    const double length = (double)idx->n / (double)idx->n_lists, share = (double)k / length;
+    const bool loose = lut_elem_bytes(lut_dtype) == 1 || idx->pq_bits == 4;
+    if (loose && share >= 0.04 && (int64_t)n_probes * 300 < idx->n_lists) return false;
+    return (double)nq * (n_probes - 1) * length >= 5e6 + 1e8 * share;
 }
 // What |r - y|^2 of a vector with R <= bound is limited by: bound * scale + add, where no entry saturates (the kernel sees to
 // those that may).  A stored entry is below its distance by at most the share `loss` (half: 2^-11, and 2^-25 where the half is
@@ -1958,7 +1966,7 @@ int search_impl(const ivfpq_index* idx, const float* d_queries, int64_t nq, cons
         // The filter's lists take the place of the ranking values, which nothing reads any more (a search with given probes has none).
         FilterLists lists = filter_lists(idx, (size_t)tq, n_probes, filter_item_vectors(idx, n_pairs));
         while (lists.bytes > plan.R - plan.D && lists.per_item < (uint32_t)kFilterVectors) lists = filter_lists(idx, (size_t)tq, n_probes, lists.per_item * 2);
-        const bool filter = grouped && filter_applies(idx, lut_dtype, a.fp8) && filter_pays(idx, tq, n_probes, k) && ((uintptr_t)qt & 7) == 0 &&
+        const bool filter = grouped && filter_applies(idx, lut_dtype, a.fp8) && filter_pays(idx, lut_dtype, tq, n_probes, k) && ((uintptr_t)qt & 7) == 0 &&
                             lists.max_items < ((size_t)1 << 31) && lists.bytes <= plan.R - plan.D;
         uint32_t* w_starts = filter ? (uint32_t*)(ws + plan.D) : nullptr;
         uint32_t* w_lc = (uint32_t*)(ws + plan.list_counts);         // counts and cursors are neighbours in the plan

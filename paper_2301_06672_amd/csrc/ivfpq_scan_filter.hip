@@ -388,7 +388,7 @@ scan_filter_kernel(FilterArgs a) {
     // LDS: codebooks in bf16 [sub-space][code][M] | per wave kWaveWords | ticket
     static_assert(S::book_bytes % 16 == 0, "the words behind the codebooks are aligned");
     uint32_t* const all_bits = reinterpret_cast<uint32_t*>(smem + S::book_bytes);
-        uint32_t* const ticket = all_bits + kFilterWaves * kWaveWords;
+    uint32_t* const ticket = all_bits + kFilterWaves * kWaveWords;
     if (threadIdx.x == 0) *ticket = 0;
     for (int i = threadIdx.x; i < S::D * S::KSUB / 4; i += kFilterThreads) {
         const float4 x = reinterpret_cast<const float4*>(a.codebooks)[i];
