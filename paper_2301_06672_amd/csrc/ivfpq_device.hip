@@ -841,7 +841,9 @@ scan_kernel(ScanArgs a) {
         row_pos0 = pair.w;
     }
     const bool bounded = a.single_list < 0 && a.mode == 1 && a.k_bound > 0;
-    if (len == 0 && !bounded) return;     // empty cluster (or a caller-given probe that was out of range)
+    // An empty cluster, or a caller-given probe that was out of range, whose l names no centroid: no residual and no table, only
+    // the bound (len is the same for the whole workgroup)
+    if (len == 0 && !bounded) return;
     uint32_t least = 0xFFFFFFFFu, largest = 0;                     // mode 1: of the finite values this lane has written
     const bool filtered = a.single_list < 0 && a.mode == 2;
     const bool prune = filtered && a.early_exit != 0;
@@ -945,8 +947,9 @@ scan_kernel(ScanArgs a) {
     }
 
     // step 2: residual of the query against this cluster's centroid
-    for (int t = threadIdx.x; t < a.d; t += blockDim.x)
-        rq[t] = a.queries[(size_t)q * a.d + t] - a.centroids[(size_t)l * a.d + t];
+    if (len != 0)
+        for (int t = threadIdx.x; t < a.d; t += blockDim.x)
+            rq[t] = a.queries[(size_t)q * a.d + t] - a.centroids[(size_t)l * a.d + t];
     __syncthreads();
     // Filtered scan with early exit, tables of two or more chunks' worth of rows: most groups are over the
     // bound after the first half of the sub-spaces, so the second half of the table is built only if some
@@ -1014,7 +1017,7 @@ scan_kernel(ScanArgs a) {
         }
     }
     // step 3: the table
-    fp8 = stage_table<LUT, BITS>(a.codebooks, rq, a.pq_dim, a.m, lut, max_slot, a.fp8, 0, a.pq_dim);
+    if (len != 0) fp8 = stage_table<LUT, BITS>(a.codebooks, rq, a.pq_dim, a.m, lut, max_slot, a.fp8, 0, a.pq_dim);
 
     // step 4: Eq. (1), one lane per coded vector; the next group is loaded into the other register
     // buffer while the current one is looked up

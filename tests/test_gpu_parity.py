@@ -802,6 +802,44 @@ def test_scan_routes_agree(P, n, d, pq_dim, pq_bits, n_lists, n_probes, nq, k, d
     assert_topk_matches(out["own"][0][:40], out["own"][1][:40], ids_o, d_o, context="own route")
 
 
+@pytest.mark.parametrize("pq_bits,pq_dim", [(8, 32), (5, 32), (4, 16)])     # chunks of 16 and of 4 bytes
+@pytest.mark.parametrize("n_probes", [1, 2, 6])
+def test_first_probe_without_vectors(P, pq_bits, pq_dim, n_probes):
+    # a query whose first probe is out of range, or an empty cluster, has no bound and no nearest segment: the other probes'
+    # vectors are all it returns, and no centroid is looked up for a number that names none
+    oidx, gidx = random_pair(P, 3000, 64, 9, pq_dim, pq_bits, salt=31, empty_lists=(2, 4))
+    nq, k = 130, 20
+    q = np.random.default_rng(31).standard_normal((nq, 64)).astype(np.float32)
+    probes = np.stack([np.random.default_rng(i).permutation(9)[:n_probes] for i in range(nq)]).astype(np.uint32)
+    skipped = np.zeros(nq, bool)
+    for i, bad in ((0, 0xFFFFFFFF), (1, 9), (2, 1 << 30), (64, 0x80000000)):
+        probes[i, 0], skipped[i] = bad, True
+    probes[3, 0], probes[4, 0] = 2, 4
+    probes[5] = 0xFFFFFFFE                    # none in range
+    skipped[5] = True
+    want = {}
+    for dtype in DTYPES:
+        for route in (0, 1, 2, 3):
+            gidx.ivfpq_set_tuning(P.TUNE_SCAN_ROUTE, route)
+            _step(f"first probe without vectors: p={pq_bits} P={n_probes} dtype={dtype} route={route}")
+            got = [t.cpu().numpy() for t in gidx.ivfpq_search_with_probes(q, probes, k, dtype)]
+            if dtype not in want:
+                want[dtype] = got
+            for a, b in zip(got, want[dtype]):
+                np.testing.assert_array_equal(a, b)
+        ids, dist = want[dtype]
+        ok = ~skipped
+        ids_o, d_o = oracle.search(oidx, q[ok], n_probes, k, dtype, probes=probes[ok])
+        assert_topk_matches(ids[ok], dist[ok], ids_o, d_o, context="probes in range")
+        for i in np.flatnonzero(skipped):     # the same query without that probe
+            rest = probes[i:i + 1, 1:] if probes[i, -1] < 9 else probes[i:i + 1, :0]
+            if rest.shape[1] == 0:
+                assert np.all(ids[i] == -1) and np.all(np.isinf(dist[i]))
+                continue
+            ids_o, d_o = oracle.search(oidx, q[i:i + 1], n_probes - 1, k, dtype, probes=rest)
+            assert_topk_matches(ids[i:i + 1], dist[i:i + 1], ids_o, d_o, context=f"query {i}")
+
+
 @pytest.mark.parametrize("d,pq_dim,pq_bits", [
     (128, 64, 8), (128, 32, 8), (96, 48, 8), (64, 32, 8), (64, 16, 8),     # two and four components a sub-space
     (96, 24, 8),                                                           # 24-byte codes: 4-byte chunks
