@@ -160,8 +160,8 @@ int ivfpq_upload(ivfpq_index_t* index, void* d_buf, size_t bytes, void* hip_stre
 
 /* Bytes of device scratch one search call needs for these parameters (probe lists, per-pair
  * descriptors, cluster ranking values, the R rows and the positions of filtered candidates).
- * Large batches are processed in query tiles so that the figure stays near the index's workspace
- * limit (one query's share can exceed it: a tile holds at least one query). */
+ * Large batches are processed in query tiles so that the figure stays within the index's workspace
+ * limit (one query's share can exceed it: a tile holds at least one query).  A smaller batch never needs more. */
 size_t ivfpq_search_workspace_bytes(const ivfpq_index_t* index, int64_t nq, int32_t n_probes,
                                     int32_t k, int32_t lut_dtype);
 

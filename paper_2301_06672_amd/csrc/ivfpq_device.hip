@@ -1467,33 +1467,13 @@ FilterLists filter_lists(const ivfpq_index* idx, size_t nq, int n_probes, uint32
     return f;
 }
 
-// given_probes: the caller chooses the clusters and may name one several times, so the bound on a
-// query's candidates is n_probes times the largest cluster rather than the n_probes largest ones
-// limit: the bytes the plan should stay within (0: the index's workspace limit); a tile holds at least one
-// query, so the caller compares plan->total with what it has.
-int make_plan(const ivfpq_index* idx, int64_t nq, int32_t n_probes, bool given_probes, Plan* plan, size_t limit = 0, bool with_filter = true) {
-    if (limit == 0) limit = idx->workspace_limit;
-    const bool need_D = !given_probes;
-    with_filter = with_filter && need_D && n_probes > 1;
-    int64_t stride = given_probes
-        ? (int64_t)n_probes * (idx->sorted_padded_sizes.empty() ? 0 : idx->sorted_padded_sizes[0])
-        : idx->max_padded_candidates(n_probes);
-    // the survivor list of a query also takes the nearest cluster's values under the bound
-    stride += idx->sorted_padded_sizes.empty() ? 0 : idx->sorted_padded_sizes[0];
-    if (stride >= ((int64_t)1 << 31))
-        return fail(IVFPQ_EUNSUPPORTED, "a query may see %lld candidates (limit 2^31)", (long long)stride);
-    if (stride < 64) stride = 64;
+// Vectors looked up beyond the nearest probes' from which the matrix-core filter pays at the earliest (filter_pays).
+constexpr double kFilterLookups = 5e6;
+
+// Places of a tile's arrays.  need_D: clusters are ranked (the caller gives none); with_filter: the filter's lists have room.
+void lay_out(const ivfpq_index* idx, int64_t tile, int32_t n_probes, bool need_D, bool with_filter, Plan* plan) {
     const size_t strips = ((size_t)idx->n_lists + 31) / 32;      // strip summaries of the ranking keys, narrowest strips
-    size_t per_query = (size_t)stride * 8 + (need_D ? ((size_t)idx->n_lists + 4 * strips + coarse_padded_dim(idx->d)) * 4 : 0);
-    // what does not grow with the tile: three per-cluster counter arrays, the centroids' bf16 halves, alignment slack
-    const size_t fixed = 3 * align_up((size_t)idx->n_lists * 4)
-                         + (need_D ? coarse_split_bytes(128, (size_t)idx->n_lists, idx->d) : 0) + 24 * kAlign;      // 128: the query rows' padding
-    if (with_filter) per_query += (size_t)n_probes * 16;
-    per_query += (size_t)n_probes * 28 + 16;      // probe lists, distances, offsets, descriptors, order, bound, counter
-    int64_t tile = limit > fixed ? (int64_t)((limit - fixed) / per_query) : 1;
-    tile = std::max<int64_t>(1, std::min<int64_t>(tile, std::max<int64_t>(nq, 1)));
     plan->tile = tile;
-    plan->stride = (size_t)stride;
     size_t at = 0;
     auto take = [&](size_t bytes) { size_t o = at; at = align_up(at + bytes); return o; };
     plan->probes = take((size_t)tile * n_probes * 4);
@@ -1510,15 +1490,60 @@ int make_plan(const ivfpq_index* idx, int64_t nq, int32_t n_probes, bool given_p
         const size_t want = filter_lists(idx, (size_t)tile, n_probes, kFilterVectors).bytes;
         if (want > at - plan->D) take(want - (at - plan->D));
     }
-    plan->R = take((size_t)tile * stride * 4);
-    plan->Rpos = take((size_t)tile * stride * 4);
+    plan->R = take((size_t)tile * plan->stride * 4);
+    plan->Rpos = take((size_t)tile * plan->stride * 4);
     plan->order = take((size_t)tile * (n_probes > 1 ? n_probes - 1 : 0) * 4);
     plan->list_counts = take((size_t)idx->n_lists * 4);
     plan->list_cursor = take((size_t)idx->n_lists * 4);
     plan->list_offsets = take((size_t)idx->n_lists * 4);
     plan->total = at;
-    // one query that fits the limit only without them does without
-    if (with_filter && tile == 1 && plan->total > limit) return make_plan(idx, nq, n_probes, given_probes, plan, limit, false);
+}
+
+// given_probes: the caller chooses the clusters and may name one several times, so the bound on a
+// query's candidates is n_probes times the largest cluster rather than the n_probes largest ones
+// limit: the bytes the plan should stay within (0: the index's workspace limit).  The tile is the largest whose plan
+// does; where one query's exceeds the limit it is one query, and the caller compares plan->total with what it has.
+// A smaller batch never needs more than a larger one: what the tile holds at most, and whether the filter's lists have
+// room, follow from the index, the probes and the limit alone.
+int make_plan(const ivfpq_index* idx, int64_t nq, int32_t n_probes, bool given_probes, Plan* plan, size_t limit = 0) {
+    if (limit == 0) limit = idx->workspace_limit;
+    const bool need_D = !given_probes;
+    int64_t stride = given_probes
+        ? (int64_t)n_probes * (idx->sorted_padded_sizes.empty() ? 0 : idx->sorted_padded_sizes[0])
+        : idx->max_padded_candidates(n_probes);
+    // the survivor list of a query also takes the nearest cluster's values under the bound
+    stride += idx->sorted_padded_sizes.empty() ? 0 : idx->sorted_padded_sizes[0];
+    if (stride >= ((int64_t)1 << 31))
+        return fail(IVFPQ_EUNSUPPORTED, "a query may see %lld candidates (limit 2^31)", (long long)stride);
+    plan->stride = (size_t)std::max<int64_t>(stride, 64);
+    // An estimate of the tile: what a query takes, and what does not grow with the tile (three per-cluster counter arrays, the
+    // centroids' bf16 halves, alignment slack).  128: the query rows' padding.
+    const size_t strips = ((size_t)idx->n_lists + 31) / 32;
+    const size_t per_query = plan->stride * 8 + (need_D ? ((size_t)idx->n_lists + 4 * strips + coarse_padded_dim(idx->d)) * 4 : 0) +
+                             (size_t)n_probes * 28 + 16;      // probe lists, distances, offsets, descriptors, order, bound, counter
+    const size_t fixed = 3 * align_up((size_t)idx->n_lists * 4)
+                         + (need_D ? coarse_split_bytes(128, (size_t)idx->n_lists, idx->d) : 0) + 24 * kAlign;
+    const int64_t most = std::max<int64_t>(1, limit > fixed ? (int64_t)((limit - fixed) / per_query) : 1);
+    // The filter's lists: where it is built for the index and a tile can hold enough work for it.
+    bool with_filter = need_D && n_probes > 1 && filter_supported(idx->pq_bits, idx->pq_dim, idx->d, chunk_width(idx)) &&
+                       (double)most * (n_probes - 1) * (double)idx->n / (double)idx->n_lists >= kFilterLookups;
+    auto fits = [&](int64_t tile) {
+        lay_out(idx, tile, n_probes, need_D, with_filter, plan);
+        return plan->total <= limit;
+    };
+    int64_t tile = std::min(most, std::max<int64_t>(nq, 1));
+    if (fits(tile)) return IVFPQ_OK;
+    if (with_filter && !fits(1)) {          // one query that fits the limit only without them does without
+        with_filter = false;
+        if (fits(tile)) return IVFPQ_OK;
+    }
+    // the estimate leaves out what the filter's work items and paddings take: a few per cent
+    int64_t lo = 1, hi = tile;              // the largest tile that fits is in [lo, hi), or is one query
+    while (hi - lo > 1) {
+        const int64_t mid = lo + (hi - lo) / 2;
+        if (fits(mid)) lo = mid; else hi = mid;
+    }
+    (void)fits(lo);
     return IVFPQ_OK;
 }
 
@@ -1818,7 +1843,7 @@ bool filter_pays(const ivfpq_index* idx, int lut_dtype, int nq, int n_probes, in
     const double length = (double)idx->n / (double)idx->n_lists, share = (double)k / length;
     const bool loose = lut_elem_bytes(lut_dtype) == 1 || idx->pq_bits == 4;
     if (loose && share >= 0.04 && (int64_t)n_probes * 300 < idx->n_lists) return false;
-    return (double)nq * (n_probes - 1) * length >= 5e6 + 1e8 * share;
+    return (double)nq * (n_probes - 1) * length >= kFilterLookups + 1e8 * share;
 }
 // What |r - y|^2 of a vector with R <= bound is limited by: bound * scale + add, where no entry saturates (the kernel sees to
 // those that may).  A stored entry is below its distance by at most the share `loss` (half: 2^-11, and 2^-25 where the half is

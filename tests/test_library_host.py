@@ -177,6 +177,36 @@ def test_static_scratch_search_refuses_what_does_not_fit(P):
     assert "((size_t)64 << 20)" in header and P.STATIC_SCRATCH_BYTES == 64 << 20
 
 
+@pytest.mark.parametrize("L,length,d,pq_dim,pq_bits", [
+    (500, 20_000, 64, 16, 4),      # work items of the matrix-core filter: six per cent of the fixed array
+    (1000, 1000, 128, 32, 4),      # a shape it is not built for
+])
+def test_tiles_shrink_until_their_plan_fits(P, L, length, d, pq_dim, pq_bits):
+    # Wherever one query's scratch fits the limit, a batch of any size is served in tiles that fit it, and a smaller batch never
+    # needs more.  The static search sizes its tiles before anything touches a device: an index without an image answers "not
+    # uploaded" (ESTATE) where they fit, and "no space" where they do not.
+    import ctypes
+    n = L * length
+    idx = P.Index.ivfpq_index_from_arrays(d, L, pq_dim, pq_bits, np.zeros((L, d), np.float32),
+                                          np.zeros((pq_dim, 1 << pq_bits, d // pq_dim), np.float32),
+                                          np.arange(L + 1, dtype=np.int64) * length,
+                                          np.zeros((n, pq_dim * pq_bits // 8), np.uint8), np.zeros(n, np.int64))
+    dummy = ctypes.c_void_p(256)
+    for n_probes in range(1, 129):
+        st = P.lib().ivfpq_search_static(idx._h, dummy, 10_000, n_probes, 10, P.LUT_FP8_E5M3, dummy, dummy, None)
+        assert st == P.ESTATE, (n_probes, st)
+    served = 0
+    for limit in (1 << 20, 5_000_000, 16 << 20, 64 << 20, 1 << 30):
+        idx.ivfpq_set_workspace_limit(limit)
+        for n_probes in list(range(1, 66)) + [128]:
+            need = [idx.ivfpq_search_workspace_bytes(nq, n_probes, 10, 0) for nq in (1, 2, 3, 10, 50, 117, 500, 10_000)]
+            assert need == sorted(need), (limit, n_probes, need)
+            assert need[0] > limit or need[-1] <= limit, (limit, n_probes, need)
+            served += need[0] <= limit
+    assert served > 200
+    idx.ivfpq_free()
+
+
 def test_device_builder_plan_is_checked_on_the_host(P):
     # the launch geometry and workspace layout of ivfpq_build_device are validated before the first launch;
     # the size query runs the same check, so it can be exercised without a GPU
