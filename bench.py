@@ -303,11 +303,12 @@ def main():
             torch.cuda.synchronize()
             for name, v in idx.ivfpq_stage_times_ms().items():
                 seen.setdefault(name, []).append(v)
+        kernel = idx.ivfpq_scan_kernel_info(lut)          # while stage timing is on: what the search just launched
         idx.ivfpq_set_stage_timing(False)
         stage = {name: statistics.median(v) for name, v in seen.items()}
         rec = tie_aware_recall(out[0][:nr], data, q[:nr], gt_d, k) if want_recall else None
         return {"qps": nq / (med * 1e-3), "ms_per_step": med, "ms_per_step_mean": 1e3 * dt / steps,
-                "ms_per_step_min": min(per_step), "ms_per_step_max": max(per_step), "recall": rec, "stage_ms": stage}
+                "ms_per_step_min": min(per_step), "ms_per_step_max": max(per_step), "recall": rec, "stage_ms": stage, "kernel": kernel}
 
     def fmt(r):
         rec = "n/a" if r["recall"] is None else f"{r['recall']:.4f}"
@@ -331,11 +332,9 @@ def main():
     if args.no_full_run or args.early_exit == 0:
         full = results[args.lut]
         full_is_exact = args.early_exit == 0
-        full_kernel = idx.ivfpq_scan_kernel_info(lut_ids[args.lut])
     else:
         idx.ivfpq_set_tuning(pkg.TUNE_EARLY_EXIT, -1)
         full = run(args.lut, other_steps, 1)
-        full_kernel = idx.ivfpq_scan_kernel_info(lut_ids[args.lut])
         idx.ivfpq_set_tuning(pkg.TUNE_EARLY_EXIT, 0 if args.early_exit is None else 1)
         full_is_exact = True
         log(f"lut={args.lut} without early exit: {fmt(full)}")
@@ -425,7 +424,7 @@ def main():
         one_launch = nearest_ms > 0 and abs(kern_ms_full / (nearest_ms * (n_probes - 1)) - 1.0) < 1e-4
         roofline = {
             "bound": "lds",
-            "kernel": "scan_kernel, one launch for all probes (kernel_ms_per_step: the share of the pairs counted)" if one_launch else full_kernel,
+            "kernel": "scan_kernel, one launch for all probes (kernel_ms_per_step: the share of the pairs counted)" if one_launch else full["kernel"],
             "achieved": round(rate, 1), "peak": LDS_PEAK_LOOKUPS, "unit": "table lookups/s",
             "frac": round(rate / LDS_PEAK_LOOKUPS, 4),
             "lookups_per_step": lookups, "kernel_ms_per_step": round(kern_ms_full, 4),
@@ -444,7 +443,7 @@ def main():
             "hbm_algorithmic": {"bytes_per_step": kern_bytes, "achieved": round(kern_bytes / (kern_ms_full * 1e-3) / 1e9, 1),
                                 "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(kern_bytes / (kern_ms_full * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
                                 "streaming_read_ceiling": round(ceiling, 1)},
-            "default_run": {"kernel": idx.ivfpq_scan_kernel_info(lut_ids[args.lut]), "kernel_ms_per_step": round(kern_ms, 4),
+            "default_run": {"kernel": head["kernel"], "kernel_ms_per_step": round(kern_ms, 4),
                             "note": "library default: large batches list the vectors that can have R <= bound with a matrix product and add up "
                                     "those alone (or, where that does not apply or pay (k a large share of a list, few of the lists probed), a 64-vector group stops adding once all its partial sums are "
                                     "over the query's bound): same results, fewer lookups made"},

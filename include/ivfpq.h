@@ -276,12 +276,13 @@ int ivfpq_set_stage_timing(ivfpq_index_t* index, int32_t enabled);
 int ivfpq_stage_times_ms(ivfpq_index_t* index, float ms[8]);
 
 /* Writes into buf (host, buf_bytes > 0, always terminated) the name, workgroup size and LDS request of the
- * kernel that scans the probes other than the nearest one (the dominant kernel of a search) for this index,
- * table dtype and current tuning: what to look for in a profiler's kernel list.  It describes large batches, whose
- * pairs run grouped by cluster, unless IVFPQ_TUNE_SCAN_ROUTE names another route: the searches of little work that the
- * library sends there run scan_kernel, and with more threads than the index asks for where its workgroups are few.
- * Where a matrix product lists the vectors to add up (an uploaded index, its usual shapes, no knob that asks for the
- * table kernels) it names that kernel and the one that adds them up. */
+ * kernel that scans the probes other than the nearest one (the dominant kernel of a search): what to look for in a
+ * profiler's kernel list.  While stage timing is enabled and the last search used this table dtype, it is what that
+ * search launched (its first query tile).  Otherwise it describes large batches on this index with the current tuning,
+ * whose pairs run grouped by cluster, unless IVFPQ_TUNE_SCAN_ROUTE names another route.  Where a matrix product can list
+ * the vectors to add up (an uploaded index, its usual shapes, no knob that asks for the table kernels) that names its
+ * kernel and the one that adds them up; a search for which the tables cost less (few vectors looked up, k a large share
+ * of a list, few of the lists probed) takes the table kernels all the same, and one of little work scan_kernel. */
 int ivfpq_scan_kernel_info(const ivfpq_index_t* index, int32_t lut_dtype, char* buf, size_t buf_bytes);
 
 /* Measurement aid, not a step of the method: a plain streaming read of `bytes` bytes of device memory

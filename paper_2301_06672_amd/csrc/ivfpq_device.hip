@@ -1760,13 +1760,17 @@ int launch_scan_group(const ivfpq_index* idx, const ScanArgs& a, int lut_dtype, 
     }
 }
 
-int launch_scan(const ivfpq_index* idx, ScanArgs a, int lut_dtype, dim3 grid, hipStream_t st) {
+// A grid that leaves wave slots of the chip empty takes larger workgroups: tables are built and lists walked by more
+// waves at once (filtered scan of one query, 19 pairs: 21.6 -> 9 us with 1024 threads instead of 256).
+int scan_threads_of_grid(const ivfpq_index* idx, int lut_dtype, size_t blocks) {
     int threads = scan_threads(idx, lut_dtype);
-    // A grid that leaves wave slots of the chip empty takes larger workgroups: tables are built and lists walked by more
-    // waves at once (filtered scan of one query, 19 pairs: 21.6 -> 9 us with 1024 threads instead of 256).
     if (!idx->tuning.scan_threads)
-        while (threads < 1024 && (size_t)grid.x * (threads / 64) < kWaveSlots &&
+        while (threads < 1024 && blocks * (threads / 64) < kWaveSlots &&
                scan_lds_bytes_staged(idx, lut_dtype, threads * 2) <= kLdsBytes) threads *= 2;
+    return threads;
+}
+int launch_scan(const ivfpq_index* idx, ScanArgs a, int lut_dtype, dim3 grid, hipStream_t st) {
+    const int threads = scan_threads_of_grid(idx, lut_dtype, grid.x);
     const size_t lds = std::max(scan_lds_bytes_staged(idx, lut_dtype, threads), a.mode == 1 && a.k_bound > 0 ? kBoundLds : (size_t)0);
     if (lds > kLdsBytes)
         return fail(IVFPQ_EUNSUPPORTED, "lookup table + residual + staging need %zu bytes of LDS (limit %zu)", lds, kLdsBytes);
@@ -1877,6 +1881,23 @@ int launch_candidates(const FilterArgs& a, int lut_dtype, hipStream_t st) {
     }
 }
 
+// ---- what ivfpq_scan_kernel_info says of a launch ----
+const char* const kLutNames[4] = {"fp32", "fp16", "e5m3", "e4m4"};
+void describe_filter(const ivfpq_index* idx, int lut_dtype, char* buf, size_t bytes) {
+    snprintf(buf, bytes, "scan_filter_kernel<%d-bit codes, %d components a sub-space, d = %d> and candidate_kernel<%s>, %zu and %zu bytes of LDS",
+             idx->pq_bits, idx->m(), idx->d, kLutNames[lut_dtype], filter_lds_bytes(idx->pq_bits, idx->d), candidate_lds_bytes(idx->pq_bits, idx->d));
+}
+void describe_group(const ivfpq_index* idx, int lut_dtype, int G, char* buf, size_t bytes) {
+    const int threads = scan_group_threads(idx, lut_dtype, G);
+    snprintf(buf, bytes, "scan_group_kernel<%s, %d-bit codes, %d chunks, %d pairs> %d threads, %zu bytes of LDS", kLutNames[lut_dtype], idx->pq_bits,
+             idx->code_bytes() / chunk_width(idx), G, threads, scan_group_lds_bytes(idx, lut_dtype, G, threads));
+}
+void describe_scan(const ivfpq_index* idx, int lut_dtype, int threads, char* buf, size_t bytes) {
+    const int cw = chunk_width(idx), nch = idx->code_bytes() / cw;
+    snprintf(buf, bytes, "scan_kernel<%s, %d-bit codes, %d-byte chunks x %d> %d threads, %zu bytes of LDS", kLutNames[lut_dtype],
+             idx->pq_bits, cw, cw == 16 ? nch : 0, threads, scan_lds_bytes_staged(idx, lut_dtype, threads));
+}
+
 // ---- stage timing ----
 int timing_mark(const ivfpq_index* idx, hipStream_t st, void** out) {
     if (idx->events_used == idx->event_pool.size()) {
@@ -1951,7 +1972,7 @@ int search_impl(const ivfpq_index* idx, const float* d_queries, int64_t nq, cons
     StripSummary* w_S = (StripSummary*)(ws + plan.S);
     float* w_R = (float*)(ws + plan.R);
 
-    if (idx->timing) { idx->events_used = 0; idx->spans.clear(); idx->stage_valid = true; }
+    if (idx->timing) { idx->events_used = 0; idx->spans.clear(); idx->stage_valid = true; idx->scan_kernel_lut = -1; }
     StageTimer whole(idx, st, 3);
     if (int s = whole.begin()) return s;
     for (int64_t q0 = 0; q0 < nq; q0 += plan.tile) {
@@ -2005,11 +2026,19 @@ int search_impl(const ivfpq_index* idx, const float* d_queries, int64_t nq, cons
             if (grouped) { a.clear[0] = w_lc; a.n_clear[0] = (uint32_t)((plan.list_offsets - plan.list_counts) / 4); }
             if (filter) { a.clear[1] = (uint32_t*)(ws + plan.D + lists.totals); a.n_clear[1] = 2u; }
         }
+        // a timed search notes what its first tile launches for the probes other than the nearest
+        auto note = [&](auto describe, auto... what) {
+            if (!idx->timing || idx->scan_kernel_lut >= 0) return;
+            describe(idx, lut_dtype, what..., idx->scan_kernel, sizeof idx->scan_kernel);
+            idx->scan_kernel_lut = lut_dtype;
+        };
+        auto note_scan = [&](size_t blocks) { note(describe_scan, scan_threads_of_grid(idx, lut_dtype, blocks)); };
         StageTimer t5(idx, st, 5);
         StageTimer t6(idx, st, 6);
         if (int s = t5.begin()) return s;
         if (int s = launch_scan(idx, a, lut_dtype, dim3((unsigned)((size_t)tq * (whole_rows ? n_probes : 1))), st)) return s;
         if (int s = t5.end()) return s;
+        if (whole_rows && n_probes > 1) note_scan((size_t)tq * n_probes);
         if (whole_rows) t5.divide(6, 1.f / (float)n_probes);      // one launch does the work of both: divided by their pairs
         if (n_probes > 1 && !whole_rows) {
             a.mode = 2;
@@ -2061,17 +2090,21 @@ int search_impl(const ivfpq_index* idx, const float* d_queries, int64_t nq, cons
                     f.nq = tq; f.n_probes = n_probes;
                     f.d = idx->d; f.pq_dim = idx->pq_dim; f.m = idx->m(); f.bits = idx->pq_bits;
                     f.code_bytes = idx->code_bytes(); f.chunk_width = chunk_width(idx);
+                    note(describe_filter);
                     if (int s = launch_filter(f, st)) return s;
                     if (int s = launch_candidates(f, lut_dtype, st)) return s;
                 } else if (const int G = scan_group_width(idx, lut_dtype, a.fp8, blk)) {
                     a.n_chunks = idx->code_bytes() / chunk_width(idx);
+                    note(describe_group, G);
                     if (int s = launch_scan_group(idx, a, lut_dtype, G, st)) return s;
                 } else {
                     const size_t grid = (n_pairs + 8 * (size_t)blk - 1) / (8 * (size_t)blk) * (8 * (size_t)blk);
+                    note_scan(grid);
                     if (int s = launch_scan(idx, a, lut_dtype, dim3((unsigned)grid), st)) return s;
                 }
             } else {
                 if (int s = t6.begin()) return s;
+                note_scan(n_pairs);
                 if (int s = launch_scan(idx, a, lut_dtype, dim3((unsigned)n_pairs), st)) return s;
             }
             if (int s = t6.end()) return s;
@@ -2442,19 +2475,17 @@ int ivfpq_stream_read(const void* d_buf, size_t bytes, uint32_t* d_out, int32_t 
 int ivfpq_scan_kernel_info(const ivfpq_index_t* idx, int32_t lut_dtype, char* buf, size_t buf_bytes) {
     if (!idx || !buf || buf_bytes == 0) return fail(IVFPQ_EINVAL, "ivfpq_scan_kernel_info: null pointer");
     if (lut_dtype < 0 || lut_dtype > 3) return fail(IVFPQ_EINVAL, "unknown lut_dtype %d", lut_dtype);
-    static const char* const names[4] = {"fp32", "fp16", "e5m3", "e4m4"};
-    const int threads = scan_threads(idx, lut_dtype), cw = chunk_width(idx), nch = idx->code_bytes() / cw;
+    if (idx->timing && idx->scan_kernel_lut == lut_dtype) {
+        snprintf(buf, buf_bytes, "%s", idx->scan_kernel);
+        return IVFPQ_OK;
+    }
     const uint32_t blk = idx->tuning.order_block > 0 ? (uint32_t)idx->tuning.order_block : kOrderBlock;
+    const Fp8Mode fp8 = fp8_mode(idx, lut_dtype);
     const bool grouped = idx->tuning.scan_route == 0 || idx->tuning.scan_route == (int)ScanRoute::kGrouped;      // 0: what large batches take
-    if (grouped && filter_applies(idx, lut_dtype, fp8_mode(idx, lut_dtype)))
-        snprintf(buf, buf_bytes, "scan_filter_kernel<%d-bit codes, %d components a sub-space, d = %d> and candidate_kernel<%s>, %zu and %zu bytes of LDS",
-                 idx->pq_bits, idx->m(), idx->d, names[lut_dtype], filter_lds_bytes(idx->pq_bits, idx->d), candidate_lds_bytes(idx->pq_bits, idx->d));
-    else if (const int G = grouped ? scan_group_width(idx, lut_dtype, fp8_mode(idx, lut_dtype), blk) : 0)
-        snprintf(buf, buf_bytes, "scan_group_kernel<%s, %d-bit codes, %d chunks, %d pairs> %d threads, %zu bytes of LDS", names[lut_dtype], idx->pq_bits, nch, G,
-                 scan_group_threads(idx, lut_dtype, G), scan_group_lds_bytes(idx, lut_dtype, G, scan_group_threads(idx, lut_dtype, G)));
-    else
-        snprintf(buf, buf_bytes, "scan_kernel<%s, %d-bit codes, %d-byte chunks x %d> %d threads, %zu bytes of LDS", names[lut_dtype],
-                 idx->pq_bits, cw, cw == 16 ? nch : 0, threads, scan_lds_bytes_staged(idx, lut_dtype, threads));
+    const int G = grouped ? scan_group_width(idx, lut_dtype, fp8, blk) : 0;
+    if (grouped && filter_applies(idx, lut_dtype, fp8)) describe_filter(idx, lut_dtype, buf, buf_bytes);
+    else if (G) describe_group(idx, lut_dtype, G, buf, buf_bytes);
+    else describe_scan(idx, lut_dtype, scan_threads(idx, lut_dtype), buf, buf_bytes);
     return IVFPQ_OK;
 }
 
@@ -2462,6 +2493,7 @@ int ivfpq_set_stage_timing(ivfpq_index_t* index, int32_t enabled) {
     if (!index) return fail(IVFPQ_EINVAL, "null index");
     index->timing = enabled != 0;
     index->stage_valid = false;
+    index->scan_kernel_lut = -1;
     return IVFPQ_OK;
 }
 

@@ -141,6 +141,8 @@ struct ivfpq_index {
     mutable std::vector<void*> event_pool;
     mutable std::vector<Span> spans;
     mutable size_t events_used = 0;
+    mutable char scan_kernel[256] = {};      // what the last timed search launched for the probes other than the nearest (ivfpq_scan_kernel_info)
+    mutable int scan_kernel_lut = -1;        // its table dtype; -1: no such launch
 
     int32_t ksub() const { return 1 << pq_bits; }
     int32_t m() const { return d / pq_dim; }

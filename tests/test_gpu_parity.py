@@ -912,6 +912,31 @@ def test_matrix_core_filter_leaves_other_calls_to_the_tables(P):
     assert not odd.ivfpq_scan_kernel_info(oracle.LUT_FP32).startswith("scan_filter_kernel")
 
 
+def test_timed_search_names_the_kernel_it_launched(P):
+    # the general description does not know the batch, the probes and k; a timed search does
+    oidx, gidx = random_pair(P, 70000, 64, 700, 32, 8, salt=5)
+    name = lambda dtype: gidx.ivfpq_scan_kernel_info(dtype).split("<")[0]
+    rng = np.random.default_rng(5)
+    e5m3, half = oracle.LUT_E5M3, oracle.LUT_FP16
+    assert name(e5m3) == name(half) == "scan_filter_kernel"
+    gidx.ivfpq_set_stage_timing(True)
+    assert name(e5m3) == "scan_filter_kernel"                           # no search yet
+    for nq, n_probes, k, dtype, kernel in (
+            (3, 5, 10, e5m3, "scan_kernel"),                            # little work: all probes in one launch
+            (10000, 4, 10, e5m3, "scan_kernel"),                        # 4 M vectors: in query order
+            (170000, 2, 10, e5m3, "scan_group_kernel"),                 # two of 700 lists, k a tenth of a list, one-byte tables
+            (170000, 2, 10, half, "scan_filter_kernel"),
+            (170000, 2, 100, half, "scan_group_kernel")):               # k a whole list
+        q = rng.standard_normal((nq, 64)).astype(np.float32)
+        gidx.ivfpq_search(q, n_probes, k, dtype)
+        torch.cuda.synchronize()
+        _step(f"nq={nq} P={n_probes} k={k} dtype={dtype}: {gidx.ivfpq_scan_kernel_info(dtype)}")
+        assert name(dtype) == kernel
+        assert name(half if dtype == e5m3 else e5m3) == "scan_filter_kernel"          # another dtype: the general description
+    gidx.ivfpq_set_stage_timing(False)
+    assert name(half) == "scan_filter_kernel"
+
+
 @pytest.mark.parametrize("nq", [1, 31, 33, 500, 2047, 2049])
 def test_candidates_of_few_queries_are_shared_by_workgroups(P, nq):
     # long candidate lists (k a third of a list) of few queries are summed by several workgroups each, of many by one: every
