@@ -62,7 +62,9 @@ centre_mean_kernel(const float* __restrict__ C, int k, int d, float* __restrict_
     }
 }
 
-// norms[c] = |c'|^2, or -1 for a centre with components that are no moderate numbers (it is at no finite distance, or at one that no other is)
+// norms[c] = |c'|^2, or -1 for a centre with components that are no moderate numbers, which is no part of the product.  One with a component
+// that is not finite is at no finite distance, hence never the nearest.  One that is finite can be: the largest norm is then infinite,
+// so is the error of a value, and every row compares all centres.
 __global__ void __launch_bounds__(1024)
 centre_stats_kernel(const float* __restrict__ C, int k, int d, const float* __restrict__ mean, float* __restrict__ norms, NearStats* __restrict__ stats) {
     // one wave per centre in turn; one addition to the shared maxima per workgroup (one per centre serialises: 230 us for 10,000)
@@ -85,6 +87,11 @@ centre_stats_kernel(const float* __restrict__ C, int k, int d, const float* __re
         ok = __builtin_amdgcn_ballot_w64(!ok) == 0;
         if (lane == 0) norms[c] = ok ? sum : -1.f;
         if (ok) { most = fmaxf(most, top); largest = fmaxf(largest, sum); }
+        else {
+            bool finite = true;
+            for (int t = lane; t < d; t += 64) finite = finite && __builtin_fabsf(C[(size_t)c * d + t]) <= 3.4028235e38f;
+            if (__builtin_amdgcn_ballot_w64(!finite) == 0) largest = __builtin_inff();
+        }
     }
     if (lane == 0) { atomicMax(&s_most[0], __float_as_uint(most)); atomicMax(&s_most[1], __float_as_uint(largest)); }
     __syncthreads();
@@ -286,7 +293,7 @@ near_decide_kernel(const uint4* __restrict__ part, size_t n_rows, int splits, in
         const float cn = __builtin_sqrtf(__uint_as_float(stats->norm_max)) * scale * 1.0001f, xn = __builtin_sqrtf(norm) * 1.001f;
         const float error = near_error(d, xn, cn);
         // (not-a-number fails every comparison: such a row looks at all centres, as one does that no finite centre was found for; so do all
-        // rows where the squares of the centres' components leave the range of a float)
+        // rows where the squares of the centres' components leave the range of a float: below it, or past it and the error with them)
         all = !(__uint_as_float(stats->component_max) > 1.0e-15f) || !(xn < 1.0e18f) || !(error < 1.0e30f) || !(first > -2.9e38f) || at >= (uint32_t)k;
         limit = first - 2.f * error - __builtin_fabsf(first) * 2.0e-6f;
         list = !all && !(second < limit);

@@ -106,6 +106,24 @@ def test_assign_device_half_precision_product(P, n, d, k, kind):
         assert 0 <= got[5] < k and 0 <= got[n - 1] < k and not np.any(got == 20)
 
 
+@pytest.mark.parametrize("d", [16, 128])
+def test_assign_device_half_precision_product_centres_past_its_range(P, d):
+    # finite centres whose components are so large that their squares leave a float's range are no part of the half-precision
+    # product, and still the nearest of the rows around them
+    n, k = 9000, 1500
+    rng = np.random.default_rng(d)
+    c = (rng.uniform(-9e17, 9e17, (k, d))).astype(np.float32)
+    c[[7, 640, 1499]] = rng.uniform(1.5e18, 2.5e18, (3, d)).astype(np.float32)
+    at = rng.integers(0, k, n)
+    at[::50] = 640
+    x = (c[at] + rng.uniform(-1e17, 1e17, (n, d))).astype(np.float32)
+    _step(f"assign, centres on both sides of 1e18: d={d}")
+    got = P.ivfpq_assign_device(x, c).cpu().numpy()
+    want, _ = oracle.assign(x, c)
+    assert np.mean(want == 640) > 0.015
+    np.testing.assert_array_equal(got, want)
+
+
 # ---------------------------------------------------------------- the whole build
 
 def _rows(n, n_lists, pq_dim, pq_bits, n_ct, n_pt, salt):
