@@ -747,7 +747,9 @@ __device__ __forceinline__ void bound_of_nearest(const ScanArgs& a, int q, uint3
         const uint32_t bin = box[2], before = box[3], in_bin = box[4];
         if (bin == 0xFFFFFFFFu) break;                       // fewer than k finite values
         // everything counted up to this bin is at most its edge: the roundings of the bin's number and of the edge are within 2^-21
-        const float edge = fminf((from + (float)(bin + 1) * width * 1.000001f) * 1.0000005f, to);
+        // (of subnormal values a bin's width is rounded to few bits or to none: the last bin, which takes all above it, and the
+        // only one where there is no width, end at the largest value)
+        const float edge = width > 0.f && bin < (uint32_t)kBoundBins - 1u ? fminf((from + (float)(bin + 1) * width * 1.000001f) * 1.0000005f, to) : to;
         bound = __float_as_uint(edge);
         if (before + in_bin <= k + k / 8 + 8 || width * 1048576.f <= to) break;
         const float start = fmaxf(from, (from + (float)bin * width * 0.999999f) * 0.9999995f);

@@ -840,6 +840,23 @@ def test_first_probe_without_vectors(P, pq_bits, pq_dim, n_probes):
             assert_topk_matches(ids[i:i + 1], dist[i:i + 1], ids_o, d_o, context=f"query {i}")
 
 
+@pytest.mark.parametrize("scale", [1e-22, 3e-22, 1e-21, 3e-21, 3e-20])
+def test_distances_in_the_subnormal_range(P, scale):
+    # R of a few to a few thousand units of 2^-149: the bins of the nearest probe's bound are narrower than one unit
+    arrays = si.random_index_arrays(4000, 64, 8, 32, 8, salt=78, scale=scale)
+    oidx = oracle.make_index(64, 8, 32, 8, *arrays)
+    gidx = to_library(P, oidx)
+    q = (scale * np.random.default_rng(78).standard_normal((65, 64))).astype(np.float32)
+    for dtype in (oracle.LUT_FP32, oracle.LUT_E5M3):
+        ids_o, d_o = oracle.search(oidx, q, 8, 20, dtype)
+        for route in (0, 1, 2, 3):
+            gidx.ivfpq_set_tuning(P.TUNE_SCAN_ROUTE, route)
+            _step(f"subnormal distances, scale={scale} dtype={dtype} route={route}")
+            ids_g, d_g = [t.cpu().numpy() for t in gidx.ivfpq_search(q, 8, 20, dtype)]
+            np.testing.assert_array_equal(d_g.view(np.uint32), d_o.view(np.uint32))
+            np.testing.assert_array_equal(ids_g, ids_o)
+
+
 @pytest.mark.parametrize("d,pq_dim,pq_bits", [
     (128, 64, 8), (128, 32, 8), (96, 48, 8), (64, 32, 8), (64, 16, 8),     # two and four components a sub-space
     (96, 24, 8),                                                           # 24-byte codes: 4-byte chunks
