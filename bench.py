@@ -445,7 +445,7 @@ def main():
                                 "streaming_read_ceiling": round(ceiling, 1)},
             "default_run": {"kernel": head["kernel"], "kernel_ms_per_step": round(kern_ms, 4),
                             "note": "library default: large batches list the vectors that can have R <= bound with a matrix product and add up "
-                                    "those alone (or, where that does not apply or pay (k a large share of a list, few of the lists probed), a 64-vector group stops adding once all its partial sums are "
+                                    "those alone (or, where that does not apply or pay (many of them could, as a sample taken at upload tells), a 64-vector group stops adding once all its partial sums are "
                                     "over the query's bound): same results, fewer lookups made"},
             "whole_scan_stage": {"scanned_vectors_per_step": scanned_vectors, "code_bytes_per_step": code_bytes,
                                  "stage_ms": round(head["stage_ms"]["scan"], 4), "stage_ms_without_early_exit": round(full["stage_ms"]["scan"], 4)},

@@ -281,8 +281,8 @@ int ivfpq_stage_times_ms(ivfpq_index_t* index, float ms[8]);
  * search launched (its first query tile).  Otherwise it describes large batches on this index with the current tuning,
  * whose pairs run grouped by cluster, unless IVFPQ_TUNE_SCAN_ROUTE names another route.  Where a matrix product can list
  * the vectors to add up (an uploaded index, its usual shapes, no knob that asks for the table kernels) that names its
- * kernel and the one that adds them up; a search for which the tables cost less (few vectors looked up, k a large share
- * of a list, few of the lists probed) takes the table kernels all the same, and one of little work scan_kernel. */
+ * kernel and the one that adds them up; a search for which the tables cost less (few vectors looked up, or many of them
+ * able to be among the results) takes the table kernels all the same, and one of little work scan_kernel. */
 int ivfpq_scan_kernel_info(const ivfpq_index_t* index, int32_t lut_dtype, char* buf, size_t buf_bytes);
 
 /* Measurement aid, not a step of the method: a plain streaming read of `bytes` bytes of device memory

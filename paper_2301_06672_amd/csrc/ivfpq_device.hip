@@ -36,6 +36,7 @@
 #include <hip/hip_fp16.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstring>
 #include <type_traits>
@@ -1831,41 +1832,53 @@ bool filter_applies(const ivfpq_index* idx, int lut_dtype, const Fp8Mode& fp8) {
     return t.early_exit >= 0 && t.scan_share == 0 && t.order_block == 0 && t.scan_threads == 0 && t.lds_pad == 0 && !fp8.per_table &&
            idx->word_norm_max >= 0.f && filter_supported(idx->pq_bits, idx->pq_dim, idx->d, chunk_width(idx));
 }
-// By the number of vectors that are looked up, as scan_route, and by k against the length of a list: the bound is the k-th of one list,
-// so k / length is the share of a similar list that passes and is added up.  The filter has a cost of its own (codebooks that two
-// kernels load, every listed vector); us a search, the better table route / filter:
+// The largest share of an entry that its stored form is below it: half 2^-11, 8-bit formats of M mantissa bits 1 / (2^(M+1) + 1) rounded to
+// nearest, 1 / (2^M + 1) truncated.
+double stored_loss(int lut_dtype, const Fp8Mode& fp8) {
+    if (lut_dtype == IVFPQ_LUT_FP32) return 0.0;
+    if (lut_dtype == IVFPQ_LUT_FP16) return 1.0 / 2048;
+    const int mantissa = lut_dtype == IVFPQ_LUT_FP8_E5M3 ? 3 : 4;
+    return 1.0 / ((1 << (fp8.truncate ? mantissa : mantissa + 1)) + 1);
+}
+// By the number of vectors that are looked up, as scan_route, and by k against the length of a list: the bound is the k-th of one list.
+// The filter has a cost of its own (codebooks that two kernels load); us a search, the better table route / filter:
 //   k / length 0.01  6 M 75 / 64, 75 / 77, 84 / 81, 68 / 71, 93 / 72, 82 / 78; 9 M 91 / 64, 91 / 81, 102 / 92, 82 / 83, 121 / 91, 125 / 85
 //              0.05  6 M 80 / 76, 90 / 88, 83 / 92; 9 M 97 / 75, 108 / 96, 97 / 107; 12 M 118 / 89, 132 / 107, 108 / 110
 //              0.1   6 M 92 / 97, 96 / 125, 97 / 95, 145 / 122; 12 M 134 / 116, 142 / 160, 140 / 113, 237 / 164; 30 M 270 / 144, 244 / 206
 // (200,000 unit-norm rows in 200 lists, 60 and 20 probes; 10^6 in 1,024, 20; 200,000 of 128 components in 100, 30, where 0.05; 100,000 in
 // 100, 30, where 0.01 and 0.1; 10^6 in 555, 4-bit codes, 30).
-// Probes that are a small share of the lists lie all about the query, and their vectors compete with those of the nearest list: with one-byte
-// tables, whose rounding (a seventeenth) widens the filter's limit, or 4-bit codes, whose tables are cheap, the tables are faster then
-// where k / length is not small.  10,000 queries, 10^8 vectors in 50,000 lists, 64 probes, 0.05, ms, tables / filter: e5m3 5.2 / 6.6, half 6.2 / 4.8,
-// float 7.9 / 4.7; 4-bit codes e5m3 5.9 / 7.0, half 4.8 / 5.0; 10^7 in 10,000, 20 probes, 0.01: e5m3 1.5 / 0.65; 50 probes, 0.1: 2.8 / 1.0; us,
-// 5,000 queries, 2 10^6 in 2,800 lists, 0.14, e5m3, 8 probes 276 / 322 and 262 / 244 (either family), 16 probes 317 / 346 and 358 / 261.
-bool filter_pays(const ivfpq_index* idx, int lut_dtype, int nq, int n_probes, int k) {
+// A listed vector costs several table lookups' worth, so of larger batches the share that passes decides, which the upload sampled
+// (pass_share; one-byte tables, whose rounding widens the limit, list more).  Filter's time over the tables' at sampled shares, 10,000
+// queries, 20 and 60 probes, 2 10^6 and 10^7 vectors of overlapping (1 to 250 Gaussian components) and separate lists, k / length 0.01 to 0.6:
+//   8-bit codes    e5m3  32 sub-spaces 0.06 0.87-0.95, 0.08 1.0, 0.1 1.29, 0.2 2.0; 48 0.055 0.71, 0.085 0.97-1.01, 0.13 1.34; 64 0.07 0.71, 0.11 1.02, 0.17 1.37
+//                  half  32 0.07 0.71-0.78, 0.15 1.0-1.06, 0.21 1.41; 48 0.08 0.68, 0.15 0.96-1.0, 0.2 1.1; 64 0.17 1.0, 0.23 1.15
+//                  float 32 0.15 0.82-0.90, 0.21 1.14-1.18; tables too large for two pairs (one-pair kernel) 0.3 0.72, 0.4 0.82
+//   7, 6           e5m3  0.07 1.07, 0.86, 0.11 1.22, 1.14; half 0.1 0.87, 0.81, 0.16 0.95, 0.90, 0.22 1.11, 1.24; float 0.1 0.81, 1.0, 0.16 0.92, 1.11
+//   4              e5m3  0.05 0.92-0.94, 0.09 1.38; half 0.035 1.02, 0.046 1.07, 0.059 1.20; float 0.035 1.05, 0.059 1.24; one-pair kernel (24-byte
+//                  codes) e5m3 0.13 0.78, 0.16 1.24, half 0.09 0.77, 0.15 0.80, 0.19 1.20
+// With few pairs a list the filter's blocks of 32 rows are mostly empty: 4 pairs, 8 bits, e5m3 0.03 1.05-1.09, half 0.055 1.0, 0.09 1.08, float 0.09 0.96.
+bool filter_pays(const ivfpq_index* idx, int lut_dtype, const Fp8Mode& fp8, int nq, int n_probes, int k) {
     if (idx->tuning.scan_route != 0) return true;
-    const double length = (double)idx->n / (double)idx->n_lists, share = (double)k / length;
-    const bool loose = lut_elem_bytes(lut_dtype) == 1 || idx->pq_bits == 4;
-    if (loose && share >= 0.04 && (int64_t)n_probes * 300 < idx->n_lists) return false;
-    return (double)nq * (n_probes - 1) * length >= kFilterLookups + 1e8 * share;
+    const double length = (double)idx->n / (double)idx->n_lists, share = (double)k / length, pairs = (double)nq * (n_probes - 1);
+    if (!(pairs * length >= kFilterLookups + 1e8 * share) || idx->pass_shares.ranks == 0) return false;
+    const int bytes = lut_elem_bytes(lut_dtype);
+    const bool nibbles = idx->pq_bits == 4, one_pair = scan_group_width(idx, lut_dtype, fp8, kOrderBlock) == 0;
+    double most;
+    if (one_pair) most = bytes == 1 ? 0.12 : nibbles ? 0.15 : bytes == 2 ? 0.28 : 0.45;
+    else if (nibbles) most = bytes == 1 ? 0.06 : 0.035;
+    else if (idx->pq_bits == 8) most = (bytes == 1 ? 0.045 : bytes == 2 ? 0.11 : 0.14) + 0.001 * idx->pq_dim;
+    else most = bytes == 1 ? 0.07 : 0.14;
+    most *= std::min(1.0, pairs / (double)idx->n_lists / 12.0);
+    const double wider = 1.0 / (1.0 - stored_loss(lut_dtype, fp8)) - 1.0 + 0.012;            // of the limit against the bound; the rest is eta's
+    return pass_share(idx->pass_shares, n_probes, share, wider) <= most;
 }
 // What |r - y|^2 of a vector with R <= bound is limited by: bound * scale + add, where no entry saturates (the kernel sees to
-// those that may).  A stored entry is below its distance by at most the share `loss` (half: 2^-11, and 2^-25 where the half is
-// subnormal; 8-bit formats of M mantissa bits: 1 / (2^(M+1) + 1) rounded to nearest, 1 / (2^M + 1) truncated); the 2^-16 cover the
+// those that may).  A stored entry is below its distance by at most the share `loss` (stored_loss; and 2^-25 where a half is subnormal); the 2^-16 cover the
 // sum of up to 128 entries and the rounding of an entry's own distance.  eta: r.y is formed from bf16 operands (2^-8 + 2^-18 of the sum
 // of magnitudes, which is at most (|r|^2 + |y|^2) / 2), summed with the threshold in any order (4 (d + 2) 2^-24 of either, with
 // a factor 4 of slack as for the ranking values), |r|^2 is a sum of d squares.
 void filter_constants(const ivfpq_index* idx, int lut_dtype, const Fp8Mode& fp8, FilterArgs* a) {
-    double loss = 0.0, below = 0.0;
-    if (lut_dtype == IVFPQ_LUT_FP16) {
-        loss = 1.0 / 2048;
-        below = idx->pq_dim * std::ldexp(1.0, -25);
-    } else if (lut_dtype != IVFPQ_LUT_FP32) {
-        const int mantissa = lut_dtype == IVFPQ_LUT_FP8_E5M3 ? 3 : 4;
-        loss = 1.0 / ((1 << (fp8.truncate ? mantissa : mantissa + 1)) + 1);
-    }
+    const double loss = stored_loss(lut_dtype, fp8), below = lut_dtype == IVFPQ_LUT_FP16 ? idx->pq_dim * std::ldexp(1.0, -25) : 0.0;
     a->scale = (float)((1.0 + std::ldexp(1.0, -15)) / (1.0 - loss));
     a->add = (float)(below / (1.0 - loss) * 1.001 + 1e-30);
     a->top = table_top(lut_dtype, fp8);
@@ -2017,7 +2030,7 @@ int search_impl(const ivfpq_index* idx, const float* d_queries, int64_t nq, cons
         // The filter's lists take the place of the ranking values, which nothing reads any more (a search with given probes has none).
         FilterLists lists = filter_lists(idx, (size_t)tq, n_probes, filter_item_vectors(idx, n_pairs));
         while (lists.bytes > plan.R - plan.D && lists.per_item < (uint32_t)kFilterVectors) lists = filter_lists(idx, (size_t)tq, n_probes, lists.per_item * 2);
-        const bool filter = grouped && filter_applies(idx, lut_dtype, a.fp8) && filter_pays(idx, lut_dtype, tq, n_probes, k) && ((uintptr_t)qt & 7) == 0 &&
+        const bool filter = grouped && filter_applies(idx, lut_dtype, a.fp8) && filter_pays(idx, lut_dtype, a.fp8, tq, n_probes, k) && ((uintptr_t)qt & 7) == 0 &&
                             lists.max_items < ((size_t)1 << 31) && lists.bytes <= plan.R - plan.D;
         uint32_t* w_starts = filter ? (uint32_t*)(ws + plan.D) : nullptr;
         uint32_t* w_lc = (uint32_t*)(ws + plan.list_counts);         // counts and cursors are neighbours in the plan
@@ -2034,7 +2047,7 @@ int search_impl(const ivfpq_index* idx, const float* d_queries, int64_t nq, cons
             describe(idx, lut_dtype, what..., idx->scan_kernel, sizeof idx->scan_kernel);
             idx->scan_kernel_lut = lut_dtype;
         };
-        auto note_scan = [&](size_t blocks) { note(describe_scan, scan_threads_of_grid(idx, lut_dtype, blocks)); };
+        auto note_scan = [&](size_t blocks) { if (idx->timing) note(describe_scan, scan_threads_of_grid(idx, lut_dtype, blocks)); };
         StageTimer t5(idx, st, 5);
         StageTimer t6(idx, st, 6);
         if (int s = t5.begin()) return s;
@@ -2233,10 +2246,46 @@ int upload_impl(ivfpq_index_t* idx, void* d_buf, size_t bytes, void* hip_stream)
     hipStream_t st = (hipStream_t)hip_stream;
     unsigned char* base = (unsigned char*)d_buf;
     const int cb = idx->code_bytes(), cw = chunk_width(idx), nch = cb / cw;
-
-    // Everything before the codes is put together on the host and travels as one (a copy of a few kB costs what 1 MB costs).
+    // Everything before the codes is put together on the host and travels as one (a copy of a few kB costs what 1 MB costs), behind the
+    // first codes.  The norms in it and the sample that filter_pays needs are made beside the transfers, which one thread of the host stages.
+    // (The scratch is made here: a new thread's first allocation sets up a heap of its own.)
+    const size_t n_words = (size_t)idx->pq_dim << idx->pq_bits;
     ivfpq::HostArray<unsigned char> head(L.codes);
+    float cn_max = 0.f, wn_max = 0.f;
+    bool moderate = true;
+    auto norms = [&] {
+        float* cnorm = (float*)(head.data() + L.centroid_norms);
+        for (int l = 0; l < idx->n_lists; l += 8) {                                       // eight sums at a time: each is one chain of additions
+            double acc[8] = {};
+            const float* c[8];
+            for (int u = 0; u < 8; ++u) c[u] = idx->centroids.data() + (size_t)std::min(l + u, idx->n_lists - 1) * idx->d;
+            for (int t = 0; t < idx->d; ++t)
+                for (int u = 0; u < 8; ++u) { double v = c[u][t]; acc[u] += v * v; }
+            for (int u = 0; u < 8 && l + u < idx->n_lists; ++u) {
+                cnorm[l + u] = (float)acc[u];
+                if (cnorm[l + u] > cn_max) cn_max = cnorm[l + u];
+            }
+        }
+        float* wnorm = (float*)(head.data() + L.word_norms);
+        for (size_t i = 0; i < n_words; ++i) {
+            float acc = 0.f;
+            for (int t = 0, m = idx->m(); t < m; ++t) { const float v = idx->codebooks[i * m + t]; acc += v * v; }
+            wnorm[i] = acc;
+            moderate = moderate && acc <= 1e28f;
+            wn_max = std::max(wn_max, acc);
+        }
+    };
+    ivfpq::PassShares shares;
+    const bool may_filter = filter_supported(idx->pq_bits, idx->pq_dim, idx->d, cw);
+    std::vector<uint64_t> near(may_filter ? (size_t)idx->n_lists : 0);
+    std::vector<float> sampled(may_filter ? 2 * (size_t)idx->d : 0);
     std::memset(head.data(), 0, head.size());
+    std::atomic<bool> normed{false};
+    ivfpq::SideTask aside([&] {
+        norms();
+        normed.store(true, std::memory_order_release);
+        if (may_filter) shares = ivfpq::sample_pass_shares(*idx, near.data(), sampled.data(), sampled.data() + idx->d);
+    });
     std::memcpy(head.data() + L.centroids, idx->centroids.data(), idx->centroids.size() * 4);
     std::memcpy(head.data() + L.codebooks, idx->codebooks.data(), idx->codebooks.size() * 4);
     std::memcpy(head.data() + L.list_offsets, idx->list_offsets.data(), idx->list_offsets.size() * 8);
@@ -2247,34 +2296,14 @@ int upload_impl(ivfpq_index_t* idx, void* d_buf, size_t bytes, void* hip_stream)
         sizes[l] = (uint32_t)len;
         goff[l + 1] = goff[l] + (len + 63) / 64;
     }
-    float* cnorm = (float*)(head.data() + L.centroid_norms);
-    float cn_max = 0.f;
-    for (int l = 0; l < idx->n_lists; l += 8) {                                           // eight sums at a time: each is one chain of additions
-        double acc[8] = {};
-        const float* c[8];
-        for (int u = 0; u < 8; ++u) c[u] = idx->centroids.data() + (size_t)std::min(l + u, idx->n_lists - 1) * idx->d;
-        for (int t = 0; t < idx->d; ++t)
-            for (int u = 0; u < 8; ++u) { double v = c[u][t]; acc[u] += v * v; }
-        for (int u = 0; u < 8 && l + u < idx->n_lists; ++u) {
-            cnorm[l + u] = (float)acc[u];
-            if (cnorm[l + u] > cn_max) cn_max = cnorm[l + u];
-        }
-    }
-    idx->centroid_norm_max = cn_max;
-    const size_t n_words = (size_t)idx->pq_dim << idx->pq_bits;
-    float* wnorm = (float*)(head.data() + L.word_norms);
-    float wn_max = 0.f;
-    bool moderate = true;
-    for (size_t i = 0; i < n_words; ++i) {
-        float acc = 0.f;
-        for (int t = 0, m = idx->m(); t < m; ++t) { const float v = idx->codebooks[i * m + t]; acc += v * v; }
-        wnorm[i] = acc;
-        moderate = moderate && acc <= 1e28f;
-        wn_max = std::max(wn_max, acc);
-    }
-    idx->word_norm_max = moderate ? std::sqrt(wn_max) * 1.0001f : -1.f;
-
-    HIP_TRY(hipMemcpyAsync(base, head.data(), head.size(), hipMemcpyHostToDevice, st));
+    bool head_sent = false;
+    auto send_head = [&]() -> int {
+        if (head_sent) return IVFPQ_OK;
+        while (!normed.load(std::memory_order_acquire)) std::this_thread::yield();
+        HIP_TRY(hipMemcpyAsync(base, head.data(), head.size(), hipMemcpyHostToDevice, st));
+        head_sent = true;
+        return IVFPQ_OK;
+    };
     // The codes travel in list order, as many whole groups at a time as fit the place of the ids, and are interleaved
     // from there on the device; the ids follow.
     const int64_t cap = idx->n == 0 ? 0 : (int64_t)((L.total - L.ids) / (size_t)cb);      // vectors in transit, 64 or more
@@ -2291,6 +2320,7 @@ int upload_impl(ivfpq_index_t* idx, void* d_buf, size_t bytes, void* hip_stream)
         if (g_end <= g || v_end - v > cap || blocks > 0x7FFFFFFFull)
             return fail(IVFPQ_EUNSUPPORTED, "internal: %lld code groups in transit", (long long)(g_end - g));
         HIP_TRY(hipMemcpyAsync(base + L.ids, idx->codes.data() + (size_t)v * cb, (size_t)(v_end - v) * cb, hipMemcpyHostToDevice, st));
+        if (int s = send_head()) return s;
         auto launch = [&](auto zero) {
             using W = decltype(zero);
             hipLaunchKernelGGL(interleave_codes_kernel<W>, dim3((unsigned)blocks), dim3(256), 0, st, (const W*)(base + L.ids), v,
@@ -2302,6 +2332,7 @@ int upload_impl(ivfpq_index_t* idx, void* d_buf, size_t bytes, void* hip_stream)
         g = g_end;
         v = v_end;
     }
+    if (int s = send_head()) return s;
     if (idx->total_groups > 0) {
         const bool in_lds = n_words * 4 <= kLdsBytes;
         if (int s = allow_full_lds(list_radii_kernel)) return s;
@@ -2314,6 +2345,10 @@ int upload_impl(ivfpq_index_t* idx, void* d_buf, size_t bytes, void* hip_stream)
     if (idx->n > 0)
         HIP_TRY(hipMemcpyAsync(base + L.ids, idx->ids.data(), idx->ids.size() * 8, hipMemcpyHostToDevice, st));
     HIP_TRY(hipStreamSynchronize(st));
+    aside.wait();
+    idx->pass_shares = shares;
+    idx->centroid_norm_max = cn_max;
+    idx->word_norm_max = moderate ? std::sqrt(wn_max) * 1.0001f : -1.f;
 
     // set-up of the static scratch for this device (ivfpq_search_static looks it up here, not in the hot loop)
     void* scratch_dev = nullptr;

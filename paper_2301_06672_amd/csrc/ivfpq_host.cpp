@@ -35,6 +35,125 @@ int fail(int status, const char* fmt, ...) {
     return status;
 }
 
+// 32 decoded vectors stand for queries.  Each is compared with up to 64 vectors of its nearest cluster, whose quantiles stand for the
+// bound (the k-th smallest R of that cluster), and with up to 12 vectors of the clusters at ranks 1, 2, 4, ... 256: counted is how many
+// are not above the quantile, widened by looseness.  (10^6 vectors of 48 codes in 1,024 lists: 1.7 ms of one thread.)
+PassShares sample_pass_shares(const ivfpq_index& idx, uint64_t* near, float* q, float* r) noexcept {
+    constexpr int kOwn = 64, kOther = 12;
+    PassShares out;
+    const int d = idx.d, m = idx.m(), bits = idx.pq_bits, n_lists = idx.n_lists, cb = idx.code_bytes();
+    if (idx.n == 0 || n_lists < 2) return out;
+    const int64_t queries = std::max<int64_t>(8, std::min<int64_t>(32, 500000000 / ((int64_t)n_lists * d)));       // bounded work
+    const uint8_t* const codes = idx.codes.data();
+    const float* const books = idx.codebooks.data();
+    auto codeword = [=](int64_t v, int sub) {
+        const uint8_t* code = codes + (size_t)v * cb;
+        const int bit = sub * bits, at = bit >> 3, sh = bit & 7;
+        uint32_t c = code[at];
+        if (bits != 8) {
+            if (sh + bits > 8) c |= (uint32_t)code[at + 1] << 8;
+            c = (c >> sh) & ((1u << bits) - 1u);
+        }
+        return books + (((size_t)sub << bits) + c) * m;
+    };
+    auto distance_to = [&](int64_t v) {
+        // four sums at a time: each is one chain of additions
+        float part[4] = {};
+        auto add = [&](int sub, float& sum) {
+            const float *y = codeword(v, sub), *x = r + (size_t)sub * m;
+            if (m == 2) sum += (x[0] - y[0]) * (x[0] - y[0]) + (x[1] - y[1]) * (x[1] - y[1]);
+            else
+                for (int u = 0; u < m; ++u) sum += (x[u] - y[u]) * (x[u] - y[u]);
+        };
+        int sub = 0;
+        for (; sub + 4 <= idx.pq_dim; sub += 4) { add(sub, part[0]); add(sub + 1, part[1]); add(sub + 2, part[2]); add(sub + 3, part[3]); }
+        for (; sub < idx.pq_dim; ++sub) add(sub, part[0]);
+        const float sum = (part[0] + part[1]) + (part[2] + part[3]);
+        return sum < 3.0e38f ? sum : 3.0e38f;                // (a number in any case: they are sorted)
+    };
+    uint32_t passed[PassShares::kRanks][PassShares::kShares][PassShares::kLoose] = {}, compared[PassShares::kRanks] = {};
+    for (int64_t s = 0; s < queries; ++s) {
+        const int64_t v = (2 * s + 1) * idx.n / (2 * queries);
+        const int64_t l0 = std::upper_bound(idx.list_offsets.begin(), idx.list_offsets.end(), v) - idx.list_offsets.begin() - 1;
+        for (int sub = 0; sub < idx.pq_dim; ++sub)
+            for (int u = 0; u < m; ++u) q[(size_t)sub * m + u] = idx.centroids[(size_t)l0 * d + (size_t)sub * m + u] + codeword(v, sub)[u];
+        for (int l = 0; l < n_lists; ++l) {
+            const float* c = idx.centroids.data() + (size_t)l * d;
+            float acc[8] = {};
+            int t = 0;
+            for (; t + 8 <= d; t += 8)
+                for (int u = 0; u < 8; ++u) { const float x = q[(size_t)(t + u)] - c[t + u]; acc[u] += x * x; }
+            for (; t < d; ++t) { const float x = q[(size_t)t] - c[t]; acc[0] += x * x; }
+            const float dist = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
+            uint32_t key;
+            std::memcpy(&key, &dist, 4);
+            near[(size_t)l] = (uint64_t)key << 32 | (uint32_t)l;
+        }
+        uint64_t* end = near + n_lists;
+        for (int rank = PassShares::kRanks - 1; rank >= 0; --rank)          // the lists at ranks 256, 128, ... 1, and before them the nearest
+            if ((1 << rank) < n_lists) {
+                std::nth_element(near, near + (1 << rank), end);
+                end = near + (1 << rank);
+            }
+        float quantile[PassShares::kShares];
+        for (int slot = 0; slot <= PassShares::kRanks; ++slot) {
+            const int64_t place = slot == 0 ? 0 : (int64_t)1 << (slot - 1);
+            if (place >= n_lists) break;
+            const int64_t l = (uint32_t)near[(size_t)place], first = idx.list_offsets[(size_t)l], len = idx.list_offsets[(size_t)l + 1] - first;
+            const int n = (int)std::min<int64_t>(len, slot == 0 ? kOwn : kOther);
+            if (slot == 0 && n == 0) break;
+            for (int t = 0; t < d; ++t) r[(size_t)t] = q[(size_t)t] - idx.centroids[(size_t)l * d + (size_t)t];
+            for (int j = 0; j < n; ++j) __builtin_prefetch(codes + (size_t)(first + len * j / n) * cb);
+            float dist[kOwn];
+            for (int j = 0; j < n; ++j) dist[j] = distance_to(first + len * j / n);
+            if (slot == 0) {
+                std::sort(dist, dist + n);
+                for (int i = 0; i < PassShares::kShares; ++i) {                  // between the two values about the place in n + 1
+                    const float place = std::min((float)n, std::max(1.f, PassShares::share(i) * (float)(n + 1)));
+                    const int below = std::min(n - 1, (int)place) - 1;
+                    quantile[i] = n == 1 ? dist[0] : dist[below] + (dist[below + 1] - dist[below]) * (place - (float)(below + 1));
+                }
+                continue;
+            }
+            compared[slot - 1] += (uint32_t)n;
+            for (int i = 0; i < PassShares::kShares; ++i)
+                for (int w = 0; w < PassShares::kLoose; ++w) {
+                    const float limit = quantile[i] * (1.f + PassShares::looseness(w));
+                    for (int j = 0; j < n; ++j) passed[slot - 1][i][w] += dist[j] <= limit ? 1u : 0u;
+                }
+        }
+    }
+    for (int rank = 0; rank < PassShares::kRanks && compared[rank] > 0; ++rank, ++out.ranks)
+        for (int i = 0; i < PassShares::kShares; ++i)
+            for (int w = 0; w < PassShares::kLoose; ++w) out.pass[rank][i][w] = (float)passed[rank][i][w] / (float)compared[rank];
+    return out;
+}
+
+double pass_share(const PassShares& p, int n_probes, double share, double loose) {
+    if (share >= 1.0) return 1.0;                       // the bound is at the end of the list, or there is none
+    auto place = [](auto value, int count, double x, auto scale) {
+        int i = 0;
+        while (i + 2 < count && value(i + 1) <= x) ++i;
+        const double a = scale((double)value(i)), b = scale((double)value(i + 1));
+        return std::make_pair(i, std::min(1.0, std::max(0.0, (scale(x) - a) / (b - a))));
+    };
+    const auto s = place(PassShares::share, PassShares::kShares, share, [](double x) { return std::log(x); });
+    const auto l = place(PassShares::looseness, PassShares::kLoose, loose, [](double x) { return x; });
+    auto at = [&](int r) {
+        const auto& v = p.pass[r];
+        auto along = [&](int i) { return v[i][l.first] + (v[i][l.first + 1] - v[i][l.first]) * l.second; };
+        return along(s.first) + (along(s.first + 1) - along(s.first)) * s.second;
+    };
+    const int last = n_probes - 1;                      // ranks 1 .. last
+    double sum = 0.0;
+    for (int r = 0; r < p.ranks && (1 << r) <= last; ++r) {
+        const double here = at(r), next = r + 1 < p.ranks ? at(r + 1) : here, width = (double)(1 << r);
+        const double n = r + 1 < p.ranks ? std::min(last - (1 << r) + 1, 1 << r) : last - (1 << r) + 1;
+        sum += n * here + (next - here) / width * n * (n - 1) / 2;
+    }
+    return sum / last;
+}
+
 int check_shape(int64_t n, int32_t d, int32_t n_lists, int32_t pq_dim, int32_t pq_bits) {
     if (n < 0 || d < 1 || n_lists < 1 || pq_dim < 1)
         return fail(IVFPQ_EINVAL, "bad shape: n=%lld d=%d n_lists=%d pq_dim=%d", (long long)n, d, n_lists, pq_dim);

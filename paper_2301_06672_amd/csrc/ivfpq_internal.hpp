@@ -94,6 +94,23 @@ inline void copy_bytes(void* dst, const void* src, size_t bytes) {
         if (t.joinable()) t.join();
 }
 
+// The share of a farther cluster's vectors that pass the matrix-core filter, a property of the indexed vectors that their number does
+// not tell: lists that overlap pass many times what lists apart from each other do.  Sampled from the saved index: for clusters at
+// ranks 1, 2, 4, ... from a query, bounds of k / length = share, and limits wider than the bound by looseness.
+struct PassShares {
+    static constexpr int kRanks = 9, kShares = 7, kLoose = 4;
+    static constexpr float share(int s) {
+        constexpr float v[kShares] = {0.01f, 0.02f, 0.05f, 0.1f, 0.2f, 0.5f, 1.f};
+        return v[s];
+    }
+    static constexpr float looseness(int i) {
+        constexpr float v[kLoose] = {0.01f, 0.04f, 0.07f, 0.13f};
+        return v[i];
+    }
+    int ranks = 0;                                 // how many ranks there are figures for; 0: none
+    float pass[kRanks][kShares][kLoose] = {};
+};
+
 // Device image of an index.  All pointers point into the single buffer the caller handed to
 // ivfpq_upload; the library owns none of them.
 struct DeviceImage {
@@ -129,6 +146,7 @@ struct ivfpq_index {
     ivfpq::Fp8Options fp8_opt[2] = {{15, 0, 0}, {7, 0, 0}};   // e5m3, e4m4 (ivfpq_set_fp8_encoding)
     float centroid_norm_max = 0.f;      // largest squared centroid norm (set by ivfpq_upload)
     float word_norm_max = -1.f;         // largest codeword norm (set by ivfpq_upload); negative: some codeword is not a moderate number
+    ivfpq::PassShares pass_shares;      // set by ivfpq_upload
     size_t workspace_limit = (size_t)32 << 30;   // search scratch (R, positions, ranking values) per query tile
 
     ivfpq::Tuning tuning;               // ivfpq_set_tuning
@@ -157,6 +175,31 @@ struct ivfpq_index {
 };
 
 namespace ivfpq {
+
+// near: [n_lists] scratch; q, r: [d]
+PassShares sample_pass_shares(const ivfpq_index& idx, uint64_t* near, float* q, float* r) noexcept;
+// The share for a search: averaged over ranks 1 .. n_probes - 1, linear between the sampled ranks, in log(share) and in the looseness.
+double pass_share(const PassShares& p, int n_probes, double share, double loose);
+
+// Work on a thread of its own, or on this one where there is none to be had.  It must not throw; the destructor waits for it.
+class SideTask {
+public:
+    template <class F>
+    explicit SideTask(F work) {
+        try {
+            thread_ = std::thread(work);
+        } catch (...) {
+            work();
+        }
+    }
+    ~SideTask() { wait(); }
+    SideTask(const SideTask&) = delete;
+    SideTask& operator=(const SideTask&) = delete;
+    void wait() { if (thread_.joinable()) thread_.join(); }
+
+private:
+    std::thread thread_;
+};
 
 void set_error(const char* fmt, ...);
 int fail(int status, const char* fmt, ...);

@@ -941,9 +941,8 @@ def test_timed_search_names_the_kernel_it_launched(P):
     for nq, n_probes, k, dtype, kernel in (
             (3, 5, 10, e5m3, "scan_kernel"),                            # little work: all probes in one launch
             (10000, 4, 10, e5m3, "scan_kernel"),                        # 4 M vectors: in query order
-            (170000, 2, 10, e5m3, "scan_group_kernel"),                 # two of 700 lists, k a tenth of a list, one-byte tables
-            (170000, 2, 10, half, "scan_filter_kernel"),
-            (170000, 2, 100, half, "scan_group_kernel")):               # k a whole list
+            (170000, 2, 10, e5m3, "scan_filter_kernel"),
+            (170000, 2, 100, e5m3, "scan_group_kernel")):               # k a whole list
         q = rng.standard_normal((nq, 64)).astype(np.float32)
         gidx.ivfpq_search(q, n_probes, k, dtype)
         torch.cuda.synchronize()
@@ -952,6 +951,33 @@ def test_timed_search_names_the_kernel_it_launched(P):
         assert name(half if dtype == e5m3 else e5m3) == "scan_filter_kernel"          # another dtype: the general description
     gidx.ivfpq_set_stage_timing(False)
     assert name(half) == "scan_filter_kernel"
+
+
+@pytest.mark.parametrize("overlap", [False, True])
+@pytest.mark.parametrize("d,pq_dim,pq_bits", [(128, 32, 8), (96, 48, 8), (128, 64, 7), (128, 64, 4)])
+def test_filter_is_left_to_the_tables_where_lists_overlap(P, d, pq_dim, pq_bits, overlap):
+    # the same sizes and the same call: lists around centroids far apart hold few vectors that can be among the results, those around
+    # nearly one point as many as the nearest list does.  One empty list, and lists of 1 vector to thousands, are sampled
+    # too.  Either way, the results of the other kernels, bit for bit.
+    arrays = list(si.random_index_arrays(30000, d, 60, pq_dim, pq_bits, salt=91, empty_lists=(7,)))
+    if overlap:
+        arrays[0] = (0.02 * arrays[0]).astype(np.float32)
+    gidx = to_library(P, oracle.make_index(d, 60, pq_dim, pq_bits, *arrays))
+    rng = np.random.default_rng(91)
+    cent = arrays[0][rng.integers(0, 60, 8000)]
+    q = (cent + 0.3 * rng.standard_normal(cent.shape)).astype(np.float32)
+    gidx.ivfpq_set_stage_timing(True)
+    out = {}
+    for dtype in (oracle.LUT_E5M3, oracle.LUT_FP32):
+        for route in (0, 2, 3):
+            gidx.ivfpq_set_tuning(P.TUNE_SCAN_ROUTE, route)
+            out[route] = [t.cpu().numpy() for t in gidx.ivfpq_search(q, 20, 250, dtype)]
+            name = gidx.ivfpq_scan_kernel_info(dtype)
+            _step(f"d={d} p={pq_bits} overlap={overlap} dtype={dtype} route={route}: {name}")
+            assert name.startswith("scan_filter_kernel") == (route == 3 or (route == 0 and not overlap))
+        for a, b, c in zip(*out.values()):
+            np.testing.assert_array_equal(a, b)
+            np.testing.assert_array_equal(a, c)
 
 
 @pytest.mark.parametrize("nq", [1, 31, 33, 500, 2047, 2049])
