@@ -42,6 +42,7 @@
 #include <type_traits>
 #include <utility>
 
+#include "ivfpq_filter_bound.hpp"
 #include "ivfpq_internal.hpp"
 #include "ivfpq_rank.hpp"
 #include "ivfpq_lds_util.hpp"
@@ -1102,7 +1103,7 @@ __global__ void __launch_bounds__(256) stream_read_kernel(const uint4* __restric
 }
 
 // Pairs whose cluster cannot hold a vector with R <= bound.  Every decoded residual y of the cluster has |y| <= its radius,
-// so |r - y| >= |r| - radius, and a vector with R <= bound has |r - y|^2 <= bound * scale + add (filter_constants) unless an
+// so |r - y| >= |r| - radius, and a vector with R <= bound has |r - y|^2 <= bound * scale + add (filter_bound) unless an
 // entry of its sum saturated, which alone makes R >= top.  The counting pass marks such a pair (its distance turned negative); the
 // scatter leaves it out.  (10^7 vectors, 50 probes, k = 100, 2,000 Gaussian components: 74 % of the pairs.)
 struct PairCull {
@@ -1116,9 +1117,8 @@ struct PairCull {
         float* const at = probe_dists + (size_t)q * n_probes + p;
         const uint32_t bnd = bounds[q];
         const float rr = *at, bound = __uint_as_float(bnd);
-        // (a relative 2^-13 for the rounding of either norm: sums of at most 128 squares)
-        const float gap = __builtin_sqrtf(rr) * 0.99987f - __builtin_sqrtf(radii2[l]) * 1.00013f;
-        const bool out = bnd < 0x7F800000u && bound < top * 0.9999f && gap > 0.f && gap * gap > __builtin_fmaf(bound, scale, add) * 1.0001f && rr < 1.0e30f;
+        const float gap = __builtin_sqrtf(rr) * kCullNear - __builtin_sqrtf(radii2[l]) * kCullRadius;
+        const bool out = bnd < 0x7F800000u && bound < top * kCullTop && gap > 0.f && gap * gap > __builtin_fmaf(bound, scale, add) * kCullLimit && rr < 1.0e30f;
         if (out) *at = -1.f;
         return !out;
     }
@@ -1832,14 +1832,6 @@ bool filter_applies(const ivfpq_index* idx, int lut_dtype, const Fp8Mode& fp8) {
     return t.early_exit >= 0 && t.scan_share == 0 && t.order_block == 0 && t.scan_threads == 0 && t.lds_pad == 0 && !fp8.per_table &&
            idx->word_norm_max >= 0.f && filter_supported(idx->pq_bits, idx->pq_dim, idx->d, chunk_width(idx));
 }
-// The largest share of an entry that its stored form is below it: half 2^-11, 8-bit formats of M mantissa bits 1 / (2^(M+1) + 1) rounded to
-// nearest, 1 / (2^M + 1) truncated.
-double stored_loss(int lut_dtype, const Fp8Mode& fp8) {
-    if (lut_dtype == IVFPQ_LUT_FP32) return 0.0;
-    if (lut_dtype == IVFPQ_LUT_FP16) return 1.0 / 2048;
-    const int mantissa = lut_dtype == IVFPQ_LUT_FP8_E5M3 ? 3 : 4;
-    return 1.0 / ((1 << (fp8.truncate ? mantissa : mantissa + 1)) + 1);
-}
 // By the number of vectors that are looked up, as scan_route, and by k against the length of a list: the bound is the k-th of one list.
 // The filter has a cost of its own (codebooks that two kernels load); us a search, the better table route / filter:
 //   k / length 0.01  6 M 75 / 64, 75 / 77, 84 / 81, 68 / 71, 93 / 72, 82 / 78; 9 M 91 / 64, 91 / 81, 102 / 92, 82 / 83, 121 / 91, 125 / 85
@@ -1869,21 +1861,16 @@ bool filter_pays(const ivfpq_index* idx, int lut_dtype, const Fp8Mode& fp8, int 
     else if (idx->pq_bits == 8) most = (bytes == 1 ? 0.045 : bytes == 2 ? 0.11 : 0.14) + 0.001 * idx->pq_dim;
     else most = bytes == 1 ? 0.07 : 0.14;
     most *= std::min(1.0, pairs / (double)idx->n_lists / 12.0);
-    const double wider = 1.0 / (1.0 - stored_loss(lut_dtype, fp8)) - 1.0 + 0.012;            // of the limit against the bound; the rest is eta's
+    const double wider = 1.0 / (1.0 - stored_loss(lut_dtype, fp8.truncate)) - 1.0 + 0.012;            // of the limit against the bound; the rest is eta's
     return pass_share(idx->pass_shares, n_probes, share, wider) <= most;
 }
-// What |r - y|^2 of a vector with R <= bound is limited by: bound * scale + add, where no entry saturates (the kernel sees to
-// those that may).  A stored entry is below its distance by at most the share `loss` (stored_loss; and 2^-25 where a half is subnormal); the 2^-16 cover the
-// sum of up to 128 entries and the rounding of an entry's own distance.  eta: r.y is formed from bf16 operands (2^-8 + 2^-18 of the sum
-// of magnitudes, which is at most (|r|^2 + |y|^2) / 2), summed with the threshold in any order (4 (d + 2) 2^-24 of either, with
-// a factor 4 of slack as for the ranking values), |r|^2 is a sum of d squares.
 void filter_constants(const ivfpq_index* idx, int lut_dtype, const Fp8Mode& fp8, FilterArgs* a) {
-    const double loss = stored_loss(lut_dtype, fp8), below = lut_dtype == IVFPQ_LUT_FP16 ? idx->pq_dim * std::ldexp(1.0, -25) : 0.0;
-    a->scale = (float)((1.0 + std::ldexp(1.0, -15)) / (1.0 - loss));
-    a->add = (float)(below / (1.0 - loss) * 1.001 + 1e-30);
+    const FilterBound bound = filter_bound(lut_dtype, fp8.truncate, idx->pq_dim, idx->d);
+    a->scale = bound.scale;
+    a->add = bound.add;
+    a->eta = bound.eta;
     a->top = table_top(lut_dtype, fp8);
     a->word_norm_max = idx->word_norm_max;
-    a->eta = (float)(0.00392 + (12.0 * idx->d + 64.0) * std::ldexp(1.0, -24));
     a->fp8 = fp8.fixed;
     a->truncate = fp8.truncate;
 }
@@ -2348,7 +2335,7 @@ int upload_impl(ivfpq_index_t* idx, void* d_buf, size_t bytes, void* hip_stream)
     aside.wait();
     idx->pass_shares = shares;
     idx->centroid_norm_max = cn_max;
-    idx->word_norm_max = moderate ? std::sqrt(wn_max) * 1.0001f : -1.f;
+    idx->word_norm_max = moderate ? std::sqrt(wn_max) * kWordNormSlack : -1.f;
 
     // set-up of the static scratch for this device (ivfpq_search_static looks it up here, not in the hot loop)
     void* scratch_dev = nullptr;

@@ -15,6 +15,7 @@
 
 #include <type_traits>
 
+#include "ivfpq_filter_bound.hpp"
 #include "ivfpq_hip_util.hpp"
 #include "ivfpq_lds_util.hpp"
 #include "ivfpq_scan_filter.hpp"
@@ -32,7 +33,6 @@ constexpr int kTurnPitch = 256 + 16;                    // bytes between rows of
 // a wave's own LDS, in words: rows of residuals in turn, then a word per (step, slot); behind them two thresholds per slot
 constexpr int kStartWords = kFilterSteps * 64 * 4 > 16 * kTurnPitch ? kFilterSteps * 64 : 16 * kTurnPitch / 4;
 constexpr int kWaveWords = kStartWords + 128;
-constexpr float kSquareLoss = 0.00394f;                 // a sum of squares of bf16 roundings is at most 1 + this times the sum of the squares
 constexpr float kNever = -3.0e38f, kAlways = 3.0e38f;
 
 // BITS: bits of a code; M: components of a sub-space; STEPS: d / 16.
@@ -163,8 +163,8 @@ __device__ __forceinline__ void filter_item(const FilterArgs& a, uint32_t* bits,
         float hidden = 0.f;
         if (a.top < 3.4e38f) {
             auto entry_max = [&](float n2) __attribute__((always_inline)) {          // n2: from components rounded to bf16
-                const float x = __builtin_sqrtf(n2 * 1.008f) + a.word_norm_max;
-                return x * x * 1.00001f;
+                const float x = __builtin_sqrtf(n2 * kRoundedNorm) + a.word_norm_max;
+                return x * x * kEntrySlack;
             };
             auto norms = [&](auto sink) __attribute__((always_inline)) {
 #pragma unroll
@@ -187,12 +187,12 @@ __device__ __forceinline__ void filter_item(const FilterArgs& a, uint32_t* bits,
             if (ballot64(!(entry_max(big) <= a.top)) != 0) {
                 norms([&](float n2) { hidden += fmaxf(entry_max(n2) - a.top, 0.f); });
                 hidden += __shfl_xor(hidden, 32, 64);
-                hidden *= 1.0001f;
+                hidden *= kHiddenSlack;
             }
         }
         // R <= bound implies r.y >= (|r|^2 + |y|^2 - limit) / 2; the product formed here is within eta (|r|^2 + |y|^2) / 2 and
         // the rounding of the threshold's own terms of r.y
-        const float limit = __builtin_fmaf(__uint_as_float(bnd), a.scale, a.add) + hidden, wide = limit * (1.f + a.eta * 0.0625f);
+        const float limit = __builtin_fmaf(__uint_as_float(bnd), a.scale, a.add) + hidden, wide = limit * (1.f + a.eta * kLimitShare);
         float c = 0.5f * (wide - (1.f - a.eta) * rr);
         // the same for the components of the first H steps alone, whose share of the distance is no more than all of it
         float rr1 = 0.f;

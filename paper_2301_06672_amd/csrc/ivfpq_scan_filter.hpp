@@ -27,7 +27,7 @@ struct FilterArgs {
     const uint32_t* n_items;
     int nq, n_probes;
     int d, pq_dim, m, bits, code_bytes, chunk_width;
-    // R <= bound needs |r - y|^2 <= bound * scale + add + (what saturation may hide); see filter_constants
+    // R <= bound needs |r - y|^2 <= bound * scale + add + (what saturation may hide); see filter_bound
     float scale, add, top, word_norm_max, eta;
     Fp8Params fp8;                // decode and encode constants of the 8-bit tables
     int truncate;

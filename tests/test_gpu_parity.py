@@ -901,6 +901,25 @@ def test_matrix_core_filter(P, d, pq_dim, pq_bits, scale):
                 assert_topk_matches(ids_f[:40], d_f[:40], ids_o, d_o, context=info)
 
 
+@pytest.mark.parametrize("dtype,bias", [(oracle.LUT_E5M3, 15), (oracle.LUT_E5M3, 24), (oracle.LUT_E5M3, 2), (oracle.LUT_E5M3, -96),
+                                        (oracle.LUT_E4M4, 7), (oracle.LUT_E4M4, 12), (oracle.LUT_E4M4, 0), (oracle.LUT_E4M4, -100)])
+@pytest.mark.parametrize("truncate", [False, True])
+def test_matrix_core_filter_other_encodings(P, dtype, bias, truncate):
+    # the filter's limit and the candidates' entries follow the encoding: biases that clamp small entries from below (all of them:
+    # every sum is the same), rounding and truncation; the table kernels' bits
+    oidx, gidx = random_pair(P, 6000, 128, 12, 64, 8, salt=79, empty_lists=(4,))
+    gidx.ivfpq_set_fp8_encoding(dtype, bias, P.ROUND_TRUNCATE if truncate else P.ROUND_NEAREST)
+    q = np.random.default_rng(79).standard_normal((222, 128)).astype(np.float32)
+    got = []
+    for route in (2, 3):
+        gidx.ivfpq_set_tuning(P.TUNE_SCAN_ROUTE, route)
+        _step(f"encoding dtype={dtype} bias={bias} truncate={truncate} route={route}: {gidx.ivfpq_scan_kernel_info(dtype)}")
+        got.append([t.cpu().numpy() for t in gidx.ivfpq_search(q, 8, 20, dtype)])
+    assert gidx.ivfpq_scan_kernel_info(dtype).startswith("scan_filter_kernel")
+    np.testing.assert_array_equal(got[0][1].view(np.uint32), got[1][1].view(np.uint32))
+    np.testing.assert_array_equal(got[0][0], got[1][0])
+
+
 def test_matrix_core_filter_leaves_other_calls_to_the_tables(P):
     # encoding by a bias per table, knobs of the table kernels, queries that are not 8-byte aligned and codebooks that are no
     # moderate numbers: the table kernels, with the same results
