@@ -931,7 +931,7 @@ int fill_u32(uint32_t* p, size_t n, uint32_t v, hipStream_t st) {
 
 // One product in half precision (nearest_by_halves), from 12 M values on: its ten launches cost more than the three products below that
 // (us, strip summaries / one product: 2.4 M 115 / 118, 5.1 M 83 / 122, 15 M 172 / 127, 20 M 150 / 104, 27 M 183 / 97, 150 M 231 / 139,
-// 500 M 899 / 326, 5,000 M 4,290 / 1,500).
+// 500 M 899 / 326, 5,000 M 4,330 / 1,280).
 bool near_pays(size_t n_rows, int k) { return n_rows * (size_t)k >= 12000000; }
 
 // labels[i] = nearest centre of X[i], for n_rows rows

@@ -14,7 +14,7 @@
 // Error of a value (near_error): half rounds either operand by 2^-11, so r.y is off by 2^-10 |x'||c'|; the sum of d + 1 terms in fp32 in any
 // order (4 (d + 10) 2^-24 of the magnitudes, a factor 4 of slack as for the other ranking values), the position in the low four bits of a value
 // (2^-19), operands below the half's normal range.
-// 500,000 rows of 96 components against 10,000 centres: 1.5 ms; three products of bf16 halves, summaries of every strip of 64 centres
+// 500,000 rows of 96 components against 10,000 centres: 1.3 ms; three products of bf16 halves, summaries of every strip of 64 centres
 // stored and read back (nearest_strips_kernel), 4.3 ms.
 #pragma once
 
