@@ -1839,28 +1839,46 @@ bool filter_applies(const ivfpq_index* idx, int lut_dtype, const Fp8Mode& fp8) {
 //              0.1   6 M 92 / 97, 96 / 125, 97 / 95, 145 / 122; 12 M 134 / 116, 142 / 160, 140 / 113, 237 / 164; 30 M 270 / 144, 244 / 206
 // (200,000 unit-norm rows in 200 lists, 60 and 20 probes; 10^6 in 1,024, 20; 200,000 of 128 components in 100, 30, where 0.05; 100,000 in
 // 100, 30, where 0.01 and 0.1; 10^6 in 555, 4-bit codes, 30).
-// A listed vector costs several table lookups' worth, so of larger batches the share that passes decides, which the upload sampled
-// (pass_share; one-byte tables, whose rounding widens the limit, list more).  Filter's time over the tables' at sampled shares, 10,000
-// queries, 20 and 60 probes, 2 10^6 and 10^7 vectors of overlapping (1 to 250 Gaussian components) and separate lists, k / length 0.01 to 0.6:
-//   8-bit codes    e5m3  32 sub-spaces 0.06 0.87-0.95, 0.08 1.0, 0.1 1.29, 0.2 2.0; 48 0.055 0.71, 0.085 0.97-1.01, 0.13 1.34; 64 0.07 0.71, 0.11 1.02, 0.17 1.37
-//                  half  32 0.07 0.71-0.78, 0.15 1.0-1.06, 0.21 1.41; 48 0.08 0.68, 0.15 0.96-1.0, 0.2 1.1; 64 0.17 1.0, 0.23 1.15
-//                  float 32 0.15 0.82-0.90, 0.21 1.14-1.18; tables too large for two pairs (one-pair kernel) 0.3 0.72, 0.4 0.82
-//   7, 6           e5m3  0.07 1.07, 0.86, 0.11 1.22, 1.14; half 0.1 0.87, 0.81, 0.16 0.95, 0.90, 0.22 1.11, 1.24; float 0.1 0.81, 1.0, 0.16 0.92, 1.11
-//   4              e5m3  0.05 0.92-0.94, 0.09 1.38; half 0.035 1.02, 0.046 1.07, 0.059 1.20; float 0.035 1.05, 0.059 1.24; one-pair kernel (24-byte
-//                  codes) e5m3 0.13 0.78, 0.16 1.24, half 0.09 0.77, 0.15 0.80, 0.19 1.20
-// With few pairs a list the filter's blocks of 32 rows are mostly empty: 4 pairs, 8 bits, e5m3 0.03 1.05-1.09, half 0.055 1.0, 0.09 1.08, float 0.09 0.96.
+// Of larger batches the cheaper side by what either spends, in listed vectors (25 to 45 ps each): the tables `pair` for a pair's table and
+// `vector` for a vector looked up; the filter one for each vector that it lists, whose share the upload sampled (pass_share; one-byte
+// tables, whose rounding widens the limit, list more), and `block` for a vector of a list and each 64 of the list's pairs, however
+// few of a block there are.  Fitted to 3,081 searches: 10^6 to 10^8 vectors in lists of 500 to 3,300 and of 1 to 1,000 Gaussian components, 1 to 2,000
+// pairs a list, k / length 0.005 to 0.8, every code length and table.  The side taken is 0.4 % slower than the better one in the
+// mean, 1.7 % of the searches lose more than a tenth, the worst takes 1.75 times as long.  Some of them, us, tables / filter, by the sampled share:
+//   10^8 vectors in 50,000 lists, 64 probes, 10,000 queries (13 pairs a list), 32-byte codes   e5m3 0.021 4,980 / 4,831, 0.048 5,284 / 7,279;
+//                  half 0.008 5,814 / 4,111, 0.017 6,165 / 5,198, 0.087 6,982 / 9,633; float 0.017 7,839 / 5,084, 0.086 8,442 / 9,489
+//                  64 codes of 4 bits e5m3 0.019 5,768 / 5,746, 0.061 5,972 / 8,017; half 0.008 4,579 / 4,999, 0.022 4,774 / 5,888
+//   the same, 20 probes (4 pairs a list), 32-byte codes   e5m3 0.039 2,425 / 3,006; half 0.015 2,820 / 2,599, 0.033 3,036 / 3,869
+//   10^7 in 5,000 (126 pairs a list)    e5m3 0.009 3,450 / 1,629, 0.024 3,655 / 2,599;  in 20,000 (32)  0.087 2,767 / 1,912, 0.285 3,215 / 4,496
+struct FilterCost {
+    double pair, vector, block;
+};
+FilterCost filter_cost(int bits, int pq_dim, int table_bytes, bool one_pair) {
+    if (one_pair) {                     // tables too large for two pairs, or codes not in 16-byte pieces
+        if (bits == 4) return table_bytes == 1 ? FilterCost{42, 0.088, 0.2} : table_bytes == 2 ? FilterCost{65, 0.14, 0.1} : FilterCost{74, 0.17, 0.1};
+        return FilterCost{100, 0.14 + 0.0024 * pq_dim, 0.4};
+    }
+    if (bits == 8)
+        return table_bytes == 1 ? FilterCost{45, 0.001 * pq_dim, 0.25}
+             : table_bytes == 2 ? FilterCost{110, 0.002 * pq_dim - 0.02, 0.4} : FilterCost{95, 0.0032 * pq_dim - 0.02, 0.44};
+    if (bits == 4) {
+        if (table_bytes == 1) return FilterCost{57, 0.00054 * pq_dim, 0.4};
+        // (float tables of 32 4-bit codes: the table kernel takes five times as long as with 64)
+        return table_bytes == 4 && pq_dim < 64 ? FilterCost{50, 0.25, 0.5} : FilterCost{24, 0.027, 0.5};
+    }
+    const FilterCost c = table_bytes == 1 ? FilterCost{20, 0.078, 0.4} : table_bytes == 2 ? FilterCost{60, 0.2, 0.4}
+                       : bits == 7 ? FilterCost{60, 0.18, 0.4} : FilterCost{50, 0.1, 0.4};
+    return FilterCost{c.pair, c.vector * pq_dim / 64.0, c.block};
+}
 bool filter_pays(const ivfpq_index* idx, int lut_dtype, const Fp8Mode& fp8, int nq, int n_probes, int k) {
     if (idx->tuning.scan_route != 0) return true;
     const double length = (double)idx->n / (double)idx->n_lists, share = (double)k / length, pairs = (double)nq * (n_probes - 1);
     if (!(pairs * length >= kFilterLookups + 1e8 * share) || idx->pass_shares.ranks == 0) return false;
-    const int bytes = lut_elem_bytes(lut_dtype);
-    const bool nibbles = idx->pq_bits == 4, one_pair = scan_group_width(idx, lut_dtype, fp8, kOrderBlock) == 0;
-    double most;
-    if (one_pair) most = bytes == 1 ? 0.12 : nibbles ? 0.15 : bytes == 2 ? 0.28 : 0.45;
-    else if (nibbles) most = bytes == 1 ? 0.06 : 0.035;
-    else if (idx->pq_bits == 8) most = (bytes == 1 ? 0.045 : bytes == 2 ? 0.11 : 0.14) + 0.001 * idx->pq_dim;
-    else most = bytes == 1 ? 0.07 : 0.14;
-    most *= std::min(1.0, pairs / (double)idx->n_lists / 12.0);
+    const FilterCost c = filter_cost(idx->pq_bits, idx->pq_dim, lut_elem_bytes(lut_dtype), scan_group_width(idx, lut_dtype, fp8, kOrderBlock) == 0);
+    // blocks a pair: of few pairs a list, some lists have none; of many, half a block more than is full
+    const double per_list = pairs / (double)idx->n_lists;
+    const double blocks = per_list < 20 ? (1.0 - std::exp(-per_list)) / per_list : std::min(1.0 / per_list, 1.0 / kFilterPairs + 0.5 / per_list);
+    const double most = std::min(0.5, c.pair / length + c.vector - c.block * blocks);       // (nothing was measured of shorter lists)
     const double wider = 1.0 / (1.0 - stored_loss(lut_dtype, fp8.truncate)) - 1.0 + 0.012;            // of the limit against the bound; the rest is eta's
     return pass_share(idx->pass_shares, n_probes, share, wider) <= most;
 }

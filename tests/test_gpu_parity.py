@@ -999,6 +999,31 @@ def test_filter_is_left_to_the_tables_where_lists_overlap(P, d, pq_dim, pq_bits,
             np.testing.assert_array_equal(a, c)
 
 
+def test_filter_is_left_to_the_tables_where_lists_have_few_pairs(P):
+    # a block of 64 pairs costs the filter the same however few there are: 4 pairs a list of 2,000 vectors take the tables, 100 the
+    # filter, with either call's results equal on both
+    arrays = si.random_index_arrays(1600000, 128, 800, 32, 8, salt=93)
+    gidx = to_library(P, oracle.make_index(128, 800, 32, 8, *arrays))
+    rng = np.random.default_rng(93)
+    gidx.ivfpq_set_stage_timing(True)
+    dtype = oracle.LUT_E5M3
+    for nq, kernel in ((320, "scan_group_kernel"), (8000, "scan_filter_kernel")):
+        cent = arrays[0][rng.integers(0, 800, nq)]
+        q = (cent + 0.3 * rng.standard_normal(cent.shape)).astype(np.float32)
+        out = []
+        for route, order_block, expected in ((0, 0, kernel), (3, 0, "scan_filter_kernel"), (3, 64, "scan_group_kernel")):
+            gidx.ivfpq_set_tuning(P.TUNE_SCAN_ROUTE, route)
+            gidx.ivfpq_set_tuning(P.TUNE_ORDER_BLOCK, order_block)
+            out.append([t.cpu().numpy() for t in gidx.ivfpq_search(q, 11, 20, dtype)])
+            name = gidx.ivfpq_scan_kernel_info(dtype)
+            _step(f"nq={nq} route={route} order_block={order_block}: {name}")
+            assert name.startswith(expected)
+        gidx.ivfpq_set_tuning(P.TUNE_ORDER_BLOCK, 0)
+        for other in out[1:]:
+            np.testing.assert_array_equal(out[0][0], other[0])
+            np.testing.assert_array_equal(out[0][1].view(np.uint32), other[1].view(np.uint32))
+
+
 @pytest.mark.parametrize("nq", [1, 31, 33, 500, 2047, 2049])
 def test_candidates_of_few_queries_are_shared_by_workgroups(P, nq):
     # long candidate lists (k a third of a list) of few queries are summed by several workgroups each, of many by one: every
