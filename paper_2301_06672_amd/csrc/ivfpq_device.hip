@@ -2253,7 +2253,6 @@ int upload_impl(ivfpq_index_t* idx, void* d_buf, size_t bytes, void* hip_stream)
     const int cb = idx->code_bytes(), cw = chunk_width(idx), nch = cb / cw;
     // Everything before the codes is put together on the host and travels as one (a copy of a few kB costs what 1 MB costs), behind the
     // first codes.  The norms in it and the sample that filter_pays needs are made beside the transfers, which one thread of the host stages.
-    // (The scratch is made here: a new thread's first allocation sets up a heap of its own.)
     const size_t n_words = (size_t)idx->pq_dim << idx->pq_bits;
     ivfpq::HostArray<unsigned char> head(L.codes);
     float cn_max = 0.f, wn_max = 0.f;
@@ -2282,14 +2281,12 @@ int upload_impl(ivfpq_index_t* idx, void* d_buf, size_t bytes, void* hip_stream)
     };
     ivfpq::PassShares shares;
     const bool may_filter = filter_supported(idx->pq_bits, idx->pq_dim, idx->d, cw);
-    std::vector<uint64_t> near(may_filter ? (size_t)idx->n_lists : 0);
-    std::vector<float> sampled(may_filter ? 2 * (size_t)idx->d : 0);
     std::memset(head.data(), 0, head.size());
     std::atomic<bool> normed{false};
     ivfpq::SideTask aside([&] {
         norms();
         normed.store(true, std::memory_order_release);
-        if (may_filter) shares = ivfpq::sample_pass_shares(*idx, near.data(), sampled.data(), sampled.data() + idx->d);
+        if (may_filter) shares = ivfpq::sample_pass_shares(*idx);
     });
     std::memcpy(head.data() + L.centroids, idx->centroids.data(), idx->centroids.size() * 4);
     std::memcpy(head.data() + L.codebooks, idx->codebooks.data(), idx->codebooks.size() * 4);

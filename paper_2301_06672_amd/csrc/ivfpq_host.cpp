@@ -2,11 +2,13 @@
 // builder (arXiv 2301.06672, Sec. I-C, first enumeration: clustering, residuals, product
 // quantisation, saved lists).  Index construction is not part of the timed search path.
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstring>
 #include <limits>
 #include <memory>
 #include <numeric>
+#include <optional>
 
 #include <omp.h>
 
@@ -38,12 +40,17 @@ int fail(int status, const char* fmt, ...) {
 // 32 decoded vectors stand for queries.  Each is compared with up to 64 vectors of its nearest cluster, whose quantiles stand for the
 // bound (the k-th smallest R of that cluster), and with up to 12 vectors of the clusters at ranks 1, 2, 4, ... 256: counted is how many
 // are not above the quantile, widened by looseness.  (10^6 vectors of 48 codes in 1,024 lists: 1.7 ms of one thread.)
-PassShares sample_pass_shares(const ivfpq_index& idx, uint64_t* near, float* q, float* r) noexcept {
-    constexpr int kOwn = 64, kOther = 12;
+PassShares sample_pass_shares(const ivfpq_index& idx) noexcept {
+    constexpr int kOwn = 64, kOther = 12, kThreads = 4, kNearest = 257, kNear = 1024, kMaxDim = 128;
     PassShares out;
-    const int d = idx.d, m = idx.m(), bits = idx.pq_bits, n_lists = idx.n_lists, cb = idx.code_bytes();
+    if (idx.d > kMaxDim) return out;
+    const int d = idx.d, m = idx.m(), bits = idx.pq_bits, pq_dim = idx.pq_dim, n_lists = idx.n_lists, cb = idx.code_bytes();
     if (idx.n == 0 || n_lists < 2) return out;
-    const int64_t queries = std::max<int64_t>(8, std::min<int64_t>(32, 500000000 / ((int64_t)n_lists * d)));       // bounded work
+    // Beside a transfer of these bytes: fewer queries where there are many lists for them.  Large indexes have a transfer for the sample to
+    // hide behind, which more threads would slow down.
+    const int64_t bytes = idx.n * (cb + 8), per_query = (int64_t)n_lists * d;
+    const int64_t queries = std::max<int64_t>(8, std::min<int64_t>(32, std::min<int64_t>(500000000, bytes + 16000000) / per_query));
+    const int threads = bytes > 32000000 ? 2 : kThreads;
     const uint8_t* const codes = idx.codes.data();
     const float* const books = idx.codebooks.data();
     auto codeword = [=](int64_t v, int sub) {
@@ -56,7 +63,7 @@ PassShares sample_pass_shares(const ivfpq_index& idx, uint64_t* near, float* q, 
         }
         return books + (((size_t)sub << bits) + c) * m;
     };
-    auto distance_to = [&](int64_t v) {
+    auto distance_to = [=](const float* r, int64_t v) {
         // four sums at a time: each is one chain of additions
         float part[4] = {};
         auto add = [&](int sub, float& sum) {
@@ -66,66 +73,94 @@ PassShares sample_pass_shares(const ivfpq_index& idx, uint64_t* near, float* q, 
                 for (int u = 0; u < m; ++u) sum += (x[u] - y[u]) * (x[u] - y[u]);
         };
         int sub = 0;
-        for (; sub + 4 <= idx.pq_dim; sub += 4) { add(sub, part[0]); add(sub + 1, part[1]); add(sub + 2, part[2]); add(sub + 3, part[3]); }
-        for (; sub < idx.pq_dim; ++sub) add(sub, part[0]);
+        for (; sub + 4 <= pq_dim; sub += 4) { add(sub, part[0]); add(sub + 1, part[1]); add(sub + 2, part[2]); add(sub + 3, part[3]); }
+        for (; sub < pq_dim; ++sub) add(sub, part[0]);
         const float sum = (part[0] + part[1]) + (part[2] + part[3]);
         return sum < 3.0e38f ? sum : 3.0e38f;                // (a number in any case: they are sorted)
     };
-    uint32_t passed[PassShares::kRanks][PassShares::kShares][PassShares::kLoose] = {}, compared[PassShares::kRanks] = {};
-    for (int64_t s = 0; s < queries; ++s) {
-        const int64_t v = (2 * s + 1) * idx.n / (2 * queries);
-        const int64_t l0 = std::upper_bound(idx.list_offsets.begin(), idx.list_offsets.end(), v) - idx.list_offsets.begin() - 1;
-        for (int sub = 0; sub < idx.pq_dim; ++sub)
-            for (int u = 0; u < m; ++u) q[(size_t)sub * m + u] = idx.centroids[(size_t)l0 * d + (size_t)sub * m + u] + codeword(v, sub)[u];
-        for (int l = 0; l < n_lists; ++l) {
-            const float* c = idx.centroids.data() + (size_t)l * d;
-            float acc[8] = {};
-            int t = 0;
-            for (; t + 8 <= d; t += 8)
-                for (int u = 0; u < 8; ++u) { const float x = q[(size_t)(t + u)] - c[t + u]; acc[u] += x * x; }
-            for (; t < d; ++t) { const float x = q[(size_t)t] - c[t]; acc[0] += x * x; }
-            const float dist = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
-            uint32_t key;
-            std::memcpy(&key, &dist, 4);
-            near[(size_t)l] = (uint64_t)key << 32 | (uint32_t)l;
-        }
-        uint64_t* end = near + n_lists;
-        for (int rank = PassShares::kRanks - 1; rank >= 0; --rank)          // the lists at ranks 256, 128, ... 1, and before them the nearest
-            if ((1 << rank) < n_lists) {
-                std::nth_element(near, near + (1 << rank), end);
-                end = near + (1 << rank);
-            }
-        float quantile[PassShares::kShares];
-        for (int slot = 0; slot <= PassShares::kRanks; ++slot) {
-            const int64_t place = slot == 0 ? 0 : (int64_t)1 << (slot - 1);
-            if (place >= n_lists) break;
-            const int64_t l = (uint32_t)near[(size_t)place], first = idx.list_offsets[(size_t)l], len = idx.list_offsets[(size_t)l + 1] - first;
-            const int n = (int)std::min<int64_t>(len, slot == 0 ? kOwn : kOther);
-            if (slot == 0 && n == 0) break;
-            for (int t = 0; t < d; ++t) r[(size_t)t] = q[(size_t)t] - idx.centroids[(size_t)l * d + (size_t)t];
-            for (int j = 0; j < n; ++j) __builtin_prefetch(codes + (size_t)(first + len * j / n) * cb);
-            float dist[kOwn];
-            for (int j = 0; j < n; ++j) dist[j] = distance_to(first + len * j / n);
-            if (slot == 0) {
-                std::sort(dist, dist + n);
-                for (int i = 0; i < PassShares::kShares; ++i) {                  // between the two values about the place in n + 1
-                    const float place = std::min((float)n, std::max(1.f, PassShares::share(i) * (float)(n + 1)));
-                    const int below = std::min(n - 1, (int)place) - 1;
-                    quantile[i] = n == 1 ? dist[0] : dist[below] + (dist[below + 1] - dist[below]) * (place - (float)(below + 1));
+    struct Counts {
+        uint32_t passed[PassShares::kRanks][PassShares::kShares][PassShares::kLoose], compared[PassShares::kRanks];
+    } counts[kThreads] = {};
+    std::atomic<int64_t> next{0};
+    auto take_queries = [&](Counts& mine) {
+        float q[kMaxDim], r[kMaxDim];
+        for (int64_t s = next++; s < queries; s = next++) {
+            const int64_t v = (2 * s + 1) * idx.n / (2 * queries);
+            const int64_t l0 = std::upper_bound(idx.list_offsets.begin(), idx.list_offsets.end(), v) - idx.list_offsets.begin() - 1;
+            for (int sub = 0; sub < pq_dim; ++sub)
+                for (int u = 0; u < m; ++u) q[(size_t)sub * m + u] = idx.centroids[(size_t)l0 * d + (size_t)sub * m + u] + codeword(v, sub)[u];
+            uint64_t near[kNear], most = UINT64_MAX;
+            int n_near = 0;
+            for (int l = 0; l < n_lists; ++l) {
+                const float* c = idx.centroids.data() + (size_t)l * d;
+                float acc[8] = {};
+                int t = 0;
+                for (; t + 8 <= d; t += 8)
+                    for (int u = 0; u < 8; ++u) { const float x = q[(size_t)(t + u)] - c[t + u]; acc[u] += x * x; }
+                for (; t < d; ++t) { const float x = q[(size_t)t] - c[t]; acc[0] += x * x; }
+                const float dist = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
+                uint32_t key;
+                std::memcpy(&key, &dist, 4);
+                // (only the nearest kNearest are asked for: what is not among them so far is dropped now and then)
+                const uint64_t entry = (uint64_t)key << 32 | (uint32_t)l;
+                if (entry >= most) continue;
+                near[n_near++] = entry;
+                if (n_near == kNear) {
+                    std::nth_element(near, near + kNearest - 1, near + kNear);
+                    most = near[kNearest - 1];
+                    n_near = kNearest;
                 }
-                continue;
             }
-            compared[slot - 1] += (uint32_t)n;
-            for (int i = 0; i < PassShares::kShares; ++i)
-                for (int w = 0; w < PassShares::kLoose; ++w) {
-                    const float limit = quantile[i] * (1.f + PassShares::looseness(w));
-                    for (int j = 0; j < n; ++j) passed[slot - 1][i][w] += dist[j] <= limit ? 1u : 0u;
+            uint64_t* end = near + n_near;
+            for (int rank = PassShares::kRanks - 1; rank >= 0; --rank)          // the lists at ranks 256, 128, ... 1, and before them the nearest
+                if ((1 << rank) < n_lists) {
+                    std::nth_element(near, near + (1 << rank), end);
+                    end = near + (1 << rank);
                 }
+            float quantile[PassShares::kShares];
+            for (int slot = 0; slot <= PassShares::kRanks; ++slot) {
+                const int64_t place = slot == 0 ? 0 : (int64_t)1 << (slot - 1);
+                if (place >= n_lists) break;
+                const int64_t l = (uint32_t)near[place], first = idx.list_offsets[(size_t)l], len = idx.list_offsets[(size_t)l + 1] - first;
+                const int n = (int)std::min<int64_t>(len, slot == 0 ? kOwn : kOther);
+                if (slot == 0 && n == 0) break;
+                for (int t = 0; t < d; ++t) r[(size_t)t] = q[(size_t)t] - idx.centroids[(size_t)l * d + (size_t)t];
+                for (int j = 0; j < n; ++j) __builtin_prefetch(codes + (size_t)(first + len * j / n) * cb);
+                float dist[kOwn];
+                for (int j = 0; j < n; ++j) dist[j] = distance_to(r, first + len * j / n);
+                if (slot == 0) {
+                    std::sort(dist, dist + n);
+                    for (int i = 0; i < PassShares::kShares; ++i) {                  // between the two values about the place in n + 1
+                        const float place = std::min((float)n, std::max(1.f, PassShares::share(i) * (float)(n + 1)));
+                        const int below = std::min(n - 1, (int)place) - 1;
+                        quantile[i] = n == 1 ? dist[0] : dist[below] + (dist[below + 1] - dist[below]) * (place - (float)(below + 1));
+                    }
+                    continue;
+                }
+                mine.compared[slot - 1] += (uint32_t)n;
+                for (int i = 0; i < PassShares::kShares; ++i)
+                    for (int w = 0; w < PassShares::kLoose; ++w) {
+                        const float limit = quantile[i] * (1.f + PassShares::looseness(w));
+                        for (int j = 0; j < n; ++j) mine.passed[slot - 1][i][w] += dist[j] <= limit ? 1u : 0u;
+                    }
+            }
         }
+    };
+    {
+        std::optional<SideTask> others[kThreads - 1];
+        for (int t = 1; t < threads; ++t) others[t - 1].emplace([&, t] { take_queries(counts[t]); });
+        take_queries(counts[0]);
     }
-    for (int rank = 0; rank < PassShares::kRanks && compared[rank] > 0; ++rank, ++out.ranks)
+    Counts& all = counts[0];
+    for (int t = 1; t < kThreads; ++t)
+        for (int rank = 0; rank < PassShares::kRanks; ++rank) {
+            all.compared[rank] += counts[t].compared[rank];
+            for (int i = 0; i < PassShares::kShares; ++i)
+                for (int w = 0; w < PassShares::kLoose; ++w) all.passed[rank][i][w] += counts[t].passed[rank][i][w];
+        }
+    for (int rank = 0; rank < PassShares::kRanks && all.compared[rank] > 0; ++rank, ++out.ranks)
         for (int i = 0; i < PassShares::kShares; ++i)
-            for (int w = 0; w < PassShares::kLoose; ++w) out.pass[rank][i][w] = (float)passed[rank][i][w] / (float)compared[rank];
+            for (int w = 0; w < PassShares::kLoose; ++w) out.pass[rank][i][w] = (float)all.passed[rank][i][w] / (float)all.compared[rank];
     return out;
 }
 

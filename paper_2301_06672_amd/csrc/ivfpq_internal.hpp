@@ -176,8 +176,8 @@ struct ivfpq_index {
 
 namespace ivfpq {
 
-// near: [n_lists] scratch; q, r: [d]
-PassShares sample_pass_shares(const ivfpq_index& idx, uint64_t* near, float* q, float* r) noexcept;
+// of an index of at most 128 components; none otherwise
+PassShares sample_pass_shares(const ivfpq_index& idx) noexcept;
 // The share for a search: averaged over ranks 1 .. n_probes - 1, linear between the sampled ranks, in log(share) and in the looseness.
 double pass_share(const PassShares& p, int n_probes, double share, double loose);
 
