@@ -37,7 +37,7 @@ int fail(int status, const char* fmt, ...) {
     return status;
 }
 
-// 32 decoded vectors stand for queries.  Each is compared with up to 64 vectors of its nearest cluster, whose quantiles stand for the
+// Up to 32 decoded vectors stand for queries.  Each is compared with up to 64 vectors of its nearest cluster, whose quantiles stand for the
 // bound (the k-th smallest R of that cluster), and with up to 12 vectors of the clusters at ranks 1, 2, 4, ... 256: counted is how many
 // are not above the quantile, widened by looseness.  (10^6 vectors of 48 codes in 1,024 lists: 1.7 ms of one thread.)
 PassShares sample_pass_shares(const ivfpq_index& idx) noexcept {

@@ -312,3 +312,56 @@ def test_host_builder_4bit_codes_pack_low_nibble_first(P):
             dist = ((cb[j].astype(np.float64) - res[r, 2 * j:2 * j + 2]) ** 2).sum(1)
             agree += int(sub[r, j] == dist.argmin())
     assert agree >= 0.99 * 1600
+
+
+SAMPLE_SHIM = r'''
+#include "ivfpq_internal.hpp"
+extern "C" int sample_of(void* index, float* pass) {
+    const ivfpq::PassShares s = ivfpq::sample_pass_shares(*(const ivfpq_index*)index);
+    std::memcpy(pass, s.pass, sizeof s.pass);
+    return s.ranks;
+}
+'''
+
+
+@pytest.mark.parametrize("n,n_lists,d,pq_dim,pq_bits", [
+    (40, 50, 64, 32, 8), (3000, 2, 64, 32, 4), (5000, 300, 96, 48, 8),
+    (4000, 1023, 128, 64, 7), (4000, 1025, 128, 32, 8), (9000, 3000, 64, 32, 8)])      # more lists than the buffer of the nearest holds
+def test_sample_of_what_passes_the_filter(P, tmp_path, n, n_lists, d, pq_dim, pq_bits):
+    # the same sample by plain numpy in float64: all lists sorted for every query.  The library sums in float32, so a
+    # vector at the limit may be counted on the other side: one per rank and limit.
+    import ctypes
+    import subprocess
+    (tmp_path / "shim.cpp").write_text(SAMPLE_SHIM)
+    subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-include", "cstring", "-I", os.path.join(os.path.dirname(P.LIB_PATH), "csrc"), str(tmp_path / "shim.cpp"),
+                    P.LIB_PATH, "-o", str(tmp_path / "shim.so")], check=True)
+    cent, cb, offs, codes, ids = si.random_index_arrays(n, d, n_lists, pq_dim, pq_bits, salt=n_lists, empty_lists=(1,) if n_lists > 2 else ())
+    idx = P.Index.ivfpq_index_from_arrays(d, n_lists, pq_dim, pq_bits, cent, cb, offs, codes, ids)
+    got = np.zeros((9, 7, 4), np.float32)
+    ranks = ctypes.CDLL(str(tmp_path / "shim.so")).sample_of(idx._h, got.ctypes.data_as(ctypes.c_void_p))
+    sub = oracle.unpack_codes(codes, pq_bits)
+    y = np.stack([cb[j][sub[:, j]] for j in range(pq_dim)], 1).reshape(n, d).astype(np.float64)
+    shares, loose = np.float64([0.01, 0.02, 0.05, 0.1, 0.2, 0.5, 1.0]), np.float64([0.01, 0.04, 0.07, 0.13])
+    queries = max(8, min(32, min(500000000, n * (codes.shape[1] + 8) + 16000000) // (n_lists * d)))
+    passed, compared = np.zeros((9, 7, 4)), np.zeros(9)
+    for s in range(queries):
+        v = (2 * s + 1) * n // (2 * queries)
+        q = cent[np.searchsorted(offs, v, side="right") - 1] + y[v]
+        order = np.argsort(((q - cent.astype(np.float64)) ** 2).sum(1), kind="stable")
+        def distances(l, most):
+            c = min(offs[l + 1] - offs[l], most)
+            at = offs[l] + (offs[l + 1] - offs[l]) * np.arange(c) // max(c, 1)
+            return ((q - cent[l] - y[at]) ** 2).sum(1)
+        own = np.sort(distances(order[0], 64))
+        if own.size == 0:
+            continue
+        place = np.clip(shares * (own.size + 1), 1, own.size)
+        limit = np.interp(place, np.arange(1, own.size + 1), own)[:, None] * (1 + loose)
+        for r in range(9):
+            if 1 << r < n_lists:
+                dist = distances(order[1 << r], 12)
+                compared[r] += dist.size
+                passed[r] += (dist[:, None, None] <= limit).sum(0)
+    assert ranks == (np.append(compared, 0) == 0).argmax()
+    for r in range(ranks):
+        assert np.abs(got[r] * compared[r] - passed[r]).max() <= 1.01
