@@ -9,7 +9,7 @@
 //   cluster_distance_kernel  few queries instead: the exact distances, which step 1b then selects from as they are
 //   select_probes_kernel step 1b: candidates by ranking value with a rigorous error bound, exact
 //                        direct-form distances for them, exact selection of the n_probes nearest
-//                        clusters; per-pair descriptors and R offsets
+//                        clusters; per-pair descriptors and R offsets (select_probes_wave_kernel: a wave per query, ivfpq_probe_wave.hpp)
 //   scan_kernel (mode 1) steps 2-4 for the nearest probe of every query: query residual, lookup table F
 //                        built in LDS as fp32 / half / e5m3 / e4m4, then every wave streams 64-vector
 //                        groups of PQ codes from HBM and accumulates R = sum_j F(y_j) (Eq. 1)
@@ -47,6 +47,7 @@
 #include "ivfpq_rank.hpp"
 #include "ivfpq_lds_util.hpp"
 #include "ivfpq_lut.hpp"
+#include "ivfpq_probe_wave.hpp"
 #include "ivfpq_scan_args.hpp"
 #include "ivfpq_scan_filter.hpp"
 #include "ivfpq_select.hpp"
@@ -414,11 +415,17 @@ int launch_step_1a(const ivfpq_index* idx, const float* q, int nq, int n_probes,
     return IVFPQ_OK;
 }
 
-template <class... Args>
 void launch_select_probes(int nq, bool exact, hipStream_t st, uint32_t* A, const StripSummary* S, int strip_w, const float* queries,
-                          const float* centroids, float centroid_norm_max, int d, int n_lists, int n_probes, Args... rest) {
+                          const float* centroids, float centroid_norm_max, int d, int n_lists, int n_probes, const uint32_t* list_sizes,
+                          const int64_t* group_offsets, uint32_t* probes, float* probe_dists, uint32_t* roff, uint4* pairs, int k_hint) {
+    if (!exact && !S && nq > kFewQueries && n_probes <= kWaveProbes) {        // (sides measured: at the kernel)
+        hipLaunchKernelGGL(select_probes_wave_kernel, dim3((unsigned)((nq + kWaveQueries - 1) / kWaveQueries)), dim3(64 * kWaveQueries), 0, st, A, queries, centroids,
+                           centroid_norm_max, d, n_lists, n_probes, nq, list_sizes, group_offsets, probes, probe_dists, roff, pairs, k_hint);
+        return;
+    }
     auto go = [&](auto kernel, int threads) {
-        hipLaunchKernelGGL(kernel, dim3(nq), dim3(threads), 0, st, A, S, strip_w, queries, centroids, centroid_norm_max, d, n_lists, n_probes, rest...);
+        hipLaunchKernelGGL(kernel, dim3(nq), dim3(threads), 0, st, A, S, strip_w, queries, centroids, centroid_norm_max, d, n_lists, n_probes, list_sizes, group_offsets,
+                           probes, probe_dists, roff, pairs, k_hint);
     };
     if (exact) go(select_probes_kernel<SEL_CAP, 1024, true>, 1024);
     else if (nq <= kFewQueries) go(select_probes_kernel<SEL_CAP, 1024>, 1024);
