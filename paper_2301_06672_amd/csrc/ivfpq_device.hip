@@ -44,6 +44,7 @@
 
 #include "ivfpq_filter_bound.hpp"
 #include "ivfpq_internal.hpp"
+#include "ivfpq_bound_wave.hpp"
 #include "ivfpq_rank.hpp"
 #include "ivfpq_lds_util.hpp"
 #include "ivfpq_lut.hpp"
@@ -109,7 +110,7 @@ select_probes_kernel(uint32_t* __restrict__ A, const StripSummary* __restrict__ 
                      int n_lists, int n_probes,
                      const uint32_t* __restrict__ list_sizes, const int64_t* __restrict__ group_offsets,
                      uint32_t* __restrict__ probes, float* __restrict__ probe_dists,
-                     uint32_t* __restrict__ roff, uint4* __restrict__ pairs, int k_hint) {
+                     uint32_t* __restrict__ roff, uint4* __restrict__ pairs, int k_hint, uint32_t* __restrict__ nearest) {
     __shared__ RowSelectSharedT<CAP> t;
     __shared__ float s_part[THREADS / kWave];
     auto& s = t.sel;
@@ -336,6 +337,7 @@ select_probes_kernel(uint32_t* __restrict__ A, const StripSummary* __restrict__ 
         if (probe_dists) probe_dists[(size_t)q * n_probes + i] = __uint_as_float(s.rec_key[p]);
         roff[(size_t)q * (n_probes + 1) + i] = at;
         pairs[(size_t)q * n_probes + i] = make_uint4(l, t.cand_key[p], t.cand_pos[p], at);
+        if (nearest && i == 0u) nearest[q] = l;
     }
 }
 
@@ -417,15 +419,15 @@ int launch_step_1a(const ivfpq_index* idx, const float* q, int nq, int n_probes,
 
 void launch_select_probes(int nq, bool exact, hipStream_t st, uint32_t* A, const StripSummary* S, int strip_w, const float* queries,
                           const float* centroids, float centroid_norm_max, int d, int n_lists, int n_probes, const uint32_t* list_sizes,
-                          const int64_t* group_offsets, uint32_t* probes, float* probe_dists, uint32_t* roff, uint4* pairs, int k_hint) {
+                          const int64_t* group_offsets, uint32_t* probes, float* probe_dists, uint32_t* roff, uint4* pairs, int k_hint, uint32_t* nearest = nullptr) {
     if (!exact && !S && nq > kFewQueries && n_probes <= kWaveProbes) {        // (sides measured: at the kernel)
         hipLaunchKernelGGL(select_probes_wave_kernel, dim3((unsigned)((nq + kWaveQueries - 1) / kWaveQueries)), dim3(64 * kWaveQueries), 0, st, A, queries, centroids,
-                           centroid_norm_max, d, n_lists, n_probes, nq, list_sizes, group_offsets, probes, probe_dists, roff, pairs, k_hint);
+                           centroid_norm_max, d, n_lists, n_probes, nq, list_sizes, group_offsets, probes, probe_dists, roff, pairs, k_hint, nearest);
         return;
     }
     auto go = [&](auto kernel, int threads) {
         hipLaunchKernelGGL(kernel, dim3(nq), dim3(threads), 0, st, A, S, strip_w, queries, centroids, centroid_norm_max, d, n_lists, n_probes, list_sizes, group_offsets,
-                           probes, probe_dists, roff, pairs, k_hint);
+                           probes, probe_dists, roff, pairs, k_hint, nearest);
     };
     if (exact) go(select_probes_kernel<SEL_CAP, 1024, true>, 1024);
     else if (nq <= kFewQueries) go(select_probes_kernel<SEL_CAP, 1024>, 1024);
@@ -679,7 +681,6 @@ __device__ inline float add_group(float acc, const unsigned char* lut, const uin
     return acc;
 }
 
-constexpr uint32_t kAdmitAll = 0xFFFFFFFEu;   // every real R is below this, the padding key is above
 constexpr int kBoundBins = 1024;
 constexpr size_t kBoundLds = (size_t)kBoundBins * 4 + 64;
 
@@ -1299,6 +1300,43 @@ filter_items_kernel(const uint32_t* __restrict__ counts, const uint32_t* __restr
     }
 }
 
+// The queries in the order of their nearest clusters, in one launch: a workgroup goes over the nearest cluster of every query (left by the
+// selection), ranks those of its own 64 clusters, counts those of the clusters before, and writes its queries.  9 us for 10,000
+// queries and 1,024 or 5,000 clusters; one workgroup for all of them took 167.
+constexpr int kNearestPerThread = 16;
+__global__ void __launch_bounds__(1024)
+nearest_order_kernel(const uint32_t* __restrict__ nearest, int nq, uint32_t* __restrict__ order) {
+    __shared__ uint32_t s_count[kWave], s_before;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t l0 = blockIdx.x * kWave;
+    uint32_t mine[kNearestPerThread];                                // cluster less l0
+#pragma unroll
+    for (int u = 0; u < kNearestPerThread; ++u) {
+        const int q = u * 1024 + tid;
+        mine[u] = q < nq ? nearest[q] : 0xFFFFFFFFu;
+    }
+    if (tid < kWave) s_count[tid] = 0u;
+    if (tid == 0) s_before = 0u;
+    __syncthreads();
+    uint32_t before = 0, rank[kNearestPerThread];
+#pragma unroll
+    for (int u = 0; u < kNearestPerThread; ++u) {
+        before += mine[u] < l0 ? 1u : 0u;
+        mine[u] -= l0;                                               // (of no query: far above 64 still)
+        rank[u] = mine[u] < (uint32_t)kWave ? atomicAdd(&s_count[mine[u]], 1u) : 0u;
+    }
+    before = wave_inclusive_scan(before);
+    if (lane == kWave - 1 && before != 0) atomicAdd(&s_before, before);
+    __syncthreads();
+    const uint32_t n = s_count[lane], first = s_before + wave_inclusive_scan(n) - n;
+    __syncthreads();
+    if (wave == 0) s_count[lane] = first;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kNearestPerThread; ++u)
+        if (mine[u] < (uint32_t)kWave) order[s_count[mine[u]] + rank[u]] = (uint32_t)(u * 1024 + tid);
+}
+
 // ================================================================================================
 // Step 5: the k smallest (R, id) of a query.  Candidates: the survivor list of the filtered scan (listed: the nearest
 // cluster's values under the bound, then what the scan kept), or the segments of all probes themselves.
@@ -1770,6 +1808,28 @@ int launch_scan_group(const ivfpq_index* idx, const ScanArgs& a, int lut_dtype, 
     }
 }
 
+// Pairs a workgroup of the group kernel takes for the queries' nearest probes, or 0 where scan_kernel takes a query each.  Two launches more (the
+// order 5 us, the bound 16 to 46) and a quarter of the workgroups: whole searches, us, a query each / in groups, k = 10 and 20 probes:
+//   queries                       600        1,200      2,000      3,000      5,000      10,000
+//   128 lists, 64 codes, e5m3     141 / 151  163 / 177  220 / 208  292 / 277  427 / 375  667 / 560
+//   512 lists, 32 codes, half     141 / 150  173 / 178  199 / 182  252 / 235  358 / 281  573 / 438
+//   1,024 lists, 48 codes, e5m3              120 / 129  137 / 131  162 / 156  217 / 197  349 / 303
+//   1,024 lists, 64 codes of 7 bits, half    157 / 185  188 / 190  230 / 223  306 / 273  493 / 435
+//   512 lists, 64 codes of 4 bits, float     130 / 245  169 / 269  213 / 284  282 / 326  416 / 387  652 / 540
+//   2,000 lists, 64 codes, e4m4                         237 / 239  307 / 317  451 / 451  846 / 779
+// (all with k = 100 and 40 probes alike; up to a twentieth of the gain is the probe selection's).  Hence 3,000 queries, 5,000 for float tables of
+// 4-bit codes, and three queries a list where only two workgroups fit a compute unit; where more do, one a list (10,000 queries of 10,000
+// lists, 48 codes: nearest probes 187 -> 180 us; 8,192 of 5,000, 32 codes: 238 -> 205).
+int nearest_group_width(const ivfpq_index* idx, int lut_dtype, const Fp8Mode& fp8, int nq, int k) {
+    const ivfpq::Tuning& t = idx->tuning;
+    if (t.scan_route != 0 || t.scan_share != 0 || t.order_block != 0 || t.scan_threads != 0 || t.lds_pad != 0) return 0;
+    if (k > kBoundWaveK || nq > 1024 * kNearestPerThread || nq < (idx->pq_bits == 4 && lut_dtype == IVFPQ_LUT_FP32 ? 5000 : 3000)) return 0;
+    const int G = scan_group_width(idx, lut_dtype, fp8, kOrderBlock);
+    if (G == 0) return 0;
+    const bool few_fit = scan_group_lds_bytes(idx, lut_dtype, G, scan_group_threads(idx, lut_dtype, G)) > kGroupLds4;
+    return nq >= (few_fit ? 3 : 1) * (int64_t)idx->n_lists ? G : 0;
+}
+
 // A grid that leaves wave slots of the chip empty takes larger workgroups: tables are built and lists walked by more
 // waves at once (filtered scan of one query, 19 pairs: 21.6 -> 9 us with 1024 threads instead of 256).
 int scan_threads_of_grid(const ivfpq_index* idx, int lut_dtype, size_t blocks) {
@@ -2018,7 +2078,7 @@ int search_impl(const ivfpq_index* idx, const float* d_queries, int64_t nq, cons
             launch_select_probes((int)tq, exact, st, (uint32_t*)w_D, (const StripSummary*)strips,
                                  coarse_strip_width(tq, idx->n_lists), qt,
                                  idx->dev.centroids, idx->centroid_norm_max, idx->d, idx->n_lists,
-                                 n_probes, idx->dev.list_sizes, idx->dev.group_offsets, w_probes, w_probe_d, w_roff, w_pairs, k);
+                                 n_probes, idx->dev.list_sizes, idx->dev.group_offsets, w_probes, w_probe_d, w_roff, w_pairs, k, w_counts);
             HIP_TRY(hipGetLastError());
         } else {
             hipLaunchKernelGGL(layout_probes_kernel, dim3((tq + 255) / 256), dim3(256), 0, st,
@@ -2063,7 +2123,22 @@ int search_impl(const ivfpq_index* idx, const float* d_queries, int64_t nq, cons
         StageTimer t5(idx, st, 5);
         StageTimer t6(idx, st, 6);
         if (int s = t5.begin()) return s;
-        if (int s = launch_scan(idx, a, lut_dtype, dim3((unsigned)((size_t)tq * (whole_rows ? n_probes : 1))), st)) return s;
+        if (const int G = grouped && !d_probes_in ? nearest_group_width(idx, lut_dtype, a.fp8, tq, k) : 0) {
+            // the selection has left the nearest clusters in w_counts; the other probes' order comes later
+            uint32_t* w_near = (uint32_t*)(ws + plan.order);
+            hipLaunchKernelGGL(nearest_order_kernel, dim3((idx->n_lists + kWave - 1) / kWave), dim3(1024), 0, st, w_counts, tq, w_near);
+            HIP_TRY(hipGetLastError());
+            ScanArgs near = a;
+            near.order = w_near;
+            near.n_pairs = (uint32_t)tq;
+            near.order_block = kOrderBlock;
+            near.n_chunks = idx->code_bytes() / chunk_width(idx);
+            if (int s = launch_scan_group(idx, near, lut_dtype, G, st)) return s;
+            hipLaunchKernelGGL(bound_wave_kernel, dim3((unsigned)((tq + kBoundQueries - 1) / kBoundQueries)), dim3(64 * kBoundQueries), 0, st, near, tq);
+            HIP_TRY(hipGetLastError());
+        } else if (int s = launch_scan(idx, a, lut_dtype, dim3((unsigned)((size_t)tq * (whole_rows ? n_probes : 1))), st)) {
+            return s;
+        }
         if (int s = t5.end()) return s;
         if (whole_rows && n_probes > 1) note_scan((size_t)tq * n_probes);
         if (whole_rows) t5.divide(6, 1.f / (float)n_probes);      // one launch does the work of both: divided by their pairs

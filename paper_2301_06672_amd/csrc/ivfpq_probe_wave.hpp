@@ -23,7 +23,8 @@ constexpr int kWaveProbes = 64, kWaveCand = 192, kWaveQueries = 4;
 __global__ void __launch_bounds__(64 * kWaveQueries)
 select_probes_wave_kernel(uint32_t* __restrict__ A, const float* __restrict__ queries, const float* __restrict__ centroids, float centroid_norm_max, int d, int n_lists, int n_probes, int nq,
                           const uint32_t* __restrict__ list_sizes, const int64_t* __restrict__ group_offsets,
-                          uint32_t* __restrict__ probes, float* __restrict__ probe_dists, uint32_t* __restrict__ roff, uint4* __restrict__ pairs, int k_hint) {
+                          uint32_t* __restrict__ probes, float* __restrict__ probe_dists, uint32_t* __restrict__ roff, uint4* __restrict__ pairs, int k_hint,
+                          uint32_t* __restrict__ nearest) {
     constexpr int kHeld = kWaveCand / kWave;
     __shared__ unsigned long long s_key[kWaveQueries][kWaveCand];
     const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -203,6 +204,7 @@ select_probes_wave_kernel(uint32_t* __restrict__ A, const float* __restrict__ qu
         roff[(size_t)q * (n_probes + 1) + lane] = upto - padded;
         pairs[(size_t)q * n_probes + lane] = make_uint4(l, len, group, upto - padded);
     }
+    if (nearest && lane == 0) nearest[q] = l;
     if (lane == kWave - 1) roff[(size_t)q * (n_probes + 1) + n_probes] = upto;
 }
 

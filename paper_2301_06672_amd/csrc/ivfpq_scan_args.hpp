@@ -38,12 +38,14 @@ struct ScanArgs {
     int early_exit;               // mode 2: stop adding for a 64-vector group once every partial sum is over the bound
 };
 
+constexpr uint32_t kAdmitAll = 0xFFFFFFFEu;   // a bound: every real R is below this, the padding key is above
 constexpr int kAliveCap = 64;        // groups of a wave that the first pass of the split scan can note for the second
 constexpr int kGroupStageAll = 128;  // survivors a wave stages before it appends them, over all queries of a run: 128 / R per query
                                      // (a 64-vector group with more survivors than that goes straight to the list)
 constexpr int kGroupHead = 128;      // bytes at the start of the kernel's LDS that hold the slot's pair descriptors
 
-// scan_group_kernel over a.n_pairs pairs, up to G of a cluster per workgroup (ivfpq_scan_group.hip, one object per LUT)
+// scan_group_kernel over a.n_pairs pairs, up to G of a cluster per workgroup (ivfpq_scan_group.hip, one object per LUT).  Mode 1: the nearest
+// probes of the queries a.order[0 .. n_pairs), all values written in place.
 template <int LUT>
 int launch_scan_group_kernel(const ScanArgs& a, int G, int threads, size_t lds, hipStream_t st);
 

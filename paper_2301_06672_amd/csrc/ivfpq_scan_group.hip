@@ -32,6 +32,9 @@
 // A run of 1, 2, 3 or 4 pairs of one cluster is processed at once (3 in the 4-wide layout with one byte of
 // every entry unused).  A workgroup takes G consecutive pairs of the grouped order and cuts them into
 // such runs at the seams between clusters.
+// Mode kAll scans the nearest probes of a large batch, whose queries share clusters too, and writes every value in place (their bound: ivfpq_bound_wave.hpp).
+// Bound by the vector ALU (2.25 instructions a lookup, tables as ever).  10,000 queries, 64 codes, e5m3, 1,024 lists: scan_kernel with the bound
+// at its end 195 us, this 128 and the bound 25; 4-bit codes, half, 2,000 lists 337 -> 227 + 46; 7 bits 183 -> 118 + 25.
 // LDS: the slot's pair descriptors | tables | R residuals of d floats | per wave kGroupStageAll staged survivors |
 // a flag and, per wave, kAliveCap group numbers of the split scan.
 #include <hip/hip_runtime.h>
@@ -46,6 +49,9 @@
 using namespace ivfpq;
 
 namespace {
+
+// Filtered; filtered, the second half of the tables built only if needed; every value written in place, added up in scan_kernel's order.
+constexpr int kFiltered = 0, kSplit = 1, kAll = 2;
 
 // 4 * R table entries -- codes u = 0..3 of one lane, queries g = 0..R-1, f[u * R + g] -- converted to the
 // table dtype and stored at `dst` (their place in the interleaved table: 4 * R * entry_bytes contiguous bytes)
@@ -80,9 +86,10 @@ __device__ __forceinline__ void store_packed(unsigned char* dst, const float (&f
 // Q pairs of one cluster, q[g], pair[g], with tables interleaved R >= Q wide (Q < R: the entries of the missing
 // queries are zero bytes that nobody decodes; three pairs run as Q = 3 in the R = 4 layout).
 // LEN: length of a vector's code, in 16-byte chunks; of bit-packed codes, in 4-byte words.
-template <int LUT, int LEN, int R, int Q, int BITS, bool SPLIT>
+template <int LUT, int LEN, int R, int Q, int BITS, int MODE>
 __device__ __forceinline__ void group_run(const ScanArgs& a, unsigned char* smem, const int (&q)[Q], const uint4 (&pair)[Q]) {
     static_assert(Q >= 1 && Q <= R, "queries of a run fit its interleave width");
+    constexpr bool SPLIT = MODE == kSplit, ALL = MODE == kAll;
     static_assert(BITS >= 4 && BITS <= 8, "codes of 4 to 8 bits");
     constexpr bool PACKED = BITS != 8 && BITS != 4;     // fields that straddle bytes and words
     constexpr int WORDS = PACKED ? LEN : 4 * LEN;
@@ -109,8 +116,8 @@ __device__ __forceinline__ void group_run(const ScanArgs& a, unsigned char* smem
     uint2* stage[Q];
 #pragma unroll
     for (int g = 0; g < Q; ++g) {
-        bound[g] = a.bounds[q[g]];
-        seg0[g] = a.pairs[(size_t)q[g] * a.n_probes + 1].w;
+        bound[g] = ALL ? 0u : a.bounds[q[g]];
+        seg0[g] = ALL ? 0u : a.pairs[(size_t)q[g] * a.n_probes + 1].w;
         row_pos0[g] = pair[g].w;
         staged[g] = 0;
         stage[g] = reinterpret_cast<uint2*>(after_rq) + ((size_t)wave * Q + g) * kGroupStage;
@@ -208,6 +215,9 @@ __device__ __forceinline__ void group_run(const ScanArgs& a, unsigned char* smem
     // both halves of a register hold the bf16 pattern of 1.0; decode constant of the 8-bit formats per half
     const bf16x2_t ones = __builtin_bit_cast(bf16x2_t, 0x3F803F80u);
     const uint32_t k2 = ((uint32_t)fp8.lo >> 16) * 0x10001u;
+    // 1.0 in one half alone; in registers, since the second is also the pattern of an inline constant that stands for 1.0 in the low half
+    uint32_t one_low = 0x00003F80u, one_high = 0x3F800000u;
+    asm volatile("" : "+s"(one_low), "+s"(one_high));
     // adds the entries of two consecutive sub-spaces, x0 then x1 (the words of all R queries), to every query's sum
     auto add_two = [&](const word_t& x0, const word_t& x1, float (&acc)[Q]) __attribute__((always_inline)) {
         if constexpr (kIsFp8<LUT>) {
@@ -217,7 +227,12 @@ __device__ __forceinline__ void group_run(const ScanArgs& a, unsigned char* smem
                 // bytes g of x0 and x1 into the low bytes of the two halves
                 uint32_t p = __builtin_amdgcn_perm((uint32_t)x1, (uint32_t)x0, 0x0c000c00u | ((4u + g) << 16) | (uint32_t)g);
                 p = (p << S) + k2;
-                acc[g] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, p), ones, acc[g], false);
+                if constexpr (ALL) {             // one after the other, as scan_kernel and candidate_kernel add them
+                    acc[g] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, p), __builtin_bit_cast(bf16x2_t, one_low), acc[g], false);
+                    acc[g] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, p), __builtin_bit_cast(bf16x2_t, one_high), acc[g], false);
+                } else {
+                    acc[g] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, p), ones, acc[g], false);
+                }
             }
         } else if constexpr (LUT == IVFPQ_LUT_FP16) {
 #pragma unroll
@@ -320,7 +335,12 @@ __device__ __forceinline__ void group_run(const ScanArgs& a, unsigned char* smem
             if (over) continue;
             if constexpr (PACKED) fields(buf, c, acc);
             else chunk(buf[c], c, acc);
-            if (c + 1 < N && a.early_exit) {
+            if constexpr (ALL) {
+                // a branch that is never taken: steps in one block are scheduled into each other, at the cost of registers (up to 500 spilled)
+                uint32_t never = 0;
+                asm volatile("" : "+s"(never));
+                over = never != 0;
+            } else if (c + 1 < N && a.early_exit) {
                 unsigned long long in_race = 0;
 #pragma unroll
                 for (int g = 0; g < Q; ++g) in_race |= ballot64(__float_as_uint(acc[g]) <= bound[g]);
@@ -369,6 +389,12 @@ __device__ __forceinline__ void group_run(const ScanArgs& a, unsigned char* smem
     auto keep = [&](int grp_i, const float (&acc)[Q]) __attribute__((always_inline)) {
         const uint32_t i = (uint32_t)grp_i * 64u + lane;
         const bool real = i < len;                  // the last group is padded with zero codes
+        if constexpr (ALL) {
+#pragma unroll
+            for (int g = 0; g < Q; ++g)
+                if (real) a.R[(size_t)q[g] * a.stride + row_pos0[g] + i] = acc[g];
+            return;
+        }
         const unsigned long long m_real = ballot64(real);
         static_for<Q>([&](auto g_tag) __attribute__((always_inline)) {
             constexpr int g = decltype(g_tag)::value;
@@ -469,7 +495,7 @@ __device__ __forceinline__ void group_run(const ScanArgs& a, unsigned char* smem
 // XCDs in blocks of order_block / G, which is the dealing of scan_kernel's pairs in blocks of order_block.
 // The first kGroupHead bytes of the LDS hold the slot's pair descriptors (the runs read them by position);
 // group_run's `smem` starts behind them.
-template <int LUT, int LEN, int G, int BITS, bool SPLIT>
+template <int LUT, int LEN, int G, int BITS, int MODE>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4, 8)))
 scan_group_kernel(ScanArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -483,10 +509,10 @@ scan_group_kernel(ScanArgs a) {
     uint4* s_pair = reinterpret_cast<uint4*>(smem);
     int* s_q = reinterpret_cast<int*>(smem + G * 16);
     if ((int)threadIdx.x < n_here) {
-        const uint32_t lin = a.order[first + threadIdx.x];
-        const int qi = (int)(lin / (uint32_t)(a.n_probes - 1));
+        const uint32_t lin = a.order[first + threadIdx.x];             // (of all values of the nearest probes: the query)
+        const int qi = MODE == kAll ? (int)lin : (int)(lin / (uint32_t)(a.n_probes - 1));
         s_q[threadIdx.x] = qi;
-        s_pair[threadIdx.x] = a.pairs[(size_t)qi * a.n_probes + 1 + (lin - (uint32_t)qi * (uint32_t)(a.n_probes - 1))];
+        s_pair[threadIdx.x] = a.pairs[(size_t)qi * a.n_probes + (MODE == kAll ? 0u : 1u + (lin - (uint32_t)qi * (uint32_t)(a.n_probes - 1)))];
     }
     __syncthreads();
     auto uni = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); };
@@ -505,12 +531,12 @@ scan_group_kernel(ScanArgs a) {
             if (r == 4) {
                 const int qq[4] = {q_at(i), q_at(i + 1), q_at(i + 2), q_at(i + 3)};
                 const uint4 pp[4] = {pair_at(i), pair_at(i + 1), pair_at(i + 2), pair_at(i + 3)};
-                group_run<LUT, LEN, 4, 4, BITS, SPLIT>(a, body, qq, pp);
+                group_run<LUT, LEN, 4, 4, BITS, MODE>(a, body, qq, pp);
                 done = true;
             } else if (r == 3) {
                 const int qq[3] = {q_at(i), q_at(i + 1), q_at(i + 2)};
                 const uint4 pp[3] = {pair_at(i), pair_at(i + 1), pair_at(i + 2)};
-                group_run<LUT, LEN, 4, 3, BITS, SPLIT>(a, body, qq, pp);
+                group_run<LUT, LEN, 4, 3, BITS, MODE>(a, body, qq, pp);
                 done = true;
             }
         }
@@ -518,11 +544,11 @@ scan_group_kernel(ScanArgs a) {
             if (r == 2) {
                 const int qq[2] = {q_at(i), q_at(i + 1)};
                 const uint4 pp[2] = {pair_at(i), pair_at(i + 1)};
-                group_run<LUT, LEN, 2, 2, BITS, SPLIT>(a, body, qq, pp);
+                group_run<LUT, LEN, 2, 2, BITS, MODE>(a, body, qq, pp);
             } else {
                 const int qq[1] = {q_at(i)};
                 const uint4 pp[1] = {pair_at(i)};
-                group_run<LUT, LEN, 1, 1, BITS, SPLIT>(a, body, qq, pp);
+                group_run<LUT, LEN, 1, 1, BITS, MODE>(a, body, qq, pp);
             }
         }
         i += r;
@@ -542,42 +568,45 @@ int ivfpq::launch_scan_group_kernel(const ScanArgs& a, int G, int threads, size_
         HIP_TRY(hipGetLastError());
         return IVFPQ_OK;
     };
-    const int nch = a.n_chunks;
+    // CAN_SPLIT: 64 sub-spaces or more: with the early exit on, the second half of the tables is built only if needed
+    auto go_mode = [&](auto len_tag, auto g_tag, auto bits_tag, auto can_split) -> int {
+        constexpr int LEN = decltype(len_tag)::value, GG = decltype(g_tag)::value, BITS = decltype(bits_tag)::value;
+        if (a.mode == 1) return go(scan_group_kernel<LUT, LEN, GG, BITS, kAll>);
+        if constexpr (decltype(can_split)::value)
+            if (a.early_exit) return go(scan_group_kernel<LUT, LEN, GG, BITS, kSplit>);
+        return go(scan_group_kernel<LUT, LEN, GG, BITS, kFiltered>);
+    };
     auto by_bits = [&](auto g_tag, auto bits_tag) -> int {
         constexpr int GG = decltype(g_tag)::value, BITS = decltype(bits_tag)::value;
         if constexpr (GG == 2 || kIsFp8<LUT>) {
-            // 64 sub-spaces or more with the early exit on: the second half of the tables is built only if needed
             switch (a.pq_dim) {
-                case 32: return go(scan_group_kernel<LUT, BITS, GG, BITS, false>);
+                case 32: return go_mode(std::integral_constant<int, BITS>{}, g_tag, bits_tag, std::false_type{});
                 case 48:
-                    if constexpr (BITS == 6) return go(scan_group_kernel<LUT, 9, GG, BITS, false>);
+                    if constexpr (BITS == 6) return go_mode(std::integral_constant<int, 9>{}, g_tag, bits_tag, std::false_type{});
                     break;
-                case 64: return a.early_exit ? go(scan_group_kernel<LUT, 2 * BITS, GG, BITS, true>) : go(scan_group_kernel<LUT, 2 * BITS, GG, BITS, false>);
-                case 96: return a.early_exit ? go(scan_group_kernel<LUT, 3 * BITS, GG, BITS, true>) : go(scan_group_kernel<LUT, 3 * BITS, GG, BITS, false>);
+                case 64: return go_mode(std::integral_constant<int, 2 * BITS>{}, g_tag, bits_tag, std::true_type{});
+                case 96: return go_mode(std::integral_constant<int, 3 * BITS>{}, g_tag, bits_tag, std::true_type{});
                 default: break;
             }
         }
         return fail(IVFPQ_EUNSUPPORTED, "internal: no group kernel for %d pairs of %d sub-spaces of %d bits", GG, a.pq_dim, BITS);
     };
     auto by_nch = [&](auto g_tag) -> int {
-        constexpr int GG = decltype(g_tag)::value;
-        if (a.bits == 7) return by_bits(g_tag, std::integral_constant<int, 7>{});
-        if (a.bits == 6) return by_bits(g_tag, std::integral_constant<int, 6>{});
-        if (a.bits == 5) return by_bits(g_tag, std::integral_constant<int, 5>{});
-        if (a.bits == 4)
-            switch (nch) {
-                case 1: return go(scan_group_kernel<LUT, 1, GG, 4, false>);
-                case 2: return go(scan_group_kernel<LUT, 2, GG, 4, false>);
-                case 3: return go(scan_group_kernel<LUT, 3, GG, 4, false>);
-                default: return go(scan_group_kernel<LUT, 4, GG, 4, false>);
+        auto whole = [&](auto bits_tag) -> int {
+            constexpr bool four_split = decltype(bits_tag)::value == 8;
+            switch (a.n_chunks) {
+                case 1: return go_mode(std::integral_constant<int, 1>{}, g_tag, bits_tag, std::false_type{});
+                case 2: return go_mode(std::integral_constant<int, 2>{}, g_tag, bits_tag, std::false_type{});
+                case 3: return go_mode(std::integral_constant<int, 3>{}, g_tag, bits_tag, std::false_type{});
+                default: return go_mode(std::integral_constant<int, 4>{}, g_tag, bits_tag, std::integral_constant<bool, four_split>{});
             }
-        switch (nch) {
-            case 1: return go(scan_group_kernel<LUT, 1, GG, 8, false>);
-            case 2: return go(scan_group_kernel<LUT, 2, GG, 8, false>);
-            case 3: return go(scan_group_kernel<LUT, 3, GG, 8, false>);
-            default:
-                // 64 sub-spaces with the early exit on: the second half of the tables is built only if needed
-                return a.early_exit ? go(scan_group_kernel<LUT, 4, GG, 8, true>) : go(scan_group_kernel<LUT, 4, GG, 8, false>);
+        };
+        switch (a.bits) {
+            case 7: return by_bits(g_tag, std::integral_constant<int, 7>{});
+            case 6: return by_bits(g_tag, std::integral_constant<int, 6>{});
+            case 5: return by_bits(g_tag, std::integral_constant<int, 5>{});
+            case 4: return whole(std::integral_constant<int, 4>{});
+            default: return whole(std::integral_constant<int, 8>{});
         }
     };
     return G == 4 ? by_nch(std::integral_constant<int, 4>{}) : by_nch(std::integral_constant<int, 2>{});

@@ -1311,3 +1311,32 @@ def test_select_probes_by_waves(P, n_lists):
     others = [i for i in range(513) if i != 9]
     assert_probes_match(probes.cpu().numpy().view(np.uint32)[others], cen, q[others], 20)
     assert len(set(probes.cpu().numpy()[9].tolist())) == 20
+
+
+@pytest.mark.parametrize("d,pq_dim,pq_bits", [(64, 16, 8), (128, 32, 8), (96, 48, 8), (128, 64, 8), (128, 64, 4), (128, 64, 7), (128, 32, 5)])
+def test_nearest_probes_by_groups(P, d, pq_dim, pq_bits):
+    # 5,000 queries on 41 clusters: their nearest probes are scanned by the group kernel and bounded by a wave each (scan route 0); with a route
+    # named, a workgroup each.  Lists of 0, 1, 63, 64, 65, 2,047, 2,049 (a wave holds 2,048 values), and 6,000 vectors, one of equal codes
+    # (more values under the bound than a wave gathers); k up to and past what a wave takes; queries that are no numbers.  Same bits.
+    rng = np.random.default_rng(1000 * d + 10 * pq_dim + pq_bits)
+    sizes = np.array([0, 1, 63, 64, 65, 127, 128, 129, 2047, 2048, 2049, 6000] + [700 + 3 * i for i in range(29)])
+    cent = (4 * rng.standard_normal((41, d))).astype(np.float32)
+    books = (0.5 * rng.standard_normal((pq_dim, 1 << pq_bits, d // pq_dim))).astype(np.float32)
+    n = int(sizes.sum())
+    codes = rng.integers(0, 256, (n, pq_dim * pq_bits // 8)).astype(np.uint8)
+    offsets = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    codes[offsets[30]:offsets[31]] = codes[offsets[30]]
+    gidx = to_library(P, oracle.make_index(d, 41, pq_dim, pq_bits, cent, books, offsets, codes, rng.permutation(n).astype(np.int64)))
+    q = (cent[rng.integers(0, 41, 5000)] + 0.5 * rng.standard_normal((5000, d))).astype(np.float32)
+    q[5] = np.nan
+    q[6, 0] = np.inf
+    q[7] *= 1e20
+    for dtype in (oracle.LUT_FP32, oracle.LUT_FP16, oracle.LUT_E5M3, oracle.LUT_E4M4):
+        for k in (1, 10, 100, 128, 129):
+            out = []
+            for route in (0, 3):
+                gidx.ivfpq_set_tuning(P.TUNE_SCAN_ROUTE, route)
+                _step(f"nearest probes by groups d={d} sub={pq_dim} bits={pq_bits} dtype={dtype} k={k} route={route}")
+                out.append([t.cpu().numpy() for t in gidx.ivfpq_search(q, 12, k, dtype)])
+            np.testing.assert_array_equal(out[0][0], out[1][0])
+            np.testing.assert_array_equal(out[0][1].view(np.uint32), out[1][1].view(np.uint32))
