@@ -242,11 +242,20 @@ __device__ inline uint32_t bf16_round(float f) {          // round to nearest ev
 // up to the tile edge of 128, so that the 128 rows x 16 components which a workgroup of the GEMM stages per
 // step are 4 KiB of consecutive memory (row-major operands give it 32 bytes out of every row: a quarter of
 // each cache line fetched, four times over).  Components d..dp-1 and rows beyond the matrix are zero.  One
-// thread per 8 components.
+// thread per 8 components; queries and centroids in one launch, the centroids' from thread t_second on.
+struct SplitRows {
+    const float* X;
+    size_t rows, rows_pad;
+    uint16_t *hi, *lo;
+};
 __host__ __device__ inline size_t split_rows_padded(size_t rows) { return (rows + 127) / 128 * 128; }
 __global__ void __launch_bounds__(256)
-split_bf16_kernel(const float* __restrict__ X, size_t rows, size_t rows_pad, int d, int dp, uint16_t* __restrict__ hi, uint16_t* __restrict__ lo) {
-    const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+split_bf16_kernel(SplitRows first, SplitRows second, size_t t_second, int d, int dp) {
+    const size_t at_thread = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const bool other = at_thread >= t_second;                // the same for the whole workgroup: t_second is a multiple of 256
+    const float* const __restrict__ X = other ? second.X : first.X;
+    const size_t rows = other ? second.rows : first.rows, rows_pad = other ? second.rows_pad : first.rows_pad, t = at_thread - (other ? t_second : 0);
+    uint16_t *const __restrict__ hi = other ? second.hi : first.hi, *const __restrict__ lo = other ? second.lo : first.lo;
     const int per_row = dp / 8;
     const size_t row = t / per_row;
     const int k0 = (int)(t % per_row) * 8;
@@ -427,12 +436,14 @@ __device__ inline float rank_error_bound(int d, float qn, float cmax) {
     return ((float)(3 * d + 8) * 2.3841858e-07f + 5.0e-05f) * (qn + cmax);
 }
 
-// Tile choice: 128 x 128 tiles on the bf16 kernel when they still cover the chip, else 64 x 64 in fp32.
+// Tile choice: 128 x 128 tiles on the bf16 kernel when they still cover the chip twice (256 compute units), else 64 x 64 in fp32.  Probe
+// selection as a whole, us, fp32 / bf16 with the split of its operands, 10 probes: 1,024 clusters of 128 components 560 tiles 52 / 48, 704
+// 60 / 51, 1,000 79 / 62; 2,000 clusters 560 tiles 48 / 42, 1,008 76 / 58; 5,000 clusters 560 tiles 38 / 35 (40 probes 48 / 49), 1,000 62 / 46.
 // The kernels store either every key, A[nq][n_lists] (S null), or only the strip summaries
 // S[n_strips][nq] for strips of coarse_strip_width() clusters (see rank_store).
 // split_ws: coarse_split_bytes() bytes of device scratch for the bf16 operands.
 inline bool coarse_big_tiles(int nq, int n_lists) {
-    return (long)((n_lists + 127) / 128) * ((nq + 127) / 128) >= 1024;
+    return (long)((n_lists + 127) / 128) * ((nq + 127) / 128) >= 512;
 }
 inline int coarse_strip_width(int nq, int n_lists) { return coarse_big_tiles(nq, n_lists) ? 64 : 32; }
 // whether a selection of the k smallest per row should work from strip summaries instead of all keys
@@ -455,9 +466,9 @@ int launch_coarse(const float* q, const float* centroids, const float* centroid_
         uint16_t* ql = (uint16_t*)((unsigned char*)split_ws + q_bytes);
         uint16_t* ch = (uint16_t*)((unsigned char*)split_ws + 2 * q_bytes);
         uint16_t* cl = (uint16_t*)((unsigned char*)split_ws + 2 * q_bytes + c_bytes);
-        const size_t q_threads = q_pad * (dp / 8), c_threads = c_pad * (dp / 8);
-        hipLaunchKernelGGL(split_bf16_kernel, dim3((unsigned)((q_threads + 255) / 256)), dim3(256), 0, st, q, (size_t)nq, q_pad, d, dp, qh, ql);
-        hipLaunchKernelGGL(split_bf16_kernel, dim3((unsigned)((c_threads + 255) / 256)), dim3(256), 0, st, centroids, (size_t)n_lists, c_pad, d, dp, ch, cl);
+        const size_t q_blocks = (q_pad * (dp / 8) + 255) / 256, c_blocks = (c_pad * (dp / 8) + 255) / 256;
+        hipLaunchKernelGGL(split_bf16_kernel, dim3((unsigned)(q_blocks + c_blocks)), dim3(256), 0, st, SplitRows{q, (size_t)nq, q_pad, qh, ql},
+                           SplitRows{centroids, (size_t)n_lists, c_pad, ch, cl}, q_blocks * 256, d, dp);
         const size_t blocks = (size_t)((n_lists + 127) / 128) * 8 * (((nq + 127) / 128 + 7) / 8);
         if (blocks > 0x7FFFFFFFull) return fail(IVFPQ_EINVAL, "ranking grid of %zu workgroups exceeds the launch limit", blocks);
         dim3 grid((unsigned)blocks);
