@@ -437,8 +437,8 @@ __device__ inline float rank_error_bound(int d, float qn, float cmax) {
 }
 
 // Tile choice: 128 x 128 tiles on the bf16 kernel when they still cover the chip twice (256 compute units), else 64 x 64 in fp32.  Probe
-// selection as a whole, us, fp32 / bf16 with the split of its operands, 10 probes: 1,024 clusters of 128 components 560 tiles 52 / 48, 704
-// 60 / 51, 1,000 79 / 62; 2,000 clusters 560 tiles 48 / 42, 1,008 76 / 58; 5,000 clusters 560 tiles 38 / 35 (40 probes 48 / 49), 1,000 62 / 46.
+// selection as a whole, us, fp32 / bf16 with the split of its operands, 10 probes: 1,024 clusters of 128 components 256 tiles 33 / 37, 360 39 / 41, 504 47 / 43, 560 tiles 52 / 48, 704
+// 60 / 51, 1,000 79 / 62; 2,000 clusters 560 tiles 48 / 42, 1,008 76 / 58; 5,000 clusters 440 tiles 32 / 35, 560 38 / 35 (40 probes 48 / 49), 1,000 62 / 46.
 // The kernels store either every key, A[nq][n_lists] (S null), or only the strip summaries
 // S[n_strips][nq] for strips of coarse_strip_width() clusters (see rank_store).
 // split_ws: coarse_split_bytes() bytes of device scratch for the bf16 operands.
