@@ -8,8 +8,13 @@
 #include <type_traits>
 
 #include "ivfpq_hip_util.hpp"
+#include "ivfpq_probe_rules.hpp"
 
 namespace {
+
+using ivfpq::coarse_big_tiles;
+using ivfpq::coarse_strip_width;
+using ivfpq::coarse_use_strips;
 
 // ================================================================================================
 // Ranking values on the matrix cores (search step 1a; the assignment step of the index build).
@@ -436,26 +441,14 @@ __device__ inline float rank_error_bound(int d, float qn, float cmax) {
     return ((float)(3 * d + 8) * 2.3841858e-07f + 5.0e-05f) * (qn + cmax);
 }
 
-// Tile choice: 128 x 128 tiles on the bf16 kernel when they still cover the chip twice (256 compute units), else 64 x 64 in fp32.  Probe
-// selection as a whole, us, fp32 / bf16 with the split of its operands, 10 probes: 1,024 clusters of 128 components 256 tiles 33 / 37, 360 39 / 41, 504 47 / 43, 560 tiles 52 / 48, 704
-// 60 / 51, 1,000 79 / 62; 2,000 clusters 560 tiles 48 / 42, 1,008 76 / 58; 5,000 clusters 440 tiles 32 / 35, 560 38 / 35 (40 probes 48 / 49), 1,000 62 / 46.
-// The kernels store either every key, A[nq][n_lists] (S null), or only the strip summaries
-// S[n_strips][nq] for strips of coarse_strip_width() clusters (see rank_store).
-// split_ws: coarse_split_bytes() bytes of device scratch for the bf16 operands.
-inline bool coarse_big_tiles(int nq, int n_lists) {
-    return (long)((n_lists + 127) / 128) * ((nq + 127) / 128) >= 512;
-}
-inline int coarse_strip_width(int nq, int n_lists) { return coarse_big_tiles(nq, n_lists) ? 64 : 32; }
-// whether a selection of the k smallest per row should work from strip summaries instead of all keys
-inline bool coarse_use_strips(int nq, int n_lists, int k) {
-    const int w = coarse_strip_width(nq, n_lists);
-    return n_lists > 1024 && (n_lists + w - 1) / w >= 2 * k;
-}
 inline int coarse_padded_dim(int d) { return (d + BK - 1) / BK * BK; }
 inline size_t coarse_split_bytes(size_t nq_max, size_t n_lists, int d) {
     return 2 * (align_up(split_rows_padded(nq_max) * coarse_padded_dim(d) * 2) + align_up(split_rows_padded(n_lists) * coarse_padded_dim(d) * 2));
 }
 
+// The kernels store either every key, A[nq][n_lists] (S null), or only the strip summaries
+// S[n_strips][nq] for strips of coarse_strip_width() clusters (see rank_store).
+// split_ws: coarse_split_bytes() bytes of device scratch for the bf16 operands.
 int launch_coarse(const float* q, const float* centroids, const float* centroid_norms, int nq, int n_lists, int d,
                   uint32_t* A, StripSummary* S, void* split_ws, hipStream_t st) {
     if (coarse_big_tiles(nq, n_lists)) {

@@ -1,0 +1,33 @@
+"""CPU checks of the rules by which a search chooses among the kernels of its probe selection: the library's own header, compiled on the spot."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+SHIM = """
+#include "ivfpq_probe_rules.hpp"
+extern "C" int big_tiles(int nq, int n_lists) { return ivfpq::coarse_big_tiles(nq, n_lists); }
+extern "C" int strip_width(int nq, int n_lists) { return ivfpq::coarse_strip_width(nq, n_lists); }
+extern "C" int use_strips(int nq, int n_lists, int k) { return ivfpq::coarse_use_strips(nq, n_lists, k); }
+"""
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    where = tmp_path_factory.mktemp("rules")
+    (where / "shim.cpp").write_text(SHIM)
+    csrc = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2301_06672_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-I", csrc, str(where / "shim.cpp"), "-o", str(where / "shim.so")], check=True)
+    return ctypes.CDLL(str(where / "shim.so"))
+
+
+def test_middling_batches_are_ranked_in_fp32(rules):
+    # fewer than 1,024 tiles of 128 x 128: the operands' products in fp32, strips of 32
+    for nq, n_lists in ((10_000, 1024), (8_065, 1024), (16_256, 1024), (10_000, 1_500), (4_096, 2_000), (2_000, 8_000)):
+        assert 512 <= -(-nq // 128) * -(-n_lists // 128) < 1024
+        assert not rules.big_tiles(nq, n_lists) and rules.strip_width(nq, n_lists) == 32
+    for nq, n_lists in ((16_257, 1024), (10_000, 1_665), (10_000, 50_000)):
+        assert rules.big_tiles(nq, n_lists) and rules.strip_width(nq, n_lists) == 64
+    # ... so that 100 probes of 8,192 clusters read strip summaries there
+    assert rules.use_strips(1_100, 8_192, 100) and not rules.use_strips(1_100, 8_192, 129) and not rules.use_strips(8_192, 8_192, 65)
