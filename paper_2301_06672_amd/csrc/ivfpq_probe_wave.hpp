@@ -14,7 +14,10 @@ namespace {
 // distances for them, the n_probes nearest of those in order, the query's descriptors.  Here
 //   - the bound on the n_probes-th smallest ranking value is that of 256 minima (four to a lane, of interleaved shares of the row), by
 //     bisection over their bits with ballots;
-//   - candidates are ranked by counting.
+//   - candidates are ranked by counting, 192 at a time: where more are within the error bound (it goes with the norms, so vectors that share
+//     an offset have hundreds) the nearest so far stay and the next join them.  8,000 clusters of 128 components, 64 probes, 4,096
+//     queries, ranking included: centred 119 us by workgroups and 108 by waves, offset by 400 167 and 164 (4,023 with all clusters' distances and a
+//     pass over them a probe); 2,000 clusters, 10,000 queries 168 and 154 (812).
 // Bound by the instructions and the waits of one wave, of which the chip holds 8,192 at once: 10,000 queries on 1,024 clusters, 20 probes,
 // 66 -> 29 us; 2,000, 64 probes, 108 -> 61; 4,096 queries on 1,024 30 -> 15.  (Strip summaries yield five times as many candidates, whose
 // distances are too much for one wave: 10,000 clusters, 50 probes, 95 us by workgroups, 173 by waves.)
@@ -38,9 +41,9 @@ select_probes_wave_kernel(uint32_t* __restrict__ A, const float* __restrict__ qu
         __builtin_amdgcn_wave_barrier();
     };
 
-    // sink(key, index, share 0 ... 3) of every ranking value; whole waves, invalid ones with the index -1
+    // sink(key, index, share 0 ... 3) of every ranking value; whole waves, invalid ones with the index -1.  more(n): the first n are done
     const uint32_t n_keys = (uint32_t)n_lists;
-    auto each_key = [&](auto sink) __attribute__((always_inline)) {
+    auto each_key = [&](auto sink, auto more) __attribute__((always_inline)) {
         if ((n_lists & 3) == 0) {
             const uint4* const row4 = reinterpret_cast<const uint4*>(row);
 #pragma unroll 1
@@ -58,6 +61,7 @@ select_probes_wave_kernel(uint32_t* __restrict__ A, const float* __restrict__ qu
                     sink(v[u].x, in ? (int)(4u * i) : -1, 0); sink(v[u].y, in ? (int)(4u * i + 1u) : -1, 1);
                     sink(v[u].z, in ? (int)(4u * i + 2u) : -1, 2); sink(v[u].w, in ? (int)(4u * i + 3u) : -1, 3);
                 }
+                if (!more(4u * base + 16u * kWave)) return;
             }
         } else {
 #pragma unroll 1
@@ -73,11 +77,13 @@ select_probes_wave_kernel(uint32_t* __restrict__ A, const float* __restrict__ qu
                     const uint32_t i = base + u * kWave + (uint32_t)lane;
                     sink(v[u], i < n_keys ? (int)i : -1, (int)u);
                 }
+                if (!more(base + 4u * kWave)) return;
             }
         }
     };
     uint32_t least[4] = {0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
-    each_key([&](uint32_t key, int i, int share) __attribute__((always_inline)) { least[share] = i >= 0 && key < least[share] ? key : least[share]; });
+    each_key([&](uint32_t key, int i, int share) __attribute__((always_inline)) { least[share] = i >= 0 && key < least[share] ? key : least[share]; },
+             [](uint32_t) { return true; });
     // |q|^2, for the error bound of the ranking values
     float qn = 0.f;
     for (int c = lane; c < d; c += kWave) qn = __builtin_fmaf(qv[c], qv[c], qn);
@@ -100,18 +106,27 @@ select_probes_wave_kernel(uint32_t* __restrict__ A, const float* __restrict__ qu
         g += __builtin_fabsf(g) * 2.3841858e-07f;                     // the addition above rounds: stay on the safe side
         limit = g == g ? ordered_key(g) : 0xFFFFFFFFu;                // NaN (from infinite inputs): admit everything
     }
-    uint32_t n_cand = 0;                                              // the same for the whole wave
+    uint32_t n = 0;                                                   // candidates in keys; the same for the whole wave
     auto append = [&](bool has, uint32_t cluster) __attribute__((always_inline)) {
         const unsigned long long m = ballot64(has);
-        const uint32_t slot = n_cand + lanes_below(m);
+        const uint32_t slot = n + lanes_below(m);
         if (has && slot < (uint32_t)kWaveCand) keys[slot] = cluster;
-        n_cand += (uint32_t)__popcll(m);
+        n += (uint32_t)__popcll(m);
     };
+    // More than the buffer holds (vectors that share an offset: the error bound grows with the norms): from the last step after which it held
+    // them on, the row is taken as many candidates at a time as fit beside the nearest so far.
+    uint32_t at = n_keys, n_held = 0, at_held = 0;                    // the row from `at` on is not in the buffer yet
     each_key([&](uint32_t key, int i, int) __attribute__((always_inline)) {
         const bool in = i >= 0 && key <= limit;
         if (ballot64(in) != 0) append(in, (uint32_t)i);
+    }, [&](uint32_t done) {
+        if (n > (uint32_t)kWaveCand) return false;
+        n_held = n;
+        at_held = done;
+        return true;
     });
-    settle();
+    if (n > (uint32_t)kWaveCand) { n = n_held; at = at_held; }
+    else if (n < (uint32_t)n_probes) { n = 0; at = 0; limit = 0xFFFFFFFFu; }        // not-a-number keys are above every limit: all clusters
     // exact squared distances in direct form: the sum of select_probes_kernel, a group of 8 adjacent lanes per cluster, two clusters a group
     // under way together
     auto distances = [&](uint32_t n, auto cluster_of, auto sink) __attribute__((always_inline)) {
@@ -136,50 +151,59 @@ select_probes_wave_kernel(uint32_t* __restrict__ A, const float* __restrict__ qu
         }
     };
     auto key_of = [](float dist, uint32_t cluster) { return (unsigned long long)__float_as_uint(dist) << 32 | cluster; };
-    unsigned long long mine = ~0ull;                                  // of lane p < n_probes: the p-th nearest, distance and cluster
-    if (n_cand >= (uint32_t)n_probes && n_cand <= (uint32_t)kWaveCand) {
-        distances(n_cand, [&](uint32_t j) { return (uint32_t)keys[j]; }, [&](uint32_t j, float dist) { keys[j] = key_of(dist, (uint32_t)keys[j]); });
+    uint32_t n_kept = 0;                                              // keys[0 .. n_kept): the nearest so far, in order
+    for (;;) {
+        if (at < n_keys) {
+            auto key_at = [&](uint32_t i) { return row[i < n_keys ? i : 0u]; };
+            uint32_t ahead = key_at(at + (uint32_t)lane);
+#pragma unroll 1
+            for (; at < n_keys && n + (uint32_t)kWave <= (uint32_t)kWaveCand; at += kWave) {
+                const uint32_t i = at + (uint32_t)lane, key = ahead;
+                ahead = key_at(i + kWave);
+                append(key <= limit && i < n_keys, i);
+            }
+        }
+        settle();
+        const uint32_t first = n_kept;
+        distances(n - first, [&](uint32_t j) { return (uint32_t)keys[first + j]; },
+                  [&](uint32_t j, float dist) { keys[first + j] = key_of(dist, (uint32_t)keys[first + j]); });
         settle();
         unsigned long long key[kHeld];
 #pragma unroll
-        for (int u = 0; u < kHeld; ++u) key[u] = (uint32_t)(u * kWave + lane) < n_cand ? keys[u * kWave + lane] : ~0ull;
+        for (int u = 0; u < kHeld; ++u) key[u] = (uint32_t)(u * kWave + lane) < n ? keys[u * kWave + lane] : ~0ull;
+        if (first == (uint32_t)n_probes) {                            // what is nearer than the last of these, moved up to them
+            const unsigned long long last = keys[first - 1u];
+            settle();
+            n = first;
+#pragma unroll
+            for (int u = 0; u < kHeld; ++u) {
+                const bool in = (uint32_t)(u * kWave + lane) >= first && key[u] < last;
+                const unsigned long long m = ballot64(in);
+                if (in) keys[n + lanes_below(m)] = key[u];
+                n += (uint32_t)__popcll(m);
+            }
+            settle();
+#pragma unroll
+            for (int u = 0; u < kHeld; ++u) key[u] = (uint32_t)(u * kWave + lane) < n ? keys[u * kWave + lane] : ~0ull;
+        }
         uint32_t rank[kHeld] = {};
 #pragma unroll 1
-        for (uint32_t j = 0; j < n_cand; j += 2) {
-            const unsigned long long k0 = keys[j], k1 = j + 1u < n_cand ? keys[j + 1u] : ~0ull;
+        for (uint32_t j = 0; n != first && j < n; j += 2) {
+            const unsigned long long k0 = keys[j], k1 = j + 1u < n ? keys[j + 1u] : ~0ull;
 #pragma unroll
             for (int u = 0; u < kHeld; ++u)
-                if ((uint32_t)(u * kWave) < n_cand) rank[u] += (k0 < key[u] ? 1u : 0u) + (k1 < key[u] ? 1u : 0u);
+                if ((uint32_t)(u * kWave) < n) rank[u] += (k0 < key[u] ? 1u : 0u) + (k1 < key[u] ? 1u : 0u);
         }
         settle();
 #pragma unroll
         for (int u = 0; u < kHeld; ++u)
-            if ((uint32_t)(u * kWave + lane) < n_cand && rank[u] < (uint32_t)n_probes) keys[rank[u]] = key[u];
+            if (n != first && (uint32_t)(u * kWave + lane) < n && rank[u] < (uint32_t)n_probes) keys[rank[u]] = key[u];
         settle();
-        if (lane < n_probes) mine = keys[lane];
-    } else {
-        // a plateau of equal ranking values, or not-a-number keys: exact distances of all clusters, the least one at a time
-        distances((uint32_t)n_lists, [&](uint32_t j) { return j; }, [&](uint32_t j, float dist) { row[j] = __float_as_uint(dist); });
-        __threadfence_block();
-        unsigned long long last = 0;
-        bool any = false;
-#pragma unroll 1
-        for (int p = 0; p < n_probes; ++p) {
-            unsigned long long best = ~0ull;
-            for (uint32_t i = (uint32_t)lane; i < (uint32_t)n_lists; i += kWave) {
-                const unsigned long long key = (unsigned long long)row[i] << 32 | i;
-                if ((!any || key > last) && key < best) best = key;
-            }
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) {
-                const unsigned long long other = (unsigned long long)__shfl_xor((long long)best, off, kWave);
-                best = other < best ? other : best;
-            }
-            last = best;
-            any = true;
-            if (lane == p) mine = best;
-        }
+        n_kept = n < (uint32_t)n_probes ? n : (uint32_t)n_probes;
+        if (at >= n_keys) break;
+        n = n_kept;
     }
+    const unsigned long long mine = lane < n_probes ? keys[lane] : ~0ull;      // of lane p < n_probes: the p-th nearest, distance and cluster
     uint32_t l = lane < n_probes ? (uint32_t)mine : 0u;
     float dist = __uint_as_float((uint32_t)(mine >> 32));
     if (!roff) {                                                      // the caller's probe lists: nearest first

@@ -1313,6 +1313,56 @@ def test_select_probes_by_waves(P, n_lists):
     assert len(set(probes.cpu().numpy()[9].tolist())) == 20
 
 
+def _offset_probes(P, n_lists, d, offset, nq, seed):
+    """Clusters and queries that all lie `offset` from the origin in every component: the ranking values' error bound goes with the norms."""
+    rng = np.random.default_rng(seed)
+    cen = (offset + 128.0 * rng.random((n_lists, d))).astype(np.float32)
+    books = rng.standard_normal((16, 16, d // 16)).astype(np.float32)
+    codes = rng.integers(0, 256, (n_lists, 8)).astype(np.uint8)
+    gidx = to_library(P, oracle.make_index(d, n_lists, 16, 4, cen, books, np.arange(n_lists + 1, dtype=np.int64), codes, np.arange(n_lists, dtype=np.int64)))
+    return cen, (cen[rng.integers(0, n_lists, nq)] + 20.0 * rng.standard_normal((nq, d))).astype(np.float32), gidx
+
+
+@pytest.mark.parametrize("n_lists,d,offset", [(320, 32, 3000), (1024, 128, 700), (1024, 128, 2000), (1190, 64, 1500), (2002, 128, 500)])
+def test_select_probes_of_vectors_that_share_an_offset(P, n_lists, d, offset):
+    # more clusters within the error bound than a wave holds at a time (192), up to all of them: taken in rounds.  Exact all the same
+    cen, q, gidx = _offset_probes(P, n_lists, d, offset, 2048, n_lists)
+    some = np.arange(0, 2048, 43)
+    dist = ((q[some, None, :].astype(np.float64) - cen[None].astype(np.float64)) ** 2).sum(-1)
+    a = np.sort(dist, axis=1)                                # ranking values but for |q|^2
+    slack = 2 * ((3 * d + 8) * 2.0 ** -22 + 5e-5) * ((q[some].astype(np.float64) ** 2).sum(1) + (cen.astype(np.float64) ** 2).sum(1).max())
+    for n_probes in (1, 10, 63, 64):
+        _step(f"select_probes at offset {offset}, L={n_lists} d={d} P={n_probes}")
+        admitted = (a <= (a[:, n_probes - 1] + slack)[:, None]).sum(1)
+        if n_probes == 64:
+            assert np.median(admitted) > 192
+        probes, pd = (x.cpu().numpy() for x in gidx.ivfpq_select_probes(q, n_probes))
+        assert_probes_match(probes[some].view(np.uint32), cen, q[some], n_probes)
+        np.testing.assert_allclose(pd[some], a[:, :n_probes], rtol=RTOL)
+        assert np.all((np.diff(pd, axis=1) > 0) | (np.diff(probes.astype(np.int64), axis=1) > 0))
+
+
+def test_an_offset_costs_the_selection_little(P):
+    # 8,000 clusters, 64 probes, hundreds of candidates a query: not many times what as many queries of centred vectors take (0.11 ms; exact distances
+    # of all clusters and then a pass over them for every probe took 36 times that)
+    took = {}
+    for offset in (0.0, 400.0):
+        cen, q, gidx = _offset_probes(P, 8000, 128, offset, 4096, 5)
+        q = torch.from_numpy(q).cuda()
+        _step(f"time of select_probes at offset {offset}")
+        runs = []
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            torch.cuda.synchronize()
+            a.record()
+            gidx.ivfpq_select_probes(q, 64)
+            b.record()
+            torch.cuda.synchronize()
+            runs.append(a.elapsed_time(b))
+        took[offset] = min(runs)
+    assert took[400.0] < 8 * took[0.0]
+
+
 @pytest.mark.parametrize("d,pq_dim,pq_bits", [(64, 16, 8), (128, 32, 8), (96, 48, 8), (128, 64, 8), (128, 64, 4), (128, 64, 7), (128, 32, 5)])
 def test_nearest_probes_by_groups(P, d, pq_dim, pq_bits):
     # 5,000 queries on 41 clusters: their nearest probes are scanned by the group kernel and bounded by a wave each (scan route 0); with a route
