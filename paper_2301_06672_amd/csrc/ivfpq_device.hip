@@ -421,7 +421,7 @@ int launch_step_1a(const ivfpq_index* idx, const float* q, int nq, int n_probes,
 void launch_select_probes(int nq, bool exact, hipStream_t st, uint32_t* A, const StripSummary* S, int strip_w, const float* queries,
                           const float* centroids, float centroid_norm_max, int d, int n_lists, int n_probes, const uint32_t* list_sizes,
                           const int64_t* group_offsets, uint32_t* probes, float* probe_dists, uint32_t* roff, uint4* pairs, int k_hint, uint32_t* nearest = nullptr) {
-    if (!exact && !S && nq > kFewQueries && n_probes <= kWaveProbes) {        // (sides measured: at the kernel)
+    if (!exact && !S && select_by_waves(nq, n_probes)) {
         hipLaunchKernelGGL(select_probes_wave_kernel, dim3((unsigned)((nq + kWaveQueries - 1) / kWaveQueries)), dim3(64 * kWaveQueries), 0, st, A, queries, centroids,
                            centroid_norm_max, d, n_lists, n_probes, nq, list_sizes, group_offsets, probes, probe_dists, roff, pairs, k_hint, nearest);
         return;

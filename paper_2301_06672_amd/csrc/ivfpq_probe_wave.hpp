@@ -21,7 +21,10 @@ namespace {
 // Bound by the instructions and the waits of one wave, of which the chip holds 8,192 at once: 10,000 queries on 1,024 clusters, 20 probes,
 // 66 -> 29 us; 2,000, 64 probes, 108 -> 61; 4,096 queries on 1,024 30 -> 15.  (Strip summaries yield five times as many candidates, whose
 // distances are too much for one wave: 10,000 clusters, 50 probes, 95 us by workgroups, 173 by waves.)
-constexpr int kWaveProbes = 64, kWaveCand = 192, kWaveQueries = 4;
+using ivfpq::kWaveProbes;
+using ivfpq::select_by_waves;
+constexpr int kWaveCand = 192, kWaveQueries = 4;
+static_assert(kWaveProbes + kWave <= kWaveCand, "the nearest so far leave room for a step of the row");
 
 __global__ void __launch_bounds__(64 * kWaveQueries)
 select_probes_wave_kernel(uint32_t* __restrict__ A, const float* __restrict__ queries, const float* __restrict__ centroids, float centroid_norm_max, int d, int n_lists, int n_probes, int nq,

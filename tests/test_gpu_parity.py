@@ -1283,9 +1283,9 @@ def test_search_index_without_vectors(P):
 
 @pytest.mark.parametrize("n_lists", [65, 127, 256, 259, 1000, 1024, 1190])
 def test_select_probes_by_waves(P, n_lists):
-    # 513 queries and up to 64 probes of at most 2 strips a probe: a wave per query.  Rows that are and are not whole 16-byte words, fewer and
-    # more clusters than the 256 minima, ties, more equal ranking values than a wave holds candidates (all distances are compared), a query that
-    # is no number; 65 probes take a workgroup a query.
+    # 1,537 queries and up to 64 probes of at most 2 strips a probe: a wave per query; 65 probes and 1,536 queries: a workgroup per query.  Rows
+    # that are and are not whole 16-byte words, fewer and more clusters than the 256 minima, ties, more equal ranking values than a wave holds
+    # candidates, a query that is no number.
     rng = np.random.default_rng(n_lists)
     d = 32
     cen = (rng.standard_normal((n_lists, d)) * 10).astype(np.float32)
@@ -1296,21 +1296,23 @@ def test_select_probes_by_waves(P, n_lists):
     codes = rng.integers(0, 256, (n_lists, 8)).astype(np.uint8)
     oidx = oracle.make_index(d, n_lists, 16, 4, cen, books, np.arange(n_lists + 1, dtype=np.int64), codes, np.arange(n_lists, dtype=np.int64))
     gidx = to_library(P, oidx)
-    q = (cen[rng.integers(0, n_lists, 513)] + rng.standard_normal((513, d))).astype(np.float32)
+    q = (cen[rng.integers(0, n_lists, 1537)] + rng.standard_normal((1537, d))).astype(np.float32)
     q[7] = cen[0]
-    for n_probes in (1, 20, 63, 64, min(65, n_lists)):
-        _step(f"select_probes by waves L={n_lists} P={n_probes}")
-        probes, pd = (x.cpu().numpy() for x in gidx.ivfpq_select_probes(q, n_probes))
-        want_d = oracle.select_probes(oidx, q, n_probes)[1]
-        assert_probes_match(probes.view(np.uint32), cen, q, n_probes)
+    some = np.r_[0:200, 1337:1537]
+    for n_probes, nq in ((1, 1537), (20, 1537), (63, 1537), (64, 1537), (min(65, n_lists), 1537), (64, 1536)):
+        _step(f"select_probes by waves L={n_lists} P={n_probes} nq={nq}")
+        at = some[some < nq]
+        probes, pd = (x.cpu().numpy()[at] for x in gidx.ivfpq_select_probes(q[:nq], n_probes))
+        want_d = oracle.select_probes(oidx, q[at], n_probes)[1]
+        assert_probes_match(probes.view(np.uint32), cen, q[at], n_probes)
         np.testing.assert_allclose(pd, want_d, rtol=RTOL)
         # ties go to the lower cluster, whichever path takes them
         assert np.all((np.diff(pd, axis=1) > 0) | (np.diff(probes.astype(np.int64), axis=1) > 0))
     q[9, 3] = np.nan
-    probes, _ = gidx.ivfpq_select_probes(q, 20)
-    others = [i for i in range(513) if i != 9]
-    assert_probes_match(probes.cpu().numpy().view(np.uint32)[others], cen, q[others], 20)
-    assert len(set(probes.cpu().numpy()[9].tolist())) == 20
+    probes = gidx.ivfpq_select_probes(q, 20)[0].cpu().numpy()
+    others = some[some != 9]
+    assert_probes_match(probes.view(np.uint32)[others], cen, q[others], 20)
+    assert len(set(probes[9].tolist())) == 20
 
 
 def _offset_probes(P, n_lists, d, offset, nq, seed):

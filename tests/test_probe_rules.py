@@ -10,6 +10,7 @@ SHIM = """
 extern "C" int big_tiles(int nq, int n_lists) { return ivfpq::coarse_big_tiles(nq, n_lists); }
 extern "C" int strip_width(int nq, int n_lists) { return ivfpq::coarse_strip_width(nq, n_lists); }
 extern "C" int use_strips(int nq, int n_lists, int k) { return ivfpq::coarse_use_strips(nq, n_lists, k); }
+extern "C" int by_waves(int nq, int n_probes) { return ivfpq::select_by_waves(nq, n_probes); }
 """
 
 
@@ -31,3 +32,10 @@ def test_middling_batches_are_ranked_in_fp32(rules):
         assert rules.big_tiles(nq, n_lists) and rules.strip_width(nq, n_lists) == 64
     # ... so that 100 probes of 8,192 clusters read strip summaries there
     assert rules.use_strips(1_100, 8_192, 100) and not rules.use_strips(1_100, 8_192, 129) and not rules.use_strips(8_192, 8_192, 65)
+
+
+def test_a_wave_per_query_where_the_chip_is_full(rules):
+    # up to 1,536 queries every workgroup is resident, and one selects faster than a wave (513 queries, 64 probes, 960 components: 73 us to 99)
+    assert not any(rules.by_waves(nq, p) for nq in (513, 777, 1_200, 1_536) for p in (1, 10, 64))
+    assert all(rules.by_waves(nq, p) for nq in (1_537, 2_000, 10_000) for p in (1, 10, 64))
+    assert not rules.by_waves(10_000, 65)
