@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include "ivfpq_lds_util.hpp"
+#include "ivfpq_nearest_rules.hpp"
 #include "ivfpq_scan_args.hpp"
 #include "ivfpq_select.hpp"
 
@@ -13,10 +14,12 @@ namespace {
 // workgroups have several queries: the k-th smallest of row[0 .. len) bounds the query's k-th smallest R; it and what is not above it
 // become the first entries of the survivor list.  Fewer than k finite values: no bound, every vector is admitted.
 // The k-th smallest of 256 minima (four to a lane, of interleaved shares of the list) is not below the k-th smallest value: what is not above
-// it is gathered (about k + k^2 / 512 values) and the k-th found exactly, by bisection over the bits with ballots.  More than a wave has
-// room for (values that cluster): the bound is that minimum, and a few values too many are listed; the selection at the end is exact.
-// k <= kBoundWaveK, for which the room is enough by a third.
-constexpr int kBoundWaveK = 128, kBoundCand = 192, kBoundQueries = 4;
+// it is gathered and the k-th found exactly, by bisection over the bits with ballots.  More than a wave has room for (rare up to k = 100, one
+// query in 25 at 128; values that cluster): the bound is that minimum, and a few values too many are listed; the selection at the end is exact.
+using ivfpq::kBoundCand;
+using ivfpq::kBoundWaveK;
+constexpr int kBoundQueries = 4;
+static_assert(ivfpq::kBoundShares == 4 * kWave && kBoundCand % kWave == 0, "four minima a lane, whole registers of values");
 
 __global__ void __launch_bounds__(64 * kBoundQueries)
 bound_wave_kernel(ivfpq::ScanArgs a, int nq) {
