@@ -33,7 +33,7 @@
 // every entry unused).  A workgroup takes G consecutive pairs of the grouped order and cuts them into
 // such runs at the seams between clusters.
 // Mode kAll scans the nearest probes of a large batch, whose queries share clusters too, and writes every value in place (their bound: ivfpq_bound_wave.hpp).
-// Bound by the vector ALU (2.25 instructions a lookup, tables as ever).  10,000 queries, 64 codes, e5m3, 1,024 lists: scan_kernel with the bound
+// Bound by the vector ALU and the LDS reads (3.25 instructions a lookup of one-byte entries, tables as ever).  10,000 queries, 64 codes, e5m3, 1,024 lists: scan_kernel with the bound
 // at its end 195 us, this 128 and the bound 25; 4-bit codes, half, 2,000 lists 337 -> 227 + 46; 7 bits 183 -> 118 + 25.
 // LDS: the slot's pair descriptors | tables | R residuals of d floats | per wave kGroupStageAll staged survivors |
 // a flag and, per wave, kAliveCap group numbers of the split scan.
@@ -215,9 +215,6 @@ __device__ __forceinline__ void group_run(const ScanArgs& a, unsigned char* smem
     // both halves of a register hold the bf16 pattern of 1.0; decode constant of the 8-bit formats per half
     const bf16x2_t ones = __builtin_bit_cast(bf16x2_t, 0x3F803F80u);
     const uint32_t k2 = ((uint32_t)fp8.lo >> 16) * 0x10001u;
-    // 1.0 in one half alone; in registers, since the second is also the pattern of an inline constant that stands for 1.0 in the low half
-    uint32_t one_low = 0x00003F80u, one_high = 0x3F800000u;
-    asm volatile("" : "+s"(one_low), "+s"(one_high));
     // adds the entries of two consecutive sub-spaces, x0 then x1 (the words of all R queries), to every query's sum
     auto add_two = [&](const word_t& x0, const word_t& x1, float (&acc)[Q]) __attribute__((always_inline)) {
         if constexpr (kIsFp8<LUT>) {
@@ -227,9 +224,12 @@ __device__ __forceinline__ void group_run(const ScanArgs& a, unsigned char* smem
                 // bytes g of x0 and x1 into the low bytes of the two halves
                 uint32_t p = __builtin_amdgcn_perm((uint32_t)x1, (uint32_t)x0, 0x0c000c00u | ((4u + g) << 16) | (uint32_t)g);
                 p = (p << S) + k2;
-                if constexpr (ALL) {             // one after the other, as scan_kernel and candidate_kernel add them
-                    acc[g] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, p), __builtin_bit_cast(bf16x2_t, one_low), acc[g], false);
-                    acc[g] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, p), __builtin_bit_cast(bf16x2_t, one_high), acc[g], false);
+                if constexpr (ALL) {
+                    // One after the other, rounded as scan_kernel and candidate_kernel round them.  (The dot product rounds otherwise now and then, where
+                    // an entry is far below the sum or far above it; two of them with 1.0 in one half alone, as one with both: one-component
+                    // sub-vectors, 1 to 5 of 10^6 sums differed by the last bit, most of them for the worse.  The plain adds take as long.)
+                    acc[g] += __uint_as_float(p << 16);
+                    acc[g] += __uint_as_float(p & 0xFFFF0000u);
                 } else {
                     acc[g] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, p), ones, acc[g], false);
                 }

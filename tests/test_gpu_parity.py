@@ -1392,3 +1392,24 @@ def test_nearest_probes_by_groups(P, d, pq_dim, pq_bits):
                 out.append([t.cpu().numpy() for t in gidx.ivfpq_search(q, 12, k, dtype)])
             np.testing.assert_array_equal(out[0][0], out[1][0])
             np.testing.assert_array_equal(out[0][1].view(np.uint32), out[1][1].view(np.uint32))
+
+
+@pytest.mark.parametrize("d,pq_dim,pq_bits", [(96, 96, 5), (96, 96, 6), (64, 64, 8)])
+def test_nearest_probes_by_groups_round_as_one_query_does(P, d, pq_dim, pq_bits):
+    # One-component sub-vectors have entries over the formats' whole range, so that sums are rounded: the group kernel's are the ones that a
+    # workgroup a query forms, to the last bit.  (The filter is kept out of both: the other probes go the same way.)
+    rng = np.random.default_rng(pq_bits)
+    cent = (4 * rng.standard_normal((40, d))).astype(np.float32)
+    books = (0.5 * rng.standard_normal((pq_dim, 1 << pq_bits, 1))).astype(np.float32)
+    codes = rng.integers(0, 256, (40_000, pq_dim * pq_bits // 8)).astype(np.uint8)
+    gidx = to_library(P, oracle.make_index(d, 40, pq_dim, pq_bits, cent, books, np.arange(41, dtype=np.int64) * 1000, codes, np.arange(40_000, dtype=np.int64)))
+    gidx.ivfpq_set_tuning(P.TUNE_EARLY_EXIT, -1)
+    q = torch.from_numpy((cent[rng.integers(0, 40, 12_000)] + 30 * rng.standard_normal((12_000, d))).astype(np.float32)).cuda()
+    for dtype in (oracle.LUT_E5M3, oracle.LUT_E4M4):
+        out = []
+        for route in (0, 3):
+            gidx.ivfpq_set_tuning(P.TUNE_SCAN_ROUTE, route)
+            _step(f"rounding of nearest probes by groups d={d} bits={pq_bits} dtype={dtype} route={route}")
+            out.append([t.cpu().numpy() for t in gidx.ivfpq_search(q, 2, 128, dtype)])
+        np.testing.assert_array_equal(out[0][1].view(np.uint32), out[1][1].view(np.uint32))
+        np.testing.assert_array_equal(out[0][0], out[1][0])
