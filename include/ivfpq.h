@@ -266,11 +266,12 @@ int ivfpq_refine(const float* d_data, int64_t n_data, int32_t d, const float* d_
  * and their bookkeeping live in the handle: while enabled, search calls on one index must not overlap).
  * After the stream has been synchronised, ivfpq_stage_times_ms reports the last call's
  * milliseconds, summed over query tiles: ms[0] = probe selection (step 1: ranking GEMM + selection),
- * ms[1] = table build + code scan (steps 2-4: the scan kernel over the nearest probe, the bound kernel,
- * the grouping of the other pairs by cluster, the scan kernel over the remaining probes), ms[2] = top-k
- * (step 5), ms[3] = whole call; and single launches inside those stages: ms[4] = the ranking GEMM of
- * step 1, ms[5] = the scan kernel over the nearest probes, ms[6] = the scan kernel over the remaining
- * probes (the dominant kernel), ms[7] = 0 (reserved).  Small searches scan all probes in one launch: its
+ * ms[1] = table build + code scan (steps 2-4: the scan of the nearest probes and their bound, the grouping of the
+ * other pairs by cluster, the scan of the remaining probes), ms[2] = top-k (step 5), ms[3] = whole call; and
+ * parts of those stages: ms[4] = the ranking GEMM of step 1, ms[5] = the scan of the nearest probes with its
+ * bound (one launch, or in large batches three: the queries' order, the scan of up to four at once, the
+ * bound), ms[6] = the scan of the remaining probes (the dominant kernel, or two), ms[7] = of ms[5] the bound where it
+ * is a launch of its own, else 0.  Small searches scan all probes in one launch: its
  * time is divided between ms[5] and ms[6] by the number of pairs, 1 : n_probes - 1. */
 int ivfpq_set_stage_timing(ivfpq_index_t* index, int32_t enabled);
 int ivfpq_stage_times_ms(ivfpq_index_t* index, float ms[8]);

@@ -2135,8 +2135,11 @@ int search_impl(const ivfpq_index* idx, const float* d_queries, int64_t nq, cons
             near.order_block = kOrderBlock;
             near.n_chunks = idx->code_bytes() / chunk_width(idx);
             if (int s = launch_scan_group(idx, near, lut_dtype, G, st)) return s;
+            StageTimer t7(idx, st, 7);
+            if (int s = t7.begin()) return s;
             hipLaunchKernelGGL(bound_wave_kernel, dim3((unsigned)((tq + kBoundQueries - 1) / kBoundQueries)), dim3(64 * kBoundQueries), 0, st, near, tq);
             HIP_TRY(hipGetLastError());
+            if (int s = t7.end()) return s;
         } else if (int s = launch_scan(idx, a, lut_dtype, dim3((unsigned)((size_t)tq * (whole_rows ? n_probes : 1))), st)) {
             return s;
         }

@@ -29,9 +29,10 @@ struct ScanArgs {
     int d, pq_dim, m, bits;
     int n_chunks;                 // chunks per vector (code_bytes / CW)
     int single_list;              // >= 0: scan this cluster for query 0, R written from offset 0
-    const uint32_t* order;        // mode 2: pairs (as q * (n_probes - 1) + probe - 1) grouped by cluster, or null
-    uint32_t n_pairs;             // mode 2: number of such pairs
-    uint32_t order_block;         // mode 2: consecutive pairs of the grouped order that stay on one XCD
+    const uint32_t* order;        // mode 2: pairs (as q * (n_probes - 1) + probe - 1) grouped by cluster, or null; mode 1 of the group kernel: queries
+                                  // in the order of their nearest clusters
+    uint32_t n_pairs;             // number of entries of the order
+    uint32_t order_block;         // consecutive ones that stay on one XCD
     int k_bound;                  // mode 1: the k of the bound to take from the nearest probe's values; 0: none is wanted
     uint32_t* clear[2];           // mode 1: counters of the grouping that follows, n_clear[] words each, to be set to zero
     uint32_t n_clear[2];

@@ -10,6 +10,8 @@ Bars (stated here, used below):
   * probe lists: same clusters rank by rank, swaps only between clusters whose float64
     distances agree to 1e-5 relative.
 """
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -1413,3 +1415,52 @@ def test_nearest_probes_by_groups_round_as_one_query_does(P, d, pq_dim, pq_bits)
             out.append([t.cpu().numpy() for t in gidx.ivfpq_search(q, 2, 128, dtype)])
         np.testing.assert_array_equal(out[0][1].view(np.uint32), out[1][1].view(np.uint32))
         np.testing.assert_array_equal(out[0][0], out[1][0])
+
+
+def _bound_ms(P, gidx):
+    # the launch that bounds the nearest probes scanned by groups; 0: a workgroup a query has scanned and bounded them
+    ms = (ctypes.c_float * 8)()
+    assert P.lib().ivfpq_stage_times_ms(gidx._h, ctypes.byref(ms)) == 0
+    assert 0 <= ms[7] <= ms[5] <= ms[1]
+    return ms[7]
+
+
+def _both_routes(P, gidx, q, n_probes, k, dtype, grouped, context):
+    # route 0 against a workgroup a query (any route named): the same bits; by the stage times, which of them has run.  The other probes go the
+    # same way in both, since the tables' sums are rounded in another order than the filter's candidates: a route named means the
+    # filter, which the knob of the early exit keeps out.
+    out = []
+    for route in (0, 3):
+        _step(f"{context} k={k} dtype={dtype} route={route}")
+        gidx.ivfpq_set_tuning(P.TUNE_SCAN_ROUTE, route)
+        gidx.ivfpq_set_stage_timing(True)
+        out.append([t.cpu().numpy() for t in gidx.ivfpq_search(q, n_probes, k, dtype)])
+        name = gidx.ivfpq_scan_kernel_info(dtype).split("<")[0]
+        assert (_bound_ms(P, gidx) > 0) == (grouped and route == 0), f"{context} k={k} dtype={dtype} route={route}"
+        gidx.ivfpq_set_stage_timing(False)
+        gidx.ivfpq_set_tuning(P.TUNE_EARLY_EXIT, -1 if route == 0 and name != "scan_filter_kernel" else 0)
+        others = name if route == 0 else others
+        assert name == others
+    np.testing.assert_array_equal(out[0][0], out[1][0])
+    np.testing.assert_array_equal(out[0][1].view(np.uint32), out[1][1].view(np.uint32))
+    return out[0]
+
+
+def test_nearest_probes_by_groups_tile_by_tile(P):
+    # tiles of which the last is too small for groups, and a batch that one launch cannot order: the results of a workgroup a query
+    rng = np.random.default_rng(4)
+    d, pq_dim, lists = 128, 64, 40
+    cent = (4 * rng.standard_normal((lists, d))).astype(np.float32)
+    books = (0.5 * rng.standard_normal((pq_dim, 256, 2))).astype(np.float32)
+    n = lists * 800
+    offsets = np.arange(lists + 1, dtype=np.int64) * 800
+    gidx = to_library(P, oracle.make_index(d, lists, pq_dim, 8, cent, books, offsets, rng.integers(0, 256, (n, pq_dim)).astype(np.uint8), np.arange(n, dtype=np.int64)))
+    q = torch.from_numpy((cent[rng.integers(0, lists, 16_385)] + 0.5 * rng.standard_normal((16_385, d))).astype(np.float32)).cuda()
+    whole = _both_routes(P, gidx, q[:16_384].contiguous(), 15, 10, oracle.LUT_E5M3, True, "16,384 queries")
+    _both_routes(P, gidx, q, 15, 10, oracle.LUT_E5M3, False, "16,385 queries")
+    need = gidx.ivfpq_search_workspace_bytes(8_000, 15, 10, oracle.LUT_E5M3)
+    gidx.ivfpq_set_workspace_limit(need)                     # 16,384 queries: two tiles of about 8,000 and a small one, or nearly so
+    parts = _both_routes(P, gidx, q[:16_384].contiguous(), 15, 10, oracle.LUT_E5M3, True, "16,384 queries in tiles")
+    np.testing.assert_array_equal(whole[0], parts[0])
+    np.testing.assert_array_equal(whole[1].view(np.uint32), parts[1].view(np.uint32))
+    _both_routes(P, gidx, q[:2_400].contiguous(), 15, 10, oracle.LUT_E5M3, False, "2,400 queries")
