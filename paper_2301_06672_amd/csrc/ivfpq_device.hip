@@ -1304,7 +1304,7 @@ filter_items_kernel(const uint32_t* __restrict__ counts, const uint32_t* __restr
 // The queries in the order of their nearest clusters, in one launch: a workgroup goes over the nearest cluster of every query (left by the
 // selection), ranks those of its own 64 clusters, counts those of the clusters before, and writes its queries.  5 us for 10,000
 // queries and 1,024 or 10,000 clusters; one workgroup for all of them took over 100.
-constexpr int kNearestPerThread = 16;
+using ivfpq::kNearestPerThread;
 __global__ void __launch_bounds__(1024)
 nearest_order_kernel(const uint32_t* __restrict__ nearest, int nq, uint32_t* __restrict__ order) {
     __shared__ uint32_t s_count[kWave], s_before;
@@ -1809,26 +1809,16 @@ int launch_scan_group(const ivfpq_index* idx, const ScanArgs& a, int lut_dtype, 
     }
 }
 
-// Pairs a workgroup of the group kernel takes for the queries' nearest probes, or 0 where scan_kernel takes a query each.  Two launches more (the
-// order 5 us, the bound 16 to 46) and a quarter of the workgroups: whole searches, us, a query each / in groups, k = 10 and 20 probes:
-//   queries                       600        1,200      2,000      3,000      5,000      10,000
-//   128 lists, 64 codes, e5m3     141 / 151  163 / 177  220 / 208  292 / 277  427 / 375  667 / 560
-//   512 lists, 32 codes, half     141 / 150  173 / 178  199 / 182  252 / 235  358 / 281  573 / 438
-//   1,024 lists, 48 codes, e5m3              120 / 129  137 / 131  162 / 156  217 / 197  349 / 303
-//   1,024 lists, 64 codes of 7 bits, half    157 / 185  188 / 190  230 / 223  306 / 273  493 / 435
-//   512 lists, 64 codes of 4 bits, float     130 / 245  169 / 269  213 / 284  282 / 326  416 / 387  652 / 540
-//   2,000 lists, 64 codes, e4m4                         237 / 239  307 / 317  451 / 451  846 / 779
-// (all with k = 100 and 40 probes alike; up to a twentieth of the gain is the probe selection's).  Hence 3,000 queries, 5,000 for float tables of
-// 4-bit codes, and three queries a list where only two workgroups fit a compute unit; where more do, one a list (10,000 queries of 10,000
-// lists, 48 codes: nearest probes 187 -> 180 us; 8,192 of 5,000, 32 codes: 238 -> 205).
+// Pairs a workgroup of the group kernel takes for the queries' nearest probes, or 0 where scan_kernel takes a query each (the line and both of
+// its sides: nearest_by_groups).
 int nearest_group_width(const ivfpq_index* idx, int lut_dtype, const Fp8Mode& fp8, int nq, int k) {
     const ivfpq::Tuning& t = idx->tuning;
     if (t.scan_route != 0 || t.scan_share != 0 || t.order_block != 0 || t.scan_threads != 0 || t.lds_pad != 0) return 0;
-    if (k > kBoundWaveK || nq > 1024 * kNearestPerThread || nq < (idx->pq_bits == 4 && lut_dtype == IVFPQ_LUT_FP32 ? 5000 : 3000)) return 0;
     const int G = scan_group_width(idx, lut_dtype, fp8, kOrderBlock);
     if (G == 0) return 0;
-    const bool few_fit = scan_group_lds_bytes(idx, lut_dtype, G, scan_group_threads(idx, lut_dtype, G)) > kGroupLds4;
-    return nq >= (few_fit ? 3 : 1) * (int64_t)idx->n_lists ? G : 0;
+    const bool eight_waves = scan_group_lds_bytes(idx, lut_dtype, G, scan_group_threads(idx, lut_dtype, G)) > kGroupLds4;
+    return ivfpq::nearest_by_groups({nq, k, idx->n, idx->list_mean, idx->list_typical, (double)idx->sorted_padded_sizes[0], idx->pq_bits, idx->pq_dim,
+                                     (int)lut_elem_bytes(lut_dtype), G, eight_waves}) ? G : 0;
 }
 
 // A grid that leaves wave slots of the chip empty takes larger workgroups: tables are built and lists walked by more

@@ -203,12 +203,17 @@ int check_shape(int64_t n, int32_t d, int32_t n_lists, int32_t pq_dim, int32_t p
 void finish_import(ivfpq_index* idx) {
     idx->total_groups = 0;
     idx->sorted_padded_sizes.resize(idx->n_lists);
+    double squares = 0.0, filled = 0.0;
     for (int32_t l = 0; l < idx->n_lists; ++l) {
         int64_t len = idx->list_offsets[l + 1] - idx->list_offsets[l];
         int64_t groups = (len + 63) / 64;
         idx->total_groups += groups;
         idx->sorted_padded_sizes[l] = (uint32_t)(groups * 64);
+        squares += (double)len * (double)len;
+        filled += len > 0 ? 1.0 : 0.0;
     }
+    idx->list_mean = filled > 0.0 ? (double)idx->n / filled : 0.0;
+    idx->list_typical = idx->n > 0 ? squares / (double)idx->n : 0.0;
     std::sort(idx->sorted_padded_sizes.begin(), idx->sorted_padded_sizes.end(), std::greater<uint32_t>());
 }
 

@@ -141,6 +141,7 @@ struct ivfpq_index {
     // derived at import
     int64_t total_groups = 0;           // sum over lists of ceil(len/64)
     std::vector<uint32_t> sorted_padded_sizes;  // padded list lengths, descending
+    double list_mean = 0.0, list_typical = 0.0; // length of a list that is not empty; of the list that a vector lies in (sum of len^2 / n)
 
     ivfpq::DeviceImage dev;
     ivfpq::Fp8Options fp8_opt[2] = {{15, 0, 0}, {7, 0, 0}};   // e5m3, e4m4 (ivfpq_set_fp8_encoding)

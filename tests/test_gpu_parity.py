@@ -1446,6 +1446,77 @@ def _both_routes(P, gidx, q, n_probes, k, dtype, grouped, context):
     return out[0]
 
 
+@pytest.mark.parametrize("d,pq_dim,pq_bits,few", [
+    (64, 16, 8, ""), (128, 32, 8, ""), (96, 48, 8, "4"), (128, 64, 8, "4"), (64, 64, 8, "42"), (96, 96, 7, "42"), (96, 96, 6, "4"), (96, 96, 5, ""),
+    (96, 48, 6, ""), (128, 64, 7, ""), (64, 32, 7, "2"), (64, 32, 5, "2"), (128, 64, 4, "1"), (128, 32, 4, "41"), (96, 96, 4, "1"), (64, 64, 4, "1")])
+def test_nearest_probes_of_every_encoding_by_groups(P, d, pq_dim, pq_bits, few):
+    # 12,000 queries on 43 clusters.  few: tables (bytes an entry) that take a workgroup a query, too large for two of them or never faster in
+    # groups; of the others the group kernel is seen to run.  Lists of 0 to 6,000 vectors, one of equal codes, queries that are no numbers.
+    rng = np.random.default_rng(1000 * d + 10 * pq_dim + pq_bits)
+    sizes = np.array([0, 1, 63, 64, 65, 127, 128, 129, 2047, 2048, 2049, 6000] + [900 + 3 * i for i in range(31)])
+    cent = (4 * rng.standard_normal((43, d))).astype(np.float32)
+    books = (0.5 * rng.standard_normal((pq_dim, 1 << pq_bits, d // pq_dim))).astype(np.float32)
+    n = int(sizes.sum())
+    codes = rng.integers(0, 256, (n, pq_dim * pq_bits // 8)).astype(np.uint8)
+    offsets = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    codes[offsets[30]:offsets[31]] = codes[offsets[30]]
+    oidx = oracle.make_index(d, 43, pq_dim, pq_bits, cent, books, offsets, codes, rng.permutation(n).astype(np.int64))
+    gidx = to_library(P, oidx)
+    q = (cent[rng.integers(0, 43, 12_000)] + 0.5 * rng.standard_normal((12_000, d))).astype(np.float32)
+    q[5] = np.nan
+    q[6, 0] = np.inf
+    q[7] *= 1e20
+    q = torch.from_numpy(q).cuda()
+    for dtype, size in ((oracle.LUT_FP32, "4"), (oracle.LUT_FP16, "2"), (oracle.LUT_E5M3, "1"), (oracle.LUT_E4M4, "1")):
+        for k in (1, 100, 128, 129):
+            ids, dist = _both_routes(P, gidx, q, 12, k, dtype, size not in few and k <= 128, f"nearest by groups d={d} sub={pq_dim} bits={pq_bits}")
+            if dtype == oracle.LUT_FP32 and k == 100:
+                at = rng.integers(8, 12_000, 24)
+                want_ids, want_d = oracle.search(oidx, q[at].cpu().numpy(), 12, k)
+                assert_topk_matches(ids[at], dist[at], want_ids, want_d, context=f"d={d} sub={pq_dim} bits={pq_bits}")
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+def test_nearest_probes_by_groups_without_a_bound(P, dtype):
+    # every probed list is shorter than k, some are empty, so that no value bounds anything: all vectors are admitted; with k small
+    # enough, only by the queries whose probes are all shorter
+    rng = np.random.default_rng(int(dtype) + 5)
+    sizes = rng.integers(40, 100, 80)
+    sizes[::9] = 0
+    sizes[1::9] = 1
+    d, pq_dim = 128, 32
+    cent = (4 * rng.standard_normal((80, d))).astype(np.float32)
+    books = (0.5 * rng.standard_normal((pq_dim, 256, 4))).astype(np.float32)
+    n = int(sizes.sum())
+    offsets = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    oidx = oracle.make_index(d, 80, pq_dim, 8, cent, books, offsets, rng.integers(0, 256, (n, pq_dim)).astype(np.uint8), rng.permutation(n).astype(np.int64))
+    gidx = to_library(P, oidx)
+    q = (cent[rng.integers(0, 80, 9_000)] + 0.5 * rng.standard_normal((9_000, d))).astype(np.float32)
+    for k in (60, 100, 128):
+        ids, dist = _both_routes(P, gidx, torch.from_numpy(q).cuda(), 20, k, dtype, True, "nearest by groups, short lists")
+        if dtype == oracle.LUT_FP32:
+            at = rng.integers(0, 9_000, 32)
+            want_ids, want_d = oracle.search(oidx, q[at], 20, k)
+            assert_topk_matches(ids[at], dist[at], want_ids, want_d, context=f"k={k}")
+
+
+def test_nearest_probes_by_groups_subnormal(P):
+    # distances below the least normal number, and a list that has fewer than k of them above zero
+    rng = np.random.default_rng(9)
+    d, pq_dim, lists = 128, 32, 30
+    tiny = np.float32(2e-21)
+    cent = (8 * rng.standard_normal((lists, d))).astype(np.float32) * tiny
+    books = rng.standard_normal((pq_dim, 256, 4)).astype(np.float32) * tiny
+    n = lists * 900
+    offsets = np.arange(lists + 1, dtype=np.int64) * 900
+    oidx = oracle.make_index(d, lists, pq_dim, 8, cent, books, offsets, rng.integers(0, 256, (n, pq_dim)).astype(np.uint8), np.arange(n, dtype=np.int64))
+    gidx = to_library(P, oidx)
+    q = (cent[rng.integers(0, lists, 8_000)] + rng.standard_normal((8_000, d)).astype(np.float32) * tiny).astype(np.float32)
+    for k in (10, 100):
+        ids, dist = _both_routes(P, gidx, torch.from_numpy(q).cuda(), 15, k, oracle.LUT_FP32, True, "nearest by groups, subnormal")
+        assert 0 < dist.max() < np.finfo(np.float32).tiny
+
+
 def test_nearest_probes_by_groups_tile_by_tile(P):
     # tiles of which the last is too small for groups, and a batch that one launch cannot order: the results of a workgroup a query
     rng = np.random.default_rng(4)
