@@ -1369,9 +1369,10 @@ def test_an_offset_costs_the_selection_little(P):
 
 @pytest.mark.parametrize("d,pq_dim,pq_bits", [(64, 16, 8), (128, 32, 8), (96, 48, 8), (128, 64, 8), (128, 64, 4), (128, 64, 7), (128, 32, 5)])
 def test_nearest_probes_by_groups(P, d, pq_dim, pq_bits):
-    # 5,000 queries on 41 clusters: their nearest probes are scanned by the group kernel and bounded by a wave each (scan route 0); with a route
-    # named, a workgroup each.  Lists of 0, 1, 63, 64, 65, 2,047, 2,049 (a wave holds 2,048 values), and 6,000 vectors, one of equal codes
-    # (more values under the bound than a wave gathers); k up to and past what a wave takes; queries that are no numbers.  Same bits.
+    # 5,000 queries on 41 clusters: where the encoding takes groups at that size (12,000 queries, and which kernels run: below), their nearest probes
+    # are scanned by the group kernel and bounded by a wave each with scan route 0; with a route named, a workgroup each.  Lists of 1,
+    # 63, 64, 65, 2,047, 2,049 (a wave holds 2,048 values), and 6,000 vectors, an empty one, one of equal codes (more values under the bound
+    # than a wave gathers); k up to and past what a wave takes; queries that are no numbers.  Same bits.
     rng = np.random.default_rng(1000 * d + 10 * pq_dim + pq_bits)
     sizes = np.array([0, 1, 63, 64, 65, 127, 128, 129, 2047, 2048, 2049, 6000] + [700 + 3 * i for i in range(29)])
     cent = (4 * rng.standard_normal((41, d))).astype(np.float32)
