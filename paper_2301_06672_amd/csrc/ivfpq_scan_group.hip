@@ -571,7 +571,14 @@ int ivfpq::launch_scan_group_kernel(const ScanArgs& a, int G, int threads, size_
     // CAN_SPLIT: 64 sub-spaces or more: with the early exit on, the second half of the tables is built only if needed
     auto go_mode = [&](auto len_tag, auto g_tag, auto bits_tag, auto can_split) -> int {
         constexpr int LEN = decltype(len_tag)::value, GG = decltype(g_tag)::value, BITS = decltype(bits_tag)::value;
-        if (a.mode == 1) return go(scan_group_kernel<LUT, LEN, GG, BITS, kAll>);
+        // (nearest_by_groups leaves these to a workgroup a query: 4-bit codes with tables of one byte, 32 of them with float tables, 32 bit-packed
+        // codes with half tables)
+        constexpr bool kNearest = !(BITS == 4 && (kIsFp8<LUT> || (LUT == IVFPQ_LUT_FP32 && LEN == 1))) &&
+                                  !(BITS != 8 && BITS != 4 && LEN == BITS && LUT == IVFPQ_LUT_FP16);
+        if (a.mode == 1) {
+            if constexpr (kNearest) return go(scan_group_kernel<LUT, LEN, GG, BITS, kAll>);
+            else return fail(IVFPQ_EUNSUPPORTED, "internal: no group kernel for the nearest probes of %d sub-spaces of %d bits", a.pq_dim, BITS);
+        }
         if constexpr (decltype(can_split)::value)
             if (a.early_exit) return go(scan_group_kernel<LUT, LEN, GG, BITS, kSplit>);
         return go(scan_group_kernel<LUT, LEN, GG, BITS, kFiltered>);
