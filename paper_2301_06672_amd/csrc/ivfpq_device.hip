@@ -419,9 +419,9 @@ int launch_step_1a(const ivfpq_index* idx, const float* q, int nq, int n_probes,
 }
 
 void launch_select_probes(int nq, bool exact, hipStream_t st, uint32_t* A, const StripSummary* S, int strip_w, const float* queries,
-                          const float* centroids, float centroid_norm_max, int d, int n_lists, int n_probes, const uint32_t* list_sizes,
+                          const float* centroids, float centroid_norm_max, const ivfpq::RankCrowd& crowd, int d, int n_lists, int n_probes, const uint32_t* list_sizes,
                           const int64_t* group_offsets, uint32_t* probes, float* probe_dists, uint32_t* roff, uint4* pairs, int k_hint, uint32_t* nearest = nullptr) {
-    if (!exact && !S && select_by_waves(nq, n_probes)) {
+    if (!exact && !S && select_by_waves(nq, n_probes, crowd.of(n_probes))) {
         hipLaunchKernelGGL(select_probes_wave_kernel, dim3((unsigned)((nq + kWaveQueries - 1) / kWaveQueries)), dim3(64 * kWaveQueries), 0, st, A, queries, centroids,
                            centroid_norm_max, d, n_lists, n_probes, nq, list_sizes, group_offsets, probes, probe_dists, roff, pairs, k_hint, nearest);
         return;
@@ -2068,7 +2068,7 @@ int search_impl(const ivfpq_index* idx, const float* d_queries, int64_t nq, cons
             if (int s = t4.end()) return s;
             launch_select_probes((int)tq, exact, st, (uint32_t*)w_D, (const StripSummary*)strips,
                                  coarse_strip_width(tq, idx->n_lists), qt,
-                                 idx->dev.centroids, idx->centroid_norm_max, idx->d, idx->n_lists,
+                                 idx->dev.centroids, idx->centroid_norm_max, idx->rank_crowd, idx->d, idx->n_lists,
                                  n_probes, idx->dev.list_sizes, idx->dev.group_offsets, w_probes, w_probe_d, w_roff, w_pairs, k, w_counts);
             HIP_TRY(hipGetLastError());
         } else {
@@ -2356,12 +2356,14 @@ int upload_impl(ivfpq_index_t* idx, void* d_buf, size_t bytes, void* hip_stream)
         }
     };
     ivfpq::PassShares shares;
+    ivfpq::RankCrowd crowd;
     const bool may_filter = filter_supported(idx->pq_bits, idx->pq_dim, idx->d, cw);
     std::memset(head.data(), 0, head.size());
     std::atomic<bool> normed{false};
     ivfpq::SideTask aside([&] {
         norms();
         normed.store(true, std::memory_order_release);
+        crowd = ivfpq::sample_rank_crowd(*idx, cn_max);
         if (may_filter) shares = ivfpq::sample_pass_shares(*idx);
     });
     std::memcpy(head.data() + L.centroids, idx->centroids.data(), idx->centroids.size() * 4);
@@ -2425,6 +2427,7 @@ int upload_impl(ivfpq_index_t* idx, void* d_buf, size_t bytes, void* hip_stream)
     HIP_TRY(hipStreamSynchronize(st));
     aside.wait();
     idx->pass_shares = shares;
+    idx->rank_crowd = crowd;
     idx->centroid_norm_max = cn_max;
     idx->word_norm_max = moderate ? std::sqrt(wn_max) * kWordNormSlack : -1.f;
 
@@ -2514,7 +2517,7 @@ int ivfpq_select_probes(const ivfpq_index_t* idx, const float* d_queries, int64_
                                    (unsigned char*)d_workspace + plan.split, st))
             return s;
         launch_select_probes((int)tq, exact, st, (uint32_t*)w_D, (const StripSummary*)strips,
-                             coarse_strip_width(tq, idx->n_lists), d_queries + (size_t)q0 * idx->d, idx->dev.centroids, idx->centroid_norm_max, idx->d,
+                             coarse_strip_width(tq, idx->n_lists), d_queries + (size_t)q0 * idx->d, idx->dev.centroids, idx->centroid_norm_max, idx->rank_crowd, idx->d,
                              idx->n_lists, n_probes, idx->dev.list_sizes, idx->dev.group_offsets, d_probes + (size_t)q0 * n_probes,
                              d_probe_dists ? d_probe_dists + (size_t)q0 * n_probes : nullptr, (uint32_t*)nullptr,
                              (uint4*)nullptr, 0);

@@ -94,6 +94,19 @@ inline void copy_bytes(void* dst, const void* src, size_t bytes) {
         if (t.joinable()) t.join();
 }
 
+// Of a search for 1, 2, 4 ... 64 probes: how many clusters' ranking values are within their error bound of what a selection by waves takes as
+// its limit, the mean of a sample.  Few where distances differ by more than the bound, which goes with the squared norms; many where
+// the vectors share an offset.
+struct RankCrowd {
+    static constexpr int kRanks = 7;
+    float within[kRanks] = {};
+    float of(int n_probes) const {
+        int rank = 0;
+        while (rank + 1 < kRanks && (1 << rank) < n_probes) ++rank;
+        return within[rank];
+    }
+};
+
 // The share of a farther cluster's vectors that pass the matrix-core filter, a property of the indexed vectors that their number does
 // not tell: lists that overlap pass many times what lists apart from each other do.  Sampled from the saved index: for clusters at
 // ranks 1, 2, 4, ... from a query, bounds of k / length = share, and limits wider than the bound by looseness.
@@ -148,6 +161,7 @@ struct ivfpq_index {
     float centroid_norm_max = 0.f;      // largest squared centroid norm (set by ivfpq_upload)
     float word_norm_max = -1.f;         // largest codeword norm (set by ivfpq_upload); negative: some codeword is not a moderate number
     ivfpq::PassShares pass_shares;      // set by ivfpq_upload
+    ivfpq::RankCrowd rank_crowd;        // set by ivfpq_upload
     size_t workspace_limit = (size_t)32 << 30;   // search scratch (R, positions, ranking values) per query tile
 
     ivfpq::Tuning tuning;               // ivfpq_set_tuning
@@ -177,6 +191,7 @@ struct ivfpq_index {
 
 namespace ivfpq {
 
+RankCrowd sample_rank_crowd(const ivfpq_index& idx, float centroid_norm_max) noexcept;
 // of an index of at most 128 components; none otherwise
 PassShares sample_pass_shares(const ivfpq_index& idx) noexcept;
 // The share for a search: averaged over ranks 1 .. n_probes - 1, linear between the sampled ranks, in log(share) and in the looseness.

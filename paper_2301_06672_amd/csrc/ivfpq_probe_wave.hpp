@@ -14,8 +14,8 @@ namespace {
 // distances for them, the n_probes nearest of those in order, the query's descriptors.  Here
 //   - the bound on the n_probes-th smallest ranking value is that of 256 minima (four to a lane, of interleaved shares of the row), by
 //     bisection over their bits with ballots;
-//   - candidates are ranked by counting, 192 at a time: where more are within the error bound (it goes with the norms, so vectors that share
-//     an offset have hundreds) the nearest so far stay and the next join them.  8,000 clusters of 128 components, 64 probes, 4,096
+//   - candidates are ranked by counting, 192 at a time: where more are within the error bound (it goes with the norms; an index whose vectors
+//     share an offset has hundreds, and is left to workgroups, but a query may lie far out) the nearest so far stay and the next join them.  8,000 clusters of 128 components, 64 probes, 4,096
 //     queries, ranking included: centred 119 us by workgroups and 108 by waves, offset by 400 167 and 164 (4,023 with all clusters' distances and a
 //     pass over them a probe); 2,000 clusters, 10,000 queries 168 and 154 (812).
 // Bound by the instructions and the waits of one wave, of which the chip holds 8,192 at once: 10,000 queries on 1,024 clusters, 20 probes,

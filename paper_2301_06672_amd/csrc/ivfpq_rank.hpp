@@ -438,7 +438,7 @@ coarse_rank_split_kernel(const uint16_t* __restrict__ Qh, const uint16_t* __rest
 // a factor 4 of slack for whatever rounding the matrix unit applies); the rounding of |c|^2 and of the
 // final multiply-add (the + 8).
 __device__ inline float rank_error_bound(int d, float qn, float cmax) {
-    return ((float)(3 * d + 8) * 2.3841858e-07f + 5.0e-05f) * (qn + cmax);
+    return ivfpq::rank_error_share(d) * (qn + cmax);
 }
 
 inline int coarse_padded_dim(int d) { return (d + BK - 1) / BK * BK; }

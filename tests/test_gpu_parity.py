@@ -1367,6 +1367,27 @@ def test_an_offset_costs_the_selection_little(P):
     assert took[400.0] < 8 * took[0.0]
 
 
+@pytest.mark.parametrize("n_lists,d", [(193, 32), (1000, 32), (1024, 128), (2000, 96), (4000, 32)])
+def test_select_probes_by_waves_of_far_queries(P, n_lists, d):
+    # centred clusters, few within each other's error bound, so that the selection goes by waves; queries so far out that all or hundreds of
+    # them are within theirs (which goes with |q|^2): rounds of 192, beside queries that need none
+    rng = np.random.default_rng(n_lists)
+    cen = (10 * rng.standard_normal((n_lists, d))).astype(np.float32)
+    books = rng.standard_normal((16, 16, d // 16)).astype(np.float32)
+    gidx = to_library(P, oracle.make_index(d, n_lists, 16, 4, cen, books, np.arange(n_lists + 1, dtype=np.int64), rng.integers(0, 256, (n_lists, 8)).astype(np.uint8),
+                                           np.arange(n_lists, dtype=np.int64)))
+    q = (cen[rng.integers(0, n_lists, 1600)] + rng.standard_normal((1600, d))).astype(np.float32)
+    for i, far in enumerate((30, 100, 300, 1000, 3000)):
+        q[i::8] += np.float32(far)
+    for n_probes in (1, 10, 63, 64):
+        _step(f"select_probes by waves, far queries, L={n_lists} d={d} P={n_probes}")
+        probes, pd = (x.cpu().numpy() for x in gidx.ivfpq_select_probes(q, n_probes))
+        assert_probes_match(probes.view(np.uint32)[::5], cen, q[::5], n_probes)
+        assert np.all((np.diff(pd, axis=1) > 0) | (np.diff(probes.astype(np.int64), axis=1) > 0))
+        few, few_d = (x.cpu().numpy() for x in gidx.ivfpq_select_probes(q[:500], n_probes))           # few queries: all distances, by workgroups
+        np.testing.assert_allclose(pd[:500], few_d, rtol=RTOL)
+
+
 @pytest.mark.parametrize("d,pq_dim,pq_bits", [(64, 16, 8), (128, 32, 8), (96, 48, 8), (128, 64, 8), (128, 64, 4), (128, 64, 7), (128, 32, 5)])
 def test_nearest_probes_by_groups(P, d, pq_dim, pq_bits):
     # 5,000 queries on 41 clusters: where the encoding takes groups at that size (12,000 queries, and which kernels run: below), their nearest probes
