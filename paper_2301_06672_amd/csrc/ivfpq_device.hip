@@ -2356,14 +2356,12 @@ int upload_impl(ivfpq_index_t* idx, void* d_buf, size_t bytes, void* hip_stream)
         }
     };
     ivfpq::PassShares shares;
-    ivfpq::RankCrowd crowd;
     const bool may_filter = filter_supported(idx->pq_bits, idx->pq_dim, idx->d, cw);
     std::memset(head.data(), 0, head.size());
     std::atomic<bool> normed{false};
     ivfpq::SideTask aside([&] {
         norms();
         normed.store(true, std::memory_order_release);
-        crowd = ivfpq::sample_rank_crowd(*idx, cn_max);
         if (may_filter) shares = ivfpq::sample_pass_shares(*idx);
     });
     std::memcpy(head.data() + L.centroids, idx->centroids.data(), idx->centroids.size() * 4);
@@ -2424,6 +2422,7 @@ int upload_impl(ivfpq_index_t* idx, void* d_buf, size_t bytes, void* hip_stream)
     }
     if (idx->n > 0)
         HIP_TRY(hipMemcpyAsync(base + L.ids, idx->ids.data(), idx->ids.size() * 8, hipMemcpyHostToDevice, st));
+    const ivfpq::RankCrowd crowd = ivfpq::sample_rank_crowd(*idx, cn_max);          // (while the last kernels run; the head had the norms)
     HIP_TRY(hipStreamSynchronize(st));
     aside.wait();
     idx->pass_shares = shares;

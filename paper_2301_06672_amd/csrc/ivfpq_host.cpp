@@ -41,13 +41,23 @@ int fail(int status, const char* fmt, ...) {
 // Up to 32 decoded vectors stand for queries.  Each is compared with up to 64 vectors of its nearest cluster, whose quantiles stand for the
 // bound (the k-th smallest R of that cluster), and with up to 12 vectors of the clusters at ranks 1, 2, 4, ... 256: counted is how many
 // are not above the quantile, widened by looseness.  (10^6 vectors of 48 codes in 1,024 lists: 1.7 ms of one thread.)
-// Eight centroids as queries against up to 512 others: 0.1 ms beside an upload of 1,024 clusters of 128 components.
+// Centroids as queries against up to 256 others: eight of them, two where these show no crowd (10 us beside an upload of 1,024 clusters of 128
+// components; all eight against 512, sorted whole, took 0.2 ms).
 RankCrowd sample_rank_crowd(const ivfpq_index& idx, float centroid_norm_max) noexcept {
-    constexpr int kQueries = 8, kOthers = 512, kMinima = 256;
+    constexpr int kQueries = 8, kFirst = 2, kOthers = 256, kMinima = 256, kFew = 120;
+    constexpr float kNoCrowd = 90.f;
     RankCrowd out;
     const int n_lists = idx.n_lists, d = idx.d, others = std::min(n_lists, kOthers);
-    for (int s = 0; s < kQueries; ++s) {
-        const int own = (int)((int64_t)(2 * s + 1) * n_lists / (2 * kQueries));
+    if (n_lists <= kFew) return out;                             // (no more than that can be within the bound)
+    int place[RankCrowd::kRanks];
+    for (int rank = 0; rank < RankCrowd::kRanks; ++rank) {
+        // the limit is the n_probes-th of 256 minima: among many clusters somewhat more are below it
+        const double probes = (double)(1 << rank), below = n_lists <= kMinima ? probes : kMinima * std::log(kMinima / (kMinima - probes));
+        place[rank] = std::min(others - 2, std::max(0, (int)(below * others / n_lists) - 1));
+    }
+    int taken = 0;
+    for (; taken < kQueries && !(taken == kFirst && out.within[RankCrowd::kRanks - 1] < kFirst * kNoCrowd); ++taken) {
+        const int own = (int)((int64_t)(2 * (taken * 5 % kQueries) + 1) * n_lists / (2 * kQueries));       // (the first two: far apart)
         const float* const q = idx.centroids.data() + (size_t)own * d;
         float dist[kOthers], norm = 0.f;
         int n = 0;
@@ -64,16 +74,16 @@ RankCrowd sample_rank_crowd(const ivfpq_index& idx, float centroid_norm_max) noe
             const float sum = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
             dist[n++] = sum < 3.0e38f ? sum : 3.0e38f;           // (a number in any case: they are sorted)
         }
-        std::sort(dist, dist + n);
-        for (int rank = 0; rank < RankCrowd::kRanks && n > 0; ++rank) {
-            // the limit is the n_probes-th of 256 minima: among many clusters somewhat more are below it
-            const double probes = (double)(1 << rank), place = n_lists <= kMinima ? probes : kMinima * std::log(kMinima / (kMinima - probes));
-            const int at = std::min(n - 1, std::max(0, (int)(place * others / n_lists) - 1));
-            const float limit = dist[at] + 2.f * rank_error_share(d) * (norm + centroid_norm_max);
-            const int64_t within = limit == limit ? std::upper_bound(dist, dist + n, limit) - dist : n;
-            out.within[rank] += (float)((double)within * n_lists / others / kQueries);
+        const float slack = 2.f * rank_error_share(d) * (norm + centroid_norm_max);
+        std::partial_sort(dist, dist + place[RankCrowd::kRanks - 1] + 1, dist + n);
+        for (int rank = 0; rank < RankCrowd::kRanks; ++rank) {
+            const float limit = dist[place[rank]] + slack;
+            int within = 0;
+            for (int i = 0; i < n; ++i) within += !(dist[i] > limit) ? 1 : 0;        // (all, where the slack is no number)
+            out.within[rank] += (float)within * (float)n_lists / (float)others;
         }
     }
+    for (float& w : out.within) w /= (float)taken;
     return out;
 }
 
