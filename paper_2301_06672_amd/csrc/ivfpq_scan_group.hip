@@ -336,7 +336,8 @@ __device__ __forceinline__ void group_run(const ScanArgs& a, unsigned char* smem
             if constexpr (PACKED) fields(buf, c, acc);
             else chunk(buf[c], c, acc);
             if constexpr (ALL) {
-                // a branch that is never taken: steps in one block are scheduled into each other, at the cost of registers (up to 500 spilled)
+                // a branch that is never taken: steps in one block are scheduled into each other, at the cost of registers (up to 500 spilled;
+                // with it none, as the compiler's -Rpass-analysis=kernel-resource-usage tells)
                 uint32_t never = 0;
                 asm volatile("" : "+s"(never));
                 over = never != 0;
@@ -572,8 +573,8 @@ int ivfpq::launch_scan_group_kernel(const ScanArgs& a, int G, int threads, size_
     auto go_mode = [&](auto len_tag, auto g_tag, auto bits_tag, auto can_split) -> int {
         constexpr int LEN = decltype(len_tag)::value, GG = decltype(g_tag)::value, BITS = decltype(bits_tag)::value;
         // (nearest_by_groups leaves these to a workgroup a query: 4-bit codes with tables of one byte, 32 of them with float tables, 32 bit-packed
-        // codes with half tables)
-        constexpr bool kNearest = !(BITS == 4 && (kIsFp8<LUT> || (LUT == IVFPQ_LUT_FP32 && LEN == 1))) &&
+        // codes with half tables; four queries of 8-bit codes with float tables are nobody's choice but a caller's, of the other probes)
+        constexpr bool kNearest = !(LUT == IVFPQ_LUT_FP32 && BITS == 8 && GG == 4) && !(BITS == 4 && (kIsFp8<LUT> || (LUT == IVFPQ_LUT_FP32 && LEN == 1))) &&
                                   !(BITS != 8 && BITS != 4 && LEN == BITS && LUT == IVFPQ_LUT_FP16);
         if (a.mode == 1) {
             if constexpr (kNearest) return go(scan_group_kernel<LUT, LEN, GG, BITS, kAll>);
